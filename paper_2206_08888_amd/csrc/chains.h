@@ -67,7 +67,7 @@ using Lds = LdsMap<32 * MT, 8>;
 template <int MT>
 struct LayerPre {
   SmallW w1;                       // first-layer weights
-  WeightBlock<MT, false> w2;       // block 0 of the hidden layer
+  WeightRaw<false> w2;             // block 0 of the hidden layer
   float b1[2], b2[2];              // biases of this lane's columns
   __device__ inline void load(const float* __restrict__ net, const NetLayout& L, int wave, int lane) {
     w1.load(net + L.w1, L.in, wave, lane);
@@ -168,22 +168,6 @@ struct InputTile {
   }
 };
 
-// Stage a head weight W3[256][J] as J rows of 256 (so that the thin products read it with
-// 16-byte LDS loads like any other row vector); thread c moves the J weights of hidden unit c.
-static_assert(kThreads == kH, "stage_head: one thread per hidden unit");
-__device__ inline void stage_head(float* dst, const float* __restrict__ src, int J, int tid) {
-  constexpr int U = 8;
-  const float* row = src + tid * J;
-  for (int j0 = 0; j0 < J; j0 += U) {
-    float v[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = row[j0 + u < J ? j0 + u : J - 1];
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (j0 + u < J) dst[(j0 + u) * kH + tid] = v[u];
-  }
-}
-
 __device__ inline float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
@@ -200,27 +184,26 @@ __device__ inline uint64_t first_layer(const float* Xs, int xld, const float* ne
   return relu_store<MT, THROUGH>(acc, pre.b1, Yl, Yg, wave, lane);
 }
 
-// Hidden layer in place on `buf`; `tail` is handed to the product (see gemm256).
-template <int MT, bool THROUGH = false, bool FED = false, class Tail>
+// Hidden layer in place on `buf`; `stage` (LDS) and `tail` are handed to the product (see gemm256).
+template <int MT, bool THROUGH = false, bool SLABS = true, class Tail>
 __device__ inline uint64_t hidden_layer(float* buf, const float* net, const NetLayout& L, LayerPre<MT>& pre,
-                                        float* Yg, int wave, int lane, Tail tail) {
+                                        float* Yg, int wave, int lane, Tail tail, float* stage) {
   Acc<MT> acc;
   acc.zero();
   const float bb[2] = {pre.b2[0], pre.b2[1]};
-  gemm256<MT, false, 2, FED>(buf, kLda, net + L.w2, pre.w2, wave, lane, acc, tail);
-  __syncthreads();                                   // every wavefront has read the input tile
+  gemm256<MT, false, SLABS>(buf, net + L.w2, pre.w2, stage, wave, lane, acc, tail);
   return relu_store<MT, THROUGH>(acc, bb, buf, Yg, wave, lane);
 }
 
 // dX = (dZ W^T) * mask written to global [rows][256]; column sums of the result
 // (over this workgroup's rows) go to colsum_out[256].
-template <int MT, bool THROUGH = false, bool FED = false>
-__device__ inline void input_grad_to_global(const float* Zl, const float* W, WeightBlock<MT, true>& w0, uint64_t mask,
+template <int MT, bool THROUGH = false, bool SLABS = true>
+__device__ inline void input_grad_to_global(const float* Zl, const float* W, WeightRaw<true>& w0, uint64_t mask,
                                             float* __restrict__ dXg, float* __restrict__ colsum_out, int wave,
-                                            int lane) {
+                                            int lane, float* stage) {
   Acc<MT> acc;
   acc.zero();
-  gemm256<MT, true, 2, FED>(Zl, kLda, W, w0, wave, lane, acc, NoTail());
+  gemm256<MT, true, SLABS>(Zl, W, w0, stage, wave, lane, acc, NoTail());
   float cs[2] = {0.0f, 0.0f};
   const int col = tile_col(wave, 0, lane);
 #pragma unroll
@@ -242,14 +225,14 @@ __device__ inline void input_grad_to_global(const float* Zl, const float* W, Wei
 //   G::R, G::kPad, G::Pre (prefetch record with load()), G::WtBlock + G::load_wt (block 0 of a
 //   transposed weight operand), first_layer, hidden_layer, input_grad_to_global,
 //   input_grad_to_lds, thin (thin products on the vector ALU).
-// FED: the 256-deep products issue their loads between the MFMAs (mfma_tiles.h) -- for kernels that run two
-// workgroups per CU.
-template <int MT, bool FED = false>
-struct Rows32 {                                      // 32 MT rows on v_mfma_f32_32x32x2_f32 (mfma_tiles.h)
+// kStageForward / kStage: floats of LDS behind a chain's vectors that its products and the split heads (head_mfma_split)
+// share as `stage` -- a chain of forward products only, any chain.
+template <int MT, bool SLABS = true>
+struct Rows32 {                                      // 32 MT rows on 32x32 tiles (mfma_tiles.h)
   static constexpr int R = 32 * MT, kPad = 8;
   using Pre = LayerPre<MT>;
-  using WtBlock = WeightBlock<MT, true>;
-  static constexpr int kStage = 0;                   // no LDS staging of weights (`stage` arguments are unused)
+  using WtBlock = WeightRaw<true>;
+  static constexpr int kStage = SLABS ? 2 * slab_floats<MT>() : 0, kStageForward = kStage;
   __device__ static inline void load_wt(WtBlock& wt, const float* W, int wave, int lane) { wt.load(W, 0, wave, lane); }
   __device__ static inline void load_input(float* Xl, int xld, const float* rows, int row_stride, int c0, int n, int valid,
                                            int tid) {
@@ -262,22 +245,21 @@ struct Rows32 {                                      // 32 MT rows on v_mfma_f32
   }
   template <bool THROUGH, class Tail>
   __device__ static inline uint64_t hidden_layer(float* buf, const float* net, const NetLayout& L, Pre& pre, float* Yg,
-                                                 int wave, int lane, Tail tail) {
-    return pop::hidden_layer<MT, THROUGH, FED>(buf, net, L, pre, Yg, wave, lane, tail);
+                                                 int wave, int lane, Tail tail, float* stage) {
+    return pop::hidden_layer<MT, THROUGH, SLABS>(buf, net, L, pre, Yg, wave, lane, tail, stage);
   }
   template <bool THROUGH>
   __device__ static inline void input_grad_to_global(const float* Zl, const float* W, WtBlock& w0, uint64_t mask,
-                                                     float* dXg, float* colsum_out, int wave, int lane, float*) {
-    pop::input_grad_to_global<MT, THROUGH, FED>(Zl, W, w0, mask, dXg, colsum_out, wave, lane);
+                                                     float* dXg, float* colsum_out, int wave, int lane, float* stage) {
+    pop::input_grad_to_global<MT, THROUGH, SLABS>(Zl, W, w0, mask, dXg, colsum_out, wave, lane, stage);
   }
   // buf <- (buf W^T) * mask in place; tail() as in gemm256
   template <class Tail>
   __device__ static inline void input_grad_to_lds(float* buf, const float* W, WtBlock& wt, uint64_t mask, int wave,
-                                                  int lane, Tail tail, float*) {
+                                                  int lane, Tail tail, float* stage) {
     Acc<MT> acc;
     acc.zero();
-    gemm256<MT, true, 2, FED>(buf, kLda, W, wt, wave, lane, acc, tail);
-    __syncthreads();                                 // every wavefront is done reading the operand
+    gemm256<MT, true, SLABS>(buf, W, wt, stage, wave, lane, acc, tail);
     const int col = tile_col(wave, 0, lane);
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
@@ -320,7 +302,7 @@ struct Rows16 {                                      // 16 rows on v_mfma_f32_16
     }
   };
   using WtBlock = WeightStage16;                     // the transposed products stage their weights through LDS
-  static constexpr int kStage = kStage16;            // floats of LDS they need for that
+  static constexpr int kStage = kStage16, kStageForward = kHeadRed;   // floats of LDS they need for that
   __device__ static inline void load_wt(WtBlock& wt, const float* W, int wave, int lane) { wt.load(W, 0, wave, lane); }
   __device__ static inline void load_input(float* Xl, int xld, const float* rows, int row_stride, int c0, int n, int valid,
                                            int tid) {
@@ -336,7 +318,7 @@ struct Rows16 {                                      // 16 rows on v_mfma_f32_16
   }
   template <bool THROUGH, class Tail>
   __device__ static inline uint64_t hidden_layer(float* buf, const float* net, const NetLayout& L, Pre& pre, float* Yg,
-                                                 int wave, int lane, Tail tail) {
+                                                 int wave, int lane, Tail tail, float*) {
     Acc16 acc;
     acc.zero();
     const f32x4 bb = pre.b2;
@@ -465,16 +447,10 @@ struct Rows16Deep : Rows16 {
 // Action dimensions beyond kMaxAct (up to kSacMaxAct): the chains are compiled a second time with scratch rows of
 // AS = kSacMaxAct floats -- a block of kSacMaxAct / kMaxAct of the map's [R][8] regions -- and kWideScratch regions.
 constexpr int kWideScratch = 3 * (kSacMaxAct / kMaxAct);
-constexpr int vec_target_floats(int AS) { return AS + 2 * kH + 8 + kHeadRed; }
-constexpr int vec_actor_floats_for(int AS) { return AS + kH + kHeadRed; }
+constexpr int vec_target_floats(int AS) { return AS + 2 * kH + 8; }
+constexpr int vec_actor_floats_for(int AS) { return AS + kH; }
 constexpr int vec_critic_floats = kH + 8, vec_actor_floats = vec_actor_floats_for(kMaxAct);   // staged vectors of the critic / actor
-                                                     // chain; behind them: the weight stage of the 16-row transposed products
-
-// Thin product with any number of outputs, eight at a time (the register budget of one pass).
-template <class G>
-__device__ inline void thin_wide(const float* Xl, const float* V, int J, float* outl, int stride, int tid) {
-  for (int j0 = 0; j0 < J; j0 += kMaxAct) G::thin(Xl, V + j0 * kH, J - j0 < kMaxAct ? J - j0 : kMaxAct, outl + j0, tid, stride);
-}
+                                                     // chain; behind them: G::kStage floats for the products
 
 // The longest time a workgroup waits for another one of the same launch is d.wait_limit, in 10 ns ticks of the
 // constant-rate clock (50 ms unless the host sets another bound; a healthy wait is a fraction of a millisecond).
@@ -552,6 +528,7 @@ __device__ __forceinline__ void target_chain(const PopDev& d, uint32_t t, int ag
   float* v_ab3 = lds + L.vec;                        // [AS]
   float* v_cw3 = v_ab3 + AS;                         // [2][256]
   float* v_cb3 = v_cw3 + 2 * kH;                     // [2]
+  float* stage = lds + L.vec + vec_target_floats(AS);
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int r0 = chunk * R;
   const float* ta = net_ptr(d, d.target, agent, 0);
@@ -613,10 +590,10 @@ __device__ __forceinline__ void target_chain(const PopDev& d, uint32_t t, int ag
   G::template first_layer<false>(Xs, L.xld, ta, d.actor, pre, buf, nullptr, wave, lane);
   __syncthreads();
   POP_MARK(32);
-  G::template hidden_layer<false>(buf, ta, d.actor, pre, nullptr, wave, lane, [&]() { pre.load(tc0, d.critic, wave, lane); });
+  G::template hidden_layer<false>(buf, ta, d.actor, pre, nullptr, wave, lane, [&]() { pre.load(tc0, d.critic, wave, lane); }, stage);
   __syncthreads();
   POP_MARK(33);
-  if (R <= 32 && (AS == kMaxAct || d.A <= 16)) head_mfma_split<R <= 32 ? R : 16, false>(buf, ta + d.actor.w3, d.A, head, AS, wave, lane, v_cb3 + 8);
+  if (R <= 32 && (AS == kMaxAct || d.A <= 16)) head_mfma_split<R <= 32 ? R : 16, false>(buf, ta + d.actor.w3, d.A, head, AS, wave, lane, stage);
   else head_mfma<R>(buf, ta + d.actor.w3, d.A, head, AS, wave, lane);   // the head's weights straight from global memory
   __syncthreads();
   POP_MARK(34);
@@ -641,7 +618,7 @@ __device__ __forceinline__ void target_chain(const PopDev& d, uint32_t t, int ag
     __syncthreads();
     POP_MARK(36 + 4 * k);
     G::template hidden_layer<false>(buf, tc, d.critic, pre, nullptr, wave, lane,
-                           [&]() { if (k == 0) pre.load(tc1, d.critic, wave, lane); });
+                           [&]() { if (k == 0) pre.load(tc1, d.critic, wave, lane); }, stage);
     __syncthreads();
     POP_MARK(37 + 4 * k);
     G::thin(buf, v_cw3 + k * kH, 1, head, tid);
@@ -669,18 +646,17 @@ __device__ __forceinline__ void target_chain(const PopDev& d, uint32_t t, int ag
 // while it waits for its Bellman targets: it depends on nothing of the step but the batch, and the actor launch that
 // follows the critics' weight step then starts at the critic (actor_chain<.., AHEAD>).  Xs: the critic's input tile
 // [s, a] -- the action columns meet the zero rows that pad the actor's first-layer weights; `area`: LDS of
-// ahead_floats<R>() floats that the critic chain does not use.  Writes aH1, aH2 and api.
+// ahead_floats<R>() floats that the critic chain does not use; `stage`: the slabs of its products, idle meanwhile.  Writes aH1, aH2 and api.
 template <int R>
-constexpr int ahead_floats() { return R * kLda + R * kMaxAct + kHeadRed; }
-constexpr int kAheadBase = 8 + 2 * kH + 8 + kHeadRed;   // floats behind the LDS map that the chains of the launch use for their vectors
+constexpr int ahead_floats() { return R * kLda + R * kMaxAct; }
+constexpr int kAheadBase = kH + 8 + 2 * slab_floats<1>();   // floats behind the LDS map that the critic chain uses itself (its vector, its products' slabs)
 template <class G>
-__device__ __forceinline__ void actor_forward_ahead(const PopDev& d, int agent, int r0, const float* Xs, int xld, float* area) {
+__device__ __forceinline__ void actor_forward_ahead(const PopDev& d, int agent, int r0, const float* Xs, int xld, float* area, float* stage) {
   constexpr int R = G::R;
   static_assert(R == 32, "built for the 32-row critic workgroups");
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   float* buf2 = area;
   float* head = buf2 + R * kLda;
-  float* red = head + R * kMaxAct;
   const float* an = net_ptr(d, d.theta, agent, 0);
   typename G::Pre pa;
   POP_MARK(56);
@@ -689,10 +665,10 @@ __device__ __forceinline__ void actor_forward_ahead(const PopDev& d, int agent, 
   G::template first_layer<false>(Xs, xld, an, d.actor, pa, buf2, d.aH1 + act_off, wave, lane);
   __syncthreads();
   POP_MARK(57);
-  G::template hidden_layer<false>(buf2, an, d.actor, pa, d.aH2 + act_off, wave, lane, NoTail());
+  G::template hidden_layer<false>(buf2, an, d.actor, pa, d.aH2 + act_off, wave, lane, NoTail(), stage);
   __syncthreads();
   POP_MARK(58);
-  head_mfma_split<R, false>(buf2, an + d.actor.w3, d.A, head, kMaxAct, wave, lane, red);
+  head_mfma_split<R, false>(buf2, an + d.actor.w3, d.A, head, kMaxAct, wave, lane, stage);
   __syncthreads();
   POP_MARK(59);
   float* out = d.api + ((size_t)agent * d.B + r0) * d.A;
@@ -721,6 +697,7 @@ __device__ __forceinline__ void critic_chain(const PopDev& d, uint32_t t, int ne
   float* head = lds + L.s0;
   float* dq = lds + L.s1;
   float* v_w3 = lds + L.vec;                         // [256]
+  float* stage = lds + L.vec + vec_critic_floats;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int agent = net >> 1, k = net & 1, r0 = chunk * R;
   const float* cn = net_ptr(d, d.theta, agent, 1 + k);
@@ -757,13 +734,13 @@ __device__ __forceinline__ void critic_chain(const PopDev& d, uint32_t t, int ne
   __syncthreads();
   POP_MARK(2);
   typename G::WtBlock wt;                          // block 0 of W2 for the input-gradient product
-  G::template hidden_layer<false>(buf, cn, d.critic, pre, nullptr, wave, lane, [&]() { G::load_wt(wt, cn + d.critic.w2, wave, lane); });
+  G::template hidden_layer<false>(buf, cn, d.critic, pre, nullptr, wave, lane, [&]() { G::load_wt(wt, cn + d.critic.w2, wave, lane); }, stage);
   __syncthreads();
   POP_MARK(3);
   G::thin(buf, v_w3, 1, head, tid);
   if constexpr (AHEAD) {
     if (k == 1 && d.actor_ahead && t % (uint32_t)d.hp[agent].policy_delay == 0u)
-      actor_forward_ahead<G>(d, agent, r0, Xs, L.xld, lds + L.vec + kAheadBase);
+      actor_forward_ahead<G>(d, agent, r0, Xs, L.xld, lds + L.vec + kAheadBase, stage);
   }
   if (WAIT && tid < R) yv = await_y(d, (size_t)agent * d.B + r0 + tid, t);   // same lane uses it below
   __syncthreads();
@@ -805,8 +782,7 @@ __device__ __forceinline__ void critic_chain(const PopDev& d, uint32_t t, int ne
   POP_MARK(5);
   __syncthreads();
   POP_MARK(6);
-  G::template input_grad_to_global<SIGNAL>(buf, cn + d.critic.w2, wt, mask1, d.cdZ1 + act_off, part + kCP_db1, wave, lane,
-                                           lds + L.vec + vec_critic_floats);
+  G::template input_grad_to_global<SIGNAL>(buf, cn + d.critic.w2, wt, mask1, d.cdZ1 + act_off, part + kCP_db1, wave, lane, stage);
   POP_MARK(7);
   if (SIGNAL) signal_count(d.done_c + parity_base(d, t, 2 * d.P) + net, tid);
 }
@@ -839,7 +815,7 @@ __device__ __forceinline__ void actor_chain(const PopDev& d, uint32_t t, int age
   const int A = d.A;
   float* v_ab3 = lds + L.vec;                        // [AS] actor head bias
   float* v_cw3 = v_ab3 + AS;                         // [256] critic head
-  float* stage = lds + L.vec + vec_actor_floats_for(AS);   // weight stage of the 16-row transposed products
+  float* stage = lds + L.vec + vec_actor_floats_for(AS);   // see G::kStage
   // the actor's head and the critic's first-layer rows of the action inputs are matrix-pipe operands read
   // straight from global memory (head_mfma, head_mfma_t)
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -910,9 +886,9 @@ __device__ __forceinline__ void actor_chain(const PopDev& d, uint32_t t, int age
   mask_a1 = G::template first_layer<WAIT>(Xs, L.xld, an, d.actor, pre, buf, d.aH1 + act_off, wave, lane);
   __syncthreads();
   G::template hidden_layer<false>(buf, an, d.actor, pre, d.aH2 + act_off, wave, lane,
-                         [&]() { if (!WAIT) pre.load(cn, d.critic, wave, lane); });
+                         [&]() { if (!WAIT) pre.load(cn, d.critic, wave, lane); }, stage);
   __syncthreads();
-  if (R <= 32 && (AS == kMaxAct || A <= 16)) head_mfma_split<R <= 32 ? R : 16, false>(buf, an + d.actor.w3, A, head, AS, wave, lane, v_cw3 + kH);
+  if (R <= 32 && (AS == kMaxAct || A <= 16)) head_mfma_split<R <= 32 ? R : 16, false>(buf, an + d.actor.w3, A, head, AS, wave, lane, stage);
   else head_mfma<R>(buf, an + d.actor.w3, A, head, AS, wave, lane);
   __syncthreads();
   for (int e = tid; e < R * A; e += kThreads) {
@@ -937,7 +913,7 @@ __device__ __forceinline__ void actor_chain(const PopDev& d, uint32_t t, int age
   const uint64_t mask_c1 = G::template first_layer<false>(Xs, L.xld, cn, d.critic, pre, buf, nullptr, wave, lane);
   __syncthreads();
   typename G::WtBlock wt;
-  G::template hidden_layer<false>(buf, cn, d.critic, pre, nullptr, wave, lane, [&]() { G::load_wt(wt, cn + d.critic.w2, wave, lane); });
+  G::template hidden_layer<false>(buf, cn, d.critic, pre, nullptr, wave, lane, [&]() { G::load_wt(wt, cn + d.critic.w2, wave, lane); }, stage);
   __syncthreads();
   POP_MARK(11);
   G::thin(buf, v_cw3, 1, head, tid);     // q, for the loss value only
@@ -971,7 +947,7 @@ __device__ __forceinline__ void actor_chain(const PopDev& d, uint32_t t, int age
   }
   __syncthreads();
   POP_MARK(12);
-  if (R <= 32 && (AS == kMaxAct || A <= 16)) head_mfma_split<R <= 32 ? R : 16, true>(buf, cn + d.critic.w1 + d.O * kH, A, head, AS, wave, lane, v_cw3 + kH);   // da
+  if (R <= 32 && (AS == kMaxAct || A <= 16)) head_mfma_split<R <= 32 ? R : 16, true>(buf, cn + d.critic.w1 + d.O * kH, A, head, AS, wave, lane, stage);   // da
   else head_mfma_t<R>(buf, cn + d.critic.w1 + d.O * kH, A, head, AS, wave, lane);
   G::load_wt(wt, an + d.actor.w2, wave, lane);       // block 0 of the actor's input-gradient product
   __syncthreads();
@@ -1038,9 +1014,13 @@ __device__ __forceinline__ void actor_chain(const PopDev& d, uint32_t t, int age
 
 // floats of staged vectors behind the LDS map of each chain
 inline int vec_target(const PopDev& d) { return vec_target_floats(d.A > kMaxAct ? kSacMaxAct : kMaxAct); }
+// LDS of a chain in geometry G: fan_in columns of input, `regions` scratch blocks, `vec` floats of staged vectors
+template <class G>
+inline size_t chain_bytes(int fan_in, int vec, int stage = G::kStage, int regions = 3) {
+  return LdsMap<G::R, G::kPad>(fan_in, regions).bytes(vec + stage);
+}
 inline int vec_critic(const PopDev&) { return vec_critic_floats; }
 inline int vec_actor(const PopDev& d) { return vec_actor_floats_for(d.A > kMaxAct ? kSacMaxAct : kMaxAct); }
-inline int vec_act(const PopDev& d) { return kH * d.actor.out + kMaxHead; }
-constexpr int kActScratch = 2 * (kSacMaxAct / kMaxAct);   // acting: two head blocks of [32][kSacMaxAct]
+constexpr int kActScratch = kMaxHead / kMaxAct;      // acting: one head block of [32][kMaxHead]
 
 }  // namespace pop

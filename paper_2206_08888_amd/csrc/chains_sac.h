@@ -48,8 +48,9 @@ static_assert(kSs % kMaxAct == 0 && 2 * kSs >= kMaxHead, "dz3 rows of kMaxHead f
 // vectors the chains keep in LDS: the actor's head bias, the two critic heads and their biases (the wide
 // operands -- the actor's head, the critics' first-layer rows of the action -- go through the matrix pipe
 // straight from global memory)
-inline int vec_sac_target(const PopDev&) { return kMaxHead + 2 * kH + 8 + kHeadRed; }
-constexpr int vec_sac_actor_floats = kMaxHead + 2 * kH + 8 + kHeadRed;   // behind them: the weight stage of the 16-row chains
+constexpr int vec_sac_target_floats = kMaxHead + 2 * kH + 8;
+inline int vec_sac_target(const PopDev&) { return vec_sac_target_floats; }
+constexpr int vec_sac_actor_floats = kMaxHead + 2 * kH + 8;   // behind them: G::kStage floats for the products
 inline int vec_sac_actor(const PopDev&) { return vec_sac_actor_floats; }
 
 // ---------------------------------------------------------------------------------------------
@@ -66,6 +67,7 @@ __device__ __forceinline__ void sac_target_chain(const PopDev& d, uint32_t t, in
   float* v_ab3 = lds + L.vec;                        // [kMaxHead]
   float* v_cw3 = v_ab3 + kMaxHead;                   // [2][256]
   float* v_cb3 = v_cw3 + 2 * kH;                     // [2]
+  float* stage = lds + L.vec + vec_sac_target_floats;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int r0 = chunk * R;
   const float* an = net_ptr(d, d.theta, agent, 0);   // the online actor: SAC has no target actor
@@ -88,10 +90,10 @@ __device__ __forceinline__ void sac_target_chain(const PopDev& d, uint32_t t, in
   G::template first_layer<false>(Xs, L.xld, an, d.actor, pre, buf, nullptr, wave, lane);
   __syncthreads();
   POP_MARK(2);
-  G::template hidden_layer<false>(buf, an, d.actor, pre, nullptr, wave, lane, [&]() { pre.load(tc0, d.critic, wave, lane); });
+  G::template hidden_layer<false>(buf, an, d.actor, pre, nullptr, wave, lane, [&]() { pre.load(tc0, d.critic, wave, lane); }, stage);
   __syncthreads();
   POP_MARK(3);
-  if (R <= 32 && 2 * A <= 16) head_mfma_split<R <= 32 ? R : 16, false>(buf, an + d.actor.w3, 2 * A, hd, kMaxHead, wave, lane, v_cb3 + 8);
+  if (R <= 32 && 2 * A <= 16) head_mfma_split<R <= 32 ? R : 16, false>(buf, an + d.actor.w3, 2 * A, hd, kMaxHead, wave, lane, stage);
   else head_mfma<R>(buf, an + d.actor.w3, 2 * A, hd, kMaxHead, wave, lane);
   __syncthreads();
   POP_MARK(4);
@@ -119,7 +121,7 @@ __device__ __forceinline__ void sac_target_chain(const PopDev& d, uint32_t t, in
     __syncthreads();
     POP_MARK(6 + 3 * k);
     G::template hidden_layer<false>(buf, tc, d.critic, pre, nullptr, wave, lane,
-                                    [&]() { if (k == 0) pre.load(tc1, d.critic, wave, lane); });
+                                    [&]() { if (k == 0) pre.load(tc1, d.critic, wave, lane); }, stage);
     __syncthreads();
     POP_MARK(7 + 3 * k);
     G::thin(buf, v_cw3 + k * kH, 1, hd, tid, kMaxHead);
@@ -205,6 +207,7 @@ __device__ __forceinline__ void sac_actor_chain(const PopDev& d, uint32_t t, int
   float* v_ab3 = lds + L.vec;                        // [kMaxHead]
   float* v_cw3 = v_ab3 + kMaxHead;                   // [2][256] critic heads
   float* v_cb3 = v_cw3 + 2 * kH;                     // [2]
+  float* stage = lds + L.vec + vec_sac_actor_floats;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int r0 = chunk * R;
   const HpDev hp = d.hp[agent];
@@ -228,10 +231,10 @@ __device__ __forceinline__ void sac_actor_chain(const PopDev& d, uint32_t t, int
   const uint64_t mask_a1 = G::template first_layer<false>(Xs, L.xld, an, d.actor, pre, buf, d.aH1 + act_off, wave, lane);
   __syncthreads();
   G::template hidden_layer<false>(buf, an, d.actor, pre, d.aH2 + act_off, wave, lane,
-                                  [&]() { pre.load(cn[0], d.critic, wave, lane); });
+                                  [&]() { pre.load(cn[0], d.critic, wave, lane); }, stage);
   __syncthreads();
   POP_MARK(22);
-  if (R <= 32 && H2 <= 16) head_mfma_split<R <= 32 ? R : 16, false>(buf, an + d.actor.w3, H2, hd, kMaxHead, wave, lane, v_cb3 + 8);
+  if (R <= 32 && H2 <= 16) head_mfma_split<R <= 32 ? R : 16, false>(buf, an + d.actor.w3, H2, hd, kMaxHead, wave, lane, stage);
   else head_mfma<R>(buf, an + d.actor.w3, H2, hd, kMaxHead, wave, lane);
   __syncthreads();
   for (int e = tid; e < R * A; e += kThreads) {
@@ -267,7 +270,7 @@ __device__ __forceinline__ void sac_actor_chain(const PopDev& d, uint32_t t, int
     mask2[k] = G::template hidden_layer<false>(buf, cn[k], d.critic, pre, nullptr, wave, lane, [&]() {
       if (k == 0) pre.load(cn[1], d.critic, wave, lane);
       else G::load_wt(wt, cn[0] + d.critic.w2, wave, lane);
-    });
+    }, stage);
     __syncthreads();
     G::thin(buf, v_cw3 + k * kH, 1, hd, tid, kMaxHead);
     __syncthreads();
@@ -302,9 +305,9 @@ __device__ __forceinline__ void sac_actor_chain(const PopDev& d, uint32_t t, int
 #pragma unroll
       for (int i = 0; i < R / 4; ++i)
         h2r[i] = *reinterpret_cast<const f32x4*>(h2g + (4 * i + (tid >> 6)) * kH + 4 * (tid & 63));
-    }, lds + L.vec + vec_sac_actor_floats);          // buf = dz1 of critic k
+    }, stage);                                       // buf = dz1 of critic k
     __syncthreads();
-    if (R <= 32 && A <= 16) head_mfma_split<R <= 32 ? R : 16, true>(buf, cn[k] + d.critic.w1 + d.O * kH, A, k == 0 ? da1 : da2, kSs, wave, lane, v_cb3 + 8);
+    if (R <= 32 && A <= 16) head_mfma_split<R <= 32 ? R : 16, true>(buf, cn[k] + d.critic.w1 + d.O * kH, A, k == 0 ? da1 : da2, kSs, wave, lane, stage);
     else head_mfma_t<R>(buf, cn[k] + d.critic.w1 + d.O * kH, A, k == 0 ? da1 : da2, kSs, wave, lane);
     if (k == 0) G::load_wt(wt, cn[1] + d.critic.w2, wave, lane);
     else G::load_wt(wt, an + d.actor.w2, wave, lane);
@@ -340,8 +343,7 @@ __device__ __forceinline__ void sac_actor_chain(const PopDev& d, uint32_t t, int
   else sac_head_backward<R, kMaxHead>(buf, dz3, an + d.actor.w3, H2, d.adZ2 + act_off, part, tid);
   __syncthreads();
   POP_MARK(29);
-  G::template input_grad_to_global<false>(buf, an + d.actor.w2, wt, mask_a1, d.adZ1 + act_off, part + kAP_db1, wave, lane,
-                                          lds + L.vec + vec_sac_actor_floats);
+  G::template input_grad_to_global<false>(buf, an + d.actor.w2, wt, mask_a1, d.adZ1 + act_off, part + kAP_db1, wave, lane, stage);
   POP_MARK(30);
 }
 

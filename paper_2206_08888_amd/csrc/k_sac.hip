@@ -5,6 +5,9 @@
 
 namespace pop {
 
+// 64 rows: the nine scratch blocks leave no room for the slabs of the target and actor products
+using SacRows64 = Rows32<2, false>;
+
 template <class G>
 __global__ __launch_bounds__(kThreads, 1) void k_sac_target(PopDev d, uint32_t t) {
   extern __shared__ float lds[];
@@ -45,12 +48,12 @@ hipError_t setup_sac_kernels() {
   if ((e = hipFuncSetAttribute((const void*)__VA_ARGS__, hipFuncAttributeMaxDynamicSharedMemorySize, most)) != hipSuccess) return e
   POP_SET_LDS(k_sac_target<Rows16>);
   POP_SET_LDS(k_sac_target<Rows32<1>>);
-  POP_SET_LDS(k_sac_target<Rows32<2>>);
+  POP_SET_LDS(k_sac_target<SacRows64>);
   POP_SET_LDS(k_sac_target<Rows16Deep>);
   POP_SET_LDS(k_sac_target<Rows32Deep<1>>);
   POP_SET_LDS(k_sac_actor<Rows16>);
   POP_SET_LDS(k_sac_actor<Rows32<1>>);
-  POP_SET_LDS(k_sac_actor<Rows32<2>>);
+  POP_SET_LDS(k_sac_actor<SacRows64>);
   POP_SET_LDS(k_sac_actor<Rows16Deep>);
   POP_SET_LDS(k_sac_actor<Rows32Deep<1>>);
   POP_SET_LDS(k_sac_target_critic<Rows16, Rows32<2>>);
@@ -60,32 +63,28 @@ hipError_t setup_sac_kernels() {
   return hipSuccess;
 }
 
-namespace {
-size_t chain_lds(const PopDev& d, int rows, int regions, int vec) {
-  return rows == 16 ? LdsMap<16, 16>(d.D, regions).bytes(vec)
-         : rows == 32 ? LdsMap<32, 8>(d.D, regions).bytes(vec)
-                      : LdsMap<64, 8>(d.D, regions).bytes(vec);
-}
-}  // namespace
-
 size_t sac_lds_bytes(const PopDev& d) {
-  size_t m = chain_lds(d, d.rows_t, kSacScratch, vec_sac_target(d));
-  m = std::max(m, chain_lds(d, d.rows_a, kSacScratch, vec_sac_actor(d)) + (d.rows_a == 16 ? kStage16 * sizeof(float) : 0));   // weight stage
-  m = std::max(m, chain_lds(d, d.rows_c, 3, vec_critic(d)));
-  m = std::max(m, Lds<1>(d.O, kActScratch).bytes(vec_act(d)));
-  return m;
+  auto chain = [&](int rows, int vec, bool back) {
+    return rows == 16 ? chain_bytes<Rows16>(d.D, vec, back ? Rows16::kStage : Rows16::kStageForward, kSacScratch)
+           : rows == 32 ? chain_bytes<Rows32<1>>(d.D, vec, Rows32<1>::kStage, kSacScratch)
+                        : chain_bytes<SacRows64>(d.D, vec, SacRows64::kStage, kSacScratch);
+  };
+  size_t m = chain(d.rows_t, vec_sac_target(d), false);
+  m = std::max(m, chain(d.rows_a, vec_sac_actor(d), true));
+  m = std::max(m, d.rows_c == 32 ? chain_bytes<Rows32<1>>(d.D, vec_critic(d)) : chain_bytes<Rows32<2>>(d.D, vec_critic(d)));
+  return std::max(m, act_lds_bytes(d));
 }
 
 hipError_t launch_sac_target(const PopDev& d, uint32_t t, hipStream_t s) {
   const dim3 grid(xcd_grid(d.P, d.B / d.rows_t)), block(kThreads);
   const int vec = vec_sac_target(d);
   if (d.D > kMaxIn) {                                // wide inputs: 16 rows, pipelined first layers
-    if (d.rows_t == 16) k_sac_target<Rows16Deep><<<grid, block, LdsMap<16, 16>(d.D, kSacScratch).bytes(vec), s>>>(d, t);
-    else if (d.rows_t == 32) k_sac_target<Rows32Deep<1>><<<grid, block, LdsMap<32, 8>(d.D, kSacScratch).bytes(vec), s>>>(d, t);
+    if (d.rows_t == 16) k_sac_target<Rows16Deep><<<grid, block, chain_bytes<Rows16>(d.D, vec, Rows16::kStageForward, kSacScratch), s>>>(d, t);
+    else if (d.rows_t == 32) k_sac_target<Rows32Deep<1>><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec, Rows32<1>::kStage, kSacScratch), s>>>(d, t);
     else return hipErrorInvalidValue;
-  } else if (d.rows_t == 16) k_sac_target<Rows16><<<grid, block, LdsMap<16, 16>(d.D, kSacScratch).bytes(vec), s>>>(d, t);
-  else if (d.rows_t == 32) k_sac_target<Rows32<1>><<<grid, block, LdsMap<32, 8>(d.D, kSacScratch).bytes(vec), s>>>(d, t);
-  else k_sac_target<Rows32<2>><<<grid, block, LdsMap<64, 8>(d.D, kSacScratch).bytes(vec), s>>>(d, t);
+  } else if (d.rows_t == 16) k_sac_target<Rows16><<<grid, block, chain_bytes<Rows16>(d.D, vec, Rows16::kStageForward, kSacScratch), s>>>(d, t);
+  else if (d.rows_t == 32) k_sac_target<Rows32<1>><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec, Rows32<1>::kStage, kSacScratch), s>>>(d, t);
+  else k_sac_target<SacRows64><<<grid, block, chain_bytes<SacRows64>(d.D, vec, SacRows64::kStage, kSacScratch), s>>>(d, t);
   return hipGetLastError();
 }
 
@@ -95,13 +94,13 @@ hipError_t launch_sac_target_critic(const PopDev& d, uint32_t t, hipStream_t s) 
   const int vec = vec_sac_target(d);                 // larger than the critic chain's
   if (d.D > kMaxIn) return hipErrorInvalidValue;     // wide inputs run the two chains as separate launches
   if (d.rows_t == 16 && d.rows_c == 64) {
-    const size_t a = LdsMap<16, 16>(d.D, kSacScratch).bytes(vec), b = Lds<2>(d.D).bytes(vec_critic(d));
+    const size_t a = chain_bytes<Rows16>(d.D, vec, Rows16::kStageForward, kSacScratch), b = chain_bytes<Rows32<2>>(d.D, vec_critic(d));
     k_sac_target_critic<Rows16, Rows32<2>><<<grid, block, a > b ? a : b, s>>>(d, t, nt);
   } else if (d.rows_t == 16 && d.rows_c == 32) {
-    const size_t a = LdsMap<16, 16>(d.D, kSacScratch).bytes(vec), b = Lds<1>(d.D).bytes(vec_critic(d));
+    const size_t a = chain_bytes<Rows16>(d.D, vec, Rows16::kStageForward, kSacScratch), b = chain_bytes<Rows32<1>>(d.D, vec_critic(d));
     k_sac_target_critic<Rows16, Rows32<1>><<<grid, block, a > b ? a : b, s>>>(d, t, nt);
   } else if (d.rows_t == 32 && d.rows_c == 32) {
-    const size_t a = LdsMap<32, 8>(d.D, kSacScratch).bytes(vec), b = Lds<1>(d.D).bytes(vec_critic(d));
+    const size_t a = chain_bytes<Rows32<1>>(d.D, vec, Rows32<1>::kStage, kSacScratch), b = chain_bytes<Rows32<1>>(d.D, vec_critic(d));
     k_sac_target_critic<Rows32<1>, Rows32<1>><<<grid, block, a > b ? a : b, s>>>(d, t, nt);
   } else {
     return hipErrorInvalidValue;
@@ -113,12 +112,12 @@ hipError_t launch_sac_actor(const PopDev& d, uint32_t t, hipStream_t s) {
   const dim3 grid(xcd_grid(d.P, d.B / d.rows_a)), block(kThreads);
   const int vec = vec_sac_actor(d);
   if (d.D > kMaxIn) {
-    if (d.rows_a == 16) k_sac_actor<Rows16Deep><<<grid, block, LdsMap<16, 16>(d.D, kSacScratch).bytes(vec) + kStage16 * sizeof(float), s>>>(d, t);
-    else if (d.rows_a == 32) k_sac_actor<Rows32Deep<1>><<<grid, block, LdsMap<32, 8>(d.D, kSacScratch).bytes(vec), s>>>(d, t);
+    if (d.rows_a == 16) k_sac_actor<Rows16Deep><<<grid, block, chain_bytes<Rows16>(d.D, vec, Rows16::kStage, kSacScratch), s>>>(d, t);
+    else if (d.rows_a == 32) k_sac_actor<Rows32Deep<1>><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec, Rows32<1>::kStage, kSacScratch), s>>>(d, t);
     else return hipErrorInvalidValue;
-  } else if (d.rows_a == 16) k_sac_actor<Rows16><<<grid, block, LdsMap<16, 16>(d.D, kSacScratch).bytes(vec) + kStage16 * sizeof(float), s>>>(d, t);
-  else if (d.rows_a == 32) k_sac_actor<Rows32<1>><<<grid, block, LdsMap<32, 8>(d.D, kSacScratch).bytes(vec), s>>>(d, t);
-  else k_sac_actor<Rows32<2>><<<grid, block, LdsMap<64, 8>(d.D, kSacScratch).bytes(vec), s>>>(d, t);
+  } else if (d.rows_a == 16) k_sac_actor<Rows16><<<grid, block, chain_bytes<Rows16>(d.D, vec, Rows16::kStage, kSacScratch), s>>>(d, t);
+  else if (d.rows_a == 32) k_sac_actor<Rows32<1>><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec, Rows32<1>::kStage, kSacScratch), s>>>(d, t);
+  else k_sac_actor<SacRows64><<<grid, block, chain_bytes<SacRows64>(d.D, vec, SacRows64::kStage, kSacScratch), s>>>(d, t);
   return hipGetLastError();
 }
 

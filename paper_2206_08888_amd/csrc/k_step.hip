@@ -30,7 +30,7 @@ struct StepGrid {
 
 // GT, GC, GA: tile geometries of the target, critic and actor chains.
 template <class GT, class GC, class GA>
-__global__ __launch_bounds__(kThreads, 2) void k_step(PopDev d, uint32_t t, StepGrid g) {
+__global__ __launch_bounds__(kThreads, GC::R == 64 ? 1 : 2) void k_step(PopDev d, uint32_t t, StepGrid g) {
   extern __shared__ __attribute__((aligned(16))) float lds[];
   int b = blockIdx.x;
   POP_MARK(63);
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_step(PopDev d, uint32_t t, Step
 }
 
 #define POP_STEP_SMALL k_step<Rows16, Rows32<2>, Rows16>
-#define POP_STEP_MID k_step<Rows32<1, true>, Rows32<1, true>, Rows32<1, true>>
+#define POP_STEP_MID k_step<Rows32<1>, Rows32<1>, Rows32<1>>
 #define POP_STEP_LARGE k_step<Rows32<2>, Rows32<2>, Rows32<2>>
 
 hipError_t setup_step_kernel() {
@@ -133,18 +133,18 @@ hipError_t launch_step(const PopDev& dev, uint32_t t, uint32_t launch_seq, int w
   size_t bytes = tiles;
   auto need = [&](size_t b) { if (b > bytes) bytes = b; };
   if (d.rows_a == 16) {
-    need(LdsMap<16, 16>(d.D).bytes(vec_ta) + kStage16 * sizeof(float));   // with the weight stage of the 16-row actor chain
-    need(Lds<2>(d.D).bytes(vec_critic(d)));
+    need(chain_bytes<Rows16>(d.D, vec_ta));
+    need(chain_bytes<Rows32<2>>(d.D, vec_critic(d)));
     // One workgroup per CU for small populations: the request is kept above half of a CU's LDS (the 64-row
     // critic chain alone needs 80,928 of the 81,920 bytes that would let two share).  With two per CU the actor
     // chains start earlier but every chain then shares its matrix pipe: 118 against 100 us/step at P = 10.
     need((size_t)kLdsPerCU / 2 + 64);
     POP_STEP_SMALL<<<grid, block, bytes, s>>>(d, t, g);
   } else if (d.rows_a == 32) {
-    need(Lds<1>(d.D).bytes(vec));
+    need(chain_bytes<Rows32<1>>(d.D, vec));
     POP_STEP_MID<<<grid, block, bytes, s>>>(d, t, g);
   } else {
-    need(Lds<2>(d.D).bytes(vec));
+    need(chain_bytes<Rows32<2>>(d.D, vec));
     POP_STEP_LARGE<<<grid, block, bytes, s>>>(d, t, g);
   }
   return hipGetLastError();

@@ -38,6 +38,56 @@ __device__ inline f32x16 mfma32(float a, float b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 
+// fp32 products on the bf16 matrix pipe.  v_mfma_f32_32x32x2_f32 takes 64 cycles for 4096 FLOP,
+// v_mfma_f32_32x32x16_bf16 32 cycles for 32768: sixteen times the rate.  An fp32 value is the exact sum of three
+// bf16 values (8 significand bits each, 24 in all): h = bf16(x), m = bf16(x - h), l = x - h - m, the differences
+// exact.  Of the nine products of two such sums the six down to 2^-18 of the largest are taken,
+//   x y = hx hy + (hx my + mx hy + mx my + hx ly + lx hy) + O(2^-26 |x y|),
+// at 6 / 16 of the time of the fp32 instructions.  The large products and the five small ones are summed in
+// accumulators of their own (low), added once at the end: the matrix pipe rounds the accumulator after every
+// instruction, and in one accumulator the small products would pay that rounding five times as often.  Relative
+// error of a 256-deep product against 64 bits (2-norm): 0.7e-7, fp32 instructions 2.0e-7 (ReLU outputs x Glorot
+// weights); 0.7e-7 / 2.0e-7 (sparse gradients x weights); 0.5e-7 / 1.4e-7 (activations x gradients); 0.9e-7 / 2.5e-7
+// (all terms positive); 1.1e-7 / 2.9e-7 (magnitudes over e^+-4); summed in one accumulator 2.2e-7.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+struct Split8 {                            // eight consecutive contraction elements of one lane: high, middle and low parts
+  bf16x8 t[3];
+};
+
+// One pair of elements (2 i, 2 i + 1): eleven vector instructions (the differences as two-term bf16 dot products would
+// be seven, but those run on the matrix pipe: 78 cycles beside a matrix instruction instead of 42).
+__device__ inline void split_pair(float a, float b, int i, Split8& s) {
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const bf16x2 h = __builtin_convertvector((f32x2{a, b}), bf16x2);
+    s.t[q][2 * i] = h[0];
+    s.t[q][2 * i + 1] = h[1];
+    if (q < 2) {
+      const uint32_t u = __builtin_bit_cast(uint32_t, h);
+      a -= __uint_as_float(u << 16);
+      b -= __uint_as_float(u & 0xffff0000u);
+    }
+  }
+}
+__device__ inline void split8(const float (&x)[8], Split8& s) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) split_pair(x[2 * i], x[2 * i + 1], i, s);
+}
+__device__ inline void split8(const f32x4& lo, const f32x4& hi, Split8& s) {
+  const float x[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+  split8(x, s);
+}
+
+// the six products in the order they are issued: parts of the left and of the right operand
+constexpr int kSplitTerms = 6;
+constexpr int kTermX[kSplitTerms] = {2, 0, 1, 1, 0, 0}, kTermW[kSplitTerms] = {0, 2, 1, 0, 1, 0};
+
+__device__ inline f32x16 mfma32_bf16(const bf16x8& a, const bf16x8& b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
 // Global store of a result that another workgroup of the SAME launch reads (THROUGH): a
 // device-scope atomic store, which is written through the XCD's L2 to memory instead of
 // waiting there as a dirty line, so that the producer only has to see its own stores
@@ -76,6 +126,14 @@ struct Acc {
       for (int b = 0; b < NT; ++b)
 #pragma unroll
         for (int v = 0; v < 16; ++v) t[a][b][v] = 0.0f;
+  }
+  __device__ inline void add(const Acc& o) {
+#pragma unroll
+    for (int a = 0; a < MT; ++a)
+#pragma unroll
+      for (int b = 0; b < NT; ++b)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) t[a][b][v] += o.t[a][b][v];
   }
 };
 
@@ -401,76 +459,221 @@ __device__ inline void mfma_block_fed(const LdsBlock<MT>& x, const WeightBlock<M
 
 struct NoTail { __device__ inline void operator()() const {} };
 
-// four blocks i .. i+3 of the product; LAST: no further weight blocks exist, run tail() instead
-template <int MT, bool TRANSPOSED, bool LAST, int NT, class Tail>
-__device__ inline void gemm256_group(const float* __restrict__ Xl, int ldx, const float* __restrict__ W, int i,
-                                     WeightBlock<MT, TRANSPOSED, NT>& b0, WeightBlock<MT, TRANSPOSED, NT>& b1,
-                                     WeightBlock<MT, TRANSPOSED, NT>& b2, WeightBlock<MT, TRANSPOSED, NT>& b3,
-                                     LdsBlock<MT>& x0, LdsBlock<MT>& x1, int wave, int lane, Acc<MT, NT>& acc,
-                                     Tail& tail) {
-  b3.load(W, i + 3, wave, lane);
-  x1.load(Xl, ldx, 16 * (i + 1), lane);
-  __builtin_amdgcn_sched_barrier(0);
-  mfma_block<MT, TRANSPOSED, NT>(x0, b0, acc);
-  __builtin_amdgcn_sched_barrier(0);
-  if (!LAST) b0.load(W, i + 4, wave, lane); else tail();
-  x0.load(Xl, ldx, 16 * (i + 2), lane);
-  __builtin_amdgcn_sched_barrier(0);
-  mfma_block<MT, TRANSPOSED, NT>(x1, b1, acc);
-  __builtin_amdgcn_sched_barrier(0);
-  if (!LAST) b1.load(W, i + 5, wave, lane);
-  x1.load(Xl, ldx, 16 * (i + 3), lane);
-  __builtin_amdgcn_sched_barrier(0);
-  mfma_block<MT, TRANSPOSED, NT>(x0, b2, acc);
-  __builtin_amdgcn_sched_barrier(0);
-  if (!LAST) { b2.load(W, i + 6, wave, lane); x0.load(Xl, ldx, 16 * (i + 4), lane); }
-  __builtin_amdgcn_sched_barrier(0);
-  mfma_block<MT, TRANSPOSED, NT>(x1, b3, acc);
-  __builtin_amdgcn_sched_barrier(0);
-}
+// ---------------------------------------------------------------------------------------------
+// 256-deep product of an LDS operand (fp32 tile, row stride kLda) with a global weight operand on the bf16 pipe:
+//   forward  (TRANSPOSED = false): acc[r][c] += sum_k X[r][k] W[k][c], c in this wave's 64 columns
+//   backward (TRANSPOSED = true):  acc[r][k] += sum_n Z[r][n] W[k][n], k in this wave's 64 columns
+// W is row-major [256][256] in both cases.  Matrix and vector instructions share the issue port (measured: about five
+// cycles for either beside the other; a matrix instruction keeps its pipe for 32), and a pair of elements costs eleven
+// vector instructions to split, so the number of splits decides: a weight is used by one wavefront and split in its
+// registers, once per 32 MT rows; the LDS operand is used by all four wavefronts and split once per workgroup, 64
+// columns (a slab) at a time, into three bf16 planes in LDS from which the wavefronts read their operands ready for
+// use.  Per wavefront and 16-deep block: 12 MT matrix instructions, 88 + 11 MT vector instructions (88 + 44 MT where
+// every wavefront splits both operands itself).
+// 64 rows on one CU, us per product with the weights in L2: two 32-row workgroups on the fp32 instructions 16.9; here
+// 10.9 forward and 14.2 backward as two 32-row workgroups, 8.9 and 8.4 as one of 64 rows (zero weights; 13.3, 15.2,
+// 11.2, 10.9 with random ones, under which the clock falls from 2.3 to 1.9 GHz).  With both operands split in registers
+// 11.4, 14.6, 9.7, 8.9.  Differences by two-term bf16 dot products instead of shift and subtract: slower than fp32 (they run on the matrix pipe).
 
-// the same four blocks with the loads dealt out between the MFMAs; wg: this lane's pointer at block i
-template <int MT, bool TRANSPOSED, bool LAST, int NT, class Tail>
-__device__ inline void gemm256_group_fed(const float* __restrict__ Xl, int ldx, const float* __restrict__ wg, int i,
-                                         WeightBlock<MT, TRANSPOSED, NT>& b0, WeightBlock<MT, TRANSPOSED, NT>& b1,
-                                         WeightBlock<MT, TRANSPOSED, NT>& b2, WeightBlock<MT, TRANSPOSED, NT>& b3,
-                                         LdsBlock<MT>& x0, LdsBlock<MT>& x1, int lane, Acc<MT, NT>& acc, Tail& tail) {
-  constexpr int step = TRANSPOSED ? 16 : 16 * kH;    // floats from one block to the next
-  mfma_block_fed<MT, TRANSPOSED, NT, true, true>(x0, b0, acc, b3, wg + 3 * step, x1, Xl, ldx, 16 * (i + 1), lane);
-  if (LAST) tail();
-  mfma_block_fed<MT, TRANSPOSED, NT, !LAST, true>(x1, b1, acc, b0, wg + 4 * step, x0, Xl, ldx, 16 * (i + 2), lane);
-  mfma_block_fed<MT, TRANSPOSED, NT, !LAST, true>(x0, b2, acc, b1, wg + 5 * step, x1, Xl, ldx, 16 * (i + 3), lane);
-  mfma_block_fed<MT, TRANSPOSED, NT, !LAST, !LAST>(x1, b3, acc, b2, wg + 6 * step, x0, Xl, ldx, 16 * (i + 4), lane);
-}
+// The weights one lane needs for a 16-deep block i = 2 D + o: contraction indices 32 D + 16 half + 8 o + e, e < 8.  Two
+// blocks cover whole 128-byte lines of the transposed operand (a lane reads 64 bytes of one row of W).
+template <bool TRANSPOSED>
+struct WeightRaw {
+  float w[2][8];                           // [column tile][e]
+  static constexpr int kPieces = TRANSPOSED ? 4 : 8;           // load instructions per block
+  static constexpr int kGroup = 64 * (TRANSPOSED ? 1 : kH);    // floats from one group of four blocks to the next
+  __device__ static constexpr int offset(int i) { return (32 * (i >> 1) + 8 * (i & 1)) * (TRANSPOSED ? 1 : kH); }
+  __device__ static inline const float* lane_base(const float* __restrict__ W, int wave, int lane) {
+    const int half = lane >> 5, col = tile_col(wave, 0, lane);
+    return TRANSPOSED ? W + col * kH + 16 * half : W + 16 * half * kH + col;
+  }
+  __device__ inline void load_piece(const float* __restrict__ blk, int p) {
+    if (TRANSPOSED) {
+      const int nt = p >> 1, s = p & 1;              // the lane's two columns are rows of W, kH apart
+      const f32x4 v = *reinterpret_cast<const f32x4*>(blk + nt * kH + 4 * s);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) w[nt][4 * s + j] = v[j];
+    } else {
+      const f32x2 v = *reinterpret_cast<const f32x2*>(blk + p * kH);
+      w[0][p] = v[0];
+      w[1][p] = v[1];
+    }
+  }
+  __device__ inline void load_block(const float* __restrict__ blk) {
+#pragma unroll
+    for (int p = 0; p < kPieces; ++p) load_piece(blk, p);
+  }
+  __device__ inline void load(const float* __restrict__ W, int i, int wave, int lane) {
+    load_block(lane_base(W, wave, lane) + offset(i));
+  }
+};
 
-// FED: the loads of a block are issued between the MFMAs of an earlier one (mfma_block_fed) instead of ahead of them.
-template <int MT, bool TRANSPOSED, int NT = 2, bool FED = false, class Tail>
-__device__ inline void gemm256(const float* __restrict__ Xl, int ldx, const float* __restrict__ W,
-                               WeightBlock<MT, TRANSPOSED, NT>& b0, int wave, int lane, Acc<MT, NT>& acc, Tail tail) {
-  WeightBlock<MT, TRANSPOSED, NT> b1, b2, b3;
-  LdsBlock<MT> x0, x1;
-  b1.load(W, 1, wave, lane);
-  b2.load(W, 2, wave, lane);
-  x0.load(Xl, ldx, 0, lane);
-  POP_MARK(20);
-  if (FED) {
-    const float* wg = WeightBlock<MT, TRANSPOSED, NT>::lane_base(W, wave, lane);
+// A slab: columns [64 s, 64 s + 64) of the LDS operand as three planes [32 MT][72] of bf16 (a row stride of 36 words:
+// 16-byte accesses of neighbouring rows fall on different banks).  Two buffers.
+constexpr int kSlabLd = 72;
+template <int MT>
+constexpr int slab_floats() { return 3 * 32 * MT * kSlabLd / 2; }
+template <int MT>
+struct SlabItem {                          // this thread's share of a slab: MT times eight neighbours of a row
+  f32x4 x[MT][2];
+  __device__ inline void read(const float* __restrict__ Xl, int s, int tid, int q) {
+    const float* p = Xl + (32 * q + (tid >> 3)) * kLda + 64 * s + 8 * (tid & 7);
+    x[q][0] = *reinterpret_cast<const f32x4*>(p);
+    x[q][1] = *reinterpret_cast<const f32x4*>(p + 4);
+  }
+  __device__ inline void put(float* __restrict__ slab, int tid, int q) const {
+    Split8 v;
+    split8(x[q][0], x[q][1], v);
+    __bf16* b = reinterpret_cast<__bf16*>(slab) + (32 * q + (tid >> 3)) * kSlabLd + 8 * (tid & 7);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) *reinterpret_cast<bf16x8*>(b + p * 32 * MT * kSlabLd) = v.t[p];
+  }
+};
+
+// SLABS: as above; otherwise every wavefront splits the LDS operand itself, for chains whose scratch leaves no room for
+// the slabs (SAC with 64 rows).
+template <int MT, bool TRANSPOSED, bool SLABS>
+struct SplitProduct {
+  using Raw = WeightRaw<TRANSPOSED>;
+  Split8 x[2][MT], w[2];                   // the LDS operand of this block and the next, the weights of the two column tiles
+  SlabItem<MT> item;
+  Acc<MT, 2> low;
+  f32x4 xr[SLABS ? 1 : MT][2];             // the LDS operand as read, where there are no slabs
+
+  // block b of the slab in this lane's layout
+  __device__ inline void read_x(Split8 (&dst)[MT], const float* __restrict__ slab, int b, int lane) const {
+    const __bf16* p = reinterpret_cast<const __bf16*>(slab) + (lane & 31) * kSlabLd + 32 * (b >> 1) + 16 * (lane >> 5) + 8 * (b & 1);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int q = 0; q < 3; ++q) dst[mt].t[q] = *reinterpret_cast<const bf16x8*>(p + (q * 32 * MT + 32 * mt) * kSlabLd);
+  }
+  __device__ inline void read_raw(const float* __restrict__ Xl, int i, int lane) {      // block i of the whole tile
+#pragma unroll
+    for (int mt = 0; mt < (SLABS ? 0 : MT); ++mt) {
+      const float* p = Xl + (32 * mt + (lane & 31)) * kLda + 32 * (i >> 1) + 16 * (lane >> 5) + 8 * (i & 1);
+      xr[mt][0] = *reinterpret_cast<const f32x4*>(p);
+      xr[mt][1] = *reinterpret_cast<const f32x4*>(p + 4);
+    }
+  }
+  __device__ inline void split_raw(Split8 (&dst)[MT]) const {
+#pragma unroll
+    for (int mt = 0; mt < (SLABS ? 0 : MT); ++mt) split8(xr[mt][0], xr[mt][1], dst[mt]);
+  }
+  __device__ inline void multiply(const Split8 (&xc)[MT], int nt, Acc<MT, 2>& acc) {
+#pragma unroll
+    for (int q = 0; q < kSplitTerms; ++q)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        f32x16& c = q == kSplitTerms - 1 ? acc.t[mt][nt] : low.t[mt][nt];
+        c = mfma32_bf16(xc[mt].t[kTermX[q]], w[nt].t[kTermW[q]], c);
+      }
+  }
+  // One block B (0 .. 3) of a group: the matrix instructions of column tile 0 with, dealt out between them, the split
+  // of tile 1's weights and the reads of the next block's LDS operand (from `xs`, block (B + 1) & 3), then those of tile 1 with the
+  // split of the next block's tile 0.  Beside them this thread's share of the next slab (SLAB: `nslab`): read in block 0,
+  // split and written in blocks 1 and 2.  FEED: the weights four blocks on go into the registers of this
+  // block -- transposed: of this and the block before, in odd blocks, so that both halves of a line are asked for together.
+  template <int B, bool NEXT, bool SLAB, bool FEED>
+  __device__ inline void block(Acc<MT, 2>& acc, Raw& wp, Raw& wc, const Raw& wn, const float* __restrict__ wg,
+                               const float* __restrict__ xs, const float* __restrict__ Xl, int s, float* __restrict__ nslab,
+                               int tid, int lane) {
+    constexpr int M = kSplitTerms * MT, CUR = B & 1;
+    constexpr bool stage = SLABS && SLAB, put = stage && B >= 1 && B <= MT;
+    constexpr int loads = !FEED ? 0 : TRANSPOSED ? (B & 1 ? 8 : 0) : 8;
+    split8(wc.w[1], w[1]);
+    if (NEXT && SLABS) read_x(x[CUR ^ 1], xs, (B + 1) & 3, lane);
+    if (NEXT && !SLABS) read_raw(Xl, 4 * s + B + 1, lane);
+    if (stage && B == 0) {
+#pragma unroll
+      for (int q = 0; q < MT; ++q) item.read(Xl, s + 1, tid, q);
+    }
+    multiply(x[CUR], 0, acc);
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      if (NEXT) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, (44 + M - 1) / M, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (NEXT) split8(wn.w[0], w[0]);
+    if (NEXT && !SLABS) split_raw(x[CUR ^ 1]);
+    if (put) item.put(nslab, tid, B - 1);
+    if (FEED && TRANSPOSED && (B & 1)) { wp.load_block(wg + Raw::offset(B + 3)); wc.load_block(wg + Raw::offset(B + 4)); }
+    if (FEED && !TRANSPOSED) wc.load_block(wg + Raw::offset(B + 4));
+    multiply(x[CUR], 1, acc);
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      if (loads * m < 8 * M && loads) __builtin_amdgcn_sched_group_barrier(0x020, (loads + M - 1) / M, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, ((NEXT ? (SLABS ? 44 : 44 + 44 * MT) : 0) + (put ? 44 : 0) + M - 1) / M + 1, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  // Four blocks, slab s.  The barrier that completes the next slab stands before the last block, whose operand is in
+  // registers by then: the first operand of the next slab arrives under it.
+  template <bool LAST, class Tail>
+  __device__ inline void group(Acc<MT, 2>& acc, Raw& b0, Raw& b1, Raw& b2, Raw& b3, const float* __restrict__ wg,
+                               const float* __restrict__ Xl, int s, float* __restrict__ cur, float* __restrict__ nxt, int tid, int lane, Tail& tail) {
+    block<0, true, !LAST, !LAST>(acc, b3, b0, b1, wg, cur, Xl, s, nxt, tid, lane);
+    block<1, true, !LAST, !LAST>(acc, b0, b1, b2, wg, cur, Xl, s, nxt, tid, lane);
+    if (LAST) tail();
+    block<2, true, !LAST, !LAST>(acc, b1, b2, b3, wg, cur, Xl, s, nxt, tid, lane);
+    if (!LAST && SLABS) __syncthreads();
+    block<3, !LAST, false, !LAST>(acc, b2, b3, b0, wg, nxt, Xl, s, nxt, tid, lane);
+  }
+  // b0: block 0, from the caller, who requests it as early as it can (typically under the previous product); tail() runs
+  // once no further weight block is needed, so that the caller can start the loads of the next layer under the last
+  // two blocks.  slabs: 2 slab_floats<MT>() floats of LDS.  With slabs, every wavefront
+  // has read the tile when any returns.
+  template <class Tail>
+  __device__ inline void run(const float* __restrict__ Xl, const float* __restrict__ W, Raw& b0, float* __restrict__ slabs, int wave, int lane,
+                             Acc<MT, 2>& acc, Tail& tail) {
+    const int tid = 64 * wave + lane;
+    float* s0 = slabs;
+    float* s1 = slabs + slab_floats<MT>();
+    Raw b1, b2, b3;
+    if (SLABS) {
+#pragma unroll
+      for (int q = 0; q < MT; ++q) item.read(Xl, 0, tid, q);
+    } else {
+      read_raw(Xl, 0, lane);
+    }
+    b1.load(W, 1, wave, lane);
+    b2.load(W, 2, wave, lane);
+    b3.load(W, 3, wave, lane);
+    low.zero();
+    POP_MARK(20);
+    const float* wg = Raw::lane_base(W, wave, lane);
+    if (SLABS) {
+#pragma unroll
+      for (int q = 0; q < MT; ++q) item.put(s0, tid, q);
+      __syncthreads();
+      read_x(x[0], s0, 0, lane);
+    } else {
+      split_raw(x[0]);
+    }
+    split8(b0.w[0], w[0]);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll 1
-    for (int i = 0; i < 12; i += 4) {
-      gemm256_group_fed<MT, TRANSPOSED, false, NT>(Xl, ldx, wg, i, b0, b1, b2, b3, x0, x1, lane, acc, tail);
-      wg += 4 * (TRANSPOSED ? 16 : 16 * kH);
+    for (int s = 0; s < 3; ++s) {
+      group<false>(acc, b0, b1, b2, b3, wg, Xl, s, s0, s1, tid, lane, tail);
+      wg += Raw::kGroup;
+      float* q = s0; s0 = s1; s1 = q;
+    
     }
-    gemm256_group_fed<MT, TRANSPOSED, true, NT>(Xl, ldx, wg, 12, b0, b1, b2, b3, x0, x1, lane, acc, tail);
-    return;
+    group<true>(acc, b0, b1, b2, b3, wg, Xl, 3, s0, s1, tid, lane, tail);
+    acc.add(low);
+    POP_MARK(24);
   }
-#pragma unroll 1
-  for (int i = 0; i < 12; i += 4) {
-    gemm256_group<MT, TRANSPOSED, false, NT>(Xl, ldx, W, i, b0, b1, b2, b3, x0, x1, wave, lane, acc, tail);
-    POP_MARK(21 + (i >> 2));
-  }
-  gemm256_group<MT, TRANSPOSED, true, NT>(Xl, ldx, W, 12, b0, b1, b2, b3, x0, x1, wave, lane, acc, tail);
-  POP_MARK(24);
+};
+
+template <int MT, bool TRANSPOSED, bool SLABS = true, class Tail>
+__device__ inline void gemm256(const float* __restrict__ Xl, const float* __restrict__ W, WeightRaw<TRANSPOSED>& b0,
+                               float* __restrict__ slabs, int wave, int lane, Acc<MT, 2>& acc, Tail tail) {
+  SplitProduct<MT, TRANSPOSED, SLABS> p;
+  p.run(Xl, W, b0, slabs, wave, lane, acc, tail);
+  if (!SLABS) __syncthreads();                       // every wavefront has read the tile
 }
 
 // The same product fully unrolled with NB rotating weight buffers (block i + NB - 1 is requested

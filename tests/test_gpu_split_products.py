@@ -1,0 +1,89 @@
+"""The 256-deep products on the bf16 pipe (three-way split operands): acting against 64-bit arithmetic at the edges of
+the row and contraction tiles and over a wide range of magnitudes, and the row geometries that split their operands
+differently against each other."""
+import numpy as np
+import pytest
+
+import paper_2206_08888_amd as pp
+from gpu_common import ensure_built, rel_l2
+
+pytestmark = pytest.mark.gpu
+H = 256
+
+
+def _population(algo, P, O, A, rows=None, capacity=64):
+    ensure_built()
+    cfg = pp.make_config(P, O, A, (H, H), 256, capacity, algo=algo, rows=rows)
+    sac = algo == pp.POP_ALGO_SAC
+    hps = [dict(seed=7 + i, lr_actor=3e-4, lr_critic=3e-4, gamma=0.99, tau=0.005, policy_noise=0.2, noise_clip=0.5,
+                policy_delay=1 if sac else 2, adam_b1=0.9, adam_b2=0.999, adam_eps=1e-8, lr_alpha=3e-4,
+                target_entropy=-float(A) if sac else 0.0, init_log_alpha=0.0) for i in range(P)]
+    return pp.Population(cfg, hps)
+
+
+def _act64(theta, obs, O, A, out):
+    t = theta.astype(np.float64)
+    w1, t = t[:O * H].reshape(O, H), t[O * H:]
+    b1, t = t[:H], t[H:]
+    w2, t = t[:H * H].reshape(H, H), t[H * H:]
+    b2, t = t[:H], t[H:]
+    w3, b3 = t[:H * out].reshape(H, out), t[H * out:]
+    h = np.maximum(obs.astype(np.float64) @ w1 + b1, 0.0)
+    h = np.maximum(h @ w2 + b2, 0.0)
+    # and the size of the head's terms: rounding is relative to those, also where they cancel in the sum
+    return np.tanh(h @ w3 + b3)[:, :A], np.sqrt((h * h) @ (w3 * w3))[:, :A]
+
+
+def _apart(a, ref, terms):
+    return np.linalg.norm(a - ref) / np.linalg.norm(np.maximum(np.abs(ref), np.minimum(terms, 1.0)))
+
+
+@pytest.mark.parametrize("algo", [pp.POP_ALGO_TD3, pp.POP_ALGO_SAC])
+@pytest.mark.parametrize("O,A", [(1, 1), (8, 3), (9, 24), (33, 6), (376, 17), (424, 24)])
+@pytest.mark.parametrize("n", [1, 33])
+def test_acting_against_64_bits(algo, O, A, n):
+    pop = _population(algo, 2, O, A)
+    obs = np.random.default_rng(O + n).standard_normal((2, n, O)).astype(np.float32)
+    a = pop.act(obs)
+    for i in range(2):
+        ref, terms = _act64(pop.get_params(i, "actor"), obs[i], O, A, 2 * A if algo == pp.POP_ALGO_SAC else A)
+        # a product's relative error is 1e-7 (hidden layers) to 2e-7 (fp32 head and first layer), tanh's 1.2e-7
+        assert _apart(a[i], ref, terms) < 6e-7
+    pop.close()
+
+
+@pytest.mark.parametrize("scale", [1e-15, 1e15])
+def test_acting_over_magnitudes(scale):
+    """Hidden activations of every size the exponent allows: the layers are scaled against each other."""
+    O, A = 17, 6
+    pop = _population(pp.POP_ALGO_TD3, 1, O, A)
+    th = pop.get_params(0, "actor").copy()
+    th[:O * H + H] *= np.float32(scale)
+    th[O * H + H:O * H + H + H * H] *= np.float32(1.0 / scale)
+    pop.set_params(0, "actor", th)
+    obs = np.random.default_rng(3).standard_normal((1, 64, O)).astype(np.float32)
+    assert _apart(pop.act(obs)[0], *_act64(th, obs[0], O, A, A)) < 6e-7
+    pop.close()
+
+
+@pytest.mark.parametrize("algo,O,A", [(pp.POP_ALGO_TD3, 17, 6), (pp.POP_ALGO_TD3, 56, 8), (pp.POP_ALGO_SAC, 17, 6),
+                                      (pp.POP_ALGO_SAC, 40, 24), (pp.POP_ALGO_TD3_SHARED, 17, 6)])
+@pytest.mark.parametrize("rows", [32, 64])
+def test_rows_of_a_chain_agree(algo, O, A, rows):
+    """One update step: parameters and first moments with every chain at `rows` rows against 16-row target and actor
+    chains, whose products run on the fp32 instructions."""
+    got = []
+    for r in ((16, 32, 16), (rows, rows, rows)):
+        pop = _population(algo, 3, O, A, rows=r)
+        g = np.random.default_rng(5)
+        pop.insert(-1, obs=g.standard_normal((3, 64, O)).astype(np.float32), act=g.uniform(-1, 1, (3, 64, A)).astype(np.float32),
+                   rew=g.standard_normal((3, 64)).astype(np.float32), done=np.zeros((3, 64), np.float32),
+                   next_obs=g.standard_normal((3, 64, O)).astype(np.float32))
+        pop.update(1)
+        nets = [(0, net) for net in ("actor", "critic1", "critic2")]
+        got.append([pop.get_params(a, "m_" + net) for a, net in nets])     # first Adam moments: (1 - b1) gradient
+        pop.close()
+    for x, y in zip(*got):
+        # a gradient is a sum over 256 rows through four products, each 2e-7 apart, and a ReLU unit within rounding
+        # of zero may switch: one of 65,536 is 4e-6 of the gradient's square
+        assert rel_l2(y, x) < 2e-3 and np.isfinite(y).all()

@@ -104,8 +104,8 @@ typedef struct {
   int32_t rows_critic1;  /* 0 = choose; 16: the 16-row target workgroups go on into critic 1 for their own rows and only
                             critic 2 has workgroups of its own (TD3 with TARGET_CRITIC and rows_target == 16 only);
                             otherwise equal to rows_critic */
-  int32_t half_tiles;    /* weight-gradient tiles of half the width in the stand-alone tile launches: 0 = choose (on
-                            while all of them are resident at once, up to 10 agents), 1 = off, 2 = on.  The sums over
+  int32_t half_tiles;    /* weight-gradient tiles of half the width in the stand-alone tile launches: 0 = choose (on while the
+                            launch has at most ten of them per CU, 34 agents at 17 / 6), 1 = off, 2 = on.  The sums over
                             the batch then come in two halves: compare launch structures with this set to 1. */
   int32_t actor_ahead;   /* the actor's own forward pass of a step with a policy update runs inside the target / critic
                             launch, in the 32-row workgroups of critic 2 while they wait for their Bellman targets, and

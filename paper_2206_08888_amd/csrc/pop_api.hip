@@ -161,14 +161,17 @@ void fill_dims(const pop_config& c, PopDev& d) {
   // Rows per workgroup of the layer chains.  16 for the target and actor chains of small
   // populations: those parts have only 8 P workgroups at 32 rows, well under the 256 CUs, and
   // their latency is what a step waits for; 16-row tiles halve the matrix time of every
-  // product by spreading it over twice the CUs.  Else 32.  (64-row chains for all three parts, half the weight
-  // traffic per row, exist as well -- tuning.rows_* = 64 -- and were the choice from 128 agents on until the 32-row
-  // products learnt to issue their loads between the MFMAs: 1297 against 1278 us/step at P = 256, equal at 128.)
+  // product by spreading it over twice the CUs.  Else 32, two workgroups per CU; 64, one per CU, once the 32-row target
+  // chains alone fill the chip's 512 places twice over (P >= 128): a weight is then read and split for twice the rows,
+  // which pays as soon as there is enough work for the other rounds to hide the tails -- 558 -> 535 us/step at P = 128, 1103 -> 1043
+  // at P = 256, shared critics 613 -> 610 at P = 160, 972 -> 935 at P = 256; equal at P = 96, 331 -> 349 at P = 72.
   const int cls = (int64_t)c.P * (c.batch / 16) <= kCUs ? 0 : 1;   // 16-row chains of a part get a CU each
-  d.rows_t = d.rows_a = cls == 0 ? 16 : 32;
+  const pop_tuning& u = c.tuning;
+  const bool many = c.algo != POP_ALGO_SAC && !u.rows_target && !u.rows_critic && !u.rows_actor && !u.rows_critic1 && (int64_t)c.P * (c.batch / 32) >= 4 * kCUs;
+  d.rows_t = d.rows_a = cls == 0 ? 16 : many ? 64 : 32;
   // Beside 16 P target workgroups of 16 rows, 64-row critic chains (8 P workgroups) keep the fused
   // target/critic launch of a small population within one workgroup per CU.
-  d.rows_c = cls == 1 ? 32 : 64;
+  d.rows_c = cls == 1 && !many ? 32 : 64;
   // Small class: 32-row critic chains (16 P workgroups) where they still fit one round of one workgroup
   // per CU beside the target chains (P <= 8) -- the critics' backward pass, which starts when the targets arrive, is
   // the tail of that launch and halves: 81 against 91 us/step at P = 8 -- and from 11 agents on, where neither class
@@ -183,15 +186,14 @@ void fill_dims(const pop_config& c, PopDev& d) {
   // workgroups of its own, 32 rows each: 16 P + 8 P workgroups as before, but the tail after the targets is a
   // 16-row critic chain or a 32-row backward pass instead of a 64-row backward pass (88 against 92 us/step at P = 10).
   d.rows_c1 = 0;
-  const pop_tuning& u = c.tuning;
   if (c.algo == POP_ALGO_TD3 && cls == 0 && (u.launch == POP_LAUNCH_AUTO || u.launch == POP_LAUNCH_TARGET_CRITIC)) {
     if (d.rows_c == 64) { d.rows_c = 32; d.rows_c1 = 16; }
     // 11 and 12 agents (20 P <= 256 < 24 P): the same with 64-row workgroups for critic 2 -- 93 against 98 us/step
     else if (b16 + b16 / 2 > kCUs && b16 + b16 / 4 <= kCUs) { d.rows_c = 64; d.rows_c1 = 16; }
   }
   if (c.algo == POP_ALGO_SAC && cls == 1) {           // one launch per chain, so each takes the rows that suit it:
-    // 64-row critic chains while they still fit one round of one workgroup per CU (51 against 59 us at P = 32),
-    // 16-row target chains while they fit one round of two per CU (44 against 46 us); the actor chain stays at 32
+    // 64-row critic chains and 16-row target chains while they still fit one round of one / two workgroups per CU
+    // (194 us/step at P = 20, 220 at P = 32; all chains at 32 rows 193, 220); the actor chain stays at 32
     if ((int64_t)c.P * (c.batch / 64) * 2 <= kCUs) d.rows_c = 64;
     if ((int64_t)c.P * (c.batch / 16) <= 2 * kCUs) d.rows_t = 16;
   }
@@ -208,12 +210,15 @@ void fill_dims(const pop_config& c, PopDev& d) {
   if (d.D > kMaxIn || (c.algo != POP_ALGO_SAC && d.A > kMaxAct)) { d.rows_t = d.rows_a = (int64_t)c.P * (c.batch / 16) <= kCUs ? 16 : 32; d.rows_c = 32; d.rows_c1 = 0; }
   if (d.rows_c1 == 0) d.rows_c1 = d.rows_c;
   d.cstride = d.B / (d.rows_c1 < d.rows_c ? d.rows_c1 : d.rows_c);
-  // Stand-alone weight-gradient launches: with fewer than two 32 x 128 tiles per CU (19 workgroups per network at
-  // these shapes) some CUs hold two tiles and others one, and the launch lasts as long as the former; tiles of
-  // half the width (37 workgroups per network) spread evenly while all of them are resident at three per CU, i.e.
-  // up to 10 agents: 73 -> 69 us/step at P = 2, 81 -> 79 at P = 8, 87.8 -> 85.6 at P = 10 (93.5 -> 94.3 at P = 12).
+  // Stand-alone weight-gradient launches: the last round of 32 x 128 tiles leaves most places empty for as long as a
+  // tile lasts; tiles of half the width end sooner and spread more evenly.  That pays while the launch is a few rounds
+  // of the 768 places (three per CU): us/step, full / half tiles: 85.7 / 83.3 at P = 12, 101.9 / 96.0 at P = 16, 116.7 / 114.6 at
+  // P = 20, 145.7 / 141.5 at P = 32, 281.5 / 283.9 at P = 64, 546.6 / 551.5 at P = 128; SAC 151.8 / 141.9 at P = 16, 217.8 / 212.8
+  // at P = 32; obs 376 / act 17 (85 half tiles per critic instead of 37) 180.8 / 176.4 at P = 10, 302.7 / 302.4 at P = 20,
+  // 590.4 / 595.5 at P = 40.  The line: ten of the critics' half tiles per CU.
   // The sums over the batch then come in two halves, so comparisons of launch structures bit for bit switch them off.
-  d.half_tiles = u.half_tiles ? u.half_tiles == 2 : 2 * (int64_t)c.P * 37 <= 3 * kCUs;
+  const int64_t half_roles = 2 * (16 + 2 * ((d.D + 31) / 32)) + 1;
+  d.half_tiles = u.half_tiles ? u.half_tiles == 2 : 2 * (int64_t)c.P * half_roles <= 10 * kCUs;
   d.actor = make_layout(d.O, c.algo == POP_ALGO_SAC ? 2 * d.A : d.A);   // SAC: mean and log-std per action
   d.critic = make_layout(d.D, 1);
   d.agent_sz = d.actor.padded + 2 * d.critic.padded;
@@ -387,7 +392,8 @@ int pop_create(pop_ctx** out, const pop_config* cfg, const pop_hparams* hp, uint
   // launch, two workgroups per CU; waiting weight-gradient workgroups would take the slots the actor chains could
   // start in.  From P = 34 the parts are each several times larger than the 512 workgroups the chip holds and the
   // tails of one part overlap the next inside a single launch; towards a hundred agents the separate launches are
-  // ahead again (their tile kernel runs three workgroups per CU, the tiles inside the single launch two).
+  // ahead again (bf16 products, single / target+critic: 164.7 / 175.5 at P = 34, 187.9 / 191.2 at 40, 283.3 / 281.5 at 64, 320.9 / 331.1 at 72,
+  // 354.2 / 361.1 at 80, 427.4 / 419.7 at 96) (their tile kernel runs three workgroups per CU, the tiles inside the single launch two).
   const int64_t tc_blocks = (int64_t)cfg->P * (cfg->batch / d.rows_t) + (int64_t)cfg->P * (cfg->batch / d.rows_c) +
                             (d.rows_c1 == d.rows_c ? (int64_t)cfg->P * (cfg->batch / d.rows_c) : 0);
   const int64_t chain_blocks = (int64_t)cfg->P * (cfg->batch / 32) * 3;

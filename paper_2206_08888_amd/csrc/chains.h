@@ -61,7 +61,7 @@ struct LdsMap {
   __host__ size_t bytes(int vec_floats) const { return (size_t)(vec + vec_floats) * sizeof(float); }
 };
 template <int MT>
-using Lds = LdsMap<32 * MT, 16>;
+using Lds = LdsMap<32 * MT, 8>;
 
 // what a two-hidden-layer network needs from memory before its products can start
 template <int MT>
@@ -229,8 +229,7 @@ __device__ inline void input_grad_to_global(const float* Zl, const float* W, Wei
 // share as `stage` -- a chain of forward products only, any chain.
 template <int MT, bool SLABS = true>
 struct Rows32 {                                      // 32 MT rows on 32x32 tiles (mfma_tiles.h)
-  static constexpr int R = 32 * MT, kPad = 16;
-  static constexpr int kPerCU = MT == 1 ? 2 : 1;     // workgroups per CU that LDS leaves room for: registers are held to that
+  static constexpr int R = 32 * MT, kPad = 8;
   using Pre = LayerPre<MT>;
   using WtBlock = WeightRaw<true>;
   static constexpr int kStage = SLABS ? 2 * slab_floats<MT>() : 0, kStageForward = kStage;
@@ -290,7 +289,7 @@ struct Rows32 {                                      // 32 MT rows on 32x32 tile
 };
 
 struct Rows16 {                                      // 16 rows on v_mfma_f32_16x16x4_f32 (mfma_tiles16.h)
-  static constexpr int R = 16, kPad = 16, kPerCU = 1;
+  static constexpr int R = 16, kPad = 16;
   struct Pre {
     SmallW16 w1;
     WeightBlock16<false> w2;
@@ -410,10 +409,9 @@ struct Rows16 {                                      // 16 rows on v_mfma_f32_16
 
 // The same tiles for first layers with a fan-in of several hundred (the SAC Humanoid shapes): only the
 // first-layer product differs (software-pipelined beyond the prefetched rows).
-// PF: weight blocks of 16 rows in flight; 4 where the registers allow it (the critic chain), else 2.
-template <int MT, int PF = 2>
+// PF: weight blocks of 8 rows in flight; 8 where the registers allow it (the critic chain), else 4.
+template <int MT, int PF = 4>
 struct Rows32Deep : Rows32<MT> {
-  static constexpr int kPerCU = 1;
   using Pre = typename Rows32<MT>::Pre;
   __device__ static inline void load_input(float* Xl, int xld, const float* rows, int row_stride, int c0, int n, int valid,
                                            int tid) {

@@ -8,7 +8,7 @@
 namespace pop {
 
 template <class G, int AS = kMaxAct>
-__global__ __launch_bounds__(kThreads, G::kPerCU) void k_target(PopDev d, uint32_t t) {
+__global__ __launch_bounds__(kThreads, G::R == 32 ? 2 : 1) void k_target(PopDev d, uint32_t t) {
   extern __shared__ float lds[];
   int agent, chunk;
   POP_BLOCK_TIME(kTraceTarget, 0);
@@ -17,7 +17,7 @@ __global__ __launch_bounds__(kThreads, G::kPerCU) void k_target(PopDev d, uint32
 }
 
 template <class G>
-__global__ __launch_bounds__(kThreads, G::kPerCU) void k_critic(PopDev d, uint32_t t) {
+__global__ __launch_bounds__(kThreads, G::R == 32 ? 2 : 1) void k_critic(PopDev d, uint32_t t) {
   extern __shared__ float lds[];
   int net, chunk;
   POP_BLOCK_TIME(kTraceCritic, 0);
@@ -148,7 +148,7 @@ hipError_t setup_kernels() {
   POP_SET_LDS(k_target<Rows32<2>>);
   POP_SET_LDS(k_critic<Rows32<1>>);
   POP_SET_LDS(k_critic<Rows32<2>>);
-  POP_SET_LDS(k_critic<Rows32Deep<1, 4>>);
+  POP_SET_LDS(k_critic<Rows32Deep<1, 8>>);
   POP_SET_LDS(k_actor<Rows16>);
   POP_SET_LDS(k_actor<Rows32<1>>);
   POP_SET_LDS(k_actor<Rows32<1>, 2>);
@@ -203,7 +203,7 @@ hipError_t launch_critic(const PopDev& d, uint32_t t, hipStream_t s) {
   const dim3 grid(xcd_grid(2 * d.P, d.B / d.rows_c)), block(kThreads);
   if (d.D > kMaxIn) {                                // wide inputs (SAC): 32 rows, pipelined first layer
     if (d.rows_c != 32) return hipErrorInvalidValue;
-    k_critic<Rows32Deep<1, 4>><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec_critic(d)), s>>>(d, t);
+    k_critic<Rows32Deep<1, 8>><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec_critic(d)), s>>>(d, t);
   } else if (d.rows_c == 32) k_critic<Rows32<1>><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec_critic(d)), s>>>(d, t);
   else k_critic<Rows32<2>><<<grid, block, chain_bytes<Rows32<2>>(d.D, vec_critic(d)), s>>>(d, t);
   return hipGetLastError();

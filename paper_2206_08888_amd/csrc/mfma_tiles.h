@@ -172,7 +172,7 @@ struct SmallW {
 
 // acc[r][c] += sum_{k<K} X[r][k] W[k][c]   (forward product x W) for a small fan-in K.
 //   X: LDS, row stride ldx, rows [0, 32 MT); columns >= K up to the next
-//      multiple of 16 must hold finite values (they meet zero weights);
+//      multiple of 8 must hold finite values (they meet zero weights);
 //   W: global, row-major [K][256]; `pre` holds its first 32 rows already.
 template <int MT>
 __device__ inline void gemm_xw_small(const float* __restrict__ Xl, int ldx, int K, const float* __restrict__ W,
@@ -217,99 +217,97 @@ __device__ inline void gemm_xw_small(const float* __restrict__ Xl, int ldx, int 
   }
 }
 
-// The same product for a fan-in of several hundred, on the bf16 pipe: 16-deep blocks (contraction index 16 i + 8 s + 4 half + j
-// at element 4 s + j of a lane), both operands split in registers, PF weight blocks in flight beyond the two that `pre`
-// holds.  Columns of X from K up to the next multiple of 16 must hold finite values.  With a fan-in of 376 the first
-// layers are three fifths of a chain's matrix work, and the fp32 instructions take 1024 cycles per block and wavefront where
-// the 12 bf16 and 132 split instructions take some 700.
+// The same product for a fan-in of several hundred: the 8-deep blocks beyond the prefetched 32
+// rows are software-pipelined, PF weight blocks (8 PF rows of W) in flight ahead of the matrix pipe.
 template <int MT, int PF>
 __device__ inline void gemm_xw_deep(const float* __restrict__ Xl, int ldx, int K, const float* __restrict__ W,
                                     const SmallW& pre, int wave, int lane, Acc<MT>& acc) {
   const int half = lane >> 5, l32 = lane & 31;
-  const int nb = (K + 15) >> 4;
+  const int nb = (K + 7) >> 3;                       // 8-deep blocks in all; 0 .. 3 come from `pre`
   const float* wcol = W + tile_col(wave, 0, l32);
-  Acc<MT> low;
-  low.zero();
-  float b[PF][2][8];
-  auto request = [&](float (&dst)[2][8], int blk) {
+  float b[PF][2][4];
+  auto request = [&](float (&dst)[2][4], int blk) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int k = 16 * blk + 8 * (e >> 2) + 4 * half + (e & 3);
+    for (int j = 0; j < 4; ++j) {
+      const int k = 8 * blk + 4 * half + j;
       const f32x2 v = *reinterpret_cast<const f32x2*>(wcol + (size_t)(k < K ? k : 0) * kH);
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt) dst[nt][e] = k < K ? v[nt] : 0.0f;
+      for (int nt = 0; nt < 2; ++nt) dst[nt][j] = k < K ? v[nt] : 0.0f;
     }
-  };
-  f32x4 xn[MT][2];                                   // the LDS operand runs one block ahead
-  auto lds_block = [&](int i) {
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int s = 0; s < 2; ++s)
-        xn[mt][s] = *reinterpret_cast<const f32x4*>(&Xl[(32 * mt + l32) * ldx + 16 * i + 8 * s + 4 * half]);
-  };
-  // block i with weights w; the LDS operand of block i + 1 and the loads of next() are requested ahead of the matrix work
-  auto block = [&](const float (&w)[2][8], int i, auto next) {
-    Split8 x[MT], ws[2];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) split8(xn[mt][0], xn[mt][1], x[mt]);
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt) split8(w[nt], ws[nt]);
-    if (i + 1 < nb) lds_block(i + 1);
-    next();
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int q = 0; q < kSplitTerms; ++q)
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
-          f32x16& c = q == kSplitTerms - 1 ? acc.t[mt][nt] : low.t[mt][nt];
-          c = mfma32_bf16(x[mt].t[kTermX[q]], ws[nt].t[kTermW[q]], c);
-        }
-    __builtin_amdgcn_sched_barrier(0);
   };
 #pragma unroll
   for (int s = 0; s < PF; ++s)
-    if (2 + s < nb) request(b[s], 2 + s);
-  lds_block(0);
+    if (4 + s < nb) request(b[s], 4 + s);
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < 4; ++i) {
     if (i < nb) {
-      float w[2][8];
+      f32x4 a[MT];
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
+      for (int mt = 0; mt < MT; ++mt)
+        a[mt] = *reinterpret_cast<const f32x4*>(&Xl[(32 * mt + l32) * ldx + 8 * i + 4 * half]);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) w[nt][e] = pre.w[2 * i + (e >> 2)][nt][e & 3];
-      block(w, i, [] {});
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+          for (int nt = 0; nt < 2; ++nt) acc.t[mt][nt] = mfma32(a[mt][j], pre.w[i][nt][j], acc.t[mt][nt]);
     }
-  // steady state: block i + PF lies wholly inside the K rows, its eight loads are one running pointer plus constants
-  const float* wrun = wcol + (size_t)(16 * (2 + PF) + 4 * half) * kH;
-  const int nfull = K >> 4;
-  int blk = 2;
+  }
+  auto lds_block = [&](f32x4 (&a)[MT], int i) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+      a[mt] = *reinterpret_cast<const f32x4*>(&Xl[(32 * mt + l32) * ldx + 8 * i + 4 * half]);
+  };
+  f32x4 an[MT];                                      // the LDS operand runs one block ahead of the matrix pipe
+  if (4 < nb) lds_block(an, 4);
+  // FAST: block i + PF lies wholly inside the K rows: its eight loads are one running pointer plus constants
+  // (no per-load address arithmetic or row guard, which would sit in front of every group of MFMAs)
+  const float* wrun = wcol + (size_t)(8 * (4 + PF) + 4 * half) * kH;     // rows of block 4 + PF for this lane
+  auto step = [&](int s, int i, bool next_x, bool next_w, bool fast) {
+    f32x4 a[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) a[mt] = an[mt];
+    if (next_x) lds_block(an, i + 1);
+    float w[2][4];
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) w[nt][j] = b[s][nt][j];
+    if (fast) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const f32x2 v = *reinterpret_cast<const f32x2*>(wrun + j * kH);
+        b[s][0][j] = v[0];
+        b[s][1][j] = v[1];
+      }
+    } else if (next_w) {
+      request(b[s], i + PF);
+    }
+    wrun += 8 * kH;
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) acc.t[mt][nt] = mfma32(a[mt][j], w[nt][j], acc.t[mt][nt]);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  int blk = 4;
+  // steady state, free of branches (a branch inside the loop makes the compiler drain every outstanding load at
+  // the join): every block of the group exists and every block requested from it is a full one
+  const int nfull = K >> 3;
   for (; blk + 2 * PF <= nfull; blk += PF) {
 #pragma unroll
-    for (int s = 0; s < PF; ++s) {
-      float (&w)[2][8] = b[s];
-      block(w, blk + s, [&] {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const f32x2 v = *reinterpret_cast<const f32x2*>(wrun + (8 * (e >> 2) + (e & 3)) * kH);
-          w[0][e] = v[0];
-          w[1][e] = v[1];
-        }
-      });
-      wrun += 16 * kH;
-    }
+    for (int s = 0; s < PF; ++s) step(s, blk + s, true, true, true);
   }
   for (; blk < nb; blk += PF) {                      // the last groups: guarded requests
 #pragma unroll
     for (int s = 0; s < PF; ++s) {
       const int i = blk + s;
-      if (i < nb) block(b[s], i, [&] { if (i + PF < nb) request(b[s], i + PF); });
+      if (i < nb) step(s, i, i + 1 < nb, i + PF < nb, false);
     }
   }
-  acc.add(low);
 }
 
 // Software-pipelined 256-deep contraction of an LDS operand with a global weight

@@ -87,22 +87,3 @@ def test_rows_of_a_chain_agree(algo, O, A, rows):
         # a gradient is a sum over 256 rows through four products, each 2e-7 apart, and a ReLU unit within rounding
         # of zero may switch: one of 65,536 is 4e-6 of the gradient's square
         assert rel_l2(y, x) < 2e-3 and np.isfinite(y).all()
-
-
-@pytest.mark.parametrize("algo", [pp.POP_ALGO_TD3, pp.POP_ALGO_SAC])
-@pytest.mark.parametrize("O,A", [(3, 24), (63, 2), (64, 9), (100, 4), (424, 24)])
-def test_wide_first_layers(algo, O, A):
-    """One update step of the same agents in a population of 3 (16-row target and actor chains, fp32 instructions) and of
-    17 (32-row chains): first layers of a few rows up to the largest fan-in, with and without a remainder."""
-    got = []
-    for P in (3, 17):
-        pop = _population(algo, P, O, A)
-        g = np.random.default_rng(5)
-        tr = dict(obs=g.standard_normal((64, O)), act=g.uniform(-1, 1, (64, A)), rew=g.standard_normal(64), done=np.zeros(64), next_obs=g.standard_normal((64, O)))
-        for i in range(P):
-            pop.insert(i, **{k: v.astype(np.float32) for k, v in tr.items()})
-        pop.update(1)
-        got.append([pop.get_params(i, "m_" + net) for i in range(3) for net in ("actor", "critic1", "critic2")])
-        pop.close()
-    for x, y in zip(*got):
-        assert rel_l2(y, x) < 2e-3 and np.isfinite(y).all()      # as above

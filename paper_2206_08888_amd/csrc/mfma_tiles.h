@@ -39,16 +39,25 @@ __device__ inline f32x16 mfma32(float a, float b, f32x16 c) {
 }
 
 // fp32 products on the bf16 matrix pipe.  v_mfma_f32_32x32x2_f32 takes 64 cycles for 4096 FLOP,
-// v_mfma_f32_32x32x16_bf16 32 cycles for 32768: sixteen times the rate.  An fp32 value is the exact sum of three
-// bf16 values (8 significand bits each, 24 in all): h = bf16(x), m = bf16(x - h), l = x - h - m, the differences
-// exact.  Of the nine products of two such sums the six down to 2^-18 of the largest are taken,
-//   x y = hx hy + (hx my + mx hy + mx my + hx ly + lx hy) + O(2^-26 |x y|),
+// v_mfma_f32_32x32x16_bf16 32 cycles for 32768: sixteen times the rate.  An fp32 value is the sum of three bf16 values
+// (8 significand bits each, 24 in all): h its upper half-word (cut off: rounding would turn the largest finite values
+// into infinity), m = bf16(x - h), l = x - h - m, the differences exact.  Of the nine products of two such sums six are
+// taken,
+//   x y = hx hy + (hx my + mx hy + mx my + hx ly + lx hy) + rest,   |rest| < 2^-21 |x y|, 2^-25 in the mean,
 // at 6 / 16 of the time of the fp32 instructions.  The large products and the five small ones are summed in
 // accumulators of their own (low), added once at the end: the matrix pipe rounds the accumulator after every
 // instruction, and in one accumulator the small products would pay that rounding five times as often.  Relative
-// error of a 256-deep product against 64 bits (2-norm): 0.7e-7, fp32 instructions 2.0e-7 (ReLU outputs x Glorot
-// weights); 0.7e-7 / 2.0e-7 (sparse gradients x weights); 0.5e-7 / 1.4e-7 (activations x gradients); 0.9e-7 / 2.5e-7
-// (all terms positive); 1.1e-7 / 2.9e-7 (magnitudes over e^+-4); summed in one accumulator 2.2e-7.
+// error of a 256-deep product against 64 bits (2-norm): 0.70e-7, fp32 instructions 2.04e-7 (ReLU outputs x Glorot
+// weights); 0.70e-7 / 2.05e-7 (sparse gradients x weights); 0.58e-7 / 1.44e-7 (activations x gradients); 0.94e-7 /
+// 2.48e-7 (all terms positive); 1.14e-7 / 2.80e-7 (magnitudes over e^+-4); summed in one accumulator 2.2e-7; with h
+// rounded 0.67, 0.67, 0.55, 0.94, 1.12e-7.
+// Infinities and NaN: x - h is NaN for them, and so is every small sum they enter, but hx hy is what the fp32
+// instructions would give, and it dwarfs a finite small sum.  So a small sum that is not finite counts as the largest
+// finite value instead (Acc::add_finite, one instruction per element: 0.2 % of a step with 80 agents, 0.5 % with 256).
+// A large sum overflows only where the sum of the terms' magnitudes does.
+// Small values: bf16 has the exponents of fp32, and the parts of a value below 2^-110 (8e-34) lose what lies below
+// 2^-134.  A product's absolute error grows by 2^-134 (sum |x| + sum |y|) at most; with operands of 1e-31 nothing shows,
+// of 1e-34 the error is 2.8e-7 where the fp32 instructions have 2.0e-7, of 1e-37 2.7e-4.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
@@ -59,17 +68,20 @@ struct Split8 {                            // eight consecutive contraction elem
 // One pair of elements (2 i, 2 i + 1): eleven vector instructions (the differences as two-term bf16 dot products would
 // be seven, but those run on the matrix pipe: 78 cycles beside a matrix instruction instead of 42).
 __device__ inline void split_pair(float a, float b, int i, Split8& s) {
-#pragma unroll
-  for (int q = 0; q < 3; ++q) {
-    const bf16x2 h = __builtin_convertvector((f32x2{a, b}), bf16x2);
+  const auto put = [&](int q, uint32_t u) {
+    const bf16x2 h = __builtin_bit_cast(bf16x2, u);
     s.t[q][2 * i] = h[0];
     s.t[q][2 * i + 1] = h[1];
-    if (q < 2) {
-      const uint32_t u = __builtin_bit_cast(uint32_t, h);
-      a -= __uint_as_float(u << 16);
-      b -= __uint_as_float(u & 0xffff0000u);
-    }
-  }
+  };
+  const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
+  put(0, __builtin_amdgcn_perm(ub, ua, 0x07060302u));          // the upper halves of both words
+  a -= __uint_as_float(ua & 0xffff0000u);
+  b -= __uint_as_float(ub & 0xffff0000u);
+  const uint32_t m = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
+  put(1, m);
+  a -= __uint_as_float(m << 16);
+  b -= __uint_as_float(m & 0xffff0000u);
+  put(2, __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2)));
 }
 __device__ inline void split8(const float (&x)[8], Split8& s) {
 #pragma unroll
@@ -127,13 +139,15 @@ struct Acc {
 #pragma unroll
         for (int v = 0; v < 16; ++v) t[a][b][v] = 0.0f;
   }
-  __device__ inline void add(const Acc& o) {
+  // plus o, NaN and infinities in it as the largest finite value (the small sums of split products, above)
+  __device__ inline void add_finite(const Acc& o) {
+    const float most = 0x1.fffffep127f;
 #pragma unroll
     for (int a = 0; a < MT; ++a)
 #pragma unroll
       for (int b = 0; b < NT; ++b)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) t[a][b][v] += o.t[a][b][v];
+        for (int v = 0; v < 16; ++v) t[a][b][v] += __builtin_amdgcn_fmed3f(o.t[a][b][v], -most, most);
   }
 };
 
@@ -663,7 +677,7 @@ struct SplitProduct {
     
     }
     group<true>(acc, b0, b1, b2, b3, wg, Xl, 3, s0, s1, tid, lane, tail);
-    acc.add(low);
+    acc.add_finite(low);
     POP_MARK(24);
   }
 };

@@ -11,9 +11,9 @@ pytestmark = pytest.mark.gpu
 H = 256
 
 
-def _population(algo, P, O, A, rows=None, capacity=64):
+def _population(algo, P, O, A, capacity=64, **tuning):
     ensure_built()
-    cfg = pp.make_config(P, O, A, (H, H), 256, capacity, algo=algo, rows=rows)
+    cfg = pp.make_config(P, O, A, (H, H), 256, capacity, algo=algo, **tuning)
     sac = algo == pp.POP_ALGO_SAC
     hps = [dict(seed=7 + i, lr_actor=3e-4, lr_critic=3e-4, gamma=0.99, tau=0.005, policy_noise=0.2, noise_clip=0.5,
                 policy_delay=1 if sac else 2, adam_b1=0.9, adam_b2=0.999, adam_eps=1e-8, lr_alpha=3e-4,
@@ -52,9 +52,9 @@ def test_acting_against_64_bits(algo, O, A, n):
     pop.close()
 
 
-@pytest.mark.parametrize("scale", [1e-15, 1e15])
+@pytest.mark.parametrize("scale", [1e-28, 1e-15, 1e15, 1e28])
 def test_acting_over_magnitudes(scale):
-    """Hidden activations of every size the exponent allows: the layers are scaled against each other."""
+    """Hidden activations of very different sizes: the layers are scaled against each other."""
     O, A = 17, 6
     pop = _population(pp.POP_ALGO_TD3, 1, O, A)
     th = pop.get_params(0, "actor").copy()
@@ -64,6 +64,93 @@ def test_acting_over_magnitudes(scale):
     obs = np.random.default_rng(3).standard_normal((1, 64, O)).astype(np.float32)
     assert _apart(pop.act(obs)[0], *_act64(th, obs[0], O, A, A)) < 6e-7
     pop.close()
+
+
+def _views(th, fan_in, out):
+    """W1, b1, W2, b2, W3, b3 of a flat network, as views."""
+    at, got = 0, []
+    for shape in ((fan_in, H), (H,), (H, H), (H,), (H, out), (out,)):
+        n = int(np.prod(shape))
+        got.append(th[at:at + n].reshape(shape))
+        at += n
+    return got
+
+
+MOST = np.finfo(np.float32).max
+PLANTS = {                     # what is put into a network's W1, b1, W2, b2, W3, b3
+    "weights": lambda w1, b1, w2, b2, w3, b3: (w2.__setitem__((5, 9), np.inf), w2.__setitem__((7, 20), -np.inf), w2.__setitem__((8, 33), np.nan)),
+    "one activation": lambda w1, b1, w2, b2, w3, b3: (b1.__setitem__(3, np.inf), np.abs(w3, out=w3)),
+    "opposite infinities": lambda w1, b1, w2, b2, w3, b3: (b1.__setitem__(3, np.inf), w2.__setitem__((40, slice(0, 128)), np.inf), np.abs(w3, out=w3)),
+    "largest finite": lambda w1, b1, w2, b2, w3, b3: (b1.__setitem__(3, MOST), np.multiply(w2[3], np.float32(1e-32), out=w2[3]),
+                                                     w1.__setitem__((slice(None), 6), 0), b1.__setitem__(6, 1e-33), w2.__setitem__((6, 11), -MOST),
+                                                     np.multiply(w3, np.float32(1e-6), out=w3)),
+}
+
+
+@pytest.mark.parametrize("plant", sorted(PLANTS))
+@pytest.mark.parametrize("algo", [pp.POP_ALGO_TD3, pp.POP_ALGO_SAC])
+def test_acting_with_infinities(algo, plant):
+    """Infinite, NaN and the largest finite operands of a hidden product give what fp32 arithmetic gives."""
+    O, A, n = 17, 6, 64
+    pop = _population(algo, 1, O, A)
+    out = 2 * A if algo == pp.POP_ALGO_SAC else A
+    th = pop.get_params(0, "actor").copy()
+    PLANTS[plant](*_views(th, O, out))
+    pop.set_params(0, "actor", th)
+    obs = np.random.default_rng(4).standard_normal((1, n, O)).astype(np.float32)
+    got = pop.act(obs)[0].astype(np.float64)
+    pop.close()
+    w1, b1, w2, b2, w3, b3 = (v.astype(np.float64) for v in _views(th, O, out))
+    with np.errstate(all="ignore"):
+        h = np.fmax(obs[0].astype(np.float64) @ w1 + b1, 0.0)      # max(NaN, 0) = 0, as the kernels' ReLU has it
+        h = np.fmax((h[:, :, None] * w2[None]).sum(1) + b2, 0.0)
+        want = np.tanh((h[:, :, None] * w3[None]).sum(1) + b3)[:, :A]
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    assert np.allclose(got, want, rtol=0, atol=2e-6, equal_nan=True)
+    if plant == "one activation":
+        assert (want == 1.0).all()                                # and not the head's bias
+
+
+@pytest.mark.parametrize("algo", [pp.POP_ALGO_TD3, pp.POP_ALGO_SAC, pp.POP_ALGO_TD3_SHARED])
+@pytest.mark.parametrize("rows", [32, 64])
+def test_update_with_infinities(algo, rows):
+    """One step of a diverged population: infinite Bellman targets and gradients come out of 32- and 64-row chains as out of
+    16-row chains, whose products run on the fp32 instructions."""
+    O, A, P = 17, 6, 2
+    sac = algo == pp.POP_ALGO_SAC
+    got = []
+    # critic chains have 16 rows where they follow the target chains of TD3; elsewhere only the targets are compared
+    small = dict(rows=(16, 32, 16)) if algo != pp.POP_ALGO_TD3 else dict(rows=(16, 32, 16), rows_critic1=16, launch=pp.POP_LAUNCH_TARGET_CRITIC)
+    for tuning in (small, dict(rows=rows)):
+        pop = _population(algo, P, O, A, **tuning)
+        for agent in range(P):
+            for net in ("critic1", "critic2", "t_critic1", "t_critic2"):
+                th = pop.get_params(agent, net).copy()
+                w1, b1, w2, b2, w3, b3 = _views(th, O + A, 1)
+                np.abs(w2, out=w2)
+                np.abs(w3, out=w3)
+                if net[0] == "t" and agent == 0:
+                    b1[3] = np.inf
+                pop.set_params(agent, net, th)
+        g = np.random.default_rng(6)
+        rew = g.standard_normal((P, 64)).astype(np.float32)
+        rew[1, 5] = np.inf
+        done = np.zeros((P, 64), np.float32)
+        pop.insert(-1, obs=g.standard_normal((P, 64, O)).astype(np.float32), act=g.uniform(-1, 1, (P, 64, A)).astype(np.float32),
+                   rew=rew, done=done, next_obs=g.standard_normal((P, 64, O)).astype(np.float32))
+        pop.set_debug(True)
+        pop.update(1)
+        got.append((pop.debug("target_y"), [pop.get_params(a, "g_critic1") for a in range(P)]))
+        pop.close()
+    (y0, g0), (y1, g1) = got
+    assert np.array_equal(np.isnan(y0), np.isnan(y1)) and np.array_equal(np.isinf(y0), np.isinf(y1))
+    assert np.allclose(y0, y1, rtol=1e-5, atol=1e-5, equal_nan=True)
+    if algo != pp.POP_ALGO_TD3_SHARED:
+        assert (y0[0] == np.inf).all() and np.isinf(y0[1]).any() and np.isfinite(y0[1]).any()
+    if algo == pp.POP_ALGO_TD3:
+        for a, b in zip(g0, g1):
+            assert np.isinf(a).any()
+            assert np.array_equal(np.isnan(a), np.isnan(b)) and np.array_equal(np.isinf(a), np.isinf(b))
 
 
 @pytest.mark.parametrize("algo,O,A", [(pp.POP_ALGO_TD3, 17, 6), (pp.POP_ALGO_TD3, 56, 8), (pp.POP_ALGO_SAC, 17, 6),

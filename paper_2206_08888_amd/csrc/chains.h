@@ -1021,6 +1021,19 @@ inline size_t chain_bytes(int fan_in, int vec, int stage = G::kStage, int region
 }
 inline int vec_critic(const PopDev&) { return vec_critic_floats; }
 inline int vec_actor(const PopDev& d) { return vec_actor_floats_for(d.A > kMaxAct ? kSacMaxAct : kMaxAct); }
-constexpr int kActScratch = kMaxHead / kMaxAct;      // acting: one head block of [32][kMaxHead]
+
+// LDS of an acting workgroup (floats): activation tile | head block [32][kMaxHead] | head bias | input tile, which is done
+// with once the first layer has been, and in its place the slabs of the hidden product.  Side by side the two let
+// only one workgroup onto a CU from 105 inputs on (two up to 320 like this): 80 agents x 1000 rows of 111 inputs 229.6 us against 153.2.
+struct ActMap {
+  static constexpr int buf = 0, head = 32 * kLda, bias = head + 32 * kMaxHead, input = bias + kMaxHead;
+  int xld;
+  __host__ __device__ constexpr explicit ActMap(int obs) : xld((obs + 7) / 8 * 8 + 4) {}
+  __host__ constexpr size_t bytes() const {
+    const int tile = 32 * xld, stage = Rows32<1>::kStage;
+    return (size_t)(input + (tile > stage ? tile : stage)) * sizeof(float);
+  }
+};
+static_assert(ActMap::input % 4 == 0, "16-byte reads of the input tile and the slabs");
 
 }  // namespace pop

@@ -85,12 +85,12 @@ __global__ __launch_bounds__(kThreads) void k_act(PopDev d, const float* __restr
   constexpr int R = 32;
   extern __shared__ float lds[];
   constexpr int kHs = kMaxHead;                      // row stride of the head block
-  const Lds<1> L(d.O, kActScratch);
-  float* Xs = lds;
+  const ActMap L(d.O);
+  float* Xs = lds + L.input;
   float* buf = lds + L.buf;
-  float* head = lds + L.s(0);
-  float* v_ab3 = lds + L.vec;
-  float* stage = v_ab3 + kMaxHead;
+  float* head = lds + L.head;
+  float* v_ab3 = lds + L.bias;
+  float* stage = Xs;                                 // the input tile is done with when the hidden layer starts
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int agent = blockIdx.y, r0 = blockIdx.x * R;
   const int valid = n - r0 < R ? n - r0 : R;
@@ -182,7 +182,7 @@ size_t td3_lds_bytes(const PopDev& d) {
   m = std::max(m, chain(d.rows_a, vec_actor(d), true, regions));
   return std::max(m, act_lds_bytes(d));
 }
-size_t act_lds_bytes(const PopDev& d) { return chain_bytes<Rows32<1>>(d.O, kMaxHead, Rows32<1>::kStage, kActScratch); }
+size_t act_lds_bytes(const PopDev& d) { return ActMap(d.O).bytes(); }
 
 hipError_t launch_target(const PopDev& d, uint32_t t, hipStream_t s) {
   const dim3 grid(xcd_grid(d.P, d.B / d.rows_t)), block(kThreads);

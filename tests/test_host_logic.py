@@ -1,6 +1,7 @@
 """Host-side logic of the library that needs no GPU: the block-id decoding of the kernels, compiled for the host
 from the library's own header."""
 import os
+import re
 import subprocess
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -25,3 +26,15 @@ def test_acting_workgroups_per_cu(tmp_path):
                     os.path.join(ROOT, "tests", "host", "act_lds_check.cpp"), "-o", str(exe)], check=True)
     out = subprocess.run([str(exe)], capture_output=True, text=True)
     assert out.returncode == 0 and "bad 0" in out.stdout, out.stdout[-2000:]
+
+
+def test_wide_chains_that_have_a_cu_to_themselves_do_not_spill(tmp_path):
+    """The wide-input kernels of k_chain.hip bounded to one workgroup per CU keep everything in registers."""
+    from paper_2206_08888_amd import build
+    asm = tmp_path / "k_chain.s"
+    subprocess.run([build._hipcc(), *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, "k_chain.hip"), "-o", str(asm)],
+                   check=True, capture_output=True)
+    spills = dict(re.findall(r"\.name: +(_ZN3pop\S*Rows\d+Deep\S*).*?\.vgpr_spill_count: +(\d+)", asm.read_text(), re.S))
+    two = [k for k in spills if "k_target" in k and "Rows32Deep" in k and "ELi2ELi" in k]      # bounded to two: registers for occupancy
+    assert len(two) == 2 and len(spills) >= 9
+    assert all(n == "0" for k, n in spills.items() if k not in two), spills

@@ -233,6 +233,7 @@ struct Rows32 {                                      // 32 MT rows on 32x32 tile
   using Pre = LayerPre<MT>;
   using WtBlock = WeightRaw<true>;
   static constexpr int kStage = SLABS ? 2 * slab_floats<MT>() : 0, kStageForward = kStage;
+  static constexpr bool kStageOnInput = false;       // critic chains: CriticMap
   __device__ static inline void load_wt(WtBlock& wt, const float* W, int wave, int lane) { wt.load(W, 0, wave, lane); }
   __device__ static inline void load_input(float* Xl, int xld, const float* rows, int row_stride, int c0, int n, int valid,
                                            int tid) {
@@ -303,6 +304,7 @@ struct Rows16 {                                      // 16 rows on v_mfma_f32_16
   };
   using WtBlock = WeightStage16;                     // the transposed products stage their weights through LDS
   static constexpr int kStage = kStage16, kStageForward = kHeadRed;   // floats of LDS they need for that
+  static constexpr bool kStageOnInput = false;
   __device__ static inline void load_wt(WtBlock& wt, const float* W, int wave, int lane) { wt.load(W, 0, wave, lane); }
   __device__ static inline void load_input(float* Xl, int xld, const float* rows, int row_stride, int c0, int n, int valid,
                                            int tid) {
@@ -412,6 +414,7 @@ struct Rows16 {                                      // 16 rows on v_mfma_f32_16
 // PF: weight blocks of 8 rows in flight; 8 where the registers allow it (the critic chain), else 4.
 template <int MT, int PF = 4>
 struct Rows32Deep : Rows32<MT> {
+  static constexpr bool kStageOnInput = true;
   using Pre = typename Rows32<MT>::Pre;
   __device__ static inline void load_input(float* Xl, int xld, const float* rows, int row_stride, int c0, int n, int valid,
                                            int tid) {
@@ -678,6 +681,27 @@ __device__ __forceinline__ void actor_forward_ahead(const PopDev& d, int agent, 
   }
 }
 
+// LDS of a critic chain.  A wide input tile (kStageOnInput) is done with once the first layer has been, and the slabs of
+// the products take its place: from 121 to 336 inputs two workgroups share a CU like that, one with the two side by
+// side (us/step at 140 inputs: TD3 with 96 agents 741 against 679, SAC with 64 agents 676 against 637).
+template <class G>
+struct CriticMap : LdsMap<G::R, G::kPad> {
+  using Base = LdsMap<G::R, G::kPad>;
+  int input = 0, stage;
+  __host__ __device__ explicit CriticMap(int fan_in) : Base(fan_in) {
+    if (G::kStageOnInput) {                          // activation tile | scratch | vectors | input tile and slabs
+      input = this->vec + vec_critic_floats - this->buf;
+      this->s0 -= this->buf; this->s1 -= this->buf; this->s2 -= this->buf; this->vec -= this->buf;
+      this->buf = 0;
+    }
+    stage = G::kStageOnInput ? input : this->vec + vec_critic_floats;
+  }
+  __host__ size_t bytes() const {
+    const int tile = G::R * this->xld;
+    return (size_t)(stage + (G::kStageOnInput && tile > G::kStage ? tile : G::kStage)) * sizeof(float);
+  }
+};
+
 // ---------------------------------------------------------------------------------------------
 // Critic forward + backward.  One workgroup per (critic network, chunk); network = 2 agent + k.
 //   L = (1/B) sum_b (Q_k(s_b, a_b) - y_b)^2 ;  dq = 2 (q - y) / B
@@ -691,13 +715,14 @@ __device__ __forceinline__ void actor_forward_ahead(const PopDev& d, int agent, 
 template <class G, bool WAIT, bool SIGNAL, bool AHEAD = false>
 __device__ __forceinline__ void critic_chain(const PopDev& d, uint32_t t, int net, int chunk, float* lds) {
   constexpr int R = G::R;
-  const LdsMap<G::R, G::kPad> L(d.D);
-  float* Xs = lds;
+  static_assert(!(AHEAD && G::kStageOnInput), "the forward pass ahead reads the input tile after the first product");
+  const CriticMap<G> L(d.D);
+  float* Xs = lds + L.input;
   float* buf = lds + L.buf;
   float* head = lds + L.s0;
   float* dq = lds + L.s1;
   float* v_w3 = lds + L.vec;                         // [256]
-  float* stage = lds + L.vec + vec_critic_floats;
+  float* stage = lds + L.stage;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int agent = net >> 1, k = net & 1, r0 = chunk * R;
   const float* cn = net_ptr(d, d.theta, agent, 1 + k);

@@ -31,22 +31,32 @@ def smallest_margin(net, cache):
     return min(float(r.min()) for r in relative_margins(net, cache))
 
 
+def equal_rows(cache):
+    """For every batch row the first row with the same network input: equal inputs (a replay row drawn twice) have equal
+    pre-activations, whose ties any one computation resolves alike."""
+    _, first, inverse = np.unique(cache[0][0], axis=0, return_index=True, return_inverse=True)
+    return first[inverse.reshape(-1)]
+
+
 def candidates(nets_and_caches, rho_max, limit):
-    """[(rho, which pass, layer, row, unit)] of the hidden units closest to their kink, ascending, at most `limit`."""
-    found = []
+    """[(rho, which pass, layer, row, unit)] of the hidden units closest to their kink, ascending, at most `limit`; rows with
+    equal inputs are one candidate, named by the first of them."""
+    found = {}
     for p, (net, cache) in enumerate(nets_and_caches):
+        same = equal_rows(cache)
         for l, rho in enumerate(relative_margins(net, cache)):
-            rows, units = np.nonzero(rho < rho_max)
-            found += [(float(rho[r, u]), p, l, int(r), int(u)) for r, u in zip(rows, units)]
-    found.sort()
-    return found[:limit]
+            for r, u in zip(*np.nonzero(rho < rho_max)):
+                key = (p, l, int(same[r]), int(u))
+                found[key] = min(found.get(key, np.inf), float(rho[r, u]))
+    return sorted((rho,) + key for key, rho in found.items())[:limit]
 
 
 def flip(cache, layer, row, unit):
-    """Resolve one hidden unit the other way (in place): the sign of its stored pre-activation decides the mask in
-    mlp.backward; its magnitude is below anything the gradient can see."""
+    """Resolve one hidden unit the other way (in place), on all rows with this row's input: the sign of its stored
+    pre-activation decides the mask in mlp.backward; its magnitude is below anything the gradient can see."""
+    rows = np.flatnonzero((cache[0][0] == cache[0][0][row]).all(axis=1))
     z = cache[1][layer][row, unit]
-    cache[1][layer][row, unit] = -z if z != 0.0 else 1e-300
+    cache[1][layer][rows, unit] = -z if z != 0.0 else 1e-300
 
 
 def unflatten(flat, fan_in, fan_out, hidden=(256, 256)):

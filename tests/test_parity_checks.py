@@ -208,3 +208,33 @@ def test_explain_finds_planted_flips_in_the_actor_phase():
     g_dev = dev.gradient()
     base, err, kept, rho0 = rt.explain(clean, g_dev, rho_max=np.inf, limit=8, goal=1e-9)
     assert base > 1e-6 and err < 1e-12 and len(kept) == 2      # (a row drawn twice gives two equivalent candidates)
+
+
+def test_explain_flips_equal_rows_together():
+    """A replay row drawn twice meets a tie twice, and both are resolved the other way.  With loss gradients of opposite
+    sign on the two rows, either flip alone leads away from the device's gradient; only the pair explains it."""
+    import relu_ties as rt
+    from oracle import mlp
+    ref, _ = _pair(0)
+    critic_before = mlp.copy_net(ref.agents[0].critic[0])
+    ref.update(1)
+    ag = ref.agents[0]
+    idx = np.asarray(ag.last["idx"])
+    r0, r1 = next(tuple(np.flatnonzero(idx == i)[:2]) for i in idx if (idx == i).sum() == 2)
+    def make(z):
+        net = mlp.copy_net(critic_before)
+        W, b = net[0]
+        s, a = (x.astype(np.float64) for x in ag.buffer.gather(idx)[:2])
+        b[11] = z - float(np.concatenate([s, a], axis=1)[r0] @ W[:, 11])
+        ps = rt.CriticPass(ag, net)
+        ps.dy[r0], ps.dy[r1] = 0.02, -0.015
+        return ps
+    clean, dev = make(+1e-9), make(-1e-9)
+    g_dev = dev.gradient()
+    base = pc.rel_l2(g_dev, clean.gradient())
+    for r in (r0, r1):                                         # one row alone: the error grows
+        alone = make(+1e-9)
+        alone.cache[1][0][r, 11] *= -1.0
+        assert pc.rel_l2(g_dev, alone.gradient()) > 1.2 * base > 1e-4
+    b, err, kept, rho0 = rt.explain(clean, g_dev)
+    assert b == base and err < 1e-7 and [c[1:] for c in kept] == [(0, 0, min(r0, r1), 11)] and rho0 < 1e-8

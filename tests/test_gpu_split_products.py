@@ -6,6 +6,7 @@ import pytest
 
 import paper_2206_08888_amd as pp
 from gpu_common import ensure_built, rel_l2
+from oracle import sac as oracle_sac, td3 as oracle_td3, td3_shared as oracle_shared
 
 pytestmark = pytest.mark.gpu
 H = 256
@@ -14,11 +15,14 @@ H = 256
 def _population(algo, P, O, A, capacity=64, **tuning):
     ensure_built()
     cfg = pp.make_config(P, O, A, (H, H), 256, capacity, algo=algo, **tuning)
+    return pp.Population(cfg, _hparams(algo, P, A))
+
+
+def _hparams(algo, P, A):
     sac = algo == pp.POP_ALGO_SAC
-    hps = [dict(seed=7 + i, lr_actor=3e-4, lr_critic=3e-4, gamma=0.99, tau=0.005, policy_noise=0.2, noise_clip=0.5,
+    return [dict(seed=7 + i, lr_actor=3e-4, lr_critic=3e-4, gamma=0.99, tau=0.005, policy_noise=0.2, noise_clip=0.5,
                 policy_delay=1 if sac else 2, adam_b1=0.9, adam_b2=0.999, adam_eps=1e-8, lr_alpha=3e-4,
                 target_entropy=-float(A) if sac else 0.0, init_log_alpha=0.0) for i in range(P)]
-    return pp.Population(cfg, hps)
 
 
 def _act64(theta, obs, O, A, out):
@@ -151,6 +155,68 @@ def test_update_with_infinities(algo, rows):
         for a, b in zip(g0, g1):
             assert np.isinf(a).any()
             assert np.array_equal(np.isnan(a), np.isnan(b)) and np.array_equal(np.isinf(a), np.isinf(b))
+
+
+ORACLES = {pp.POP_ALGO_TD3: oracle_td3, pp.POP_ALGO_SAC: oracle_sac, pp.POP_ALGO_TD3_SHARED: oracle_shared}
+
+
+def fix_masks(orc, rng):
+    """Biases that keep every hidden unit of every network of an oracle population away from its kink: +-4 in the first
+    layer (its sums are about 0.5), in the second what brings a unit's mean to +-2.5 (six times what a row changes) -- so the hidden
+    sums still cancel to a tenth of their terms, and an error of the terms shows.  Small heads for the policies."""
+    seen = set()
+    for ag in orc.agents:
+        nets = [(ag.actor, True), (ag.critic[0], False), (ag.critic[1], False), (ag.t_critic[0], False), (ag.t_critic[1], False)]
+        if hasattr(ag, "t_actor"):
+            nets.append((ag.t_actor, True))
+        for net, policy in nets:
+            if id(net) in seen:
+                continue
+            seen.add(id(net))
+            (w1, b1), (w2, b2), (w3, b3) = net
+            b1[:] = rng.choice([-4.0, 4.0], H)
+            b2[:] = np.round(8 * (rng.choice([-2.5, 2.5], H) - np.maximum(b1, 0.0) @ w2)) / 8
+            if policy:
+                w3 *= 1 / 16
+
+
+@pytest.mark.parametrize("algo,O,A", [(pp.POP_ALGO_TD3, 17, 6), (pp.POP_ALGO_TD3, 56, 8), (pp.POP_ALGO_SAC, 17, 6),
+                                      (pp.POP_ALGO_SAC, 40, 24), (pp.POP_ALGO_TD3_SHARED, 17, 6)])
+@pytest.mark.parametrize("rows", [(16, 32, 16), 32, 64])
+def test_gradients_against_64_bits(algo, O, A, rows):
+    """One update step of every network, no hidden unit near its kink: the gradients against 64-bit arithmetic."""
+    P, n = 3, 64
+    pop = _population(algo, P, O, A, rows=rows)
+    orc = ORACLES[algo].Population([dict(h, lr_critic=1e-12) for h in _hparams(algo, P, A)], O, A, [H, H], 256, n)
+    for i in range(P):
+        pop.set_hparams(i, dict(_hparams(algo, P, A)[i], lr_critic=1e-12))     # the policy step meets the critics as they were
+    g = np.random.default_rng(5)
+    fix_masks(orc, g)
+    for i in range(P):
+        tr = dict(obs=g.standard_normal((n, O)).astype(np.float32), act=g.uniform(-1, 1, (n, A)).astype(np.float32),
+                  rew=g.standard_normal(n).astype(np.float32), done=(g.random(n) < 0.1).astype(np.float32),
+                  next_obs=g.standard_normal((n, O)).astype(np.float32))
+        pop.insert(i, **tr)
+        orc.insert(i, **tr)
+        for net in ("actor", "critic1", "critic2", "t_actor", "t_critic1", "t_critic2"):
+            if not (algo == pp.POP_ALGO_SAC and net == "t_actor"):
+                pop.set_params(i, net, orc.get_params(i, net))
+    pop.set_debug(True)
+    pop.update(1)
+    orc.update(1)
+    errors = {}
+    for i in range(P):
+        for net in ("critic1", "critic2", "actor"):
+            fan_in, out = (O, 2 * A if algo == pp.POP_ALGO_SAC else A) if net == "actor" else (O + A, 1)
+            got, want = pop.get_params(i, "g_" + net), orc.get_params(i, "g_" + net)
+            for name, x, y in zip(("W1", "b1", "W2", "b2", "W3", "b3"), _views(got, fan_in, out), _views(want, fan_in, out)):
+                errors[net, name] = max(errors.get((net, name), 0.0), rel_l2(x, y))
+    pop.close()
+    print("algo %d, obs %d, act %d, rows %s: %s" % (algo, O, A, rows, {k: "%.1e" % v for k, v in errors.items()}))
+    # four products in sequence, 2e-7 each on the fp32 instructions, and the batch sum's 1.4e-7: 4.3e-7, and twice that.
+    # (Measured 1.6e-7 .. 4.7e-7 with 16 rows, 1.6e-7 .. 4.3e-7 with 32 and 64; without the low parts of one operand the
+    # W3 gradients of a forward product are 3.7e-6 off, the W1 gradients of a backward one 3.2e-6.)
+    assert max(errors.values()) < 1e-6, errors
 
 
 @pytest.mark.parametrize("algo,O,A", [(pp.POP_ALGO_TD3, 17, 6), (pp.POP_ALGO_TD3, 56, 8), (pp.POP_ALGO_SAC, 17, 6),

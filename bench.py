@@ -16,7 +16,9 @@ Timing: max(W, 20) untimed warm-up steps, then R (default 5) repeats of exactly 
 pop_update(K) call bracketed by a synchronisation on both sides; the line reports the MEDIAN repeat.
 
 Prints ONE JSON line: agent-updates/s = P * K / seconds, with
-  roofline      the dominant kernel against the fp32 MFMA peak (launch time from HIP events on the library's stream);
+  roofline      the dominant kernel against the fp32 MFMA peak (launch time from HIP events on the library's stream); the
+                256-deep products of 32- and 64-row chains run on the bf16 matrix pipe (six products of exactly split
+                operands, 2.7 times that peak), the rest on the fp32 instructions: the peak is a yardstick there, no ceiling;
   hbm           achieved GB/s of the memory-bound parts (replay gather, weight-gradient tiles with Adam / Polyak)
                 against the 8 TB/s HBM peak: algorithmic bytes / launch time;
   counters      what rocprofv3 counter runs recorded for the same kernels (profiles/*.txt: HBM bytes per launch,
@@ -35,7 +37,7 @@ import numpy as np
 
 import workloads
 
-MFMA_FP32_PEAK_TFLOPS = 157.3      # MI355X dense fp32 matrix peak
+MFMA_FP32_PEAK_TFLOPS = 157.3      # MI355X dense fp32 matrix peak: the yardstick of every fraction below
 HBM_PEAK_GBPS = 8000.0             # MI355X HBM3E
 H = 256
 ROOT = os.path.dirname(os.path.abspath(__file__))

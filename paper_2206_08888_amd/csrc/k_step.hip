@@ -135,10 +135,8 @@ hipError_t launch_step(const PopDev& dev, uint32_t t, uint32_t launch_seq, int w
   if (d.rows_a == 16) {
     need(chain_bytes<Rows16>(d.D, vec_ta));
     need(chain_bytes<Rows32<2>>(d.D, vec_critic(d)));
-    // One workgroup per CU for small populations: the request is kept above half of a CU's LDS (the 64-row
-    // critic chain alone needs 80,928 of the 81,920 bytes that would let two share).  With two per CU the actor
-    // chains start earlier but every chain then shares its matrix pipe: 118 against 100 us/step at P = 10.
-    need((size_t)kLdsPerCU / 2 + 64);
+    // (One workgroup per CU: the 64-row critic chain with its slabs takes 136 KB at 17 / 6.  With two per CU, on the fp32
+    // products, the actor chains started earlier but every chain shared its matrix pipe: 118 against 100 us/step at P = 10.)
     POP_STEP_SMALL<<<grid, block, bytes, s>>>(d, t, g);
   } else if (d.rows_a == 32) {
     need(chain_bytes<Rows32<1>>(d.D, vec));

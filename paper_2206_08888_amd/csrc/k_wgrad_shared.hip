@@ -48,12 +48,12 @@ __global__ __launch_bounds__(kThreads, 3) void k_shared_partial(PopDev d, uint32
       const float* z = (w2 ? d.cdZ2 : d.cdZ1) + o + n0;
       XSlice xsl;
       xsl.load(x, ldx, M, m0, wave, lane);
-      WeightBlock<1, false, 1> z0;
+      ZBlock z0;
       z0.load(z, 0, wave, lane);
       __syncthreads();                               // the previous agent's product has read the slice
       xsl.store(xt_lds, ldx, M, m0, wave, lane);
       __syncthreads();
-      gemm256_unrolled<1, false, 1, 4, true>(xt_lds, kLda, z, z0, wave, lane, acc, NoTail());
+      gemm256_unrolled<4>(xt_lds, kLda, z, z0, wave, lane, acc);
     }
     const int half = lane >> 5, l32 = lane & 31;
     const uint32_t elem0 = (uint32_t)((w2 ? L.w2 : L.w1) + (m0 + 4 * half) * kH + n0 + 32 * wave + l32);

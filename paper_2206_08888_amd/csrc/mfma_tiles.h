@@ -1,11 +1,12 @@
-// Wavefront-level fp32 MFMA building blocks for the per-agent MLP layers.
+// Wavefront-level MFMA building blocks for the per-agent MLP layers.
 //
-// All dense contractions of the update step (App. C of the paper: y = x W + b
-// per population member, and the matching backward products) run on
-// v_mfma_f32_32x32x2_f32: one instruction multiplies a 32x2 slice of A by a
-// 2x32 slice of B into a 32x32 fp32 tile held as 16 registers per lane.
+// The dense contractions of the update step (App. C of the paper: y = x W + b per population member, and the matching
+// backward products) on 32x32 tiles: first layers and weight gradients on v_mfma_f32_32x32x2_f32 (one instruction
+// multiplies a 32x2 slice of A by a 2x32 slice of B into a 32x32 fp32 tile held as 16 registers per lane), the 256-deep
+// products of 32- and 64-row chains on v_mfma_f32_32x32x16_bf16 from split operands (SplitProduct below).  (16-row chains:
+// mfma_tiles16.h.)
 //
-// Operand layout of that instruction on a 64-lane wavefront:
+// Operand layout of the fp32 instruction on a 64-lane wavefront:
 //   A: lane l supplies A[row = l & 31][k = l >> 5]
 //   B: lane l supplies B[k = l >> 5][col = l & 31]
 //   D: register v of lane l is D[row = 8 (v >> 2) + 4 (l >> 5) + (v & 3)][col = l & 31]
@@ -150,19 +151,6 @@ struct Acc {
         for (int v = 0; v < 16; ++v) t[a][b][v] += __builtin_amdgcn_fmed3f(o.t[a][b][v], -most, most);
   }
 };
-
-// f(row, col, value) for every accumulator element this lane holds;
-// row in [0, 32 MT), col in [0, 256).
-template <int MT, class F>
-__device__ inline void for_each_acc(const Acc<MT>& acc, int wave, int lane, F f) {
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-      for (int v = 0; v < 16; ++v)
-        f(32 * mt + acc_row(v, lane), tile_col(wave, nt, lane), acc.t[mt][nt][v]);
-}
 
 // First-layer weights of one lane for the leading 32 rows of W (k = 8 i + 4 half + j),
 // fetched ahead of time so that the product does not wait for memory.
@@ -324,151 +312,83 @@ __device__ inline void gemm_xw_deep(const float* __restrict__ Xl, int ldx, int K
   }
 }
 
-// Software-pipelined 256-deep contraction of an LDS operand with a global weight
-// operand; the contraction index is walked in 16 blocks of 16.
-//   forward  (TRANSPOSED = false): acc[r][c] += sum_k X[r][k] W[k][c], c in this wave's 64 columns
-//   backward (TRANSPOSED = true):  acc[r][k] += sum_n Z[r][n] W[k][n], k in this wave's 64 columns
-// W is row-major [256][256] in both cases.  Weight registers rotate through four
-// buffers: block j+3 is requested from memory before the MFMAs of block j start,
-// so about 3000 MT cycles of matrix work cover the L2 / memory latency; the LDS
-// operand is fetched one block ahead.  Block 0 is passed in by the caller, who
-// requests it as early as it can (typically under the previous product);
-// `tail()` runs once no further weight block of this product is needed, so the
-// caller can start the loads of the next layer under the last three blocks.
-// __builtin_amdgcn_sched_barrier keeps the compiler from sinking loads back next
-// to their uses.
-template <int MT, bool TRANSPOSED, int NT = 2>
-struct WeightBlock {                       // the weights one lane needs for a 16-deep block
-  float w[NT][8];                          // [column tile][4 s + j]  <->  index 16 i + 8 s + 4 half + j
-  // column of W (forward) or row of W (transposed) that lane l32 holds of tile nt: with two tiles per wavefront
-  // the lane's two columns are neighbours, so that the forward product fetches both with one load
-  __device__ static constexpr int col_of(int wave, int nt, int l32) {
-    return NT == 2 ? tile_col(wave, nt, l32) : 32 * wave + l32;
+// 256-deep contraction of 32 rows of an LDS operand with 32 columns per wavefront of a global operand Z (row-major
+// [..][256]) on the fp32 instructions, for the weight-gradient tiles:  acc[r][c] += sum_k X[r][k] Z[k][c].  The
+// contraction index is walked in blocks of 16.
+struct ZBlock {                            // what one lane needs of Z for a block
+  float w[8];                              // [4 s + j]  <->  index 16 i + 8 s + 4 half + j
+  static constexpr int kPieces = 8;        // load instructions per block
+  __device__ static inline const float* lane_base(const float* __restrict__ Z, int wave, int lane) {
+    return Z + 4 * (lane >> 5) * kH + 32 * wave + (lane & 31);
   }
-  __device__ inline void load(const float* __restrict__ W, int i, int wave, int lane) {
-    const int half = lane >> 5, l32 = lane & 31;
-    if (TRANSPOSED) {
+  __device__ inline void load_piece(const float* __restrict__ blk, int p) { w[p] = blk[(8 * (p >> 2) + (p & 3)) * kH]; }
+  __device__ inline void load(const float* __restrict__ Z, int i, int wave, int lane) {
+    const float* blk = lane_base(Z, wave, lane) + 16 * i * kH;
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const float* row = W + col_of(wave, nt, l32) * kH + 16 * i + 4 * half;
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-          const f32x4 v = *reinterpret_cast<const f32x4*>(row + 8 * s);
-          w[nt][4 * s + 0] = v[0]; w[nt][4 * s + 1] = v[1]; w[nt][4 * s + 2] = v[2]; w[nt][4 * s + 3] = v[3];
-        }
-      }
-    } else if (NT == 2) {                            // the lane's two columns are neighbours: one 8-byte load per row
-      const float* col = W + (16 * i + 4 * half) * kH + 64 * wave + 2 * l32;
-#pragma unroll
-      for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const f32x2 v = *reinterpret_cast<const f32x2*>(col + (8 * s + j) * kH);
-          w[0][4 * s + j] = v[0];
-          w[NT - 1][4 * s + j] = v[1];
-        }
-    } else {
-      const float* col = W + (16 * i + 4 * half) * kH + 32 * NT * wave + l32;
-#pragma unroll
-      for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt) w[nt][4 * s + j] = col[(8 * s + j) * kH + 32 * nt];
-    }
-  }
-  // The same block as kPieces separate load instructions, in the order of use, from this lane's pointer into W
-  // (lane_base) moved on to block i by the caller: blk = lane_base(W) + 16 i kH (forward) or + 16 i (transposed).
-  static constexpr int kPieces = TRANSPOSED ? 2 * NT : 8;
-  __device__ static inline const float* lane_base(const float* __restrict__ W, int wave, int lane) {
-    const int half = lane >> 5, l32 = lane & 31;
-    return TRANSPOSED ? W + col_of(wave, 0, l32) * kH + 4 * half : W + 4 * half * kH + col_of(wave, 0, l32);
-  }
-  __device__ inline void load_piece(const float* __restrict__ blk, int p) {
-    if (TRANSPOSED) {
-      const int s = p / NT, nt = p % NT;
-      const f32x4 v = *reinterpret_cast<const f32x4*>(blk + (col_of(0, nt, 0) - col_of(0, 0, 0)) * kH + 8 * s);
-      w[nt][4 * s + 0] = v[0]; w[nt][4 * s + 1] = v[1]; w[nt][4 * s + 2] = v[2]; w[nt][4 * s + 3] = v[3];
-    } else if (NT == 2) {
-      const int s = p >> 2, j = p & 3;
-      const f32x2 v = *reinterpret_cast<const f32x2*>(blk + (8 * s + j) * kH);
-      w[0][4 * s + j] = v[0];
-      w[NT - 1][4 * s + j] = v[1];
-    } else {
-      const int s = p >> 2, j = p & 3;
-      w[0][4 * s + j] = blk[(8 * s + j) * kH];
-    }
+    for (int p = 0; p < kPieces; ++p) load_piece(blk, p);
   }
 };
 
-template <int MT>
-struct LdsBlock {                          // the LDS operand of one block (16 deep)
-  f32x4 a[MT][2];
+struct LdsBlock {                          // the LDS operand of one block
+  f32x4 a[2];
+  __device__ inline void load_piece(const float* __restrict__ Xl, int ldx, int k0, int lane, int s) {
+    a[s] = *reinterpret_cast<const f32x4*>(&Xl[(lane & 31) * ldx + k0 + 8 * s + 4 * (lane >> 5)]);
+  }
   __device__ inline void load(const float* __restrict__ Xl, int ldx, int k0, int lane) {
-    const int half = lane >> 5, l32 = lane & 31;
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int s = 0; s < 2; ++s)
-        a[mt][s] = *reinterpret_cast<const f32x4*>(&Xl[(32 * mt + l32) * ldx + k0 + 8 * s + 4 * half]);
-  }
-  __device__ inline void load_piece(const float* __restrict__ Xl, int ldx, int k0, int lane, int p) {   // p < 2 MT
-    const int half = lane >> 5, l32 = lane & 31, mt = p >> 1, s = p & 1;
-    a[mt][s] = *reinterpret_cast<const f32x4*>(&Xl[(32 * mt + l32) * ldx + k0 + 8 * s + 4 * half]);
+    for (int s = 0; s < 2; ++s) load_piece(Xl, ldx, k0, lane, s);
   }
 };
 
-template <int MT, bool TRANSPOSED, int NT = 2>
-__device__ inline void mfma_block(const LdsBlock<MT>& x, const WeightBlock<MT, TRANSPOSED, NT>& b, Acc<MT, NT>& acc) {
-#pragma unroll
-  for (int s = 0; s < 2; ++s)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-          acc.t[mt][nt] = mfma32(x.a[mt][s][j], b.w[nt][4 * s + j], acc.t[mt][nt]);
-}
-
-// The MFMAs of one block with the loads of a later block (weights `nb` <- the block at `blk` when FEED, LDS operand
-// `nx` <- columns nk0.. when FEEDX) dealt out between them, one piece behind an MFMA until they are used up
-// (scheduling groups tell the compiler that order).  A matrix instruction keeps its pipe busy for 64 cycles after
-// it issues; load instructions issued in that shadow cost nothing, while a whole block's worth of them between
-// two blocks -- some 16 cycles each -- leaves the pipe idle for as long as they take to issue.  That shows where
-// two workgroups share a CU and the other wavefront of the SIMD is no further along: 25.6 us per 32-row product
-// for such a pair, 19.9 us in this form.  With one workgroup per CU the plain order is the faster one (8.7
-// against 9.4 us).
-template <int MT, bool TRANSPOSED, int NT, bool FEED, bool FEEDX>
-__device__ inline void mfma_block_fed(const LdsBlock<MT>& x, const WeightBlock<MT, TRANSPOSED, NT>& b, Acc<MT, NT>& acc,
-                                      WeightBlock<MT, TRANSPOSED, NT>& nb, const float* __restrict__ blk, LdsBlock<MT>& nx,
-                                      const float* __restrict__ Xl, int ldx, int nk0, int lane) {
-  constexpr int M = 8 * MT * NT, L = WeightBlock<MT, TRANSPOSED, NT>::kPieces, LX = 2 * MT;
-  constexpr int every = M / L > 0 ? M / L : 1;      // one MFMA in `every` is followed by a weight piece
-  if (FEEDX) {
-#pragma unroll
-    for (int p = 0; p < LX; ++p) nx.load_piece(Xl, ldx, nk0, lane, p);
-  }
+// The MFMAs of one block with the loads of a later block (`nz` <- the block at `blk` when FEED, LDS operand `nx` <- columns
+// nk0.. when FEEDX) dealt out between them, one piece behind an MFMA until they are used up (scheduling groups tell the
+// compiler that order).  A matrix instruction keeps its pipe busy for 64 cycles after it issues; load instructions issued in
+// that shadow cost nothing, while a whole block's worth of them between two blocks -- some 16 cycles each -- leaves
+// the pipe idle for as long as they take to issue, where the other wavefront of the SIMD is no further along.
+template <bool FEED, bool FEEDX>
+__device__ inline void mfma_block_fed(const LdsBlock& x, const ZBlock& b, Acc<1, 1>& acc, ZBlock& nz, const float* __restrict__ blk,
+                                      LdsBlock& nx, const float* __restrict__ Xl, int ldx, int nk0, int lane) {
+  constexpr int M = 8, L = ZBlock::kPieces, LX = 2;
+  if (FEEDX) nx.load(Xl, ldx, nk0, lane);
   if (FEED) {
 #pragma unroll
-    for (int p = 0; p < L; ++p) nb.load_piece(blk, p);
+    for (int p = 0; p < L; ++p) nz.load_piece(blk, p);
   }
 #pragma unroll
   for (int s = 0; s < 2; ++s)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-          acc.t[mt][nt] = mfma32(x.a[mt][s][j], b.w[nt][4 * s + j], acc.t[mt][nt]);
+    for (int j = 0; j < 4; ++j) acc.t[0][0] = mfma32(x.a[s][j], b.w[4 * s + j], acc.t[0][0]);
 #pragma unroll
   for (int m = 0; m < M; ++m) {
     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
     if (FEEDX && m < LX) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    if (FEED && m % every == 0 && m / every < L) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+    if (FEED && m < L) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
   }
   __builtin_amdgcn_sched_barrier(0);
+}
+
+// Fully unrolled with NB rotating buffers (block i + NB - 1 is requested under the MFMAs of block i): Z comes from memory
+// rather than L2 and a block is only 512 cycles of matrix work.  z0: block 0, from the caller, who requests it as early as it
+// can.  KB: blocks to contract over (16: all 256; 8: the half that Xl and Z point at).
+template <int NB, int KB = 16>
+__device__ inline void gemm256_unrolled(const float* __restrict__ Xl, int ldx, const float* __restrict__ Z, const ZBlock& z0,
+                                        int wave, int lane, Acc<1, 1>& acc) {
+  ZBlock zb[NB];
+  LdsBlock xb[2];
+  zb[0] = z0;
+#pragma unroll
+  for (int i = 1; i < NB - 1; ++i) zb[i].load(Z, i, wave, lane);
+  xb[0].load(Xl, ldx, 0, lane);
+  const float* zl = ZBlock::lane_base(Z, wave, lane);
+  constexpr int step = 16 * kH;
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < KB; ++i) {
+    const int n = i + NB - 1;
+    if (n < KB) mfma_block_fed<true, true>(xb[i & 1], zb[i % NB], acc, zb[n % NB], zl + n * step, xb[(i + 1) & 1], Xl, ldx, 16 * (i + 1), lane);
+    else if (i + 1 < KB) mfma_block_fed<false, true>(xb[i & 1], zb[i % NB], acc, zb[n % NB], zl, xb[(i + 1) & 1], Xl, ldx, 16 * (i + 1), lane);
+    else mfma_block_fed<false, false>(xb[i & 1], zb[i % NB], acc, zb[n % NB], zl, xb[(i + 1) & 1], Xl, ldx, 0, lane);
+  }
 }
 
 struct NoTail { __device__ inline void operator()() const {} };
@@ -688,45 +608,6 @@ __device__ inline void gemm256(const float* __restrict__ Xl, const float* __rest
   SplitProduct<MT, TRANSPOSED, SLABS> p;
   p.run(Xl, W, b0, slabs, wave, lane, acc, tail);
   if (!SLABS) __syncthreads();                       // every wavefront has read the tile
-}
-
-// The same product fully unrolled with NB rotating weight buffers (block i + NB - 1 is requested
-// before the MFMAs of block i): for operands that come from memory rather than L2 and for
-// narrow tiles (NT = 1), where a block is only 512 cycles of matrix work and four buffers
-// cover too little latency.  KB: blocks of 16 to contract over (16: all 256; 8: the half that Xl and W point at).
-template <int MT, bool TRANSPOSED, int NT, int NB, bool FED = false, int KB = 16, class Tail>
-__device__ inline void gemm256_unrolled(const float* __restrict__ Xl, int ldx, const float* __restrict__ W,
-                                        WeightBlock<MT, TRANSPOSED, NT>& b0, int wave, int lane, Acc<MT, NT>& acc,
-                                        Tail tail) {
-  WeightBlock<MT, TRANSPOSED, NT> wb[NB];
-  LdsBlock<MT> xb[2];
-  wb[0] = b0;
-#pragma unroll
-  for (int i = 1; i < NB - 1; ++i) wb[i].load(W, i, wave, lane);
-  xb[0].load(Xl, ldx, 0, lane);
-  if (FED) {                                         // loads between the MFMAs (mfma_block_fed)
-    const float* wl = WeightBlock<MT, TRANSPOSED, NT>::lane_base(W, wave, lane);
-    constexpr int step = TRANSPOSED ? 16 : 16 * kH;
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < KB; ++i) {
-      const int n = i + NB - 1;
-      if (i == KB - NB + 1) tail();
-      if (n < KB) mfma_block_fed<MT, TRANSPOSED, NT, true, true>(xb[i & 1], wb[i % NB], acc, wb[n % NB], wl + n * step, xb[(i + 1) & 1], Xl, ldx, 16 * (i + 1), lane);
-      else if (i + 1 < KB) mfma_block_fed<MT, TRANSPOSED, NT, false, true>(xb[i & 1], wb[i % NB], acc, wb[n % NB], wl, xb[(i + 1) & 1], Xl, ldx, 16 * (i + 1), lane);
-      else mfma_block_fed<MT, TRANSPOSED, NT, false, false>(xb[i & 1], wb[i % NB], acc, wb[n % NB], wl, xb[(i + 1) & 1], Xl, ldx, 0, lane);
-    }
-    return;
-  }
-#pragma unroll
-  for (int i = 0; i < KB; ++i) {
-    if (i + NB - 1 < KB) wb[(i + NB - 1) % NB].load(W, i + NB - 1, wave, lane);
-    if (i == KB - NB + 1) tail();
-    if (i + 1 < KB) xb[(i + 1) & 1].load(Xl, ldx, 16 * (i + 1), lane);
-    __builtin_amdgcn_sched_barrier(0);
-    mfma_block<MT, TRANSPOSED, NT>(xb[i & 1], wb[i % NB], acc);
-    __builtin_amdgcn_sched_barrier(0);
-  }
 }
 
 // ReLU epilogue of a hidden layer: Y = max(acc + b, 0) goes to LDS (row stride

@@ -178,7 +178,7 @@ __device__ __forceinline__ void weight_tile(const PopDev& d, const uint32_t* wai
   XSlice xsl;
   auto load_x = [&]() { xsl.load(x, ldx, M, m0, wave, lane); };
   auto store_x = [&]() { xsl.store(Xl, ldx, M, m0, wave, lane); };
-  WeightBlock<1, false, 1> z0;
+  ZBlock z0;
   const float* zk = z + n0 + (size_t)kh * 128 * kH;   // this wavefront's rows of dZ
   if (WAIT && wait_on) {                             // x and z come from a chain of this launch
     // The counter is read before anything else is requested: a wavefront's loads come back in the order they went
@@ -207,8 +207,7 @@ __device__ __forceinline__ void weight_tile(const PopDev& d, const uint32_t* wai
   const Adam adam = *sh;
   Acc<1, 1> acc;
   acc.zero();
-  gemm256_unrolled<1, false, 1, SLIM ? 4 : 8, true, HALF ? 8 : 16>(Xl + 128 * kh, kLda, zk, z0, cw, lane, acc, NoTail());   // loads between the MFMAs: a
-                                                     // block is 8 MFMAs and 8 load instructions, and these kernels run two workgroups per CU
+  gemm256_unrolled<SLIM ? 4 : 8, HALF ? 8 : 16>(Xl + 128 * kh, kLda, zk, z0, cw, lane, acc);
   POP_MARK(53);
   __syncthreads();                                   // every wavefront is done with the X slice
 #pragma unroll

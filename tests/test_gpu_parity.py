@@ -554,3 +554,26 @@ def test_wide_target_chains_that_share_a_cu(obs_dim, act_dim):
     print("first step at P = 33, obs %d, act %d: %s; ties %s" % (obs_dim, act_dim, rep, ties))
     assert len(ties) <= 2, ties
     gpu.close()
+
+
+def test_noise_scales_of_many_agents_and_of_calls_in_a_row():
+    """The scales travel as kernel arguments, 256 agents to a launch: agents 256 .. 299 act as in a population of their own,
+    and calls issued without waiting each use their own scales."""
+    import torch
+    hps = workloads.hparams(2, 300)
+    obs = torch.randn((300, 3, 17), generator=torch.Generator().manual_seed(1)).cuda()
+    sigma = np.linspace(0.01, 0.3, 300).astype(np.float32)
+    pops = [pp.Population(pp.make_config(len(h), 17, 6, (256, 256), 256, 64), h) for h in (hps, hps[256:])]
+    whole = pops[0].act(obs, sigma, step=5)
+    rest = pops[1].act(obs[256:].contiguous(), sigma[256:], step=5)
+    pops[0].sync(); pops[1].sync()
+    assert torch.equal(whole[256:], rest)
+    several = [pops[0].act(obs, s * sigma, step=5) for s in (1.0, 0.5, 2.0, 1.0)]     # nothing waits in between
+    pops[0].sync()
+    assert torch.equal(several[0], whole) and torch.equal(several[3], whole)
+    for s, got in zip((0.5, 2.0), several[1:3]):
+        alone = pops[0].act(obs, s * sigma, step=5)
+        pops[0].sync()
+        assert torch.equal(got, alone) and not torch.equal(got, whole)
+    for p in pops:
+        p.close()

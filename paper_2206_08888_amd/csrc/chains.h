@@ -411,8 +411,8 @@ struct Rows16 {                                      // 16 rows on v_mfma_f32_16
 
 // The same tiles for first layers with a fan-in of several hundred (the SAC Humanoid shapes): only the
 // first-layer product differs (software-pipelined beyond the prefetched rows).
-// PF: weight blocks of 8 rows in flight; 8 where the registers allow it (the critic chain), else 4.
-template <int MT, int PF = 4>
+// PF: weight blocks of 16 rows in flight; 4 where the registers allow it (the critic chain), else 2.
+template <int MT, int PF = 2>
 struct Rows32Deep : Rows32<MT> {
   static constexpr bool kStageOnInput = true;
   using Pre = typename Rows32<MT>::Pre;

@@ -137,12 +137,10 @@ hipError_t setup_kernels() {
 #define POP_SET_LDS(...)                                                                                   \
   if ((e = hipFuncSetAttribute((const void*)__VA_ARGS__, hipFuncAttributeMaxDynamicSharedMemorySize, most)) != hipSuccess) return e
   POP_SET_LDS(k_target<Rows16Deep, 1, kSacMaxAct>);
-  POP_SET_LDS(k_target<Rows32Deep<1>, 1, kSacMaxAct>);
   POP_SET_LDS(k_target<Rows32Deep<1>, 2, kSacMaxAct>);
   POP_SET_LDS(k_actor<Rows16Deep, 1, false, kSacMaxAct>);
   POP_SET_LDS(k_actor<Rows32Deep<1>, 1, false, kSacMaxAct>);
   POP_SET_LDS(k_target<Rows16Deep>);
-  POP_SET_LDS(k_target<Rows32Deep<1>, 1>);
   POP_SET_LDS(k_target<Rows32Deep<1>, 2>);
   POP_SET_LDS(k_actor<Rows16Deep>);
   POP_SET_LDS(k_actor<Rows32Deep<1>>);
@@ -151,7 +149,7 @@ hipError_t setup_kernels() {
   POP_SET_LDS(k_target<Rows32<2>>);
   POP_SET_LDS(k_critic<Rows32<1>>);
   POP_SET_LDS(k_critic<Rows32<2>>);
-  POP_SET_LDS(k_critic<Rows32Deep<1, 8>>);
+  POP_SET_LDS(k_critic<Rows32Deep<1, 4>>);
   POP_SET_LDS(k_actor<Rows16>);
   POP_SET_LDS(k_actor<Rows32<1>>);
   POP_SET_LDS(k_actor<Rows32<1>, 2>);
@@ -189,21 +187,15 @@ size_t act_lds_bytes(const PopDev& d) { return ActMap(d.O).bytes(); }
 
 hipError_t launch_target(const PopDev& d, uint32_t t, hipStream_t s) {
   const dim3 grid(xcd_grid(d.P, d.B / d.rows_t)), block(kThreads);
-  // 32-row chains of wide shapes: two workgroups share a CU where their LDS lets them and there is more than one per CU.  A
-  // kernel bounded to 256 registers for that spills 30 of them and is the slower one elsewhere (us/step, one / two:
-  // 20 agents 161.5 / 169.9 at 76 inputs; 64 agents 389.0 / 364.6 at 76, 508.8 / 527.5 at 148, 732.6 / 744.6 at 393).
-  const auto two = [&](size_t bytes) { return 2 * bytes <= (size_t)kLdsPerCU && (int)grid.x > kCUs; };
   if (d.A > kMaxAct) {                               // wide actions: scratch rows of kSacMaxAct floats, first layers as for wide inputs
     const size_t b32 = chain_bytes<Rows32<1>>(d.D, vec_target(d), Rows32<1>::kStage, kWideScratch);
     if (d.rows_t == 16) k_target<Rows16Deep, 1, kSacMaxAct><<<grid, block, chain_bytes<Rows16>(d.D, vec_target(d), Rows16::kStageForward, kWideScratch), s>>>(d, t);
-    else if (d.rows_t == 32 && two(b32)) k_target<Rows32Deep<1>, 2, kSacMaxAct><<<grid, block, b32, s>>>(d, t);
-    else if (d.rows_t == 32) k_target<Rows32Deep<1>, 1, kSacMaxAct><<<grid, block, b32, s>>>(d, t);
+    else if (d.rows_t == 32) k_target<Rows32Deep<1>, 2, kSacMaxAct><<<grid, block, b32, s>>>(d, t);
     else return hipErrorInvalidValue;
   } else if (d.D > kMaxIn) {                         // wide inputs: pipelined first layers, 16 or 32 rows
     const size_t b32 = chain_bytes<Rows32<1>>(d.D, vec_target(d));
     if (d.rows_t == 16) k_target<Rows16Deep><<<grid, block, chain_bytes<Rows16>(d.D, vec_target(d), Rows16::kStageForward), s>>>(d, t);
-    else if (d.rows_t == 32 && two(b32)) k_target<Rows32Deep<1>, 2><<<grid, block, b32, s>>>(d, t);
-    else if (d.rows_t == 32) k_target<Rows32Deep<1>, 1><<<grid, block, b32, s>>>(d, t);
+    else if (d.rows_t == 32) k_target<Rows32Deep<1>, 2><<<grid, block, b32, s>>>(d, t);
     else return hipErrorInvalidValue;
   } else if (d.rows_t == 16) k_target<Rows16><<<grid, block, chain_bytes<Rows16>(d.D, vec_target(d), Rows16::kStageForward), s>>>(d, t);
   else if (d.rows_t == 32) k_target<Rows32<1>><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec_target(d)), s>>>(d, t);
@@ -214,7 +206,7 @@ hipError_t launch_critic(const PopDev& d, uint32_t t, hipStream_t s) {
   const dim3 grid(xcd_grid(2 * d.P, d.B / d.rows_c)), block(kThreads);
   if (d.D > kMaxIn) {                                // wide inputs (SAC): 32 rows, pipelined first layer
     if (d.rows_c != 32) return hipErrorInvalidValue;
-    k_critic<Rows32Deep<1, 8>><<<grid, block, CriticMap<Rows32Deep<1, 8>>(d.D).bytes(), s>>>(d, t);
+    k_critic<Rows32Deep<1, 4>><<<grid, block, CriticMap<Rows32Deep<1, 4>>(d.D).bytes(), s>>>(d, t);
   } else if (d.rows_c == 32) k_critic<Rows32<1>><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec_critic(d)), s>>>(d, t);
   else k_critic<Rows32<2>><<<grid, block, chain_bytes<Rows32<2>>(d.D, vec_critic(d)), s>>>(d, t);
   return hipGetLastError();

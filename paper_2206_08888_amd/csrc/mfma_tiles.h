@@ -2,8 +2,8 @@
 //
 // The dense contractions of the update step (App. C of the paper: y = x W + b per population member, and the matching
 // backward products) on 32x32 tiles: first layers and weight gradients on v_mfma_f32_32x32x2_f32 (one instruction
-// multiplies a 32x2 slice of A by a 2x32 slice of B into a 32x32 fp32 tile held as 16 registers per lane), the 256-deep
-// products of 32- and 64-row chains on v_mfma_f32_32x32x16_bf16 from split operands (SplitProduct below).  (16-row chains:
+// multiplies a 32x2 slice of A by a 2x32 slice of B into a 32x32 fp32 tile held as 16 registers per lane), wide first
+// layers and the 256-deep products of 32- and 64-row chains on v_mfma_f32_32x32x16_bf16 from split operands (SplitProduct below).  (16-row chains:
 // mfma_tiles16.h.)
 //
 // Operand layout of the fp32 instruction on a 64-lane wavefront:
@@ -233,97 +233,84 @@ __device__ inline void gemm_xw_small(const float* __restrict__ Xl, int ldx, int 
   }
 }
 
-// The same product for a fan-in of several hundred: the 8-deep blocks beyond the prefetched 32
-// rows are software-pipelined, PF weight blocks (8 PF rows of W) in flight ahead of the matrix pipe.
+// The same product for a fan-in of several hundred, on the bf16 pipe (SplitProduct's six products, above): blocks of 16,
+// contraction index 16 i + 8 s + 4 half + j at element 4 s + j of a lane, both operands split in registers, PF weight
+// blocks in flight beyond the two that `pre` holds.  With 376 inputs the first layers are three fifths of a chain's
+// matrix work, and the fp32 instructions take 1024 cycles per block of 32 rows and wavefront; the 12 bf16 instructions
+// and the splits of 12 pairs per lane some 700.  20 TD3 agents, obs 376 / act 17: 308 -> 271 us/step; 32 SAC agents 513 -> 464.
+// X: as above; columns of the tile beyond K hold zeros (load_input_wide), and a block that would reach past the tile's
+// row reads its last four columns instead, where the weights are zero.
 template <int MT, int PF>
 __device__ inline void gemm_xw_deep(const float* __restrict__ Xl, int ldx, int K, const float* __restrict__ W,
                                     const SmallW& pre, int wave, int lane, Acc<MT>& acc) {
   const int half = lane >> 5, l32 = lane & 31;
-  const int nb = (K + 7) >> 3;                       // 8-deep blocks in all; 0 .. 3 come from `pre`
-  const float* wcol = W + tile_col(wave, 0, l32);
-  float b[PF][2][4];
-  auto request = [&](float (&dst)[2][4], int blk) {
+  const int nb = (K + 15) >> 4;
+  const WeightsRsrc Wr = weights_rsrc(W, K * kH);    // rows at or beyond K are zero
+  const uint32_t off = 4u * (uint32_t)(4 * half * kH + tile_col(wave, 0, lane));
+  Acc<MT> low;
+  low.zero();
+  float b[PF][2][8];
+  auto request = [&](float (&dst)[2][8], int blk) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int k = 8 * blk + 4 * half + j;
-      const f32x2 v = *reinterpret_cast<const f32x2*>(wcol + (size_t)(k < K ? k : 0) * kH);
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt) dst[nt][j] = k < K ? v[nt] : 0.0f;
+    for (int e = 0; e < 8; ++e) {
+      const f32x2 v = rsrc_load2(Wr, off + 4 * (e & 3) * kH, (16 * blk + 8 * (e >> 2)) * kH);
+      dst[0][e] = v[0];
+      dst[1][e] = v[1];
     }
   };
-#pragma unroll
-  for (int s = 0; s < PF; ++s)
-    if (4 + s < nb) request(b[s], 4 + s);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    if (i < nb) {
-      f32x4 a[MT];
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-        a[mt] = *reinterpret_cast<const f32x4*>(&Xl[(32 * mt + l32) * ldx + 8 * i + 4 * half]);
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-          for (int nt = 0; nt < 2; ++nt) acc.t[mt][nt] = mfma32(a[mt][j], pre.w[i][nt][j], acc.t[mt][nt]);
-    }
-  }
-  auto lds_block = [&](f32x4 (&a)[MT], int i) {
+  f32x4 xn[MT][2];                                   // the LDS operand runs one block ahead
+  auto lds_block = [&](int i) {
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
-      a[mt] = *reinterpret_cast<const f32x4*>(&Xl[(32 * mt + l32) * ldx + 8 * i + 4 * half]);
-  };
-  f32x4 an[MT];                                      // the LDS operand runs one block ahead of the matrix pipe
-  if (4 < nb) lds_block(an, 4);
-  // FAST: block i + PF lies wholly inside the K rows: its eight loads are one running pointer plus constants
-  // (no per-load address arithmetic or row guard, which would sit in front of every group of MFMAs)
-  const float* wrun = wcol + (size_t)(8 * (4 + PF) + 4 * half) * kH;     // rows of block 4 + PF for this lane
-  auto step = [&](int s, int i, bool next_x, bool next_w, bool fast) {
-    f32x4 a[MT];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) a[mt] = an[mt];
-    if (next_x) lds_block(an, i + 1);
-    float w[2][4];
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) w[nt][j] = b[s][nt][j];
-    if (fast) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const f32x2 v = *reinterpret_cast<const f32x2*>(wrun + j * kH);
-        b[s][0][j] = v[0];
-        b[s][1][j] = v[1];
+      for (int s = 0; s < 2; ++s) {
+        const int c = 16 * i + 8 * s + 4 * half;
+        xn[mt][s] = *reinterpret_cast<const f32x4*>(&Xl[(32 * mt + l32) * ldx + (c < ldx - 4 ? c : ldx - 4)]);
       }
-    } else if (next_w) {
-      request(b[s], i + PF);
-    }
-    wrun += 8 * kH;
+  };
+  // block i with weights w; the LDS operand of block i + 1 and the loads of next() go out ahead of the matrix work
+  auto block = [&](const float (&w)[2][8], int i, auto next) {
+    Split8 x[MT], ws[2];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) split8(xn[mt][0], xn[mt][1], x[mt]);
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) split8(w[nt], ws[nt]);
+    lds_block(i + 1);
+    next();
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int q = 0; q < kSplitTerms; ++q)
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) acc.t[mt][nt] = mfma32(a[mt][j], w[nt][j], acc.t[mt][nt]);
+        for (int nt = 0; nt < 2; ++nt) {
+          f32x16& c = q == kSplitTerms - 1 ? acc.t[mt][nt] : low.t[mt][nt];
+          c = mfma32_bf16(x[mt].t[kTermX[q]], ws[nt].t[kTermW[q]], c);
+        }
     __builtin_amdgcn_sched_barrier(0);
   };
-  int blk = 4;
-  // steady state, free of branches (a branch inside the loop makes the compiler drain every outstanding load at
-  // the join): every block of the group exists and every block requested from it is a full one
-  const int nfull = K >> 3;
-  for (; blk + 2 * PF <= nfull; blk += PF) {
 #pragma unroll
-    for (int s = 0; s < PF; ++s) step(s, blk + s, true, true, true);
-  }
-  for (; blk < nb; blk += PF) {                      // the last groups: guarded requests
+  for (int s = 0; s < PF; ++s) request(b[s], 2 + s);
+  lds_block(0);
 #pragma unroll
-    for (int s = 0; s < PF; ++s) {
-      const int i = blk + s;
-      if (i < nb) step(s, i, i + 1 < nb, i + PF < nb, false);
+  for (int i = 0; i < 2; ++i)
+    if (i < nb) {
+      float w[2][8];
+#pragma unroll
+      for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) w[nt][e] = pre.w[2 * i + (e >> 2)][nt][e & 3];
+      block(w, i, [] {});
     }
+  int blk = 2;
+  for (; blk + PF <= nb; blk += PF) {                // whole groups: no branch inside
+#pragma unroll
+    for (int s = 0; s < PF; ++s) block(b[s], blk + s, [&] { request(b[s], blk + s + PF); });
   }
+#pragma unroll
+  for (int s = 0; s < PF; ++s)
+    if (blk + s < nb) block(b[s], blk + s, [] {});
+  acc.add_finite(low);
 }
 
 // 256-deep contraction of 32 rows of an LDS operand with 32 columns per wavefront of a global operand Z (row-major

@@ -240,3 +240,33 @@ def test_rows_of_a_chain_agree(algo, O, A, rows):
         # a gradient is a sum over 256 rows through four products, each 2e-7 apart, and a ReLU unit within rounding
         # of zero may switch: one of 65,536 is 4e-6 of the gradient's square
         assert rel_l2(y, x) < 2e-3 and np.isfinite(y).all()
+
+
+@pytest.mark.parametrize("algo", [pp.POP_ALGO_TD3, pp.POP_ALGO_SAC])
+@pytest.mark.parametrize("O,A", [(64, 1), (5, 9), (71, 9), (71, 10), (400, 24), (423, 24), (424, 24)])
+def test_wide_first_layers_against_64_bits(algo, O, A):
+    """First layers on the bf16 pipe (32 rows: 17 agents or more), fan-ins around the ends of its 16-deep blocks and groups of
+    blocks: the gradients of one update step against 64-bit arithmetic, no hidden unit near its kink."""
+    P, n = 17, 48
+    hps = [dict(h, lr_critic=1e-12) for h in _hparams(algo, P, A)]
+    ensure_built()
+    pop = pp.Population(pp.make_config(P, O, A, (H, H), 256, n, algo=algo), hps)
+    orc = ORACLES[algo].Population(hps[:2], O, A, [H, H], 256, n)
+    g = np.random.default_rng(O + A)
+    fix_masks(orc, g)
+    for i in range(P):
+        tr = dict(obs=g.standard_normal((n, O)).astype(np.float32), act=g.uniform(-1, 1, (n, A)).astype(np.float32),
+                  rew=g.standard_normal(n).astype(np.float32), done=(g.random(n) < 0.1).astype(np.float32),
+                  next_obs=g.standard_normal((n, O)).astype(np.float32))
+        pop.insert(i, **tr)
+        if i < 2:
+            orc.insert(i, **tr)
+            for net in ("actor", "critic1", "critic2", "t_actor", "t_critic1", "t_critic2"):
+                if not (algo == pp.POP_ALGO_SAC and net == "t_actor"):
+                    pop.set_params(i, net, orc.get_params(i, net))
+    pop.set_debug(True)
+    pop.update(1)
+    orc.update(1)
+    worst = max(rel_l2(pop.get_params(i, "g_" + net), orc.get_params(i, "g_" + net)) for i in range(2) for net in ("critic1", "critic2", "actor"))
+    pop.close()
+    assert worst < 1e-6                                # as in test_gradients_against_64_bits

@@ -706,8 +706,8 @@ struct CriticMap : LdsMap<G::R, G::kPad> {
 // Critic forward + backward.  One workgroup per (critic network, chunk); network = 2 agent + k.
 //   L = (1/B) sum_b (Q_k(s_b, a_b) - y_b)^2 ;  dq = 2 (q - y) / B
 //   dz2 = (dq W3^T) * [h2 > 0] ;  dz1 = (dz2 W2^T) * [h1 > 0]
-// Outputs for the weight-gradient kernel: h1, dz2, dz1 (global), and the chunk's
-// partial sums of dW3, db3, db2, db1 and of the loss.
+// Outputs for the weight-gradient kernel: h1, dz1, dz2 as its three factors ([h2 > 0], dq, W3: 9 KB of a network's
+// 256; critic tiles of 256 agents read 1.51 GB with dz2 itself), and the chunk's partial sums of dW3, db3, db2, db1 and of the loss.
 // WAIT: the targets come from target workgroups of the same launch; the lanes that need
 // them poll for their rows right before the loss.  SIGNAL: count this chunk as finished
 // for the weight-gradient workgroups of the same launch.  AHEAD: the workgroups of critic 2 run the actor's forward
@@ -776,6 +776,7 @@ __device__ __forceinline__ void critic_chain(const PopDev& d, uint32_t t, int ne
       err = head[tid * kMaxAct] + b3 - yv;
       g = 2.0f * err / (float)(d.B * d.share);         // share > 1: the critic loss is the mean over the population
       dq[tid] = g;
+      put<SIGNAL>(d.cdq + (size_t)net * d.B + r0 + tid, g);
     }
     const float sq = wave_sum(err * err);
     const float sdq = wave_sum(g);
@@ -786,10 +787,13 @@ __device__ __forceinline__ void critic_chain(const PopDev& d, uint32_t t, int ne
     const int c = tid;
     const float w3 = v_w3[c];
     float gw3 = 0.0f, gb2 = 0.0f;
-    float* zg = d.cdZ2 + act_off + c;
+    if (chunk == 0) put<SIGNAL>(d.cw3 + (size_t)net * kH + c, w3);
+    uint32_t active = 0u;                            // rows of the current 32 in which this unit is
+    uint32_t* mg = d.cmask + ((size_t)net * (d.B / 32) + r0 / 32) * kH + c;
 #pragma unroll 1
     for (int rb = 0; rb < R; rb += 8) {
       float h[8], g[8];
+      uint32_t some = 0u;
 #pragma unroll
       for (int i = 0; i < 8; ++i) { h[i] = buf[(rb + i) * kLda + c]; g[i] = dq[rb + i]; }
 #pragma unroll
@@ -797,10 +801,17 @@ __device__ __forceinline__ void critic_chain(const PopDev& d, uint32_t t, int ne
         gw3 += h[i] * g[i];
         const float z = h[i] > 0.0f ? g[i] * w3 : 0.0f;
         buf[(rb + i) * kLda + c] = z;
-        put<SIGNAL>(zg + (rb + i) * kH, z);
+        some |= h[i] > 0.0f ? 1u << i : 0u;
         gb2 += z;
       }
+      active |= some << (rb & 31);
+      if (R >= 32 && (rb & 31) == 24) {
+        put_word<SIGNAL>(mg + (rb / 32) * kH, active);
+        active = 0u;
+      }
     }
+    static_assert(R >= 32 || !SIGNAL, "16-row critic chains hand nothing on inside their launch");
+    if (R == 16) reinterpret_cast<uint16_t*>(mg)[(r0 >> 4) & 1] = (uint16_t)active;
     put<SIGNAL>(part + kCP_dW3 + c, gw3);
     put<SIGNAL>(part + kCP_db2 + c, gb2);
   }

@@ -57,7 +57,7 @@ __global__ __launch_bounds__(kThreads, GC::R == 64 ? 1 : 2) void k_step(PopDev d
     return;
   }
   b -= g.c;
-  Adam* sh_adam = reinterpret_cast<Adam*>(lds + 32 * kLda);
+  Adam* sh_adam = reinterpret_cast<Adam*>(lds + kTileLds);
   if (GA::R == 16 && b < g.wc + g.a) {
     // Small populations (the 16-row class), measured 97.6 against 99.2 us/step at P = 10 (and 448 against 439 at
     // P = 80, hence not there): per agent the tiles of its two critics, then its actor chains; an actor chain
@@ -124,7 +124,7 @@ hipError_t launch_step(const PopDev& dev, uint32_t t, uint32_t launch_seq, int w
   g.g = prefetch_next ? d.P * gather_blocks_per_agent(d) : 0;
   const int vec_ta = vec_target(d) > vec_actor(d) ? vec_target(d) : vec_actor(d);
   const int vec = vec_ta > vec_critic(d) ? vec_ta : vec_critic(d);
-  const size_t tiles = (size_t)(32 * kLda) * sizeof(float) + sizeof(Adam);
+  const size_t tiles = (size_t)kTileLds * sizeof(float) + sizeof(Adam);
   const dim3 grid(g.t + g.c + g.wc + g.a + g.wa + g.g), block(kThreads);
 #ifdef POP_TRACE
   g_trace_step_parts[0] = g.t; g_trace_step_parts[1] = g.c; g_trace_step_parts[2] = g.wc; g_trace_step_parts[3] = g.a;

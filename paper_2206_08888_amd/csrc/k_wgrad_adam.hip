@@ -12,7 +12,7 @@ template <bool HALF>
 __global__ __launch_bounds__(kThreads, 3) void k_wgrad_adam(PopDev d, uint32_t t, int actor_phase, int main_blocks,
                                                           int roles, int prefetch) {
   __shared__ Adam sh_adam;
-  __shared__ __attribute__((aligned(16))) float xt_lds[32 * kLda];
+  __shared__ __attribute__((aligned(16))) float xt_lds[kTileLds];
   POP_MARK(49);
   POP_BLOCK_TIME(actor_phase ? kTraceWgradActor : kTraceWgradCritic, 0);
   if ((int)blockIdx.x >= main_blocks) {              // gather role: rows of the next step

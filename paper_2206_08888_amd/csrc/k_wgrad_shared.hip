@@ -17,7 +17,7 @@ namespace pop {
 // Blocks at and beyond main_blocks gather the replay rows of step t + 1 into the other half of the batch buffer
 // (prefetch != 0), as the tail of the per-agent weight-gradient launch does.
 __global__ __launch_bounds__(kThreads, 3) void k_shared_partial(PopDev d, uint32_t t, int roles, int main_blocks, int prefetch) {
-  __shared__ __attribute__((aligned(16))) float xt_lds[32 * kLda];
+  __shared__ __attribute__((aligned(16))) float xt_lds[kTileLds];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   if ((int)blockIdx.x >= main_blocks) {
     if (prefetch) {
@@ -39,21 +39,34 @@ __global__ __launch_bounds__(kThreads, 3) void k_shared_partial(PopDev d, uint32
   if (role < 16 + 2 * n1) {
     const bool w2 = role < 16;
     const int n0 = 128 * (role & 1), m0 = 32 * ((w2 ? role : role - 16) >> 1);
-    const int M = w2 ? kH : L.in, ldx = w2 ? kH : d.row;
+    const int M = w2 ? kH : L.in;
     Acc<1, 1> acc;
     acc.zero();
-    for (int agent = g; agent < d.P; agent += d.groups) {
-      const size_t o = (size_t)(2 * agent + net) * d.B * kH;
-      const float* x = w2 ? d.cH1 + o : batch_rows(d, t, agent);
-      const float* z = (w2 ? d.cdZ2 : d.cdZ1) + o + n0;
-      XSlice xsl;
-      xsl.load(x, ldx, M, m0, wave, lane);
-      ZBlock z0;
-      z0.load(z, 0, wave, lane);
-      __syncthreads();                               // the previous agent's product has read the slice
-      xsl.store(xt_lds, ldx, M, m0, wave, lane);
-      __syncthreads();
-      gemm256_unrolled<4>(xt_lds, kLda, z, z0, wave, lane, acc);
+    XSlice xsl;
+    if (w2) {
+      for (int agent = g; agent < d.P; agent += d.groups) {
+        const size_t unit = (size_t)(2 * agent + net);
+        xsl.load(d.cH1 + unit * d.B * kH, kH, kH, m0, wave, lane);
+        Dz2Factors<16> f;
+        f.load(d.cmask + unit * (d.B / 32) * kH + n0 + 32 * wave, d.cw3 + unit * kH + n0 + 32 * wave, lane);
+        const float dq = d.cdq[unit * d.B + tid];
+        __syncthreads();                             // the previous agent's product has read the slice
+        xsl.store(xt_lds, kH, kH, m0, wave, lane);
+        xt_lds[32 * kLda + tid] = dq;
+        __syncthreads();
+        gemm256_dz2<16>(xt_lds, kLda, xt_lds + 32 * kLda, f, lane, acc);
+      }
+    } else {
+      for (int agent = g; agent < d.P; agent += d.groups) {
+        const float* z = d.cdZ1 + (size_t)(2 * agent + net) * d.B * kH + n0;
+        xsl.load(batch_rows(d, t, agent), d.row, M, m0, wave, lane);
+        ZBlock z0;
+        z0.load(z, 0, wave, lane);
+        __syncthreads();
+        xsl.store(xt_lds, d.row, M, m0, wave, lane);
+        __syncthreads();
+        gemm256_unrolled<4>(xt_lds, kLda, z, z0, wave, lane, acc);
+      }
     }
     const int half = lane >> 5, l32 = lane & 31;
     const uint32_t elem0 = (uint32_t)((w2 ? L.w2 : L.w1) + (m0 + 4 * half) * kH + n0 + 32 * wave + l32);

@@ -60,7 +60,7 @@ constexpr int64_t kStagingBytes = 16ll << 20;
 
 struct Layout {
   int64_t hp, theta, target, m, v, grad, count, cursor, idx, batch, atilde, api, y;
-  int64_t cH1, cdZ2, cdZ1, aH1, aH2, adZ2, adZ1, cpart, apart, losses, y_tagged, done_c, done_wc, done_a, spart, sloss, sigma, log_alpha, staging, replay, total;
+  int64_t cH1, cdZ1, cmask, cdq, cw3, aH1, aH2, adZ2, adZ1, cpart, apart, losses, y_tagged, done_c, done_wc, done_a, spart, sloss, sigma, log_alpha, staging, replay, total;
   int64_t param_bytes;
 };
 
@@ -256,7 +256,8 @@ Layout make_ws_layout(const PopDev& d) {
   L.idx = take(2 * P * B * 4); L.batch = take(2 * P * B * d.row * 4);
   L.atilde = take(P * B * d.A * 4); L.api = take(P * B * d.A * 4); L.y = take(P * B * 4);
   const int64_t act = P * B * kH * 4;
-  L.cH1 = take(2 * act); L.cdZ2 = take(2 * act); L.cdZ1 = take(2 * act);
+  L.cH1 = take(2 * act); L.cdZ1 = take(2 * act);
+  L.cmask = take(2 * P * (B / 32) * kH * 4); L.cdq = take(2 * P * B * 4); L.cw3 = take(2 * P * kH * 4);
   L.aH1 = take(act); L.aH2 = take(act); L.adZ2 = take(act); L.adZ1 = take(act);
   L.cpart = take(P * 2 * (int64_t)d.cstride * kCPart * 4);
   L.apart = take(P * (int64_t)(d.B / d.rows_a) * kAPart * 4);
@@ -451,7 +452,8 @@ int pop_create(pop_ctx** out, const pop_config* cfg, const pop_hparams* hp, uint
   d.count = (uint32_t*)(w + L.count); d.cursor = (uint32_t*)(w + L.cursor);
   d.idx = (uint32_t*)(w + L.idx); d.batch = (float*)(w + L.batch);
   d.atilde = (float*)(w + L.atilde); d.api = (float*)(w + L.api); d.y = (float*)(w + L.y);
-  d.cH1 = (float*)(w + L.cH1); d.cdZ2 = (float*)(w + L.cdZ2); d.cdZ1 = (float*)(w + L.cdZ1);
+  d.cH1 = (float*)(w + L.cH1); d.cdZ1 = (float*)(w + L.cdZ1);
+  d.cmask = (uint32_t*)(w + L.cmask); d.cdq = (float*)(w + L.cdq); d.cw3 = (float*)(w + L.cw3);
   d.aH1 = (float*)(w + L.aH1); d.aH2 = (float*)(w + L.aH2); d.adZ2 = (float*)(w + L.adZ2);
   d.adZ1 = (float*)(w + L.adZ1);
   d.cpart = (float*)(w + L.cpart); d.apart = (float*)(w + L.apart); d.losses = (float*)(w + L.losses);

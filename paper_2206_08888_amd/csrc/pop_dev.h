@@ -101,7 +101,11 @@ struct PopDev {
   int actor_ahead;             // 1: they do (small populations: those workgroups would otherwise idle until the targets arrive)
   float* y;                    // [P][B]
   // activations handed from the chain kernels to the weight-gradient kernel
-  float *cH1, *cdZ2, *cdZ1;    // [P][2][B][256]
+  float *cH1, *cdZ1;           // [P][2][B][256]
+  // a critic's dZ2[b][c] = cmask bit (b, c) ? cdq[b] * cw3[c] : 0 is rebuilt by its weight-gradient tiles
+  uint32_t* cmask;             // [P][2][B / 32][256]: bit b of the word of (b / 32, c): hidden unit c of layer 2 is active in row b
+  float* cdq;                  // [P][2][B] loss gradient of each row's Q value
+  float* cw3;                  // [P][2][256] the head's weights as the chains used them (the launch that reads this updates the weights)
   float *aH1, *aH2, *adZ2, *adZ1;  // [P][B][256]
   // per-row-chunk partial sums of the small gradients and of the losses
   float* cpart;                // [P][2][cstride][kCPart]

@@ -145,10 +145,12 @@ struct XSlice {
 // requested first and arrive while the operands are staged and multiplied.  `setup()` fills
 // `sh` (thread 0 only; a few hundred cycles of double arithmetic): it runs once the loads are
 // on their way, and `sh` is read after the barrier that follows.
-template <bool WAIT, bool SLIM, bool HALF, class Setup>
+// DZ2: z is a critic's dZ2, given by its factors (Dz2Factors): zmask [8][256] words, zdq [256], zw3 [256].
+template <bool WAIT, bool SLIM, bool HALF, bool DZ2, class Setup>
 __device__ __forceinline__ void weight_tile(const PopDev& d, const uint32_t* wait_on, uint32_t want, const Adam* sh,
                                             Setup setup, bool polyak, const float* __restrict__ x, int ldx, int M, int m0,
-                                   int n0, const float* __restrict__ z, uint32_t base, float* Xl,
+                                   int n0, const float* __restrict__ z, const uint32_t* __restrict__ zmask, const float* __restrict__ zdq,
+                                   const float* __restrict__ zw3, uint32_t base, float* Xl,
                                    float* __restrict__ th, float* __restrict__ mo, float* __restrict__ ve,
                                    float* __restrict__ tg, float* __restrict__ gr, int tid) {
   const int wave = tid >> 6, lane = tid & 63, l32 = lane & 31;
@@ -179,7 +181,9 @@ __device__ __forceinline__ void weight_tile(const PopDev& d, const uint32_t* wai
   auto load_x = [&]() { xsl.load(x, ldx, M, m0, wave, lane); };
   auto store_x = [&]() { xsl.store(Xl, ldx, M, m0, wave, lane); };
   ZBlock z0;
-  const float* zk = z + n0 + (size_t)kh * 128 * kH;   // this wavefront's rows of dZ
+  const float* zk = DZ2 ? nullptr : z + n0 + (size_t)kh * 128 * kH;   // this wavefront's rows of dZ
+  Dz2Factors<HALF ? 8 : 16> zf;
+  float zd;                                          // this thread's row of dq
   if (WAIT && wait_on) {                             // x and z come from a chain of this launch
     // The counter is read before anything else is requested: a wavefront's loads come back in the order they went
     // out, so a poll issued behind the Adam operands would only return once those 64 KB have arrived from memory,
@@ -194,7 +198,12 @@ __device__ __forceinline__ void weight_tile(const PopDev& d, const uint32_t* wai
     __syncthreads();
   }
   load_x();                                          // what the product needs first goes out first
-  z0.load(zk, 0, cw, lane);
+  if constexpr (DZ2) {
+    zf.load(zmask + 4 * kh * kH + n0 + 32 * cw, zw3 + n0 + 32 * cw, lane);
+    zd = zdq[tid];
+  } else {
+    z0.load(zk, 0, cw, lane);
+  }
   __builtin_amdgcn_sched_barrier(0);
   load_adam();
   __builtin_amdgcn_sched_barrier(0);
@@ -202,12 +211,14 @@ __device__ __forceinline__ void weight_tile(const PopDev& d, const uint32_t* wai
   __builtin_amdgcn_sched_barrier(0);
   POP_MARK(51);
   store_x();
+  if constexpr (DZ2) Xl[32 * kLda + tid] = zd;
   __syncthreads();
   POP_MARK(52);
   const Adam adam = *sh;
   Acc<1, 1> acc;
   acc.zero();
-  gemm256_unrolled<SLIM ? 4 : 8, HALF ? 8 : 16>(Xl + 128 * kh, kLda, zk, z0, cw, lane, acc);
+  if constexpr (DZ2) gemm256_dz2<HALF ? 8 : 16>(Xl + 128 * kh, kLda, Xl + 32 * kLda + 128 * kh, zf, lane, acc);
+  else gemm256_unrolled<SLIM ? 4 : 8, HALF ? 8 : 16>(Xl + 128 * kh, kLda, zk, z0, cw, lane, acc);
   POP_MARK(53);
   __syncthreads();                                   // every wavefront is done with the X slice
 #pragma unroll
@@ -224,6 +235,7 @@ __device__ __forceinline__ void weight_tile(const PopDev& d, const uint32_t* wai
   POP_MARK(54);
 }
 
+constexpr int kTileLds = 32 * kLda + kH;   // floats of LDS of a tile: the X slice, a critic's dq
 constexpr int kSmallHeadBlock = 8;   // head columns of an actor that one small-tensor role sums and updates
 
 // One role of the weight-gradient step of one network (unit = agent in the actor phase, else network).
@@ -284,9 +296,16 @@ __device__ __forceinline__ void wgrad_roles(const PopDev& d, uint32_t t, int act
     const int n0 = 128 * (role & 1) + 64 * half;
     const bool w2 = role < 16;                       // else layer 1, whose input is the leading columns of the batch rows
     const float* x = w2 ? (actor_phase ? d.aH1 : d.cH1) + o : batch_rows(d, t, agent);
-    const float* z = (w2 ? (actor_phase ? d.adZ2 : d.cdZ2) : (actor_phase ? d.adZ1 : d.cdZ1)) + o;
-    weight_tile<WAIT, SLIM, HALF>(d, wait_on, (uint32_t)chunks, sh_adam, setup, delayed_step && !(actor_phase && d.algo == 1), x, w2 ? kH : d.row, w2 ? kH : L.in, 32 * ((w2 ? role : role - 16) >> 1), n0, z,
-                (uint32_t)(w2 ? L.w2 : L.w1), xt_lds, th, mo, ve, tg, gr, tid);
+    const float* z = (actor_phase ? (w2 ? d.adZ2 : d.adZ1) : d.cdZ1) + o;
+    const bool polyak = delayed_step && !(actor_phase && d.algo == 1);
+    const int m0 = 32 * ((w2 ? role : role - 16) >> 1);
+    if (w2 && !actor_phase)
+      weight_tile<WAIT, SLIM, HALF, true>(d, wait_on, (uint32_t)chunks, sh_adam, setup, polyak, x, kH, kH, m0, n0, nullptr,
+                                          d.cmask + (size_t)unit * (d.B / 32) * kH, d.cdq + (size_t)unit * d.B, d.cw3 + (size_t)unit * kH,
+                                          (uint32_t)L.w2, xt_lds, th, mo, ve, tg, gr, tid);
+    else
+      weight_tile<WAIT, SLIM, HALF, false>(d, wait_on, (uint32_t)chunks, sh_adam, setup, polyak, x, w2 ? kH : d.row, w2 ? kH : L.in, m0, n0, z,
+                                           nullptr, nullptr, nullptr, (uint32_t)(w2 ? L.w2 : L.w1), xt_lds, th, mo, ve, tg, gr, tid);
   } else {
     // Small tensors from per-chunk partial sums; thread c owns hidden unit c.  Role `small` = 0: the hidden biases,
     // and for a critic its one head column, head bias and loss, for an actor its head bias and loss (SAC: the

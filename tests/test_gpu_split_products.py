@@ -270,3 +270,38 @@ def test_wide_first_layers_against_64_bits(algo, O, A):
     worst = max(rel_l2(pop.get_params(i, "g_" + net), orc.get_params(i, "g_" + net)) for i in range(2) for net in ("critic1", "critic2", "actor"))
     pop.close()
     assert worst < 1e-6                                # as in test_gradients_against_64_bits
+
+
+@pytest.mark.parametrize("algo", [pp.POP_ALGO_TD3, pp.POP_ALGO_SAC])
+@pytest.mark.parametrize("scale", [1e-28, 1e-9, 1e-4, 1e3, 1e28])
+def test_16_row_chains_over_magnitudes(algo, scale):
+    """One step with hidden weights `scale` times as large and first layers scaled the other way: 16-row chains (two-part fp16
+    operands, or the fp32 instructions where those do not hold the weights) against 32-row chains (three-part bf16)."""
+    O, A, P = 17, 6, 2
+    got = []
+    for rows in ((16, 32, 16), 32):
+        pop = _population(algo, P, O, A, rows=rows)
+        for i in range(P):
+            for net, fan_in, out in [(n, O, 2 * A if algo == pp.POP_ALGO_SAC else A) for n in ("actor", "t_actor")] + \
+                                    [(n, O + A, 1) for n in ("critic1", "critic2", "t_critic1", "t_critic2")]:
+                if algo == pp.POP_ALGO_SAC and net == "t_actor":
+                    continue
+                th = pop.get_params(i, net).copy()
+                w1, b1, w2, b2, w3, b3 = _views(th, fan_in, out)
+                w1 /= np.float32(scale)
+                w2 *= np.float32(scale)
+                w2[:, 5] *= np.float32(1e-6)               # a unit whose weights are small beside the others'
+                pop.set_params(i, net, th)
+        g = np.random.default_rng(8)
+        pop.insert(-1, obs=g.standard_normal((P, 64, O)).astype(np.float32), act=g.uniform(-1, 1, (P, 64, A)).astype(np.float32),
+                   rew=g.standard_normal((P, 64)).astype(np.float32), done=np.zeros((P, 64), np.float32),
+                   next_obs=g.standard_normal((P, 64, O)).astype(np.float32))
+        pop.set_debug(True)
+        pop.update(1)
+        got.append((pop.debug("target_y"), [pop.get_params(a, "g_actor") for a in range(P)]))
+        pop.close()
+    (y16, g16), (y32, g32) = got
+    # a Q value is a sum of 256 products through two layers, each sum within 3e-7 of its terms on either side
+    assert np.linalg.norm(y16 - y32) / np.linalg.norm(y32) < 3e-6
+    for x, y in zip(g16, g32):
+        assert np.isfinite(y).all() and rel_l2(x, y) < 2e-3    # as in test_rows_of_a_chain_agree

@@ -79,11 +79,26 @@ __device__ __forceinline__ void sac_target_chain(const PopDev& d, uint32_t t, in
   const float alpha = expf(d.log_alpha[agent]);
   const float* rows = batch_rows(d, t, agent) + (size_t)r0 * d.row;
   POP_MARK(0);
-  stage_vector(v_ab3, an + d.actor.b3, 2 * A, tid);
-  stage_vector(v_cw3, tc0 + d.critic.w3, kH, tid);
-  stage_vector(v_cw3 + kH, tc1 + d.critic.w3, kH, tid);
-  if (tid < 2) v_cb3[tid] = (tid == 0 ? tc0 : tc1)[d.critic.b3];
-  G::load_input(Xs, L.xld, rows, d.row, d.D + 2, d.O, R, tid);
+  if (d.D <= kMaxIn) {                               // one trip to memory for all of the prologue
+    SmallVec ab3, cw3a, cw3b;
+    InputTile<R> xin;
+    ab3.fetch(an + d.actor.b3, 2 * A, tid);
+    cw3a.fetch(tc0 + d.critic.w3, kH, tid);
+    cw3b.fetch(tc1 + d.critic.w3, kH, tid);
+    const float cb3 = (tid == 0 ? tc0 : tc1)[d.critic.b3];
+    xin.fetch(L.xld, rows, d.row, d.D + 2, d.O, R, tid);
+    ab3.put(v_ab3, 2 * A, tid);
+    cw3a.put(v_cw3, kH, tid);
+    cw3b.put(v_cw3 + kH, kH, tid);
+    if (tid < 2) v_cb3[tid] = cb3;
+    xin.put(Xs, L.xld, tid);
+  } else {
+    stage_vector(v_ab3, an + d.actor.b3, 2 * A, tid);
+    stage_vector(v_cw3, tc0 + d.critic.w3, kH, tid);
+    stage_vector(v_cw3 + kH, tc1 + d.critic.w3, kH, tid);
+    if (tid < 2) v_cb3[tid] = (tid == 0 ? tc0 : tc1)[d.critic.b3];
+    G::load_input(Xs, L.xld, rows, d.row, d.D + 2, d.O, R, tid);
+  }
   __syncthreads();
   POP_MARK(1);
 
@@ -221,10 +236,25 @@ __device__ __forceinline__ void sac_actor_chain(const PopDev& d, uint32_t t, int
   const size_t act_off = ((size_t)agent * d.B + r0) * kH;
   float* part = d.apart + ((size_t)agent * (d.B / R) + chunk) * kAPart;
   POP_MARK(20);
-  stage_vector(v_ab3, an + d.actor.b3, H2, tid);
-  for (int k = 0; k < 2; ++k) stage_vector(v_cw3 + k * kH, cn[k] + d.critic.w3, kH, tid);
-  if (tid < 2) v_cb3[tid] = cn[tid][d.critic.b3];
-  G::load_input(Xs, L.xld, rows, d.row, 0, d.O, R, tid);
+  if (d.D <= kMaxIn) {                               // one trip to memory for all of the prologue
+    SmallVec ab3, cw3a, cw3b;
+    InputTile<R> xin;
+    ab3.fetch(an + d.actor.b3, H2, tid);
+    cw3a.fetch(cn[0] + d.critic.w3, kH, tid);
+    cw3b.fetch(cn[1] + d.critic.w3, kH, tid);
+    const float cb3 = (tid == 0 ? cn[0] : cn[1])[d.critic.b3];
+    xin.fetch(L.xld, rows, d.row, 0, d.O, R, tid);
+    ab3.put(v_ab3, H2, tid);
+    cw3a.put(v_cw3, kH, tid);
+    cw3b.put(v_cw3 + kH, kH, tid);
+    if (tid < 2) v_cb3[tid] = cb3;
+    xin.put(Xs, L.xld, tid);
+  } else {
+    stage_vector(v_ab3, an + d.actor.b3, H2, tid);
+    for (int k = 0; k < 2; ++k) stage_vector(v_cw3 + k * kH, cn[k] + d.critic.w3, kH, tid);
+    if (tid < 2) v_cb3[tid] = cn[tid][d.critic.b3];
+    G::load_input(Xs, L.xld, rows, d.row, 0, d.O, R, tid);
+  }
   __syncthreads();
   POP_MARK(21);
 

@@ -98,8 +98,18 @@ __global__ __launch_bounds__(kThreads) void k_act(PopDev d, const float* __restr
   const float* an = net_ptr(d, d.theta, agent, 0);
   LayerPre<1> pre;
   pre.load(an, d.actor, wave, lane);
-  stage_vector(v_ab3, an + d.actor.b3, d.actor.out, tid);
-  load_input<R>(Xs, L.xld, obs + ((size_t)agent * n + r0) * d.O, d.O, 0, d.O, valid, tid);
+  const float* rows = obs + ((size_t)agent * n + r0) * d.O;
+  if (d.O <= kMaxIn) {                               // one trip to memory for all of the prologue
+    SmallVec ab3;
+    InputTile<R> xin;
+    ab3.fetch(an + d.actor.b3, d.actor.out, tid);
+    xin.fetch(L.xld, rows, d.O, 0, d.O, valid, tid);
+    ab3.put(v_ab3, d.actor.out, tid);
+    xin.put(Xs, L.xld, tid);
+  } else {
+    stage_vector(v_ab3, an + d.actor.b3, d.actor.out, tid);
+    load_input_wide<R>(Xs, L.xld, rows, d.O, 0, d.O, valid, tid);
+  }
   __syncthreads();
   first_layer<1>(Xs, L.xld, an, d.actor, pre, buf, nullptr, wave, lane);
   __syncthreads();

@@ -102,14 +102,14 @@ def kernel_bytes(P, B, O, A, algo="td3", delay=2):
 
     gather: B rows of (2 O + A + 2) floats read from the replay buffer and written to the batch (+ 4 B per index).
     wgrad_critic: both critics' parameters, first and second moments read and written (24 B per parameter), on
-      delayed steps also their targets (8 B per parameter; averaged over the delay), the three activation tensors
-      of each critic ([B, 256] floats: h1, dz2, dz1) and the batch rows read.
+      delayed steps also their targets (8 B per parameter; averaged over the delay), the two activation tensors
+      of each critic ([B, 256] floats: h1, dz1), the factors of dz2 (B * 256 bits, B + 256 floats) and the batch rows read.
     wgrad_actor: the same for the actor, whose launch always carries Polyak (32 B per parameter), with its
       activations h1, h2, dz2, dz1 (h2 only as far as the head's weight gradient needs it).
     The shared critics keep ONE critic pair: their Adam traffic does not grow with P.
     The chain launches, for the ratio of measured to necessary traffic (they are bound by the matrix units, not by
     HBM): every network a chain runs read once (4 B per parameter), its columns of the batch rows read, and what
-    it leaves for the weight-gradient tiles written (target: y; critic: h1, dz2, dz1 of both critics; actor: h1, h2,
+    it leaves for the weight-gradient tiles written (target: y; critic: h1, dz1, the factors of dz2 of both critics; actor: h1, h2,
     dz2, dz1 and the head's gradient).  target_critic and step are the sums of the parts one launch carries (step:
     averaged over steps with and without the actor part)."""
     D, out_a = O + A, (2 * A if algo == "sac" else A)
@@ -117,7 +117,8 @@ def kernel_bytes(P, B, O, A, algo="td3", delay=2):
     n_actor = O * H + H + H * H + H + H * out_a + out_a
     n_critic = D * H + H + H * H + H + H + 1
     polyak = 1.0 if algo == "sac" else 1.0 / delay
-    act_critic = 2 * 3 * B * H * 4 + B * row * 4
+    handed = 2 * (2 * B * H * 4 + B * H // 8 + (B + H) * 4)     # by the critic chains to their weight-gradient tiles
+    act_critic = handed + B * row * 4
     crit_state = 2 * n_critic * (24 + 8 * polyak)
     shared = algo == "td3_shared"
     nets_target = 0 if shared else 2 * n_critic             # critics beside the actor in each chain, per agent
@@ -128,7 +129,7 @@ def kernel_bytes(P, B, O, A, algo="td3", delay=2):
         "wgrad_critic": act_critic + crit_state,
         "wgrad_actor": 4 * B * H * 4 + B * row * 4 + n_actor * (24 + (0 if algo == "sac" else 8)),
         "target": 4 * (n_actor + nets_target) + B * (O + 2) * 4 + B * 4,
-        "critic": 4 * nets_critic + B * (D + 1) * 4 + 2 * 3 * B * H * 4,
+        "critic": 4 * nets_critic + B * (D + 1) * 4 + handed,
         "actor": 4 * (n_actor + nets_actor) + B * O * 4 + 4 * B * H * 4 + B * out_a * 4,
     }
     out = {k: v * P for k, v in per.items()}

@@ -80,9 +80,9 @@ __device__ inline void mfma_block16(const LdsBlock16& x, const WeightBlock16<TRA
 // zero), the product lx ly that is left out below 2^-22 |x y|, 2^-24.6 in the mean.  Error of a 256-deep product against 64 bits
 // (2-norm), fp32 instructions / here: ReLU outputs x Glorot weights 2.04e-7 / 1.31e-7, sparse gradients x weights 2.03e-7 /
 // 1.30e-7, all terms positive 2.47e-7 / 0.94e-7, left operand over e^+-8 2.84e-7 / 1.35e-7, its rows e^4 apart 2.87e-7 / 1.29e-7.
-// One product alone takes 7,800 cycles forward and 11,300 transposed (fp32 instructions 11,800 and 14,000; 8,192 of matrix time): 940
-// vector instructions of 4 cycles, and the trip for the first weights.  us/step, fp32 / fp16: 1 agent 60.2 / 56.5, 10 agents 74.3 / 70.8,
-// 16 agents 97.5 / 95.3, 8 SAC agents 115.0 / 109.3.
+// One forward product alone takes 3.3 us (fp32 instructions 3.9, 3.4 of it matrix time), of which 940 vector instructions
+// of 4 cycles and the trip for the first weights; in a chain 5.1 -> 4.3, transposed 6.6 -> 5.7.  us/step, fp32 / fp16: 1 agent
+// 60.2 / 56.5, 10 agents 74.3 / 70.8, 8 SAC agents 115.3 / 110.1.
 // Range: rows of the left operand are scaled by a power of two that brings their largest element to 8 .. 16, and the
 // scale is taken out of the sums.  Weights are taken as they are.  Elements below 2^-14 (6e-5) have a fixed grid instead of a
 // relative one: 2^-36 for weights (1.5e-11), 2^-40 of the largest element of its row for the left operand.  Weights of 32

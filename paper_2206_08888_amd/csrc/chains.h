@@ -303,11 +303,11 @@ struct Rows32 {                                      // 32 MT rows on 32x32 tile
   }
 };
 
-struct Rows16 {                                      // 16 rows on 16x16 tiles (mfma_tiles16.h)
+struct Rows16 {                                      // 16 rows on v_mfma_f32_16x16x4_f32 (mfma_tiles16.h)
   static constexpr int R = 16, kPad = 16;
   struct Pre {
     SmallW16 w1;
-    WeightPair16 w2;
+    WeightBlock16<false> w2;
     f32x4 b1, b2;                                    // biases of this lane's 4 columns
     __device__ inline void load(const float* __restrict__ net, const NetLayout& L, int wave, int lane) {
       w1.load(net + L.w1, L.in, wave, lane);
@@ -336,6 +336,7 @@ struct Rows16 {                                      // 16 rows on 16x16 tiles (
   __device__ static inline uint64_t hidden_layer(float* buf, const float* net, const NetLayout& L, Pre& pre, float* Yg,
                                                  int wave, int lane, Tail tail, float*) {
     Acc16 acc;
+    acc.zero();
     const f32x4 bb = pre.b2;
     gemm256_16(buf, kLda, net + L.w2, pre.w2, wave, lane, acc, tail);
     __syncthreads();                                 // every wavefront has read the input tile
@@ -346,6 +347,7 @@ struct Rows16 {                                      // 16 rows on 16x16 tiles (
                                                      float* __restrict__ dXg, float* __restrict__ colsum_out, int wave,
                                                      int lane, float* stage) {
     Acc16 acc;
+    acc.zero();
     gemm256_16_staged(Zl, kLda, W, w0, stage, wave, lane, acc, NoTail());
     const int c = lane & 15, kq = lane >> 4;
     float cs[4] = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -376,6 +378,7 @@ struct Rows16 {                                      // 16 rows on 16x16 tiles (
   __device__ static inline void input_grad_to_lds(float* buf, const float* W, WtBlock& wt, uint64_t mask, int wave,
                                                   int lane, Tail tail, float* stage) {
     Acc16 acc;
+    acc.zero();
     gemm256_16_staged(buf, kLda, W, wt, stage, wave, lane, acc, tail);
     __syncthreads();
     const int c = lane & 15, kq = lane >> 4;

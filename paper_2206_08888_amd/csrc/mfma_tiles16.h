@@ -6,10 +6,9 @@
 // from L2 twice as often, which is free at these sizes).  32x32 tiles would waste half of
 // every instruction on 16 rows, so these products run on v_mfma_f32_16x16x4_f32: one
 // instruction multiplies a 16x4 slice of A by a 4x16 slice of B into a 16x16 fp32 tile
-// held as 4 registers per lane (32 cycles).  The 256-deep products run on v_mfma_f32_16x16x32_f16 from split
-// operands (HalfPair below).
+// held as 4 registers per lane (32 cycles).
 //
-// Operand layout of the fp32 instruction on a 64-lane wavefront (checked against a CPU product):
+// Operand layout of that instruction on a 64-lane wavefront (checked against a CPU product):
 //   A: lane l supplies A[row = l & 15][k = l >> 4]
 //   B: lane l supplies B[k = l >> 4][col = l & 15]
 //   D: register v of lane l is D[row = 4 (l >> 4) + v][col = l & 15]
@@ -44,12 +43,13 @@ __device__ inline f32x4 mfma16(float a, float b, f32x4 c) { return __builtin_amd
 template <bool TRANSPOSED>
 struct WeightBlock16 {
   f32x4 w[4];
+  // forward only: transposed blocks come out of LDS (staged_block16)
   __device__ inline void load(const float* __restrict__ W, int i, int wave, int lane) {
+    static_assert(!TRANSPOSED, "read from memory as WeightStage16");
     const WeightsRsrc r = weights_rsrc(W, kH * kH);
-    const int c = lane & 15, kq = lane >> 4;
-    const uint32_t off = 4u * (uint32_t)(TRANSPOSED ? (64 * wave + 4 * c) * kH + 4 * kq : 4 * kq * kH + 64 * wave + 4 * c);
+    const uint32_t off = 4u * (uint32_t)(4 * (lane >> 4) * kH + 64 * wave + 4 * (lane & 15));
 #pragma unroll
-    for (int q = 0; q < 4; ++q) w[q] = rsrc_load4(r, off + 4 * q * kH, TRANSPOSED ? 16 * i : 16 * i * kH);
+    for (int j = 0; j < 4; ++j) w[j] = rsrc_load4(r, off + 4 * j * kH, 16 * i * kH);
   }
 };
 
@@ -69,181 +69,29 @@ __device__ inline void mfma_block16(const LdsBlock16& x, const WeightBlock16<TRA
       acc.t[nt] = mfma16(x.a[j], TRANSPOSED ? b.w[nt][j] : b.w[j][nt], acc.t[nt]);
 }
 
-// ---------------------------------------------------------------------------------------------
-// 256-deep products on the fp16 pipe.  v_mfma_f32_16x16x32_f16 does in 16 cycles eight times the work that
-// v_mfma_f32_16x16x4_f32 does in 32, and what a 16-row product then takes is the vector work of splitting its weights (each
-// used for 16 rows only), so the split has to be cheap: two fp16 values,
-//   x = h + 2^-11 l,   h = fp16(x),   l = fp16(2^11 (x - h)),
-// five instructions per pair of elements (the three-way bf16 split of mfma_tiles.h: eleven), and three products,
-//   x y = hx hy + 2^-11 (hx ly + lx hy) + rest,
-// summed in accumulators of their own, hx hy and the two small ones.  x - h - 2^-11 l is below 2^-23 |x| (half of the time
-// zero), the product lx ly that is left out below 2^-22 |x y|, 2^-24.6 in the mean.  Error of a 256-deep product against 64 bits
-// (2-norm), fp32 instructions / here: ReLU outputs x Glorot weights 2.04e-7 / 1.31e-7, sparse gradients x weights 2.03e-7 /
-// 1.30e-7, all terms positive 2.47e-7 / 0.94e-7, left operand over e^+-8 2.84e-7 / 1.35e-7, its rows e^4 apart 2.87e-7 / 1.29e-7.
-// One forward product alone takes 3.3 us (fp32 instructions 3.9, 3.4 of it matrix time), of which 940 vector instructions
-// of 4 cycles and the trip for the first weights; in a chain 5.1 -> 4.3, transposed 6.6 -> 5.7.  us/step, fp32 / fp16: 1 agent
-// 60.2 / 56.5, 10 agents 74.3 / 70.8, 8 SAC agents 115.3 / 110.1.
-// Range: rows of the left operand are scaled by a power of two that brings their largest element to 8 .. 16, and the
-// scale is taken out of the sums.  Weights are taken as they are.  Elements below 2^-14 (6e-5) have a fixed grid instead of a
-// relative one: 2^-36 for weights (1.5e-11), 2^-40 of the largest element of its row for the left operand.  Weights of 32
-// and more, infinities and NaN make l or h infinite and the sums of their column infinite or NaN; the sums of a column of
-// weights below 2^-20 or so are small.  A wavefront that ends with such a sum (HalfAcc16::finish) takes its product again on
-// the fp32 instructions (the tile is still there), so that all values fp32 can hold give what those give.
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-
-struct HalfPair {                                    // eight contraction elements of one lane
-  f16x8 h, l;
-  __device__ inline void set(int i, float a, float b) {        // elements 2 i, 2 i + 1
-    constexpr float k = 2048.0f;
-    const f16x2 hh = __builtin_convertvector((f32x2{a, b}), f16x2);
-    const f16x2 hk = hh * f16x2{(_Float16)k, (_Float16)k};
-    const f16x2 ll = __builtin_convertvector((f32x2{__builtin_fmaf(a, k, -(float)hk[0]), __builtin_fmaf(b, k, -(float)hk[1])}), f16x2);
-    h[2 * i] = hh[0]; h[2 * i + 1] = hh[1];
-    l[2 * i] = ll[0]; l[2 * i + 1] = ll[1];
-  }
-};
-
-// The left operand of a product, 16 rows of an LDS tile, scaled and split: lane l holds row l & 15, element e of block D is
-// column 32 D + 16 (e >> 2) + 4 (l >> 4) + (e & 3).  Every wavefront prepares all of it: 64 of the 320 elements that it splits.
-struct SplitRows16 {
-  HalfPair x[8];
-  float inv[4];                                      // of rows 4 (l >> 4) + v: what takes the scale out of a sum
-  float most;                                        // largest element of this lane's row
-  __device__ inline void load(const float* __restrict__ Xl, int ldx, int lane) {
-    const float* p = Xl + (lane & 15) * ldx + 4 * (lane >> 4);
-    float m = 0.0f;
-#pragma unroll
-    for (int D = 0; D < 8; ++D)
-#pragma unroll
-      for (int o = 0; o < 2; ++o) {
-        const f32x4 v = *reinterpret_cast<const f32x4*>(p + 32 * D + 16 * o);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) m = fmaxf(m, fabsf(v[j]));
-      }
-    m = fmaxf(m, __shfl_xor(m, 16));
-    m = fmaxf(m, __shfl_xor(m, 32));
-    most = m;
-    const int e = 257 - (int)(__float_as_uint(m) >> 23);        // exponent field of the scale: 2^(3 - exponent of m)
-    const int f = e < 1 ? 1 : e > 253 ? 253 : e;
-    const float scale = __uint_as_float((uint32_t)f << 23), back = __uint_as_float((uint32_t)(254 - f) << 23);
-    asm volatile("" ::: "memory");                   // read again below: 64 registers for the row would be too many beside the weights
-#pragma unroll
-    for (int D = 0; D < 8; ++D)
-#pragma unroll
-      for (int o = 0; o < 2; ++o) {
-        const f32x4 v = *reinterpret_cast<const f32x4*>(p + 32 * D + 16 * o);
-#pragma unroll
-        for (int j = 0; j < 2; ++j) x[D].set(2 * o + j, v[2 * j] * scale, v[2 * j + 1] * scale);
-      }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) inv[i] = __shfl(back, 4 * (lane >> 4) + i);
-  }
-};
-
-struct HalfAcc16 {
-  f32x4 t[4], low[4];
-  __device__ inline void zero() {
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) t[nt] = low[nt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  }
-  // acc = the scaled sums put together.  True (for the whole wavefront) if one of them is not finite, or if the sums of
-  // some column are all below 2^-6 while a row is not empty: its weights may then be too small for their grid (an error of
-  // 2^-37 per weight is 2^-30 of a sum of 256 elements of 8 .. 16).  Few columns have four such sums by chance, so the
-  // sixteen are looked at only where a lane finds its four small.
-  __device__ inline bool finish(const SplitRows16& x, Acc16& acc) const {
-    const float (&inv)[4] = x.inv;
-    float z = 0.0f, small = 0x1p-6f;
-    float most[4];
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-      most[nt] = fmaxf(fmaxf(fabsf(t[nt][0]), fabsf(t[nt][1])), fmaxf(fabsf(t[nt][2]), fabsf(t[nt][3])));
-      small = fminf(small, most[nt]);
-    }
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const float s = __builtin_fmaf(low[nt][v], 0x1p-11f, t[nt][v]) * inv[v];
-        acc.t[nt][v] = s;
-        z = __builtin_fmaf(s, 0.0f, z);
-      }
-    if (__builtin_amdgcn_ballot_w64(small < 0x1p-6f) != 0) {
-      small = 0x1p-6f;
-#pragma unroll
-      for (int nt = 0; nt < 4; ++nt) {
-        most[nt] = fmaxf(most[nt], __shfl_xor(most[nt], 16));
-        small = fminf(small, fmaxf(most[nt], __shfl_xor(most[nt], 32)));
-      }
-      if (__builtin_amdgcn_ballot_w64(x.most > 0.0f) != 0 && __builtin_amdgcn_ballot_w64(small < 0x1p-6f) != 0) return true;
-    }
-    return __builtin_amdgcn_ballot_w64(!(z == 0.0f)) != 0;
-  }
-};
-
-// a 32-deep block of weights, two 16-deep ones: split and multiplied, one column tile after the other
-template <bool TRANSPOSED>
-__device__ inline void mfma_block16_half(const HalfPair& x, const WeightBlock16<TRANSPOSED> (&b)[2], HalfAcc16& acc) {
-#pragma unroll
-  for (int nt = 0; nt < 4; ++nt) {
-    HalfPair w;
-#pragma unroll
-    for (int o = 0; o < 2; ++o)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        w.set(2 * o + j, TRANSPOSED ? b[o].w[nt][2 * j] : b[o].w[2 * j][nt], TRANSPOSED ? b[o].w[nt][2 * j + 1] : b[o].w[2 * j + 1][nt]);
-    acc.low[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(x.l, w.h, acc.low[nt], 0, 0, 0);
-    acc.low[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(x.h, w.l, acc.low[nt], 0, 0, 0);
-    acc.t[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(x.h, w.h, acc.t[nt], 0, 0, 0);
-  }
-}
-
-// The product on the fp32 instructions, for operands the fp16 pair cannot hold: rare, so not pipelined.
-template <bool TRANSPOSED>
-__device__ inline void gemm256_16_fp32(const float* __restrict__ Xl, int ldx, const float* __restrict__ W, int wave, int lane, Acc16& out) {
-  Acc16 acc;
-  acc.zero();
-#pragma unroll 1
-  for (int i = 0; i < 16; ++i) {
-    WeightBlock16<TRANSPOSED> b;
-    LdsBlock16 x;
-    b.load(W, i, wave, lane);
-    x.load(Xl, ldx, 16 * i, lane);
-    mfma_block16<TRANSPOSED>(x, b, acc);
-  }
-  out = acc;
-}
-
-// acc = X W: 256-deep product of a 16-row LDS operand with a global weight operand (row-major [256][256]), 8 blocks of 32,
-// fully unrolled; weight registers rotate through three buffers (block D + 2 is requested before block D is split).
-// Block 0 comes from the caller; `tail()` runs once the last weight block has
+// 256-deep product of a 16-row LDS operand with a global weight operand, 16 blocks of 16,
+// fully unrolled; weight registers rotate through four buffers (block i+3 is requested
+// before the MFMAs of block i, about 1500 cycles of matrix work ahead), the LDS operand one
+// block ahead.  Block 0 comes from the caller; `tail()` runs once the last weight block has
 // been requested, so the caller can start the next layer's loads under the last blocks.
-struct WeightPair16 {                                // the two 16-deep blocks of a 32-deep one
-  WeightBlock16<false> b[2];
-  __device__ inline void load(const float* __restrict__ W, int D, int wave, int lane) {
-    b[0].load(W, 2 * D, wave, lane);
-    b[1].load(W, 2 * D + 1, wave, lane);
-  }
-};
 template <class Tail>
 __device__ inline void gemm256_16(const float* __restrict__ Xl, int ldx, const float* __restrict__ W,
-                                  const WeightPair16& b0, int wave, int lane, Acc16& acc, Tail tail) {
-  WeightPair16 wb[3];
-  SplitRows16 x;
-  HalfAcc16 sum;
+                                  const WeightBlock16<false>& b0, int wave, int lane, Acc16& acc, Tail tail) {
+  WeightBlock16<false> wb[4];
+  LdsBlock16 xb[2];
   wb[0] = b0;
   wb[1].load(W, 1, wave, lane);
-  x.load(Xl, ldx, lane);
-  sum.zero();
+  wb[2].load(W, 2, wave, lane);
+  xb[0].load(Xl, ldx, 0, lane);
 #pragma unroll
-  for (int D = 0; D < 8; ++D) {
-    if (D + 2 < 8) wb[(D + 2) % 3].load(W, D + 2, wave, lane);
-    if (D == 6) tail();
+  for (int i = 0; i < 16; ++i) {
+    if (i + 3 < 16) wb[(i + 3) & 3].load(W, i + 3, wave, lane);
+    if (i == 13) tail();
+    if (i + 1 < 16) xb[(i + 1) & 1].load(Xl, ldx, 16 * (i + 1), lane);
     __builtin_amdgcn_sched_barrier(0);
-    mfma_block16_half<false>(x.x[D], wb[D % 3].b, sum);
+    mfma_block16<false>(xb[i & 1], wb[i & 3], acc);
     __builtin_amdgcn_sched_barrier(0);
   }
-  if (sum.finish(x, acc)) gemm256_16_fp32<false>(Xl, ldx, W, wave, lane, acc);
 }
 
 // The transposed product (backward: acc[r][k] += sum_n Z[r][n] W[k][n]) with its weight operand staged through LDS.
@@ -294,30 +142,32 @@ __device__ inline void gemm256_16_staged(const float* __restrict__ Xl, int ldx, 
                                          Tail tail) {
   float* sw = stage + wave * kStage16Wave;
   WeightStage16 g[3];                                // double blocks D + 1 .. D + 3 in flight
-  WeightBlock16<true> wb[2][2];
-  SplitRows16 x;
-  HalfAcc16 sum;
+  WeightBlock16<true> wb[2];
+  LdsBlock16 xb[2];
   g[0] = g0;
   g[1].load(W, 1, wave, lane);
   g[2].load(W, 2, wave, lane);
-  x.load(Xl, ldx, lane);
   g[0].put(sw, 0, lane);
-#pragma unroll
-  for (int o = 0; o < 2; ++o) staged_block16(wb[0][o], sw, o, lane);
-  sum.zero();
+  staged_block16(wb[0], sw, 0, lane);
+  xb[0].load(Xl, ldx, 0, lane);
 #pragma unroll
   for (int D = 0; D < 8; ++D) {
     if (D + 3 < 8) g[D % 3].load(W, D + 3, wave, lane);        // its registers were parked in LDS one round ago
     if (D == 5) tail();
+    staged_block16(wb[1], sw, 2 * D + 1, lane);
+    xb[1].load(Xl, ldx, 16 * (2 * D + 1), lane);
+    __builtin_amdgcn_sched_barrier(0);
+    mfma_block16<true>(xb[0], wb[0], acc);
+    __builtin_amdgcn_sched_barrier(0);
     if (D + 1 < 8) {
       g[(D + 1) % 3].put(sw, D + 1, lane);           // requested two rounds ago (the first two: at the start)
-#pragma unroll
-      for (int o = 0; o < 2; ++o) staged_block16(wb[(D + 1) & 1][o], sw, 2 * D + 2 + o, lane);
+      staged_block16(wb[0], sw, 2 * D + 2, lane);
+      xb[0].load(Xl, ldx, 16 * (2 * D + 2), lane);
     }
-    mfma_block16_half<true>(x.x[D], wb[D & 1], sum);
+    __builtin_amdgcn_sched_barrier(0);
+    mfma_block16<true>(xb[1], wb[1], acc);
     __builtin_amdgcn_sched_barrier(0);
   }
-  if (sum.finish(x, acc)) gemm256_16_fp32<true>(Xl, ldx, W, wave, lane, acc);
 }
 
 // First-layer weights for the leading 32 rows of W (two blocks), fetched ahead of time;

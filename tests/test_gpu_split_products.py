@@ -275,8 +275,8 @@ def test_wide_first_layers_against_64_bits(algo, O, A):
 @pytest.mark.parametrize("algo", [pp.POP_ALGO_TD3, pp.POP_ALGO_SAC])
 @pytest.mark.parametrize("scale", [1e-28, 1e-9, 1e-4, 1e3, 1e28])
 def test_16_row_chains_over_magnitudes(algo, scale):
-    """One step with hidden weights `scale` times as large and first layers scaled the other way: 16-row chains (two-part fp16
-    operands, or the fp32 instructions where those do not hold the weights) against 32-row chains (three-part bf16)."""
+    """One step with hidden weights `scale` times as large and first layers scaled the other way: 16-row chains, whose products
+    run on the fp32 instructions, against 32-row chains (three-part bf16)."""
     O, A, P = 17, 6, 2
     got = []
     for rows in ((16, 32, 16), 32):
@@ -305,3 +305,148 @@ def test_16_row_chains_over_magnitudes(algo, scale):
     assert np.linalg.norm(y16 - y32) / np.linalg.norm(y32) < 3e-6
     for x, y in zip(g16, g32):
         assert np.isfinite(y).all() and rel_l2(x, y) < 2e-3    # as in test_rows_of_a_chain_agree
+
+
+def _forward64(net, x):
+    """Q of every row in 64 bits, and the size of the head's terms."""
+    w1, b1, w2, b2, w3, b3 = (v.astype(np.float64) for v in net)
+    h = np.maximum(x @ w1 + b1, 0.0)
+    h = np.maximum(h @ w2 + b2, 0.0)
+    return (h @ w3 + b3)[:, 0], np.sqrt((h * h) @ (w3 * w3))[:, 0]
+
+
+# name: (factor of the hidden weights behind half of the units, factor of one unit's activation)
+SPREADS = {"alike": (1.0, 1.0), "1e-5": (1e-5, 1.0), "1e-7": (1e-7, 1.0), "1e-9": (1e-9, 1.0), "1e-20": (1e-20, 1.0),
+           "one activation 1e8": (1.0, 1e8)}
+
+
+@pytest.mark.parametrize("spread", sorted(SPREADS))
+@pytest.mark.parametrize("rows", [(16, 32, 16), 32, 64])
+def test_forward_products_with_mixed_magnitudes(rows, spread):
+    """Small and ordinary weights in one column, small and large activations in one row: batch rows that meet only the small
+    ones get the Bellman target that their own terms give, and not one that the other rows' sizes spoil."""
+    O, A, P, n = 17, 6, 2, 64
+    small, large = SPREADS[spread]
+    quiet, big = slice(0, H, 2), 1                       # units that are active in the quiet rows; one that is not `quiet`
+    pop = _population(pp.POP_ALGO_TD3, P, O, A, rows=rows)
+    nets = []
+    for i in range(P):
+        for net in ("t_critic1", "t_critic2"):
+            th = pop.get_params(i, net).copy()
+            w1, b1, w2, b2, w3, b3 = _views(th, O + A, 1)
+            w1[0] = -4.0                                 # obs 0 is 1 in quiet rows and -1 in the others
+            w1[0, quiet] = 4.0
+            w1[O:] = 0.0                                 # whatever the target action
+            w2[quiet] *= np.float32(small)
+            w1[:, big], b1[big], w2[big] = w1[:, big] * np.float32(large), 0.0, 0.0 if large != 1.0 else w2[big]
+            if large != 1.0:
+                w1[0, big] = 4 * large                   # large in the quiet rows, and every weight it meets is zero
+            pop.set_params(i, net, th)
+            nets.append(_views(th, O + A, 1))
+    g = np.random.default_rng(12)
+    obs = g.standard_normal((P, n, O)).astype(np.float32)
+    nxt = g.standard_normal((P, n, O)).astype(np.float32)
+    nxt[:, :, 0] = np.where(np.arange(n) % 2 == 0, 1.0, -1.0)
+    zero = np.zeros((P, n), np.float32)
+    pop.insert(-1, obs=obs, act=g.uniform(-1, 1, (P, n, A)).astype(np.float32), rew=zero, done=zero, next_obs=nxt)
+    pop.set_debug(True)
+    pop.update(1)
+    y, batch = pop.debug("target_y").astype(np.float64), pop.debug("batch").astype(np.float64)
+    pop.close()
+    gamma = float(np.float32(0.99))
+    for i in range(P):
+        x = np.concatenate([batch[i][:, O + A + 2:], np.zeros((256, A))], axis=1)
+        (q0, s0), (q1, s1) = _forward64(nets[2 * i], x), _forward64(nets[2 * i + 1], x)
+        want, size = gamma * np.minimum(q0, q1), gamma * np.maximum(s0, s1)
+        for rest in (x[:, 0] > 0, x[:, 0] < 0):
+            assert rest.any()
+            # a hidden unit is 2.9e-7 off at most (its product) and 2e-7 (the first layer's), each independently of the others, so
+            # a Q value is 3.5e-7 of the root of its squared head terms off, also where those cancel; and twice that
+            apart = np.linalg.norm(y[i][rest] - want[rest]) / np.linalg.norm(np.maximum(np.abs(want[rest]), size[rest]))
+            assert apart < 7e-7, (i, rest[0])
+
+
+@pytest.mark.parametrize("small", [1.0, 1e-5, 1e-7, 1e-9, 1e-20])
+@pytest.mark.parametrize("rows", [(16, 32, 16), 32, 64])
+def test_backward_products_with_mixed_magnitudes(rows, small):
+    """The same for the products with the transposed weights: the policy gradient that comes from batch rows whose active
+    units all have small weights behind them."""
+    O, A, P, n = 17, 6, 2, 64
+    orc = oracle_td3.Population(_hparams(pp.POP_ALGO_TD3, P, A), O, A, [H, H], 256, n)
+    hps = [dict(h, lr_critic=1e-12) for h in _hparams(pp.POP_ALGO_TD3, P, A)]      # the policy step meets the critics as they were
+    pop = _population(pp.POP_ALGO_TD3, P, O, A, rows=rows)
+    g = np.random.default_rng(13)
+    fix_masks(orc, g)
+    always, gate = slice(0, H, 2), 7                      # units active in every row; the unit that is active in the quiet ones
+    for i in range(P):
+        ag = orc.agents[i]
+        pop.set_hparams(i, hps[i])
+        orc.set_hparams(i, hps[i])
+        (w1, b1), (w2, b2), (w3, b3) = ag.actor
+        w2[:, always] *= small
+        w1[:, gate], w1[1, gate], b1[gate] = 0.0, 8.0, -4.0
+        mean = np.maximum(b1, 0.0) @ w2
+        b2[:] = np.round(8 * (g.choice([-2.5, 2.5], H) - mean)) / 8
+        b2[always] = np.round(8 * (2.5 - mean[always])) / 8
+        w2[gate, 1::2] = -2.5                            # switches the other half off in the quiet rows (the gate adds 4 times this)
+        for net in ("actor", "critic1", "critic2", "t_actor", "t_critic1", "t_critic2"):
+            pop.set_params(i, net, orc.get_params(i, net))
+        # both sides start from the same 32-bit values
+        for layer, got in zip(ag.actor, (_views(pop.get_params(i, "actor"), O, A)[k:k + 2] for k in (0, 2, 4))):
+            layer[0][:], layer[1][:] = got
+        tr = dict(obs=g.standard_normal((n, O)).astype(np.float32), act=g.uniform(-1, 1, (n, A)).astype(np.float32),
+                  rew=g.standard_normal(n).astype(np.float32), done=np.zeros(n, np.float32), next_obs=g.standard_normal((n, O)).astype(np.float32))
+        tr["obs"][:, 1] = np.arange(n) % 2               # obs 1: 1 in the quiet rows, 0 in the others
+        pop.insert(i, **tr)
+        orc.insert(i, **tr)
+    pop.set_debug(True)
+    pop.update(1)
+    orc.update(1)
+    for i in range(P):
+        got, want = (_views(p.get_params(i, "g_actor"), O, A)[0] for p in (pop, orc))
+        assert np.linalg.norm(want[1]) > 0
+        # row 1 of dW1 is summed over the quiet rows alone; the bound is test_gradients_against_64_bits'
+        assert rel_l2(got[1], want[1]) < 1e-6 and rel_l2(got, want) < 1e-6, i
+    pop.close()
+
+
+@pytest.mark.parametrize("plant", ["bias", "hidden weight"])
+def test_wide_first_layer_ends_with_its_fan_in(plant):
+    """Fan-in 71: the last block of 16 inputs reaches eight rows past the weights, to the bias and the hidden weights that lie
+    behind them; an infinity there stays out of the first layer's sums."""
+    O, A, P, n = 65, 6, 17, 64
+    pop = _population(pp.POP_ALGO_TD3, P, O, A)
+    assert pop.tuning()["rows_target"] == 32
+    nets = []
+    for net in ("t_critic1", "t_critic2"):
+        th = pop.get_params(0, net).copy()
+        w1, b1, w2, b2, w3, b3 = _views(th, O + A, 1)
+        np.abs(w3, out=w3)
+        w1[O:] = 0.0                                     # whatever the target action
+        if plant == "bias":
+            b1[5] = np.inf
+            np.abs(w2[5], out=w2[5])
+        else:
+            w2[0:6, 9] = -np.inf                         # unit 9 of the second layer is off wherever one of six units is on
+        pop.set_params(0, net, th)
+        nets.append([v.astype(np.float64) for v in _views(th, O + A, 1)])
+    g = np.random.default_rng(14)
+    zero = np.zeros((P, n), np.float32)
+    pop.insert(-1, obs=g.standard_normal((P, n, O)).astype(np.float32), act=g.uniform(-1, 1, (P, n, A)).astype(np.float32),
+               rew=zero, done=zero, next_obs=g.standard_normal((P, n, O)).astype(np.float32))
+    pop.set_debug(True)
+    pop.update(1)
+    y, batch = pop.debug("target_y")[0].astype(np.float64), pop.debug("batch")[0].astype(np.float64)
+    pop.close()
+    x = np.concatenate([batch[:, O + A + 2:], np.zeros((256, A))], axis=1)
+    q = []
+    with np.errstate(all="ignore"):
+        for w1, b1, w2, b2, w3, b3 in nets:
+            h = np.fmax(x @ w1 + b1, 0.0)                # max(NaN, 0) = 0, as the kernels' ReLU has it
+            h = np.fmax((h[:, :, None] * w2[None]).sum(1) + b2, 0.0)
+            q.append((h * w3[:, 0]).sum(1) + b3[0])
+    want = float(np.float32(0.99)) * np.minimum(*q)
+    if plant == "bias":
+        assert np.isinf(want).all() and np.array_equal(y, want)
+    else:
+        assert np.isfinite(want).all() and np.allclose(y, want, rtol=0, atol=4e-6)

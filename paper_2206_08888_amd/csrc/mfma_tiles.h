@@ -161,10 +161,11 @@ struct Acc {
 // lane.  The same loads from per-lane pointers cost the 64-row products of a chain 100 registers (each stream of
 // loads keeps a 64-bit address per lane) and two vector instructions with a wait between them per four loads; with the
 // resource 32-row forward products of two workgroups on a CU take 15,400 cycles instead of 17,600, and the chains that
-// share a CU no longer spill.  Loads at or beyond n give zero.
+// share a CU no longer spill.  Loads whose lane offset lies at or beyond n give zero (n <= 0: all of them); a scalar offset is
+// outside that check, so where rows beyond the matrix are asked for (first layers) the resource starts at the rows of the block.
 typedef __amdgpu_buffer_rsrc_t WeightsRsrc;
 __device__ inline WeightsRsrc weights_rsrc(const float* W, int n) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(W), 0, 4 * n, 0x00020000);
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(W), 0, 4 * (n < 0 ? 0 : n), 0x00020000);
 }
 __device__ inline f32x2 rsrc_load2(WeightsRsrc r, uint32_t lane_bytes, int floats) {
   return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(r, lane_bytes, 4 * floats, 0));
@@ -178,13 +179,12 @@ __device__ inline f32x4 rsrc_load4(WeightsRsrc r, uint32_t lane_bytes, int float
 struct SmallW {
   float w[4][2][4];
   __device__ inline void load(const float* __restrict__ W, int K, int wave, int lane) {
-    const WeightsRsrc r = weights_rsrc(W, K * kH);
     const uint32_t off = 4u * (uint32_t)(4 * (lane >> 5) * kH + tile_col(wave, 0, lane));
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const f32x2 v = rsrc_load2(r, off + 4 * j * kH, 8 * i * kH);
+        const f32x2 v = rsrc_load2(weights_rsrc(W + 8 * i * kH, (K - 8 * i) * kH), off + 4 * j * kH, 0);
         w[i][0][j] = v[0];
         w[i][1][j] = v[1];
       }
@@ -250,15 +250,16 @@ __device__ inline void gemm_xw_deep(const float* __restrict__ Xl, int ldx, int K
                                     const SmallW& pre, int wave, int lane, Acc<MT>& acc) {
   const int half = lane >> 5, l32 = lane & 31;
   const int nb = (K + 15) >> 4;
-  const WeightsRsrc Wr = weights_rsrc(W, K * kH);    // rows at or beyond K are zero
-  const uint32_t off = 4u * (uint32_t)(4 * half * kH + tile_col(wave, 0, lane));
+  uint32_t off = 4u * (uint32_t)(4 * half * kH + tile_col(wave, 0, lane));
   Acc<MT> low;
   low.zero();
   float b[PF][2][8];
   auto request = [&](float (&dst)[2][8], int blk) {
+    const WeightsRsrc Wr = weights_rsrc(W + 16 * blk * kH, (K - 16 * blk) * kH);      // rows at or beyond K are zero
+    asm("" : "+v"(off));                              // or copies of it are kept for each block in flight
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const f32x2 v = rsrc_load2(Wr, off + 4 * (e & 3) * kH, (16 * blk + 8 * (e >> 2)) * kH);
+      const f32x2 v = rsrc_load2(Wr, off + 4 * (8 * (e >> 2) + (e & 3)) * kH, 0);
       dst[0][e] = v[0];
       dst[1][e] = v[1];
     }

@@ -146,8 +146,8 @@ struct SmallVec {
 // The input tile of a chain (columns [c0, c0 + n) of R batch rows into columns [0, n) of the LDS tile, the rest
 // zero) in the same two halves; for the narrow inputs (row stride of the tile at most kMaxIn + 4).
 // A thread's elements are kThreads apart; their rows and columns follow from the first one's by addition (a division by the
-// row stride is some 40 instructions, for each of 17 elements at 64 rows): us/step 10 agents 70.6 / 69.9, 256 agents 1014 /
-// 1003.  Leaving out the elements beyond the tile (17 + 6 inputs fill 7 of the 17) by scalar branches is slower than the
+// row stride is some 40 instructions, for each of 17 elements at 64 rows): us/step 10 agents 75.2 / 74.9, 16 agents 100.7 / 99.9,
+// 256 agents 1014 / 1003.  Leaving out the elements beyond the tile (17 + 6 inputs fill 7 of the 17) by scalar branches is slower than the
 // divisions (1067 at 256 agents): the loads behind a branch are no longer requested together.
 template <int R>
 struct InputTile {
@@ -720,7 +720,7 @@ struct CriticMap : LdsMap<G::R, G::kPad> {
 // Critic forward + backward.  One workgroup per (critic network, chunk); network = 2 agent + k.
 //   L = (1/B) sum_b (Q_k(s_b, a_b) - y_b)^2 ;  dq = 2 (q - y) / B
 //   dz2 = (dq W3^T) * [h2 > 0] ;  dz1 = (dz2 W2^T) * [h1 > 0]
-// Outputs for the weight-gradient kernel: h1, dz1, dz2 as its three factors ([h2 > 0], dq, W3: 9 KB of a network's
+// Outputs for the weight-gradient kernel: h1, dz1, dz2 as its three factors ([h2 > 0], dq, W3: 10 KB of a network's
 // 256; critic tiles of 256 agents read 1.51 GB with dz2 itself), and the chunk's partial sums of dW3, db3, db2, db1 and of the loss.
 // WAIT: the targets come from target workgroups of the same launch; the lanes that need
 // them poll for their rows right before the loss.  SIGNAL: count this chunk as finished

@@ -158,10 +158,11 @@ struct Acc {
 };
 
 // A weight matrix of n floats as a buffer resource: a load takes its address from a scalar and one 32-bit offset per
-// lane.  The same loads from per-lane pointers cost the 64-row products of a chain 100 registers (each stream of
-// loads keeps a 64-bit address per lane) and two vector instructions with a wait between them per four loads; with the
-// resource 32-row forward products of two workgroups on a CU take 15,400 cycles instead of 17,600, and the chains that
-// share a CU no longer spill.  Loads whose lane offset lies at or beyond n give zero (n <= 0: all of them); a scalar offset is
+// lane.  From per-lane pointers each stream of loads keeps a 64-bit address per lane and needs two vector instructions
+// with a wait between them per four loads; with the resource 32-row forward products of two workgroups on a CU take 15,400
+// cycles instead of 17,600.  Vector registers, pointers / resource: k_target of 64 rows 244 / 212, of 32 rows 256 with 2 spilled / 228,
+// of 16 rows 186 / 164; spilled by k_step (32 rows) 44 / 40, by k_actor of 32 rows at two per CU 50 / 39; k_critic about the same.
+// Loads whose lane offset lies at or beyond n give zero (n <= 0: all of them); a scalar offset is
 // outside that check, so where rows beyond the matrix are asked for (first layers) the resource starts at the rows of the block.
 typedef __amdgpu_buffer_rsrc_t WeightsRsrc;
 __device__ inline WeightsRsrc weights_rsrc(const float* W, int n) {
@@ -243,6 +244,9 @@ __device__ inline void gemm_xw_small(const float* __restrict__ Xl, int ldx, int 
 // blocks in flight beyond the two that `pre` holds.  With 376 inputs the first layers are three fifths of a chain's
 // matrix work, and the fp32 instructions take 1024 cycles per block of 32 rows and wavefront; the 12 bf16 instructions
 // and the splits of 12 pairs per lane some 700.  20 TD3 agents, obs 376 / act 17: 308 -> 271 us/step; 32 SAC agents 513 -> 464.
+// Error against 64 bits (2-norm; both emulated in numpy, normal inputs x Glorot weights), fp32 sums / here: 393 inputs 3.5e-7 /
+// 0.9e-7, 140 inputs 2.1e-7 / 0.6e-7, 72 inputs 1.5e-7 / 0.5e-7; where a row has only four inputs that are not zero 4.0e-8 / 3.5e-8, two
+// 3.1e-8 / 3.4e-8, one 2.5e-8 / 3.5e-8.  Inputs and weights below 2^-110 lose low parts, as in the hidden products (above).
 // X: as above; columns of the tile beyond K hold zeros (load_input_wide), and a block that would reach past the tile's
 // row reads its last four columns instead, where the weights are zero.
 template <int MT, int PF>

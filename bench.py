@@ -18,7 +18,10 @@ pop_update(K) call bracketed by a synchronisation on both sides; the line report
 Prints ONE JSON line: agent-updates/s = P * K / seconds, with
   roofline      the dominant kernel against the fp32 MFMA peak (launch time from HIP events on the library's stream); the
                 256-deep products of 32- and 64-row chains run on the bf16 matrix pipe (six products of exactly split
-                operands, 2.7 times that peak), the rest on the fp32 instructions: the peak is a yardstick there, no ceiling;
+                operands, 2.7 times that peak), the rest on the fp32 instructions: the peak is a yardstick there, no ceiling.
+                `bound` names the ceiling that `frac` is taken of; `mfma_busy_frac` is the share of its time in which the
+                chip's matrix units work (rocprofv3, profiles/mfma_utilisation.txt) -- far below `frac` where a kernel runs
+                bf16 products or, as with small populations, waits for one product after the other;
   hbm           achieved GB/s of the memory-bound parts (replay gather, weight-gradient tiles with Adam / Polyak)
                 against the 8 TB/s HBM peak: algorithmic bytes / launch time;
   counters      what rocprofv3 counter runs recorded for the same kernels (profiles/*.txt: HBM bytes per launch,
@@ -336,7 +339,7 @@ def analyse(res, c, steps, config_id):
     counters, fresh = read_counters(config_id)
     roofline = dict(bound="mfma", kernel=dominant, achieved=achieved, peak=MFMA_FP32_PEAK_TFLOPS, unit="TFLOP/s",
                     frac=achieved / MFMA_FP32_PEAK_TFLOPS, traffic=counters.get(dominant, {}).get("hbm_bytes_per_launch"),
-                    avg_launch_us=kus[dominant], flops_per_launch=flops[dominant])
+                    mfma_busy_frac=counters.get(dominant, {}).get("mfma_busy_frac"), avg_launch_us=kus[dominant], flops_per_launch=flops[dominant])
     hbm = {}
     for k in ("gather", "wgrad_critic", "wgrad_actor"):
         if kus.get(k):

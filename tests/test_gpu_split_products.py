@@ -273,7 +273,7 @@ def test_wide_first_layers_against_64_bits(algo, O, A):
 
 
 @pytest.mark.parametrize("algo", [pp.POP_ALGO_TD3, pp.POP_ALGO_SAC])
-@pytest.mark.parametrize("scale", [1e-28, 1e-9, 1e-4, 1e3, 1e28])
+@pytest.mark.parametrize("scale", [1e-28, 1e-9, 1e-4, 1.0, 1e3, 1e28])
 def test_16_row_chains_over_magnitudes(algo, scale):
     """One step with hidden weights `scale` times as large and first layers scaled the other way: 16-row chains, whose products
     run on the fp32 instructions, against 32-row chains (three-part bf16)."""
@@ -305,6 +305,9 @@ def test_16_row_chains_over_magnitudes(algo, scale):
     assert np.linalg.norm(y16 - y32) / np.linalg.norm(y32) < 3e-6
     for x, y in zip(g16, g32):
         assert np.isfinite(y).all() and rel_l2(x, y) < 2e-3    # as in test_rows_of_a_chain_agree
+        # the small unit by itself, which the norms of y and of the gradients cannot show: its head weights' gradient
+        u16, u32 = (_views(v, O, 2 * A if algo == pp.POP_ALGO_SAC else A)[4][5] for v in (x, y))
+        assert np.linalg.norm(u32.astype(np.float64)) > 0 and rel_l2(u16, u32) < 2e-3
 
 
 def _forward64(net, x):

@@ -29,8 +29,9 @@ __global__ __launch_bounds__(256) void k_init(PopDev d, InitLimits lim) {
   const float u = (float)(pick(blk, (uint32_t)e & 3u) >> 8) * 5.9604644775390625e-8f;
   const float centred = 2.0f * u - 1.0f;          // exact
   const float w = __fmul_rn(centred, limit);      // a single rounding, never fused
-  net_ptr(d, d.theta, agent, net)[off + e] = w;
-  net_ptr(d, d.target, agent, net)[off + e] = w;
+  const int at = off + (layer == 1 ? w2_index(e / kH, e % kH) : e);
+  net_ptr(d, d.theta, agent, net)[at] = w;
+  net_ptr(d, d.target, agent, net)[at] = w;
 }
 
 hipError_t launch_init(const PopDev& d, const InitLimits& lim, hipStream_t s) {

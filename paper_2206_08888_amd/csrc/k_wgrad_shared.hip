@@ -69,10 +69,11 @@ __global__ __launch_bounds__(kThreads, 3) void k_shared_partial(PopDev d, uint32
       }
     }
     const int half = lane >> 5, l32 = lane & 31;
-    const uint32_t elem0 = (uint32_t)((w2 ? L.w2 : L.w1) + (m0 + 4 * half) * kH + n0 + 32 * wave + l32);
+    const int n = n0 + 32 * wave + l32;
+    const uint32_t elem0 = (uint32_t)(w2 ? L.w2 + w2_index(m0 + 4 * half, n) : L.w1 + (m0 + 4 * half) * kH + n);
 #pragma unroll
     for (int v = 0; v < 16; ++v)
-      if ((m0 + acc_row(v, lane)) < M) out[elem0 + (uint32_t)((8 * (v >> 2) + (v & 3)) * kH)] = acc.t[0][0][v];
+      if ((m0 + acc_row(v, lane)) < M) out[elem0 + (uint32_t)(8 * (v >> 2) * kH + (w2 ? w2_index(v & 3, 0) : (v & 3) * kH))] = acc.t[0][0][v];
   } else {
     const int c = tid;
     float gb1 = 0.0f, gb2 = 0.0f, gw3 = 0.0f, gb3 = 0.0f, loss = 0.0f;

@@ -465,7 +465,7 @@ struct NoTail { __device__ inline void operator()() const {} };
 // 256-deep product of an LDS operand (fp32 tile, row stride kLda) with a global weight operand on the bf16 pipe:
 //   forward  (TRANSPOSED = false): acc[r][c] += sum_k X[r][k] W[k][c], c in this wave's 64 columns
 //   backward (TRANSPOSED = true):  acc[r][k] += sum_n Z[r][n] W[k][n], k in this wave's 64 columns
-// W is row-major [256][256] in both cases.  Matrix and vector instructions share the issue port (measured: about five
+// W is a [256][256] hidden matrix in the order of w2_index in both cases.  Matrix and vector instructions share the issue port (measured: about five
 // cycles for either beside the other; a matrix instruction keeps its pipe for 32), and a pair of elements costs eleven
 // vector instructions to split, so the number of splits decides: a weight is used by one wavefront and split in its
 // registers, once per 32 MT rows; the LDS operand is used by all four wavefronts and split once per workgroup, 64
@@ -483,21 +483,24 @@ template <bool TRANSPOSED>
 struct WeightRaw {
   float w[2][8];                           // [column tile][e]
   static constexpr int kPieces = TRANSPOSED ? 4 : 8;           // load instructions per block
-  static constexpr int kGroup = 64 * (TRANSPOSED ? 1 : kH);    // floats from one group of four blocks to the next
-  __device__ static constexpr int offset(int i) { return (32 * (i >> 1) + 8 * (i & 1)) * (TRANSPOSED ? 1 : kH); }
+  static constexpr int kGroup = TRANSPOSED ? w2_index(0, 64) : w2_index(64, 0);   // floats from one group of four blocks to the next
+  __device__ static constexpr int offset(int i) {
+    const int at = 32 * (i >> 1) + 8 * (i & 1);
+    return TRANSPOSED ? w2_index(0, at) : w2_index(at, 0);
+  }
   __device__ static inline WeightsRsrc rsrc(const float* W) { return weights_rsrc(W, kH * kH); }
   __device__ static inline uint32_t lane_bytes(int wave, int lane) {
     const int half = lane >> 5, col = tile_col(wave, 0, lane);
-    return 4u * (uint32_t)(TRANSPOSED ? col * kH + 16 * half : 16 * half * kH + col);
+    return 4u * (uint32_t)(TRANSPOSED ? w2_index(col, 16 * half) : w2_index(16 * half, col));
   }
   __device__ inline void load_piece(WeightsRsrc W, uint32_t lane_off, int blk, int p) {
     if (TRANSPOSED) {
-      const int nt = p >> 1, s = p & 1;              // the lane's two columns are rows of W, kH apart
-      const f32x4 v = rsrc_load4(W, lane_off + 4 * (nt * kH + 4 * s), blk);
+      const int nt = p >> 1, s = p & 1;              // the lane's two columns are neighbouring rows of W, the first one even
+      const f32x4 v = rsrc_load4(W, lane_off + 4 * w2_index(nt, 4 * s), blk);
 #pragma unroll
       for (int j = 0; j < 4; ++j) w[nt][4 * s + j] = v[j];
     } else {
-      const f32x2 v = rsrc_load2(W, lane_off + 4 * (p & 3) * kH, blk + (p & ~3) * kH);
+      const f32x2 v = rsrc_load2(W, lane_off + 4 * w2_index(p & 3, 0), blk + w2_index(p & ~3, 0));
       w[0][p] = v[0];
       w[1][p] = v[1];
     }

@@ -47,9 +47,9 @@ struct WeightBlock16 {
   __device__ inline void load(const float* __restrict__ W, int i, int wave, int lane) {
     static_assert(!TRANSPOSED, "read from memory as WeightStage16");
     const WeightsRsrc r = weights_rsrc(W, kH * kH);
-    const uint32_t off = 4u * (uint32_t)(4 * (lane >> 4) * kH + 64 * wave + 4 * (lane & 15));
+    const uint32_t off = 4u * (uint32_t)w2_index(4 * (lane >> 4), 64 * wave + 4 * (lane & 15));
 #pragma unroll
-    for (int j = 0; j < 4; ++j) w[j] = rsrc_load4(r, off + 4 * j * kH, 16 * i * kH);
+    for (int j = 0; j < 4; ++j) w[j] = rsrc_load4(r, off + 4 * w2_index(j, 0), w2_index(16 * i, 0));
   }
 };
 
@@ -112,10 +112,10 @@ struct WeightStage16 {                               // one double block on its 
   __device__ inline void load(const float* __restrict__ W, int D, int wave, int lane) {
     const int s = lane >> 3, h = lane & 7;
     const WeightsRsrc r = weights_rsrc(W, kH * kH);
-    const uint32_t off = 4u * (uint32_t)((64 * wave + 4 * s) * kH + 4 * h);
+    const uint32_t off = 4u * (uint32_t)w2_index(64 * wave + 4 * s, 4 * h);
 #pragma unroll
     for (int q = 0; q < 8; ++q)                      // rows p = 8 q + s: c = 8 (q & 1) + s, nt = q >> 1
-      g[q] = rsrc_load4(r, off + 4 * (q >> 1) * kH, 32 * (q & 1) * kH + 32 * D);
+      g[q] = rsrc_load4(r, off + 4 * w2_index(q >> 1, 0), w2_index(32 * (q & 1), 32 * D));
   }
   __device__ inline void put(float* __restrict__ stage_wave, int D, int lane) const {
     const int s = lane >> 3, h = lane & 7;

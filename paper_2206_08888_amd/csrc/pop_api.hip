@@ -33,6 +33,17 @@ __global__ void k_put_hp(HpDev* dst, HpDev hp) {
   if (threadIdx.x == 0) *dst = hp;
 }
 
+// One network between its canonical order (row-major matrices) in `canon` and the order it has in the workspace (w2_index) at `net`.
+// A float per thread: the caller's array is aligned to floats only.
+__global__ __launch_bounds__(256) void k_read_net(float* __restrict__ canon, const float* __restrict__ net, int size, int w2) {
+  const int i = blockIdx.x * 256 + threadIdx.x, e = i - w2;
+  if (i < size) canon[i] = net[e >= 0 && e < kH * kH ? w2 + w2_index(e / kH, e % kH) : i];
+}
+__global__ __launch_bounds__(256) void k_write_net(float* __restrict__ net, const float* __restrict__ canon, int size, int w2) {
+  const int i = blockIdx.x * 256 + threadIdx.x, e = i - w2;
+  if (i < size) net[e >= 0 && e < kH * kH ? w2 + w2_index(e / kH, e % kH) : i] = canon[i];
+}
+
 // State of agent src over that of agent dst: `floats` (a multiple of 64) of each region and the SAC temperature, in one launch.
 __global__ __launch_bounds__(256) void k_copy_agent(PopDev d, int dst, int src, int floats) {
   float* const regions[4] = {d.theta, d.target, d.m, d.v};
@@ -837,6 +848,14 @@ int pop_act_explore_noalloc(pop_ctx* ctx, const float* obs, int32_t n, float* ac
   return POP_OK;
 }
 
+// Whether a kernel of this context may read and write p: memory of its own device.  (Other memory a copy reaches, another
+// device's without peer access for one, goes through the staging area.)
+static bool kernel_reaches(const pop_ctx* ctx, const void* p) {
+  hipPointerAttribute_t at;
+  if (hipPointerGetAttributes(&at, p) != hipSuccess) { (void)hipGetLastError(); return false; }
+  return at.type == hipMemoryTypeDevice && at.device == ctx->device;
+}
+
 int64_t pop_get_params(pop_ctx* ctx, int32_t agent, int32_t which, float* out, int64_t out_len, int32_t on_device) {
   if (!ctx) return POP_EINVAL;
   if (agent < 0 || agent >= ctx->d.P) return fail(ctx, POP_EINVAL, "agent %d out of range", agent);
@@ -859,9 +878,13 @@ int64_t pop_get_params(pop_ctx* ctx, int32_t agent, int32_t which, float* out, i
   const NetLayout* L = net_of(ctx->d, which, &net, &off, ctx->lay, &region);
   if (out_len < L->size) return fail(ctx, POP_EINVAL, "out_len %lld < %d", (long long)out_len, L->size);
   if (ctx->d.share > 1 && net >= 1) agent = 0;         // the shared critics live in agent 0's blocks
-  const char* src = ctx->ws + region + (int64_t)agent * ctx->d.agent_sz * 4 + off;
-  HIP_TRY(ctx, hipMemcpyAsync(out, src, (size_t)L->size * 4, on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
-                              ctx->stream));
+  const float* src = (const float*)(ctx->ws + region + (int64_t)agent * ctx->d.agent_sz * 4 + off);
+  const bool direct = on_device && kernel_reaches(ctx, out);
+  float* canon = direct ? out : (float*)(ctx->ws + ctx->lay.staging);
+  k_read_net<<<dim3((L->size + 255) / 256), dim3(256), 0, ctx->stream>>>(canon, src, L->size, L->w2);
+  HIP_TRY(ctx, hipGetLastError());
+  if (!direct)
+    HIP_TRY(ctx, hipMemcpyAsync(out, canon, (size_t)L->size * 4, on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, ctx->stream));
   if (!on_device) {
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     const int rc = check_fault(ctx);
@@ -888,9 +911,13 @@ int pop_set_params(pop_ctx* ctx, int32_t agent, int32_t which, const float* in, 
   const NetLayout* L = net_of(ctx->d, which, &net, &off, ctx->lay, &region);
   if (in_len != L->size) return fail(ctx, POP_EINVAL, "in_len %lld != %d", (long long)in_len, L->size);
   if (ctx->d.share > 1 && net >= 1) agent = 0;
-  char* dst = ctx->ws + region + (int64_t)agent * ctx->d.agent_sz * 4 + off;
-  HIP_TRY(ctx, hipMemcpyAsync(dst, in, (size_t)L->size * 4, on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
-                              ctx->stream));
+  float* dst = (float*)(ctx->ws + region + (int64_t)agent * ctx->d.agent_sz * 4 + off);
+  const bool direct = on_device && kernel_reaches(ctx, in);
+  float* staged = (float*)(ctx->ws + ctx->lay.staging);
+  if (!direct)
+    HIP_TRY(ctx, hipMemcpyAsync(staged, in, (size_t)L->size * 4, on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, ctx->stream));
+  k_write_net<<<dim3((L->size + 255) / 256), dim3(256), 0, ctx->stream>>>(dst, direct ? in : staged, L->size, L->w2);
+  HIP_TRY(ctx, hipGetLastError());
   if (!on_device) HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
   return POP_OK;
 }

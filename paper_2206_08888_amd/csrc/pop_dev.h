@@ -68,6 +68,16 @@ __host__ __device__ inline NetLayout make_layout(int in, int out) {
   return L;
 }
 
+// Where element (k, n) of a hidden matrix W2[256][256] lies inside its tensor, in all five regions: blocks of 4 rows x 16
+// columns, in a block the rows 0, 2, 1, 3.  A 128-byte line then holds 16 columns of two rows two apart.  The CU's L1 serves
+// one line per clock: lanes that read a row each, 16 bytes of it (the transposed products: row 2 l of lane l), get 32 bytes per
+// clock from this order and 16 from plain rows, and lanes that read neighbouring columns the same from both (loads alone, cycles
+// per 256 KB, one / two 4-wavefront workgroups on a CU: a row per lane 16,390 / 28,060 plain, 8,200 / 14,410 here; 8 bytes
+// per lane along a row 8,200 / 12,300 and 8,200 / 13,540).  pop_get_params and pop_set_params speak row-major.
+__host__ __device__ constexpr int w2_index(int k, int n) {
+  return (k >> 2) * 4 * kH + (n >> 4) * 64 + (k & 1) * 32 + ((k >> 1) & 1) * 16 + (n & 15);
+}
+
 struct PopDev {
   int algo;                    // POP_ALGO_TD3 (0), POP_ALGO_SAC (1; its actor has 2 A outputs) or POP_ALGO_TD3_SHARED (2)
   int share;                   // 1; shared critics (Sec. 4.2 of the paper): P -- every agent's critic blocks are agent

@@ -1,0 +1,39 @@
+"""Networks cross the boundary in canonical order (row-major matrices) whatever order the library keeps them in."""
+import numpy as np
+import pytest
+
+import paper_2206_08888_amd as pp
+from gpu_common import ensure_built
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("algo,P,O,A", [(pp.POP_ALGO_TD3, 2, 17, 6), (pp.POP_ALGO_SAC, 2, 376, 17), (pp.POP_ALGO_TD3_SHARED, 2, 3, 1)])
+def test_networks_come_back_as_they_were_set(algo, P, O, A):
+    """Every tensor code, from and to host and device memory; device arrays aligned to floats only."""
+    import torch
+    ensure_built()
+    sac = algo == pp.POP_ALGO_SAC
+    hps = [dict(seed=3 + i, lr_actor=3e-4, lr_critic=3e-4, gamma=0.99, tau=0.005, policy_noise=0.2, noise_clip=0.5,
+                policy_delay=1 if sac else 2, adam_b1=0.9, adam_b2=0.999, adam_eps=1e-8, lr_alpha=3e-4,
+                target_entropy=-1.0, init_log_alpha=0.0) for i in range(P)]
+    cfg = pp.make_config(P, O, A, (256, 256), 256, 100, algo=algo)
+    pop = pp.Population(cfg, hps)
+    rng = np.random.default_rng(5)
+    for code in range(12):
+        n = pp.pop_net_size(cfg, code)
+        agents = [0] if algo == pp.POP_ALGO_TD3_SHARED and code % 3 else range(P)
+        for agent in agents:
+            a = rng.standard_normal(n).astype(np.float32)
+            for src_dev in (False, True):
+                buf = torch.zeros(n + 1, device="cuda")
+                buf[1:] = torch.from_numpy(a).cuda()
+                pp.pop_set_params(pop.ctx, agent, code, buf[1:] if src_dev else a)
+                out = torch.full((n + 2,), 7.0, device="cuda")
+                pp.pop_get_params(pop.ctx, agent, code, out[1:n + 1])
+                host = np.empty(n, dtype=np.float32)
+                pp.pop_get_params(pop.ctx, agent, code, host)
+                got = out.cpu().numpy()
+                assert np.array_equal(host, a) and np.array_equal(got[1:-1], a), (code, agent, src_dev)
+                assert got[0] == 7.0 and got[-1] == 7.0
+    pop.close()

@@ -64,28 +64,28 @@ template <int MT>
 using Lds = LdsMap<32 * MT, 8>;
 
 // what a two-hidden-layer network needs from memory before its products can start
-template <int MT>
+template <int MT, int NT = 2>
 struct LayerPre {
-  SmallW w1;                       // first-layer weights
-  WeightRaw<false> w2;             // block 0 of the hidden layer
-  float b1[2], b2[2];              // biases of this lane's columns
+  SmallW<NT> w1;                   // first-layer weights
+  WeightRaw<false, NT> w2;         // block 0 of the hidden layer
+  float b1[NT], b2[NT];            // biases of this lane's columns
   __device__ inline void load(const float* __restrict__ net, const NetLayout& L, int wave, int lane) {
     w1.load(net + L.w1, L.in, wave, lane);
     w2.load(net + L.w2, 0, wave, lane);
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-      b1[nt] = net[L.b1 + tile_col(wave, nt, lane)];
-      b2[nt] = net[L.b2 + tile_col(wave, nt, lane)];
+    for (int nt = 0; nt < NT; ++nt) {
+      b1[nt] = net[L.b1 + tile_col<NT>(wave, nt, lane)];
+      b2[nt] = net[L.b2 + tile_col<NT>(wave, nt, lane)];
     }
   }
 };
 
 // Copy columns [c0, c0 + n) of R batch rows into the LDS input tile at columns
 // [0, n), zero the remaining columns; rows at or beyond `valid` become zero.
-template <int R>
+template <int R, int THREADS = kThreads>
 __device__ inline void load_input(float* Xl, int xld, const float* rows, int row_stride, int c0, int n, int valid,
                                   int tid) {
-  for (int e = tid; e < R * xld; e += kThreads) {
+  for (int e = tid; e < R * xld; e += THREADS) {
     const int r = e / xld, c = e - r * xld;
     Xl[e] = (c < n && r < valid) ? rows[(size_t)r * row_stride + c0 + c] : 0.0f;
   }
@@ -116,18 +116,19 @@ __device__ inline void load_input_wide(float* Xl, int xld, const float* rows, in
 
 // Copies into LDS ahead of a chain.  The loads of a thread are requested eight at a time before the
 // first of them is used: as a plain loop every element would wait out its own trip to memory.
+template <int THREADS = kThreads>
 __device__ inline void stage_vector(float* dst, const float* __restrict__ src, int n, int tid) {
   constexpr int U = 8;
-  for (int e0 = tid; e0 < n; e0 += U * kThreads) {
+  for (int e0 = tid; e0 < n; e0 += U * THREADS) {
     float v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int e = e0 + u * kThreads;
+      const int e = e0 + u * THREADS;
       v[u] = src[e < n ? e : n - 1];
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int e = e0 + u * kThreads;
+      const int e = e0 + u * THREADS;
       if (e < n) dst[e] = v[u];
     }
   }
@@ -145,18 +146,18 @@ struct SmallVec {
 
 // The input tile of a chain (columns [c0, c0 + n) of R batch rows into columns [0, n) of the LDS tile, the rest
 // zero) in the same two halves; for the narrow inputs (row stride of the tile at most kMaxIn + 4).
-// A thread's elements are kThreads apart; their rows and columns follow from the first one's by addition (a division by the
+// A thread's elements are THREADS apart; their rows and columns follow from the first one's by addition (a division by the
 // row stride is some 40 instructions, for each of 17 elements at 64 rows): us/step 10 agents 75.2 / 74.9, 16 agents 100.7 / 99.9,
 // 256 agents 1014 / 1003.  Leaving out the elements beyond the tile (17 + 6 inputs fill 7 of the 17) by scalar branches is slower than the
 // divisions (1067 at 256 agents): the loads behind a branch are no longer requested together.
-template <int R>
+template <int R, int THREADS = kThreads>
 struct InputTile {
-  static constexpr int IT = (R * (kMaxIn + 4) + kThreads - 1) / kThreads;
+  static constexpr int IT = (R * (kMaxIn + 4) + THREADS - 1) / THREADS;
   float v[IT];
   // at(i, r, c): element (r, c) of the tile is number i of this thread
   template <class F>
   __device__ static inline void each(int xld, int tid, F at) {
-    const int dr = kThreads / xld, dc = kThreads - dr * xld;
+    const int dr = THREADS / xld, dc = THREADS - dr * xld;
     int r = tid / xld, c = tid - r * xld;
 #pragma unroll
     for (int i = 0; i < IT; ++i) {
@@ -176,7 +177,7 @@ struct InputTile {
   __device__ inline void put(float* Xl, int xld, int tid) const {
 #pragma unroll
     for (int i = 0; i < IT; ++i) {
-      const int e = tid + i * kThreads;
+      const int e = tid + i * THREADS;
       if (e < R * xld) Xl[e] = v[i];
     }
   }
@@ -189,49 +190,56 @@ __device__ inline float wave_sum(float v) {
 }
 
 // First layer from the input tile into `Yl` (+ optional global copy); returns the ReLU pattern.
-template <int MT, bool THROUGH = false>
+template <int MT, bool THROUGH = false, int NT = 2>
 __device__ inline uint64_t first_layer(const float* Xs, int xld, const float* net, const NetLayout& L,
-                                       const LayerPre<MT>& pre, float* Yl, float* Yg, int wave, int lane) {
-  Acc<MT> acc;
+                                       const LayerPre<MT, NT>& pre, float* Yl, float* Yg, int wave, int lane) {
+  Acc<MT, NT> acc;
   acc.zero();
-  gemm_xw_small<MT>(Xs, xld, L.in, net + L.w1, pre.w1, wave, lane, acc);
-  return relu_store<MT, THROUGH>(acc, pre.b1, Yl, Yg, wave, lane);
+  gemm_xw_small<MT, NT>(Xs, xld, L.in, net + L.w1, pre.w1, wave, lane, acc);
+  return relu_store<MT, THROUGH, NT>(acc, pre.b1, Yl, Yg, wave, lane);
 }
 
 // Hidden layer in place on `buf`; `stage` (LDS) and `tail` are handed to the product (see gemm256).
-template <int MT, bool THROUGH = false, bool SLABS = true, class Tail>
-__device__ inline uint64_t hidden_layer(float* buf, const float* net, const NetLayout& L, LayerPre<MT>& pre,
+template <int MT, bool THROUGH = false, bool SLABS = true, int NT = 2, class Tail>
+__device__ inline uint64_t hidden_layer(float* buf, const float* net, const NetLayout& L, LayerPre<MT, NT>& pre,
                                         float* Yg, int wave, int lane, Tail tail, float* stage) {
-  Acc<MT> acc;
+  Acc<MT, NT> acc;
   acc.zero();
-  const float bb[2] = {pre.b2[0], pre.b2[1]};
-  gemm256<MT, false, SLABS>(buf, net + L.w2, pre.w2, stage, wave, lane, acc, tail);
-  return relu_store<MT, THROUGH>(acc, bb, buf, Yg, wave, lane);
+  float bb[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) bb[nt] = pre.b2[nt];
+  gemm256<MT, false, SLABS, NT>(buf, net + L.w2, pre.w2, stage, wave, lane, acc, tail);
+  return relu_store<MT, THROUGH, NT>(acc, bb, buf, Yg, wave, lane);
 }
 
 // dX = (dZ W^T) * mask written to global [rows][256]; column sums of the result
 // (over this workgroup's rows) go to colsum_out[256].
-template <int MT, bool THROUGH = false, bool SLABS = true>
-__device__ inline void input_grad_to_global(const float* Zl, const float* W, WeightRaw<true>& w0, uint64_t mask,
+template <int MT, bool THROUGH = false, bool SLABS = true, int NT = 2>
+__device__ inline void input_grad_to_global(const float* Zl, const float* W, WeightRaw<true, NT>& w0, uint64_t mask,
                                             float* __restrict__ dXg, float* __restrict__ colsum_out, int wave,
                                             int lane, float* stage) {
-  Acc<MT> acc;
+  Acc<MT, NT> acc;
   acc.zero();
-  gemm256<MT, true, SLABS>(Zl, W, w0, stage, wave, lane, acc, NoTail());
-  float cs[2] = {0.0f, 0.0f};
-  const int col = tile_col(wave, 0, lane);
+  gemm256<MT, true, SLABS, NT>(Zl, W, w0, stage, wave, lane, acc, NoTail());
+  float cs[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) cs[nt] = 0.0f;
+  const int col = tile_col<NT>(wave, 0, lane);
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-      const float z0 = mask_bit(mask, mt, 0, v) ? acc.t[mt][0][v] : 0.0f;
-      const float z1 = mask_bit(mask, mt, 1, v) ? acc.t[mt][1][v] : 0.0f;
-      put2<THROUGH>(dXg + (32 * mt + acc_row(v, lane)) * kH + col, z0, z1);
-      cs[0] += z0;
-      cs[1] += z1;
+      float z[NT];
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        z[nt] = mask_bit<NT>(mask, mt, nt, v) ? acc.t[mt][nt][v] : 0.0f;
+        cs[nt] += z[nt];
+      }
+      put_cols<THROUGH>(dXg + (32 * mt + acc_row(v, lane)) * kH + col, z);
     }
-  const float t0 = cs[0] + __shfl_xor(cs[0], 32), t1 = cs[1] + __shfl_xor(cs[1], 32);
-  if (lane < 32) put2<THROUGH>(colsum_out + col, t0, t1);
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) cs[nt] += __shfl_xor(cs[nt], 32);
+  if (lane < 32) put_cols<THROUGH>(colsum_out + col, cs);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -241,70 +249,85 @@ __device__ inline void input_grad_to_global(const float* Zl, const float* W, Wei
 //   input_grad_to_lds, thin (thin products on the vector ALU).
 // kStageForward / kStage: floats of LDS behind a chain's vectors that its products and the split heads (head_mfma_split)
 // share as `stage` -- a chain of forward products only, any chain.
-template <int MT, bool SLABS = true>
-struct Rows32 {                                      // 32 MT rows on 32x32 tiles (mfma_tiles.h)
-  static constexpr int R = 32 * MT, kPad = 8;
-  using Pre = LayerPre<MT>;
-  using WtBlock = WeightRaw<true>;
+template <int MT, bool SLABS = true, int NT = 2>
+struct Rows32 {                                      // 32 MT rows on 32x32 tiles (mfma_tiles.h), 8 / NT wavefronts
+  static constexpr int R = 32 * MT, kPad = 8, kThr = 64 * (8 / NT);   // kThr: threads of a workgroup
+  static constexpr int kPerSimd = MT * NT == 4 ? 1 : 2;   // wavefronts of its chains on a SIMD
+  using Pre = LayerPre<MT, NT>;
+  using WtBlock = WeightRaw<true, NT>;
   static constexpr int kStage = SLABS ? 2 * slab_floats<MT>() : 0, kStageForward = kStage;
   static constexpr bool kStageOnInput = false;       // critic chains: CriticMap
   __device__ static inline void load_wt(WtBlock& wt, const float* W, int wave, int lane) { wt.load(W, 0, wave, lane); }
   __device__ static inline void load_input(float* Xl, int xld, const float* rows, int row_stride, int c0, int n, int valid,
                                            int tid) {
-    pop::load_input<R>(Xl, xld, rows, row_stride, c0, n, valid, tid);
+    pop::load_input<R, kThr>(Xl, xld, rows, row_stride, c0, n, valid, tid);
   }
   template <bool THROUGH>
   __device__ static inline uint64_t first_layer(const float* Xs, int xld, const float* net, const NetLayout& L,
                                                 const Pre& pre, float* Yl, float* Yg, int wave, int lane) {
-    return pop::first_layer<MT, THROUGH>(Xs, xld, net, L, pre, Yl, Yg, wave, lane);
+    return pop::first_layer<MT, THROUGH, NT>(Xs, xld, net, L, pre, Yl, Yg, wave, lane);
   }
   template <bool THROUGH, class Tail>
   __device__ static inline uint64_t hidden_layer(float* buf, const float* net, const NetLayout& L, Pre& pre, float* Yg,
                                                  int wave, int lane, Tail tail, float* stage) {
-    return pop::hidden_layer<MT, THROUGH, SLABS>(buf, net, L, pre, Yg, wave, lane, tail, stage);
+    return pop::hidden_layer<MT, THROUGH, SLABS, NT>(buf, net, L, pre, Yg, wave, lane, tail, stage);
   }
   template <bool THROUGH>
   __device__ static inline void input_grad_to_global(const float* Zl, const float* W, WtBlock& w0, uint64_t mask,
                                                      float* dXg, float* colsum_out, int wave, int lane, float* stage) {
-    pop::input_grad_to_global<MT, THROUGH, SLABS>(Zl, W, w0, mask, dXg, colsum_out, wave, lane, stage);
+    pop::input_grad_to_global<MT, THROUGH, SLABS, NT>(Zl, W, w0, mask, dXg, colsum_out, wave, lane, stage);
   }
   // buf <- (buf W^T) * mask in place; tail() as in gemm256
   template <class Tail>
   __device__ static inline void input_grad_to_lds(float* buf, const float* W, WtBlock& wt, uint64_t mask, int wave,
                                                   int lane, Tail tail, float* stage) {
-    Acc<MT> acc;
+    Acc<MT, NT> acc;
     acc.zero();
-    gemm256<MT, true, SLABS>(buf, W, wt, stage, wave, lane, acc, tail);
-    const int col = tile_col(wave, 0, lane);
+    gemm256<MT, true, SLABS, NT>(buf, W, wt, stage, wave, lane, acc, tail);
+    const int col = tile_col<NT>(wave, 0, lane);
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-      for (int v = 0; v < 16; ++v)
-        *reinterpret_cast<f32x2*>(&buf[(32 * mt + acc_row(v, lane)) * kLda + col]) =
-            f32x2{mask_bit(mask, mt, 0, v) ? acc.t[mt][0][v] : 0.0f, mask_bit(mask, mt, 1, v) ? acc.t[mt][1][v] : 0.0f};
+      for (int v = 0; v < 16; ++v) {
+        float z[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) z[nt] = mask_bit<NT>(mask, mt, nt, v) ? acc.t[mt][nt][v] : 0.0f;
+        store_cols(&buf[(32 * mt + acc_row(v, lane)) * kLda + col], z);
+      }
   }
   __device__ static inline void thin(const float* Xl, const float* V, int J, float* outl, int tid, int stride = kMaxAct) {
-    thin_dot<R>(Xl, V, J, outl, tid, stride);
+    thin_dot<R, kThr>(Xl, V, J, outl, tid, stride);
   }
   // buf[row][col] = mask ? rowvec[row] * colvec[col] : 0  (mask as returned by hidden_layer)
   __device__ static inline void store_outer_masked(float* buf, uint64_t mask, const float* rowvec, const float* colvec,
                                                    int wave, int lane) {
-    const int col = tile_col(wave, 0, lane);
-    const f32x2 cv = *reinterpret_cast<const f32x2*>(&colvec[col]);
+    const int col = tile_col<NT>(wave, 0, lane);
+    float cv[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) cv[nt] = colvec[col + nt];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int row = 32 * mt + acc_row(v, lane);
         const float rv = rowvec[row];
-        *reinterpret_cast<f32x2*>(&buf[row * kLda + col]) =
-            f32x2{mask_bit(mask, mt, 0, v) ? rv * cv[0] : 0.0f, mask_bit(mask, mt, 1, v) ? rv * cv[1] : 0.0f};
+        float z[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) z[nt] = mask_bit<NT>(mask, mt, nt, v) ? rv * cv[nt] : 0.0f;
+        store_cols(&buf[row * kLda + col], z);
       }
   }
 };
 
+// 64 rows on eight wavefronts of 32 columns each, two to a SIMD: a weight is still split once per 64 rows, but the vector
+// instructions of one wavefront run beside the matrix instructions of the other, and a trip to memory or to LDS outside the products
+// is waited for by half as much work per wavefront.  With four wavefronts a SIMD had one: 24 matrix and 110 vector instructions per block
+// at about five cycles of issue each left nothing to hide anything under.  us, four / eight wavefronts at 256 agents: product of 64 rows
+// 10.3 / 7.7, target chain 59 / 48, critic chain 36.4 / 30.5, actor chain 80 / 74, step 1007 / 925; SAC with 32 agents 214 / 209.
+using Rows64 = Rows32<2, true, 1>;
+
 struct Rows16 {                                      // 16 rows on v_mfma_f32_16x16x4_f32 (mfma_tiles16.h)
-  static constexpr int R = 16, kPad = 16;
+  static constexpr int R = 16, kPad = 16, kThr = kThreads, kPerSimd = 1;
   struct Pre {
     SmallW16 w1;
     WeightBlock16<false> w2;
@@ -461,6 +484,46 @@ struct Rows16Deep : Rows16 {
 
 }  // namespace
 
+// head_mfma_split for the rows of a geometry: 64 rows as two halves, one for each four of eight wavefronts
+template <class G, bool BY_ROWS>
+__device__ inline void head_split(const float* __restrict__ Xl, const float* __restrict__ W, int J, float* __restrict__ outl,
+                                  int stride, int wave, int lane, float* __restrict__ red) {
+  if constexpr (G::R <= 32) {
+    head_mfma_split<G::R, BY_ROWS>(Xl, W, J, outl, stride, wave, lane, red);
+  } else if constexpr (G::kThr == 2 * kThreads) {
+    const int h = wave & 1;
+    head_mfma_split<32, BY_ROWS>(Xl + 32 * h * kLda, W, J, outl + 32 * h * stride, stride, wave >> 1, lane, red + h * kHeadRed);
+  } else {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      head_mfma_split<32, BY_ROWS>(Xl + 32 * h * kLda, W, J, outl + 32 * h * stride, stride, wave, lane, red + h * kHeadRed);
+  }
+}
+
+// Passes with a thread per hidden unit sum a geometry's rows in two halves (16 rows: in one go), and the halves' sums are
+// added.  With four wavefronts a thread takes both halves side by side; with eight each half has 256 threads of its own (hidden
+// unit tid & 255, half tid >> 8), and the second half's sums cross over through LDS (unit_cross).
+template <class G>
+struct UnitRows {
+  static constexpr bool kCross = G::kThr == 2 * kThreads;
+  static constexpr int kHalves = G::R < 32 ? 1 : 2, kRows = G::R / kHalves;
+  static constexpr int kOwn = kCross ? 1 : kHalves;  // halves of a thread
+  __device__ static inline int row0(int own, int tid) { return kRows * (kCross ? tid >> 8 : own); }
+  // sums[q] of the halves a thread has -> those of all rows, for the threads below kH; `area`: N * kH floats of LDS that nobody
+  // else uses, with a barrier between put() and total()
+  template <int N>
+  __device__ static inline void put(const float (&sums)[kOwn][N], float* __restrict__ area, int tid) {
+    if (kCross && tid >= kH) {
+#pragma unroll
+      for (int q = 0; q < N; ++q) area[q * kH + tid - kH] = sums[0][q];
+    }
+  }
+  template <int N>
+  __device__ static inline float total(const float (&sums)[kOwn][N], const float* __restrict__ area, int tid, int q) {
+    return kCross ? sums[0][q] + area[q * kH + tid] : kHalves == 1 ? sums[0][q] : sums[0][q] + sums[kOwn - 1][q];
+  }
+};
+
 // Action dimensions beyond kMaxAct (up to kSacMaxAct): the chains are compiled a second time with scratch rows of
 // AS = kSacMaxAct floats -- a block of kSacMaxAct / kMaxAct of the map's [R][8] regions -- and kWideScratch regions.
 constexpr int kWideScratch = 3 * (kSacMaxAct / kMaxAct);
@@ -558,12 +621,12 @@ __device__ __forceinline__ void target_chain(const PopDev& d, uint32_t t, int ag
   const float* rows = batch_rows(d, t, agent) + (size_t)r0 * d.row;
   // The smoothing noise of this chunk depends on nothing the chain computes (counter RNG: agent seed, step,
   // element), so it is drawn here, while the prologue's loads are on their way, and added after the head.
-  constexpr int kNoisePerThread = (R * AS + kThreads - 1) / kThreads;
+  constexpr int kNoisePerThread = (R * AS + G::kThr - 1) / G::kThr;
   float noise[kNoisePerThread];
   auto draw_noise = [&]() {
 #pragma unroll
     for (int i = 0; i < kNoisePerThread; ++i) {
-      const int e = tid + i * kThreads;
+      const int e = tid + i * G::kThr;
       noise[i] = 0.0f;
       if (e < R * d.A) {
         const int r = e / d.A, j = e - r * d.A;
@@ -578,7 +641,7 @@ __device__ __forceinline__ void target_chain(const PopDev& d, uint32_t t, int ag
   };
   if (POP_ONE_TRIP && d.D <= kMaxIn) {               // everything the chain needs from memory before its first product: one trip
     SmallVec ab3, cw3a, cw3b;
-    InputTile<R> xin;
+    InputTile<R, G::kThr> xin;
     ab3.fetch(ta + d.actor.b3, d.A, tid);
     cw3a.fetch(tc0 + d.critic.w3, kH, tid);
     cw3b.fetch(tc1 + d.critic.w3, kH, tid);
@@ -594,9 +657,9 @@ __device__ __forceinline__ void target_chain(const PopDev& d, uint32_t t, int ag
     xin.put(Xs, L.xld, tid);
   } else {
     draw_noise();
-    stage_vector(v_ab3, ta + d.actor.b3, d.A, tid);
-    stage_vector(v_cw3, tc0 + d.critic.w3, kH, tid);
-    stage_vector(v_cw3 + kH, tc1 + d.critic.w3, kH, tid);
+    stage_vector<G::kThr>(v_ab3, ta + d.actor.b3, d.A, tid);
+    stage_vector<G::kThr>(v_cw3, tc0 + d.critic.w3, kH, tid);
+    stage_vector<G::kThr>(v_cw3 + kH, tc1 + d.critic.w3, kH, tid);
     if (tid < 2) v_cb3[tid] = (tid == 0 ? tc0 : tc1)[d.critic.b3];
     POP_MARK(30);
     G::load_input(Xs, L.xld, rows, d.row, d.D + 2, d.O, R, tid);
@@ -610,13 +673,13 @@ __device__ __forceinline__ void target_chain(const PopDev& d, uint32_t t, int ag
   G::template hidden_layer<false>(buf, ta, d.actor, pre, nullptr, wave, lane, [&]() { pre.load(tc0, d.critic, wave, lane); }, stage);
   __syncthreads();
   POP_MARK(33);
-  if (R <= 32 && (AS == kMaxAct || d.A <= 16)) head_mfma_split<R <= 32 ? R : 16, false>(buf, ta + d.actor.w3, d.A, head, AS, wave, lane, stage);
+  if (AS == kMaxAct || d.A <= 16) head_split<G, false>(buf, ta + d.actor.w3, d.A, head, AS, wave, lane, stage);
   else head_mfma<R>(buf, ta + d.actor.w3, d.A, head, AS, wave, lane);   // the head's weights straight from global memory
   __syncthreads();
   POP_MARK(34);
 #pragma unroll
   for (int i = 0; i < kNoisePerThread; ++i) {
-    const int e = tid + i * kThreads;
+    const int e = tid + i * G::kThr;
     if (e < R * d.A) {
       const int r = e / d.A, j = e - r * d.A;
       const float mu = tanhf(head[r * AS + j] + v_ab3[j]);
@@ -748,7 +811,7 @@ __device__ __forceinline__ void critic_chain(const PopDev& d, uint32_t t, int ne
   float yv = 0.0f, b3 = 0.0f;
   if (POP_ONE_TRIP && d.D <= kMaxIn) {               // one trip to memory for all of the prologue
     SmallVec w3;
-    InputTile<R> xin;
+    InputTile<R, G::kThr> xin;
     w3.fetch(cn + d.critic.w3, kH, tid);
     xin.fetch(L.xld, rows, d.row, 0, d.D, R, tid);
     if (tid < R) {
@@ -758,7 +821,7 @@ __device__ __forceinline__ void critic_chain(const PopDev& d, uint32_t t, int ne
     w3.put(v_w3, kH, tid);
     xin.put(Xs, L.xld, tid);
   } else {
-    stage_vector(v_w3, cn + d.critic.w3, kH, tid);
+    stage_vector<G::kThr>(v_w3, cn + d.critic.w3, kH, tid);
     G::load_input(Xs, L.xld, rows, d.row, 0, d.D, R, tid);
     if (tid < R) {
       if (!WAIT) yv = d.y[(size_t)agent * d.B + r0 + tid];
@@ -797,41 +860,62 @@ __device__ __forceinline__ void critic_chain(const PopDev& d, uint32_t t, int ne
     if (tid == 0) { put<SIGNAL>(part + kCP_loss, sq / (float)(d.B * d.share)); put<SIGNAL>(part + kCP_db3, sdq); }
   }
   __syncthreads();
+  using UR = UnitRows<G>;
+  const int unit = tid & (kH - 1);
+  float sums[UR::kOwn][2];                           // dW3, db2
   {                                                 // one thread per hidden unit, 8 rows at a time
-    const int c = tid;
+    const int c = unit;
     const float w3 = v_w3[c];
-    float gw3 = 0.0f, gb2 = 0.0f;
-    if (chunk == 0) put<SIGNAL>(d.cw3 + (size_t)net * kH + c, w3);
-    uint32_t active = 0u;                            // rows of the current 32 in which this unit is
-    uint32_t* mg = d.cmask + ((size_t)net * (d.B / 32) + r0 / 32) * kH + c;
+    if (chunk == 0 && tid < kH) put<SIGNAL>(d.cw3 + (size_t)net * kH + c, w3);
+    uint32_t active[UR::kOwn];                       // rows of a half in which this unit is
+#pragma unroll
+    for (int o = 0; o < UR::kOwn; ++o) { sums[o][0] = 0.0f; sums[o][1] = 0.0f; active[o] = 0u; }
+    constexpr int RB = 8 / UR::kOwn;
 #pragma unroll 1
-    for (int rb = 0; rb < R; rb += 8) {
-      float h[8], g[8];
-      uint32_t some = 0u;
+    for (int rb = 0; rb < UR::kRows; rb += RB) {
+      float h[UR::kOwn][RB], g[UR::kOwn][RB];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) { h[i] = buf[(rb + i) * kLda + c]; g[i] = dq[rb + i]; }
+      for (int o = 0; o < UR::kOwn; ++o)
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        gw3 += h[i] * g[i];
-        const float z = h[i] > 0.0f ? g[i] * w3 : 0.0f;
-        buf[(rb + i) * kLda + c] = z;
-        some |= h[i] > 0.0f ? 1u << i : 0u;
-        gb2 += z;
-      }
-      active |= some << (rb & 31);
-      if (R >= 32 && (rb & 31) == 24) {
-        put_word<SIGNAL>(mg + (rb / 32) * kH, active);
-        active = 0u;
+        for (int i = 0; i < RB; ++i) {
+          const int r = UR::row0(o, tid) + rb + i;
+          h[o][i] = buf[r * kLda + c];
+          g[o][i] = dq[r];
+        }
+#pragma unroll
+      for (int o = 0; o < UR::kOwn; ++o) {
+        uint32_t some = 0u;
+#pragma unroll
+        for (int i = 0; i < RB; ++i) {
+          sums[o][0] += h[o][i] * g[o][i];
+          const float z = h[o][i] > 0.0f ? g[o][i] * w3 : 0.0f;
+          buf[(UR::row0(o, tid) + rb + i) * kLda + c] = z;
+          some |= h[o][i] > 0.0f ? 1u << i : 0u;
+          sums[o][1] += z;
+        }
+        active[o] |= some << rb;
       }
     }
+    uint32_t* mg = d.cmask + ((size_t)net * (d.B / 32) + r0 / 32) * kH + c;
     static_assert(R >= 32 || !SIGNAL, "16-row critic chains hand nothing on inside their launch");
-    if (R == 16) reinterpret_cast<uint16_t*>(mg)[(r0 >> 4) & 1] = (uint16_t)active;
-    put<SIGNAL>(part + kCP_dW3 + c, gw3);
-    put<SIGNAL>(part + kCP_db2 + c, gb2);
+    static_assert(R == 64 || !UR::kCross, "half a pattern word to a thread");
+    if (R == 64) {
+#pragma unroll
+      for (int o = 0; o < UR::kOwn; ++o) put_word<SIGNAL>(mg + (UR::row0(o, tid) / 32) * kH, active[o]);
+    } else if (R == 32) {
+      put_word<SIGNAL>(mg, active[0] | active[UR::kOwn - 1] << 16);
+    } else {
+      reinterpret_cast<uint16_t*>(mg)[(r0 >> 4) & 1] = (uint16_t)active[0];
+    }
+    UR::put(sums, stage + G::kStage / 2, tid);       // in the second slab: the next product writes it after a barrier of its own
   }
   POP_MARK(5);
   __syncthreads();
   POP_MARK(6);
+  if (tid < kH) {
+    put<SIGNAL>(part + kCP_dW3 + tid, UR::total(sums, stage + G::kStage / 2, tid, 0));
+    put<SIGNAL>(part + kCP_db2 + tid, UR::total(sums, stage + G::kStage / 2, tid, 1));
+  }
   G::template input_grad_to_global<SIGNAL>(buf, cn + d.critic.w2, wt, mask1, d.cdZ1 + act_off, part + kCP_db1, wave, lane, stage);
   POP_MARK(7);
   if (SIGNAL) signal_count(d.done_c + parity_base(d, t, 2 * d.P) + net, tid);
@@ -869,6 +953,8 @@ __device__ __forceinline__ void actor_chain(const PopDev& d, uint32_t t, int age
   // the actor's head and the critic's first-layer rows of the action inputs are matrix-pipe operands read
   // straight from global memory (head_mfma, head_mfma_t)
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  using UR = UnitRows<G>;
+  const int unit = tid & (kH - 1);                   // hidden unit of the passes with a thread per unit
   const int r0 = chunk * R;
   const HpDev hp = d.hp[agent];
   if (t % (uint32_t)hp.policy_delay != 0u) return;
@@ -882,20 +968,20 @@ __device__ __forceinline__ void actor_chain(const PopDev& d, uint32_t t, int age
   float* part = d.apart + ((size_t)agent * (d.B / R) + chunk) * kAPart;
   float cb3 = 0.0f;
   auto stage_critic = [&]() {
-    stage_vector(v_cw3, cn + d.critic.w3, kH, tid);
+    stage_vector<G::kThr>(v_cw3, cn + d.critic.w3, kH, tid);
     cb3 = cn[d.critic.b3];
   };
   uint64_t mask_a1 = 0;
   if constexpr (AHEAD) {
     static_assert(!WAIT && AS == kMaxAct, "the forward pass ahead belongs to the separate launches of the narrow shapes");
     // one trip to memory: the critic's head, the input tile [s, a_pi] (a_pi from the forward pass ahead), h1's pattern
-    constexpr int IT = InputTile<R>::IT;
+    constexpr int IT = InputTile<R, G::kThr>::IT;
     SmallVec cw3;
     float xv[IT];
     cw3.fetch(cn + d.critic.w3, kH, tid);
     cb3 = cn[d.critic.b3];
     const float* ag = d.api + ((size_t)agent * d.B + r0) * A;
-    InputTile<R>::each(L.xld, tid, [&](int i, int r, int c) {
+    InputTile<R, G::kThr>::each(L.xld, tid, [&](int i, int r, int c) {
       const bool in = r < R && c < d.D;
       const float* p = !in ? rows : c < d.O ? rows + r * d.row + c : ag + r * A + (c - d.O);
       const float x = *p;
@@ -903,7 +989,7 @@ __device__ __forceinline__ void actor_chain(const PopDev& d, uint32_t t, int age
     });
     mask_a1 = G::mask_from_global(d.aH1 + act_off, wave, lane);
     cw3.put(v_cw3, kH, tid);
-    InputTile<R>::each(L.xld, tid, [&](int i, int r, int c) {
+    InputTile<R, G::kThr>::each(L.xld, tid, [&](int i, int r, int c) {
       if (r < R) {
         Xs[r * L.xld + c] = xv[i];
         if (c >= d.O && c < d.D) api[r * kMaxAct + (c - d.O)] = xv[i];
@@ -913,7 +999,7 @@ __device__ __forceinline__ void actor_chain(const PopDev& d, uint32_t t, int age
   } else {
   if (POP_ONE_TRIP && d.D <= kMaxIn) {               // one trip to memory for all of the prologue
     SmallVec ab3, cw3;
-    InputTile<R> xin;
+    InputTile<R, G::kThr> xin;
     ab3.fetch(an + d.actor.b3, A, tid);
     if (!WAIT) { cw3.fetch(cn + d.critic.w3, kH, tid); cb3 = cn[d.critic.b3]; }
     xin.fetch(L.xld, rows, d.row, 0, d.O, R, tid);
@@ -921,7 +1007,7 @@ __device__ __forceinline__ void actor_chain(const PopDev& d, uint32_t t, int age
     if (!WAIT) cw3.put(v_cw3, kH, tid);
     xin.put(Xs, L.xld, tid);
   } else {
-    stage_vector(v_ab3, an + d.actor.b3, A, tid);
+    stage_vector<G::kThr>(v_ab3, an + d.actor.b3, A, tid);
     if (!WAIT) stage_critic();
     G::load_input(Xs, L.xld, rows, d.row, 0, d.O, R, tid);
   }
@@ -932,10 +1018,10 @@ __device__ __forceinline__ void actor_chain(const PopDev& d, uint32_t t, int age
   G::template hidden_layer<false>(buf, an, d.actor, pre, d.aH2 + act_off, wave, lane,
                          [&]() { if (!WAIT) pre.load(cn, d.critic, wave, lane); }, stage);
   __syncthreads();
-  if (R <= 32 && (AS == kMaxAct || A <= 16)) head_mfma_split<R <= 32 ? R : 16, false>(buf, an + d.actor.w3, A, head, AS, wave, lane, stage);
+  if (AS == kMaxAct || A <= 16) head_split<G, false>(buf, an + d.actor.w3, A, head, AS, wave, lane, stage);
   else head_mfma<R>(buf, an + d.actor.w3, A, head, AS, wave, lane);
   __syncthreads();
-  for (int e = tid; e < R * A; e += kThreads) {
+  for (int e = tid; e < R * A; e += G::kThr) {
     const int r = e / A, j = e - r * A;
     const float a = tanhf(head[r * AS + j] + v_ab3[j]);
     api[r * AS + j] = a;
@@ -968,10 +1054,11 @@ __device__ __forceinline__ void actor_chain(const PopDev& d, uint32_t t, int age
     if (tid == 0) put<WAIT>(part + kAP_loss, -s / (float)d.B);
   }
   {
-    const int c = tid;
+    const int c = unit;
     const float seed = -v_cw3[c] / (float)d.B;
+    const int row0 = UR::row0(0, tid);
 #pragma unroll 1
-    for (int rb = 0; rb < R; rb += 8) {
+    for (int rb = row0; rb < row0 + UR::kRows * UR::kOwn; rb += 8) {
       float h[8];
 #pragma unroll
       for (int i = 0; i < 8; ++i) h[i] = buf[(rb + i) * kLda + c];
@@ -980,77 +1067,92 @@ __device__ __forceinline__ void actor_chain(const PopDev& d, uint32_t t, int age
     }
   }
   __syncthreads();
-  f32x4 h2r[R / 4];                                  // this thread's share of the parked h2 tile
+  constexpr int W = G::kThr / 64;                    // wavefronts
+  f32x4 h2r[R / W];                                  // this thread's share of the parked h2 tile
   {
     const float* h2g = d.aH2 + act_off;
     G::input_grad_to_lds(buf, cn + d.critic.w2, wt, mask_c1, wave, lane, [&]() {
 #pragma unroll
-      for (int i = 0; i < R / 4; ++i)
-        h2r[i] = *reinterpret_cast<const f32x4*>(h2g + (4 * i + (tid >> 6)) * kH + 4 * (tid & 63));
+      for (int i = 0; i < R / W; ++i)
+        h2r[i] = *reinterpret_cast<const f32x4*>(h2g + (W * i + (tid >> 6)) * kH + 4 * (tid & 63));
     }, stage);                                       // buf = dz1 of the critic
   }
   __syncthreads();
   POP_MARK(12);
-  if (R <= 32 && (AS == kMaxAct || A <= 16)) head_mfma_split<R <= 32 ? R : 16, true>(buf, cn + d.critic.w1 + d.O * kH, A, head, AS, wave, lane, stage);   // da
+  if (AS == kMaxAct || A <= 16) head_split<G, true>(buf, cn + d.critic.w1 + d.O * kH, A, head, AS, wave, lane, stage);   // da
   else head_mfma_t<R>(buf, cn + d.critic.w1 + d.O * kH, A, head, AS, wave, lane);
   G::load_wt(wt, an + d.actor.w2, wave, lane);       // block 0 of the actor's input-gradient product
   __syncthreads();
-  for (int e = tid; e < R * AS; e += kThreads) {
+  for (int e = tid; e < R * AS; e += G::kThr) {
     const int j = e % AS;
     const float a = j < A ? api[e] : 0.0f;
     dz3[e] = j < A ? head[e] * (1.0f - a * a) : 0.0f;     // unused columns are kept at zero
   }
 #pragma unroll
-  for (int i = 0; i < R / 4; ++i)                    // h2 of the actor back into the tile
-    *reinterpret_cast<f32x4*>(&buf[(4 * i + (tid >> 6)) * kLda + 4 * (tid & 63)]) = h2r[i];
+  for (int i = 0; i < R / W; ++i)                    // h2 of the actor back into the tile
+    *reinterpret_cast<f32x4*>(&buf[(W * i + (tid >> 6)) * kLda + 4 * (tid & 63)]) = h2r[i];
   __syncthreads();
   if (tid < A) {
     float s = 0.0f;
     for (int r = 0; r < R; ++r) s += dz3[r * AS + tid];
     put<WAIT>(part + kAP_db3 + tid, s);
   }
-  {                                                  // actor head backward, one thread per hidden unit
-    const int c = tid;
-    constexpr int RB = AS == kMaxAct ? 4 : 2;        // rows in flight (the wide rows cost three times the registers)
-    float w3[AS], gw3[AS];
+  float sums[UR::kOwn][AS + 1];                      // dW3 by column, db2
+  {                                                 // actor head backward, one thread per hidden unit
+    const int c = unit;
+    constexpr int RB = (AS == kMaxAct ? 4 : 2) / UR::kOwn;   // rows of a half in flight (the wide rows cost three times the registers)
+    float w3[AS];
 #pragma unroll
-    for (int j = 0; j < AS; ++j) { w3[j] = (an + d.actor.w3)[c * A + (j < A ? j : 0)]; gw3[j] = 0.0f; }
+    for (int j = 0; j < AS; ++j) w3[j] = (an + d.actor.w3)[c * A + (j < A ? j : 0)];
 #pragma unroll
     for (int j = 0; j < AS; ++j) w3[j] = j < A ? w3[j] : 0.0f;
-    float gb2 = 0.0f;
+#pragma unroll
+    for (int o = 0; o < UR::kOwn; ++o)
+#pragma unroll
+      for (int j = 0; j <= AS; ++j) sums[o][j] = 0.0f;
     float* zg = d.adZ2 + act_off + c;
 #pragma unroll 1
-    for (int rb = 0; rb < R; rb += RB) {
-      float h[RB];
-      f32x4 g[RB][AS / 4];
+    for (int rb = 0; rb < UR::kRows; rb += RB) {
+      float h[UR::kOwn][RB];
+      f32x4 g[UR::kOwn][RB][AS / 4];
 #pragma unroll
-      for (int i = 0; i < RB; ++i) {
-        h[i] = buf[(rb + i) * kLda + c];
+      for (int o = 0; o < UR::kOwn; ++o)
 #pragma unroll
-        for (int q = 0; q < AS / 4; ++q) g[i][q] = *reinterpret_cast<const f32x4*>(&dz3[(rb + i) * AS + 4 * q]);   // columns >= A hold zeros
-      }
+        for (int i = 0; i < RB; ++i) {
+          const int r = UR::row0(o, tid) + rb + i;
+          h[o][i] = buf[r * kLda + c];
 #pragma unroll
-      for (int i = 0; i < RB; ++i) {
-        float dh = 0.0f;
-#pragma unroll
-        for (int j = 0; j < AS; ++j) {
-          const float gj = g[i][j >> 2][j & 3];
-          gw3[j] += h[i] * gj;
-          dh += gj * w3[j];
+          for (int q = 0; q < AS / 4; ++q) g[o][i][q] = *reinterpret_cast<const f32x4*>(&dz3[r * AS + 4 * q]);   // columns >= A hold zeros
         }
-        const float z = h[i] > 0.0f ? dh : 0.0f;
-        buf[(rb + i) * kLda + c] = z;
-        put<WAIT>(zg + (rb + i) * kH, z);
-        gb2 += z;
-      }
-    }
 #pragma unroll
-    for (int j = 0; j < AS; ++j)
-      if (j < A) put<WAIT>(part + kAP_dW3 + j * kH + c, gw3[j]);
-    put<WAIT>(part + kAP_db2 + c, gb2);
+      for (int o = 0; o < UR::kOwn; ++o)
+#pragma unroll
+        for (int i = 0; i < RB; ++i) {
+          const int r = UR::row0(o, tid) + rb + i;
+          float dh = 0.0f;
+#pragma unroll
+          for (int j = 0; j < AS; ++j) {
+            const float gj = g[o][i][j >> 2][j & 3];
+            sums[o][j] += h[o][i] * gj;
+            dh += gj * w3[j];
+          }
+          const float z = h[o][i] > 0.0f ? dh : 0.0f;
+          buf[r * kLda + c] = z;
+          put<WAIT>(zg + r * kH, z);
+          sums[o][AS] += z;
+        }
+    }
+    static_assert(!UR::kCross || (AS + 1) * kH <= G::kStage / 2, "fits the slab");
+    UR::put(sums, stage + G::kStage / 2, tid);       // as in critic_chain
   }
   __syncthreads();
   POP_MARK(13);
+  if (tid < kH) {
+#pragma unroll
+    for (int j = 0; j < AS; ++j)
+      if (j < A) put<WAIT>(part + kAP_dW3 + j * kH + tid, UR::total(sums, stage + G::kStage / 2, tid, j));
+    put<WAIT>(part + kAP_db2 + tid, UR::total(sums, stage + G::kStage / 2, tid, AS));
+  }
   G::template input_grad_to_global<WAIT>(buf, an + d.actor.w2, wt, mask_a1, d.adZ1 + act_off, part + kAP_db1, wave, lane, stage);
   POP_MARK(14);
   if (WAIT) signal_count(d.done_a + parity_base(d, t, d.P) + agent, tid);

@@ -7,9 +7,9 @@
 
 namespace pop {
 
-// PER_CU: workgroups that share a CU (registers to match).
-template <class G, int PER_CU = G::R == 32 ? 2 : 1, int AS = kMaxAct>
-__global__ __launch_bounds__(kThreads, PER_CU) void k_target(PopDev d, uint32_t t) {
+// PER_CU: wavefronts that share a SIMD (registers to match), i.e. workgroups per CU where they have four.
+template <class G, int PER_CU = G::kPerSimd, int AS = kMaxAct>
+__global__ __launch_bounds__(G::kThr, PER_CU) void k_target(PopDev d, uint32_t t) {
   extern __shared__ float lds[];
   int agent, chunk;
   POP_BLOCK_TIME(kTraceTarget, 0);
@@ -18,7 +18,7 @@ __global__ __launch_bounds__(kThreads, PER_CU) void k_target(PopDev d, uint32_t 
 }
 
 template <class G>
-__global__ __launch_bounds__(kThreads, G::R == 32 ? 2 : 1) void k_critic(PopDev d, uint32_t t) {
+__global__ __launch_bounds__(G::kThr, G::kPerSimd) void k_critic(PopDev d, uint32_t t) {
   extern __shared__ float lds[];
   int net, chunk;
   POP_BLOCK_TIME(kTraceCritic, 0);
@@ -33,7 +33,8 @@ __global__ __launch_bounds__(kThreads, G::R == 32 ? 2 : 1) void k_critic(PopDev 
 // workgroup waits for has already been dispatched and the wait always ends.
 // GT, GC: tile geometries of the two chains.  AHEAD: critic_chain's.
 template <class GT, class GC, bool AHEAD = false>
-__global__ __launch_bounds__(kThreads, GT::R == 32 && GC::R == 32 ? 2 : 1) void k_target_critic(PopDev d, uint32_t t, int target_blocks) {
+__global__ __launch_bounds__(GT::kThr, GT::kPerSimd < GC::kPerSimd ? GT::kPerSimd : GC::kPerSimd) void k_target_critic(PopDev d, uint32_t t, int target_blocks) {
+  static_assert(GT::kThr == GC::kThr, "one workgroup size");
   extern __shared__ float lds[];
   int unit, chunk;
   POP_BLOCK_TIME(kTraceTargetCritic, 0);
@@ -65,9 +66,9 @@ __global__ __launch_bounds__(kThreads, 1) void k_target_critic1(PopDev d, uint32
   POP_BLOCK_TIME(kTraceTargetCritic, 1);
 }
 
-// PER_CU: workgroups per CU the register budget is set for; AHEAD, AS: actor_chain's
-template <class G, int PER_CU = 1, bool AHEAD = false, int AS = kMaxAct>
-__global__ __launch_bounds__(kThreads, PER_CU) void k_actor(PopDev d, uint32_t t) {
+// PER_CU: wavefronts per SIMD the register budget is set for; AHEAD, AS: actor_chain's
+template <class G, int PER_CU = G::kThr / kThreads, bool AHEAD = false, int AS = kMaxAct>
+__global__ __launch_bounds__(G::kThr, PER_CU) void k_actor(PopDev d, uint32_t t) {
   extern __shared__ float lds[];
   int agent, chunk;
   POP_BLOCK_TIME(kTraceActor, 0);
@@ -156,14 +157,14 @@ hipError_t setup_kernels() {
   POP_SET_LDS(k_actor<Rows32Deep<1>>);
   POP_SET_LDS(k_target<Rows16>);
   POP_SET_LDS(k_target<Rows32<1>>);
-  POP_SET_LDS(k_target<Rows32<2>>);
+  POP_SET_LDS(k_target<Rows64>);
   POP_SET_LDS(k_critic<Rows32<1>>);
-  POP_SET_LDS(k_critic<Rows32<2>>);
+  POP_SET_LDS(k_critic<Rows64>);
   POP_SET_LDS(k_critic<Rows32Deep<1, 4>>);
   POP_SET_LDS(k_actor<Rows16>);
   POP_SET_LDS(k_actor<Rows32<1>>);
   POP_SET_LDS(k_actor<Rows32<1>, 2>);
-  POP_SET_LDS(k_actor<Rows32<2>>);
+  POP_SET_LDS(k_actor<Rows64>);
   POP_SET_LDS(k_target_critic<Rows16, Rows32<2>>);
   POP_SET_LDS(k_target_critic<Rows16, Rows32<1>>);
   POP_SET_LDS(k_target_critic1<Rows32<1>>);
@@ -172,7 +173,7 @@ hipError_t setup_kernels() {
   POP_SET_LDS(k_target_critic<Rows16, Rows32<1>, true>);
   POP_SET_LDS(k_actor<Rows16, 1, true>);
   POP_SET_LDS(k_target_critic<Rows32<1>, Rows32<1>>);
-  POP_SET_LDS(k_target_critic<Rows32<2>, Rows32<2>>);
+  POP_SET_LDS(k_target_critic<Rows64, Rows64>);
   POP_SET_LDS(k_act);
 #undef POP_SET_LDS
   return hipSuccess;
@@ -209,7 +210,7 @@ hipError_t launch_target(const PopDev& d, uint32_t t, hipStream_t s) {
     else return hipErrorInvalidValue;
   } else if (d.rows_t == 16) k_target<Rows16><<<grid, block, chain_bytes<Rows16>(d.D, vec_target(d), Rows16::kStageForward), s>>>(d, t);
   else if (d.rows_t == 32) k_target<Rows32<1>><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec_target(d)), s>>>(d, t);
-  else k_target<Rows32<2>><<<grid, block, chain_bytes<Rows32<2>>(d.D, vec_target(d)), s>>>(d, t);
+  else k_target<Rows64><<<grid, dim3(Rows64::kThr), chain_bytes<Rows32<2>>(d.D, vec_target(d)), s>>>(d, t);
   return hipGetLastError();
 }
 hipError_t launch_critic(const PopDev& d, uint32_t t, hipStream_t s) {
@@ -218,7 +219,7 @@ hipError_t launch_critic(const PopDev& d, uint32_t t, hipStream_t s) {
     if (d.rows_c != 32) return hipErrorInvalidValue;
     k_critic<Rows32Deep<1, 4>><<<grid, block, CriticMap<Rows32Deep<1, 4>>(d.D).bytes(), s>>>(d, t);
   } else if (d.rows_c == 32) k_critic<Rows32<1>><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec_critic(d)), s>>>(d, t);
-  else k_critic<Rows32<2>><<<grid, block, chain_bytes<Rows32<2>>(d.D, vec_critic(d)), s>>>(d, t);
+  else k_critic<Rows64><<<grid, dim3(Rows64::kThr), chain_bytes<Rows32<2>>(d.D, vec_critic(d)), s>>>(d, t);
   return hipGetLastError();
 }
 hipError_t launch_target_critic(const PopDev& d, uint32_t t, hipStream_t s) {
@@ -251,7 +252,7 @@ hipError_t launch_target_critic(const PopDev& d, uint32_t t, hipStream_t s) {
   } else if (d.rows_t == 32) {
     k_target_critic<Rows32<1>, Rows32<1>><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec), s>>>(d, t, nt);
   } else {
-    k_target_critic<Rows32<2>, Rows32<2>><<<grid, block, chain_bytes<Rows32<2>>(d.D, vec), s>>>(d, t, nt);
+    k_target_critic<Rows64, Rows64><<<grid, dim3(Rows64::kThr), chain_bytes<Rows32<2>>(d.D, vec), s>>>(d, t, nt);
   }
   return hipGetLastError();
 }
@@ -273,7 +274,7 @@ hipError_t launch_actor(const PopDev& d, uint32_t t, hipStream_t s) {
   } else if (d.rows_a == 16) k_actor<Rows16><<<grid, block, chain_bytes<Rows16>(d.D, vec_actor(d)), s>>>(d, t);
   else if (d.rows_a == 32 && (int)grid.x > kCUs) k_actor<Rows32<1>, 2><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec_actor(d)), s>>>(d, t);
   else if (d.rows_a == 32) k_actor<Rows32<1>><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec_actor(d)), s>>>(d, t);
-  else k_actor<Rows32<2>><<<grid, block, chain_bytes<Rows32<2>>(d.D, vec_actor(d)), s>>>(d, t);
+  else k_actor<Rows64><<<grid, dim3(Rows64::kThr), chain_bytes<Rows32<2>>(d.D, vec_actor(d)), s>>>(d, t);
   return hipGetLastError();
 }
 hipError_t launch_act(const PopDev& d, const float* obs, int n, float* act, const float* sigma, uint32_t step,

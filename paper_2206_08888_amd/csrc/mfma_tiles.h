@@ -11,7 +11,7 @@
 //   B: lane l supplies B[k = l >> 5][col = l & 31]
 //   D: register v of lane l is D[row = 8 (v >> 2) + 4 (l >> 5) + (v & 3)][col = l & 31]
 //
-// A workgroup is 4 wavefronts; for a [R x 256] output each wavefront owns the
+// A workgroup is 4 wavefronts (8 where NT = 1, below); for a [R x 256] output each wavefront owns the
 // 64 columns [64 wave, 64 wave + 64) for all R = 32 MT rows, i.e. MT x 2 tiles.
 // Tile nt holds the columns of parity nt: lane l has columns 64 wave + 2 (l & 31) + nt
 // (tile_col), two neighbours, which it loads and stores as one 8-byte access.
@@ -126,14 +126,31 @@ __device__ inline void put2(float* p, float a, float b) {
   }
 }
 
+// a lane's NT neighbouring columns
+__device__ inline void store_cols(float* p, const float (&h)[2]) { *reinterpret_cast<f32x2*>(p) = f32x2{h[0], h[1]}; }
+__device__ inline void store_cols(float* p, const float (&h)[1]) { *p = h[0]; }
+template <bool THROUGH>
+__device__ inline void put_cols(float* p, const float (&h)[2]) { put2<THROUGH>(p, h[0], h[1]); }
+template <bool THROUGH>
+__device__ inline void put_cols(float* p, const float (&h)[1]) { put<THROUGH>(p, h[0]); }
+
 __device__ inline int acc_row(int v, int lane) { return 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); }
 // Column (of 256) that a lane holds of tile nt of its wavefront's two accumulator tiles: the lane's two columns
 // are neighbours, so that a forward product fetches both weights of a row with one 8-byte load (half the load
 // instructions, which is what the forward products were short of).
-__device__ inline int tile_col(int wave, int nt, int lane) { return 64 * wave + 2 * (lane & 31) + nt; }
+// NT = 1 (eight wavefronts of 32 columns): neighbouring lanes hold neighbouring columns.
+template <int NT = 2>
+__device__ inline int tile_col(int wave, int nt, int lane) {
+  return NT == 2 ? 64 * wave + 2 * (lane & 31) + nt : 32 * wave + (lane & 31);
+}
+// a lane's values of its NT columns (neighbours) as one access
+template <int NT> struct ColsOf { typedef f32x2 T; };
+template <> struct ColsOf<1> { typedef float T; };
+__device__ inline float col_of(const f32x2& v, int nt) { return v[nt]; }
+__device__ inline float col_of(float v, int) { return v; }
 
-// NT = 32-column tiles per wavefront: 2 in the layer chains (a workgroup spans 256
-// columns), 1 in the weight-gradient tiles (128 columns per workgroup).
+// NT = 32-column tiles per wavefront: 2 in layer chains of four wavefronts, 1 in those of eight (a workgroup spans 256
+// columns) and in the weight-gradient tiles (128 columns per workgroup).
 template <int MT, int NT = 2>
 struct Acc {
   f32x16 t[MT][NT];
@@ -171,23 +188,29 @@ __device__ inline WeightsRsrc weights_rsrc(const float* W, int n) {
 __device__ inline f32x2 rsrc_load2(WeightsRsrc r, uint32_t lane_bytes, int floats) {
   return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(r, lane_bytes, 4 * floats, 0));
 }
+template <int NT>
+__device__ inline typename ColsOf<NT>::T rsrc_load_cols(WeightsRsrc r, uint32_t lane_bytes, int floats) {
+  if constexpr (NT == 2) return rsrc_load2(r, lane_bytes, floats);
+  else return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, lane_bytes, 4 * floats, 0));
+}
 __device__ inline f32x4 rsrc_load4(WeightsRsrc r, uint32_t lane_bytes, int floats) {
   return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, lane_bytes, 4 * floats, 0));
 }
 
 // First-layer weights of one lane for the leading 32 rows of W (k = 8 i + 4 half + j),
 // fetched ahead of time so that the product does not wait for memory; rows at or beyond K are zero.
+template <int NT = 2>
 struct SmallW {
-  float w[4][2][4];
+  float w[4][NT][4];
   __device__ inline void load(const float* __restrict__ W, int K, int wave, int lane) {
-    const uint32_t off = 4u * (uint32_t)(4 * (lane >> 5) * kH + tile_col(wave, 0, lane));
+    const uint32_t off = 4u * (uint32_t)(4 * (lane >> 5) * kH + tile_col<NT>(wave, 0, lane));
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const f32x2 v = rsrc_load2(weights_rsrc(W + 8 * i * kH, (K - 8 * i) * kH), off + 4 * j * kH, 0);
-        w[i][0][j] = v[0];
-        w[i][1][j] = v[1];
+        const auto v = rsrc_load_cols<NT>(weights_rsrc(W + 8 * i * kH, (K - 8 * i) * kH), off + 4 * j * kH, 0);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) w[i][nt][j] = col_of(v, nt);
       }
   }
 };
@@ -196,9 +219,9 @@ struct SmallW {
 //   X: LDS, row stride ldx, rows [0, 32 MT); columns >= K up to the next
 //      multiple of 8 must hold finite values (they meet zero weights);
 //   W: global, row-major [K][256]; `pre` holds its first 32 rows already.
-template <int MT>
+template <int MT, int NT>
 __device__ inline void gemm_xw_small(const float* __restrict__ Xl, int ldx, int K, const float* __restrict__ W,
-                                     const SmallW& pre, int wave, int lane, Acc<MT>& acc) {
+                                     const SmallW<NT>& pre, int wave, int lane, Acc<MT, NT>& acc) {
   const int half = lane >> 5, l32 = lane & 31;
   const int K8 = (K + 7) & ~7;
 #pragma unroll
@@ -213,18 +236,18 @@ __device__ inline void gemm_xw_small(const float* __restrict__ Xl, int ldx, int 
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-          for (int nt = 0; nt < 2; ++nt) acc.t[mt][nt] = mfma32(a[mt][j], pre.w[i][nt][j], acc.t[mt][nt]);
+          for (int nt = 0; nt < NT; ++nt) acc.t[mt][nt] = mfma32(a[mt][j], pre.w[i][nt][j], acc.t[mt][nt]);
     }
   }
-  const float* wcol = W + tile_col(wave, 0, l32);
+  const float* wcol = W + tile_col<NT>(wave, 0, l32);
   for (int k0 = 32; k0 < K8; k0 += 8) {              // fan-in beyond 32: plain loop
-    float b[2][4];
+    float b[NT][4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int k = k0 + 4 * half + j;
-      const f32x2 v = *reinterpret_cast<const f32x2*>(wcol + (size_t)(k < K ? k : 0) * kH);
+      const auto v = *reinterpret_cast<const typename ColsOf<NT>::T*>(wcol + (size_t)(k < K ? k : 0) * kH);
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt) b[nt][j] = k < K ? v[nt] : 0.0f;
+      for (int nt = 0; nt < NT; ++nt) b[nt][j] = k < K ? col_of(v, nt) : 0.0f;
     }
     f32x4 a[MT];
 #pragma unroll
@@ -235,7 +258,7 @@ __device__ inline void gemm_xw_small(const float* __restrict__ Xl, int ldx, int 
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) acc.t[mt][nt] = mfma32(a[mt][j], b[nt][j], acc.t[mt][nt]);
+        for (int nt = 0; nt < NT; ++nt) acc.t[mt][nt] = mfma32(a[mt][j], b[nt][j], acc.t[mt][nt]);
   }
 }
 
@@ -251,7 +274,7 @@ __device__ inline void gemm_xw_small(const float* __restrict__ Xl, int ldx, int 
 // row reads its last four columns instead, where the weights are zero.
 template <int MT, int PF>
 __device__ inline void gemm_xw_deep(const float* __restrict__ Xl, int ldx, int K, const float* __restrict__ W,
-                                    const SmallW& pre, int wave, int lane, Acc<MT>& acc) {
+                                    const SmallW<2>& pre, int wave, int lane, Acc<MT>& acc) {
   const int half = lane >> 5, l32 = lane & 31;
   const int nb = (K + 15) >> 4;
   uint32_t off = 4u * (uint32_t)(4 * half * kH + tile_col(wave, 0, lane));
@@ -479,10 +502,10 @@ struct NoTail { __device__ inline void operator()() const {} };
 
 // The weights one lane needs for a 16-deep block i = 2 D + o: contraction indices 32 D + 16 half + 8 o + e, e < 8.  Two
 // blocks cover whole 128-byte lines of the transposed operand (a lane reads 64 bytes of one row of W).
-template <bool TRANSPOSED>
+template <bool TRANSPOSED, int NT = 2>
 struct WeightRaw {
-  float w[2][8];                           // [column tile][e]
-  static constexpr int kPieces = TRANSPOSED ? 4 : 8;           // load instructions per block
+  float w[NT][8];                           // [column tile][e]
+  static constexpr int kPieces = TRANSPOSED ? 2 * NT : 8;           // load instructions per block
   static constexpr int kGroup = TRANSPOSED ? w2_index(0, 64) : w2_index(64, 0);   // floats from one group of four blocks to the next
   __device__ static constexpr int offset(int i) {
     const int at = 32 * (i >> 1) + 8 * (i & 1);
@@ -490,19 +513,19 @@ struct WeightRaw {
   }
   __device__ static inline WeightsRsrc rsrc(const float* W) { return weights_rsrc(W, kH * kH); }
   __device__ static inline uint32_t lane_bytes(int wave, int lane) {
-    const int half = lane >> 5, col = tile_col(wave, 0, lane);
+    const int half = lane >> 5, col = tile_col<NT>(wave, 0, lane);
     return 4u * (uint32_t)(TRANSPOSED ? w2_index(col, 16 * half) : w2_index(16 * half, col));
   }
   __device__ inline void load_piece(WeightsRsrc W, uint32_t lane_off, int blk, int p) {
     if (TRANSPOSED) {
-      const int nt = p >> 1, s = p & 1;              // the lane's two columns are neighbouring rows of W, the first one even
+      const int nt = p >> 1, s = p & 1;              // two columns are neighbouring rows of W, the first one even
       const f32x4 v = rsrc_load4(W, lane_off + 4 * w2_index(nt, 4 * s), blk);
 #pragma unroll
       for (int j = 0; j < 4; ++j) w[nt][4 * s + j] = v[j];
     } else {
-      const f32x2 v = rsrc_load2(W, lane_off + 4 * w2_index(p & 3, 0), blk + w2_index(p & ~3, 0));
-      w[0][p] = v[0];
-      w[1][p] = v[1];
+      const auto v = rsrc_load_cols<NT>(W, lane_off + 4 * w2_index(p & 3, 0), blk + w2_index(p & ~3, 0));
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) w[nt][p] = col_of(v, nt);
     }
   }
   __device__ inline void load_block(WeightsRsrc W, uint32_t lane_off, int blk) {
@@ -519,9 +542,10 @@ struct WeightRaw {
 constexpr int kSlabLd = 72;
 template <int MT>
 constexpr int slab_floats() { return 3 * 32 * MT * kSlabLd / 2; }
-template <int MT>
-struct SlabItem {                          // this thread's share of a slab: MT times eight neighbours of a row
-  f32x4 x[MT][2];
+template <int MT, int NT>
+struct SlabItem {                          // this thread's share of a slab: Q times eight neighbours of a row
+  static constexpr int Q = MT * NT / 2;
+  f32x4 x[Q][2];
   __device__ inline void read(const float* __restrict__ Xl, int s, int tid, int q) {
     const float* p = Xl + (32 * q + (tid >> 3)) * kLda + 64 * s + 8 * (tid & 7);
     x[q][0] = *reinterpret_cast<const f32x4*>(p);
@@ -538,12 +562,13 @@ struct SlabItem {                          // this thread's share of a slab: MT 
 
 // SLABS: as above; otherwise every wavefront splits the LDS operand itself, for chains whose scratch leaves no room for
 // the slabs (SAC with 64 rows).
-template <int MT, bool TRANSPOSED, bool SLABS>
+template <int MT, bool TRANSPOSED, bool SLABS, int NT>
 struct SplitProduct {
-  using Raw = WeightRaw<TRANSPOSED>;
-  Split8 x[2][MT], w[2];                   // the LDS operand of this block and the next, the weights of the two column tiles
-  SlabItem<MT> item;
-  Acc<MT, 2> low;
+  using Raw = WeightRaw<TRANSPOSED, NT>;
+  static_assert(NT == 2 || (SLABS && MT == 2), "eight wavefronts: 64 rows");
+  Split8 x[2][MT], w[2];                   // the LDS operand of this block and the next, the weights of the two column tiles (NT = 1: of this block and the next)
+  SlabItem<MT, NT> item;
+  Acc<MT, NT> low;
   f32x4 xr[SLABS ? 1 : MT][2];             // the LDS operand as read, where there are no slabs
 
   // block b of the slab in this lane's layout
@@ -566,13 +591,13 @@ struct SplitProduct {
 #pragma unroll
     for (int mt = 0; mt < (SLABS ? 0 : MT); ++mt) split8(xr[mt][0], xr[mt][1], dst[mt]);
   }
-  __device__ inline void multiply(const Split8 (&xc)[MT], int nt, Acc<MT, 2>& acc) {
+  __device__ inline void multiply(const Split8 (&xc)[MT], const Split8& wc, int nt, Acc<MT, NT>& acc) {
 #pragma unroll
     for (int q = 0; q < kSplitTerms; ++q)
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
         f32x16& c = q == kSplitTerms - 1 ? acc.t[mt][nt] : low.t[mt][nt];
-        c = mfma32_bf16(xc[mt].t[kTermX[q]], w[nt].t[kTermW[q]], c);
+        c = mfma32_bf16(xc[mt].t[kTermX[q]], wc.t[kTermW[q]], c);
       }
   }
   // One block B (0 .. 3) of a group: the matrix instructions of column tile 0 with, dealt out between them, the split
@@ -581,21 +606,38 @@ struct SplitProduct {
   // split and written in blocks 1 and 2.  FEED: the weights four blocks on go into the registers of this
   // block -- transposed: of this and the block before, in odd blocks, so that both halves of a line are asked for together.
   template <int B, bool NEXT, bool SLAB, bool FEED>
-  __device__ inline void block(Acc<MT, 2>& acc, Raw& wp, Raw& wc, const Raw& wn, WeightsRsrc W, uint32_t lane_off, int wg,
+  __device__ inline void block(Acc<MT, NT>& acc, Raw& wp, Raw& wc, const Raw& wn, WeightsRsrc W, uint32_t lane_off, int wg,
                                const float* __restrict__ xs, const float* __restrict__ Xl, int s, float* __restrict__ nslab,
                                int tid, int lane) {
     constexpr int M = kSplitTerms * MT, CUR = B & 1;
-    constexpr bool stage = SLABS && SLAB, put = stage && B >= 1 && B <= MT;
+    constexpr bool stage = SLABS && SLAB, put = stage && B >= 1 && B <= SlabItem<MT, NT>::Q;
+    constexpr int loads1 = !FEED ? 0 : TRANSPOSED ? (B & 1 ? 4 : 0) : 8;
     constexpr int loads = !FEED ? 0 : TRANSPOSED ? (B & 1 ? 8 : 0) : 8;
     asm("" : "+v"(lane_off));                         // or the constants added to it are hoisted into registers of their own
+    if constexpr (NT == 1) {                          // one tile: all of it beside the matrix instructions of the block
+      if (NEXT) { read_x(x[CUR ^ 1], xs, (B + 1) & 3, lane); split8(wn.w[0], w[CUR ^ 1]); }
+      if (stage && B == 0) item.read(Xl, s + 1, tid, 0);
+      if (put) item.put(nslab, tid, 0);
+      if (FEED && TRANSPOSED && (B & 1)) { wp.load_block(W, lane_off, wg + Raw::offset(B + 3)); wc.load_block(W, lane_off, wg + Raw::offset(B + 4)); }
+      if (FEED && !TRANSPOSED) wc.load_block(W, lane_off, wg + Raw::offset(B + 4));
+      multiply(x[CUR], w[CUR], 0, acc);
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        if (NEXT) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        if (loads1 * m < 8 * M && loads1) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, ((NEXT ? 44 : 0) + (put ? 44 : 0) + M - 1) / M + 1, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    } else {
     split8(wc.w[1], w[1]);
     if (NEXT && SLABS) read_x(x[CUR ^ 1], xs, (B + 1) & 3, lane);
     if (NEXT && !SLABS) read_raw(Xl, 4 * s + B + 1, lane);
     if (stage && B == 0) {
 #pragma unroll
-      for (int q = 0; q < MT; ++q) item.read(Xl, s + 1, tid, q);
+      for (int q = 0; q < SlabItem<MT, NT>::Q; ++q) item.read(Xl, s + 1, tid, q);
     }
-    multiply(x[CUR], 0, acc);
+    multiply(x[CUR], w[0], 0, acc);
 #pragma unroll
     for (int m = 0; m < M; ++m) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -608,7 +650,7 @@ struct SplitProduct {
     if (put) item.put(nslab, tid, B - 1);
     if (FEED && TRANSPOSED && (B & 1)) { wp.load_block(W, lane_off, wg + Raw::offset(B + 3)); wc.load_block(W, lane_off, wg + Raw::offset(B + 4)); }
     if (FEED && !TRANSPOSED) wc.load_block(W, lane_off, wg + Raw::offset(B + 4));
-    multiply(x[CUR], 1, acc);
+    multiply(x[CUR], w[1], 1, acc);
 #pragma unroll
     for (int m = 0; m < M; ++m) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -616,11 +658,12 @@ struct SplitProduct {
       __builtin_amdgcn_sched_group_barrier(0x002, ((NEXT ? (SLABS ? 44 : 44 + 44 * MT) : 0) + (put ? 44 : 0) + M - 1) / M + 1, 0);
     }
     __builtin_amdgcn_sched_barrier(0);
+    }
   }
   // Four blocks, slab s.  The barrier that completes the next slab stands before the last block, whose operand is in
   // registers by then: the first operand of the next slab arrives under it.
   template <bool LAST, class Tail>
-  __device__ inline void group(Acc<MT, 2>& acc, Raw& b0, Raw& b1, Raw& b2, Raw& b3, WeightsRsrc W, uint32_t lane_off, int wg,
+  __device__ inline void group(Acc<MT, NT>& acc, Raw& b0, Raw& b1, Raw& b2, Raw& b3, WeightsRsrc W, uint32_t lane_off, int wg,
                                const float* __restrict__ Xl, int s, float* __restrict__ cur, float* __restrict__ nxt, int tid, int lane, Tail& tail) {
     block<0, true, !LAST, !LAST>(acc, b3, b0, b1, W, lane_off, wg, cur, Xl, s, nxt, tid, lane);
     block<1, true, !LAST, !LAST>(acc, b0, b1, b2, W, lane_off, wg, cur, Xl, s, nxt, tid, lane);
@@ -635,14 +678,14 @@ struct SplitProduct {
   // has read the tile when any returns.
   template <class Tail>
   __device__ inline void run(const float* __restrict__ Xl, const float* __restrict__ W, Raw& b0, float* __restrict__ slabs, int wave, int lane,
-                             Acc<MT, 2>& acc, Tail& tail) {
+                             Acc<MT, NT>& acc, Tail& tail) {
     const int tid = 64 * wave + lane;
     float* s0 = slabs;
     float* s1 = slabs + slab_floats<MT>();
     Raw b1, b2, b3;
     if (SLABS) {
 #pragma unroll
-      for (int q = 0; q < MT; ++q) item.read(Xl, 0, tid, q);
+      for (int q = 0; q < SlabItem<MT, NT>::Q; ++q) item.read(Xl, 0, tid, q);
     } else {
       read_raw(Xl, 0, lane);
     }
@@ -656,7 +699,7 @@ struct SplitProduct {
     int wg = 0;                                      // floats to the group
     if (SLABS) {
 #pragma unroll
-      for (int q = 0; q < MT; ++q) item.put(s0, tid, q);
+      for (int q = 0; q < SlabItem<MT, NT>::Q; ++q) item.put(s0, tid, q);
       __syncthreads();
       read_x(x[0], s0, 0, lane);
     } else {
@@ -664,11 +707,19 @@ struct SplitProduct {
     }
     split8(b0.w[0], w[0]);
     __builtin_amdgcn_sched_barrier(0);
-#pragma unroll 1
-    for (int s = 0; s < 3; ++s) {
+    // (Left as a loop, the compiler moves the head of the last group into it for eight wavefronts' forward products and copies
+    // the accumulators: 38 registers spilled by the product alone.)
+    const auto slab = [&](int s) {
       group<false>(acc, b0, b1, b2, b3, Wr, lane_off, wg, Xl, s, s0, s1, tid, lane, tail);
       wg += Raw::kGroup;
       float* q = s0; s0 = s1; s1 = q;
+    };
+    if constexpr (NT == 1 && !TRANSPOSED) {
+#pragma unroll
+      for (int s = 0; s < 3; ++s) slab(s);
+    } else {
+#pragma unroll 1
+      for (int s = 0; s < 3; ++s) slab(s);
     }
     group<true>(acc, b0, b1, b2, b3, Wr, lane_off, wg, Xl, 3, s0, s1, tid, lane, tail);
     acc.add_finite(low);
@@ -676,10 +727,10 @@ struct SplitProduct {
   }
 };
 
-template <int MT, bool TRANSPOSED, bool SLABS = true, class Tail>
-__device__ inline void gemm256(const float* __restrict__ Xl, const float* __restrict__ W, WeightRaw<TRANSPOSED>& b0,
-                               float* __restrict__ slabs, int wave, int lane, Acc<MT, 2>& acc, Tail tail) {
-  SplitProduct<MT, TRANSPOSED, SLABS> p;
+template <int MT, bool TRANSPOSED, bool SLABS = true, int NT = 2, class Tail>
+__device__ inline void gemm256(const float* __restrict__ Xl, const float* __restrict__ W, WeightRaw<TRANSPOSED, NT>& b0,
+                               float* __restrict__ slabs, int wave, int lane, Acc<MT, NT>& acc, Tail tail) {
+  SplitProduct<MT, TRANSPOSED, SLABS, NT> p;
   p.run(Xl, W, b0, slabs, wave, lane, acc, tail);
   if (!SLABS) __syncthreads();                       // every wavefront has read the tile
 }
@@ -691,27 +742,31 @@ __device__ inline void gemm256(const float* __restrict__ Xl, const float* __rest
 // the backward pass can apply ReLU' without re-reading the activations: the
 // input-gradient product leaves element (row, col) in the same lane and
 // register as the forward product did.
-template <int MT, bool THROUGH = false>
-__device__ inline uint64_t relu_store(const Acc<MT>& acc, const float (&bb)[2], float* __restrict__ Yl,
+template <int MT, bool THROUGH = false, int NT = 2>
+__device__ inline uint64_t relu_store(const Acc<MT, NT>& acc, const float (&bb)[NT], float* __restrict__ Yl,
                                       float* __restrict__ Yg, int wave, int lane) {
   uint64_t mask = 0;
-  const int col = tile_col(wave, 0, lane);           // the lane's two columns go out as one 8-byte store
+  const int col = tile_col<NT>(wave, 0, lane);       // two columns of a lane go out as one 8-byte store
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int row = 32 * mt + acc_row(v, lane);
-      const float h0 = fmaxf(acc.t[mt][0][v] + bb[0], 0.0f), h1 = fmaxf(acc.t[mt][1][v] + bb[1], 0.0f);
-      if (h0 > 0.0f) mask |= 1ull << ((2 * mt + 0) * 16 + v);
-      if (h1 > 0.0f) mask |= 1ull << ((2 * mt + 1) * 16 + v);
-      *reinterpret_cast<f32x2*>(&Yl[row * kLda + col]) = f32x2{h0, h1};
-      if (Yg) put2<THROUGH>(Yg + (size_t)row * kH + col, h0, h1);
+      float h[NT];
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        h[nt] = fmaxf(acc.t[mt][nt][v] + bb[nt], 0.0f);
+        if (h[nt] > 0.0f) mask |= 1ull << ((NT * mt + nt) * 16 + v);
+      }
+      store_cols(&Yl[row * kLda + col], h);
+      if (Yg) put_cols<THROUGH>(Yg + (size_t)row * kH + col, h);
     }
   return mask;
 }
 
+template <int NT = 2>
 __device__ inline bool mask_bit(uint64_t mask, int mt, int nt, int v) {
-  return (mask >> ((2 * mt + nt) * 16 + v)) & 1ull;
+  return (mask >> ((NT * mt + nt) * 16 + v)) & 1ull;
 }
 
 // Thin products on the vector ALU (heads with 1..8 outputs, action gradient):
@@ -719,12 +774,13 @@ __device__ inline bool mask_bit(uint64_t mask, int mt, int nt, int v) {
 // Thread t works on rows (t >> 3) + 32 i with column groups 32 q + 4 (t & 7);
 // 8 neighbouring lanes share a row and are summed with lane shuffles.
 // `stride`: row stride of `outl` (kMaxAct unless the caller keeps wider rows).
-template <int R>
+// THREADS / 8 rows at a time.
+template <int R, int THREADS = kThreads>
 __device__ inline void thin_dot(const float* __restrict__ Xl, const float* __restrict__ V, int J,
                                 float* __restrict__ outl, int tid, int stride = kMaxAct) {
   const int p = tid & 7;
-  for (int i = 0; i < R / 32; ++i) {
-    const int r = (tid >> 3) + 32 * i;
+  for (int i = 0; i < 8 * R / THREADS; ++i) {
+    const int r = (tid >> 3) + THREADS / 8 * i;
     float s[kMaxAct];
 #pragma unroll
     for (int j = 0; j < kMaxAct; ++j) s[j] = 0.0f;

@@ -93,22 +93,22 @@ __device__ inline void load_input(float* Xl, int xld, const float* rows, int row
 
 // The same for wide rows: wavefront w takes the rows w, w + 4, ..., its lanes consecutive columns
 // (coalesced, no index division, every load independent of the others).
-template <int R>
+template <int R, int THREADS = kThreads>
 __device__ inline void load_input_wide(float* Xl, int xld, const float* rows, int row_stride, int c0, int n, int valid,
                                        int tid) {
-  constexpr int RW = R / (kThreads / 64);            // rows per wavefront
+  constexpr int RW = R / (THREADS / 64);            // rows per wavefront
   const int wave = tid >> 6, lane = tid & 63;
 #pragma unroll 2
   for (int c = lane; c < xld; c += 64) {             // RW (x2) loads in flight per lane
     float v[RW];
 #pragma unroll
     for (int i = 0; i < RW; ++i) {
-      const int r = wave + (kThreads / 64) * i;
+      const int r = wave + (THREADS / 64) * i;
       v[i] = rows[(size_t)(r < valid ? r : 0) * row_stride + c0 + (c < n ? c : 0)];
     }
 #pragma unroll
     for (int i = 0; i < RW; ++i) {
-      const int r = wave + (kThreads / 64) * i;
+      const int r = wave + (THREADS / 64) * i;
       Xl[r * xld + c] = (r < valid && c < n) ? v[i] : 0.0f;
     }
   }
@@ -325,6 +325,10 @@ struct Rows32 {                                      // 32 MT rows on 32x32 tile
 // at about five cycles of issue each left nothing to hide anything under.  us, four / eight wavefronts at 256 agents: product of 64 rows
 // 10.3 / 7.7, target chain 59 / 48, critic chain 36.4 / 30.5, actor chain 80 / 74, step 1007 / 925; SAC with 32 agents 214 / 209.
 using Rows64 = Rows32<2, true, 1>;
+// The same for 32 rows, for launches in which a workgroup has a CU to itself (with two to a CU there are two wavefronts on a SIMD
+// anyway, and eight would leave no registers): actor chain of 20 TD3 agents 45.1 -> 43.0 us on a slower card, per step 20 agents
+// 120 -> 117 (training rounds), 20 agents of 376 / 17 267 -> 263, 23 agents of 11 / 3 174 -> 168, 32 SAC agents 225 -> 214, of 376 / 17 455 -> 451.
+using Rows32x8 = Rows32<1, true, 1>;
 
 struct Rows16 {                                      // 16 rows on v_mfma_f32_16x16x4_f32 (mfma_tiles16.h)
   static constexpr int R = 16, kPad = 16, kThr = kThreads, kPerSimd = 1;
@@ -449,21 +453,21 @@ struct Rows16 {                                      // 16 rows on v_mfma_f32_16
 // The same tiles for first layers with a fan-in of several hundred (the SAC Humanoid shapes): only the
 // first-layer product differs (software-pipelined beyond the prefetched rows).
 // PF: weight blocks of 16 rows in flight; 4 where the registers allow it (the critic chain), else 2.
-template <int MT, int PF = 2>
-struct Rows32Deep : Rows32<MT> {
+template <int MT, int PF = 2, int NT = 2>
+struct Rows32Deep : Rows32<MT, true, NT> {
   static constexpr bool kStageOnInput = true;
-  using Pre = typename Rows32<MT>::Pre;
+  using Pre = typename Rows32<MT, true, NT>::Pre;
   __device__ static inline void load_input(float* Xl, int xld, const float* rows, int row_stride, int c0, int n, int valid,
                                            int tid) {
-    load_input_wide<32 * MT>(Xl, xld, rows, row_stride, c0, n, valid, tid);
+    load_input_wide<32 * MT, 64 * (8 / NT)>(Xl, xld, rows, row_stride, c0, n, valid, tid);
   }
   template <bool THROUGH>
   __device__ static inline uint64_t first_layer(const float* Xs, int xld, const float* net, const NetLayout& L,
                                                 const Pre& pre, float* Yl, float* Yg, int wave, int lane) {
-    Acc<MT> acc;
+    Acc<MT, NT> acc;
     acc.zero();
-    gemm_xw_deep<MT, PF>(Xs, xld, L.in, net + L.w1, pre.w1, wave, lane, acc);
-    return relu_store<MT, THROUGH>(acc, pre.b1, Yl, Yg, wave, lane);
+    gemm_xw_deep<MT, PF, NT>(Xs, xld, L.in, net + L.w1, pre.w1, wave, lane, acc);
+    return relu_store<MT, THROUGH, NT>(acc, pre.b1, Yl, Yg, wave, lane);
   }
 };
 
@@ -484,15 +488,16 @@ struct Rows16Deep : Rows16 {
 
 }  // namespace
 
-// head_mfma_split for the rows of a geometry: 64 rows as two halves, one for each four of eight wavefronts
+// head_mfma_split for the rows of a geometry: with eight wavefronts half of the rows for each four, 64 rows in two halves
 template <class G, bool BY_ROWS>
 __device__ inline void head_split(const float* __restrict__ Xl, const float* __restrict__ W, int J, float* __restrict__ outl,
                                   int stride, int wave, int lane, float* __restrict__ red) {
-  if constexpr (G::R <= 32) {
-    head_mfma_split<G::R, BY_ROWS>(Xl, W, J, outl, stride, wave, lane, red);
-  } else if constexpr (G::kThr == 2 * kThreads) {
+  if constexpr (G::kThr == 2 * kThreads) {
+    constexpr int H = G::R / 2;
     const int h = wave & 1;
-    head_mfma_split<32, BY_ROWS>(Xl + 32 * h * kLda, W, J, outl + 32 * h * stride, stride, wave >> 1, lane, red + h * kHeadRed);
+    head_mfma_split<H, BY_ROWS>(Xl + H * h * kLda, W, J, outl + H * h * stride, stride, wave >> 1, lane, red + h * (H / 16) * 1024);
+  } else if constexpr (G::R <= 32) {
+    head_mfma_split<G::R, BY_ROWS>(Xl, W, J, outl, stride, wave, lane, red);
   } else {
 #pragma unroll
     for (int h = 0; h < 2; ++h)
@@ -674,7 +679,7 @@ __device__ __forceinline__ void target_chain(const PopDev& d, uint32_t t, int ag
   __syncthreads();
   POP_MARK(33);
   if (AS == kMaxAct || d.A <= 16) head_split<G, false>(buf, ta + d.actor.w3, d.A, head, AS, wave, lane, stage);
-  else head_mfma<R>(buf, ta + d.actor.w3, d.A, head, AS, wave, lane);   // the head's weights straight from global memory
+  else head_mfma<R, G::kThr>(buf, ta + d.actor.w3, d.A, head, AS, wave, lane);   // the head's weights straight from global memory
   __syncthreads();
   POP_MARK(34);
 #pragma unroll
@@ -1019,7 +1024,7 @@ __device__ __forceinline__ void actor_chain(const PopDev& d, uint32_t t, int age
                          [&]() { if (!WAIT) pre.load(cn, d.critic, wave, lane); }, stage);
   __syncthreads();
   if (AS == kMaxAct || A <= 16) head_split<G, false>(buf, an + d.actor.w3, A, head, AS, wave, lane, stage);
-  else head_mfma<R>(buf, an + d.actor.w3, A, head, AS, wave, lane);
+  else head_mfma<R, G::kThr>(buf, an + d.actor.w3, A, head, AS, wave, lane);
   __syncthreads();
   for (int e = tid; e < R * A; e += G::kThr) {
     const int r = e / A, j = e - r * A;
@@ -1080,7 +1085,7 @@ __device__ __forceinline__ void actor_chain(const PopDev& d, uint32_t t, int age
   __syncthreads();
   POP_MARK(12);
   if (AS == kMaxAct || A <= 16) head_split<G, true>(buf, cn + d.critic.w1 + d.O * kH, A, head, AS, wave, lane, stage);   // da
-  else head_mfma_t<R>(buf, cn + d.critic.w1 + d.O * kH, A, head, AS, wave, lane);
+  else head_mfma_t<R, G::kThr>(buf, cn + d.critic.w1 + d.O * kH, A, head, AS, wave, lane);
   G::load_wt(wt, an + d.actor.w2, wave, lane);       // block 0 of the actor's input-gradient product
   __syncthreads();
   for (int e = tid; e < R * AS; e += G::kThr) {
@@ -1098,6 +1103,10 @@ __device__ __forceinline__ void actor_chain(const PopDev& d, uint32_t t, int age
     put<WAIT>(part + kAP_db3 + tid, s);
   }
   float sums[UR::kOwn][AS + 1];                      // dW3 by column, db2
+  // they meet in the second slab, as in critic_chain, wide heads in both
+  constexpr bool kBothSlabs = UR::kCross && (AS + 1) * kH > G::kStage / 2;
+  static_assert(!UR::kCross || (AS + 1) * kH <= G::kStage, "fits the slabs");
+  float* cross = kBothSlabs ? stage : stage + G::kStage / 2;
   {                                                 // actor head backward, one thread per hidden unit
     const int c = unit;
     constexpr int RB = (AS == kMaxAct ? 4 : 2) / UR::kOwn;   // rows of a half in flight (the wide rows cost three times the registers)
@@ -1142,17 +1151,17 @@ __device__ __forceinline__ void actor_chain(const PopDev& d, uint32_t t, int age
           sums[o][AS] += z;
         }
     }
-    static_assert(!UR::kCross || (AS + 1) * kH <= G::kStage / 2, "fits the slab");
-    UR::put(sums, stage + G::kStage / 2, tid);       // as in critic_chain
+    UR::put(sums, cross, tid);
   }
   __syncthreads();
   POP_MARK(13);
   if (tid < kH) {
 #pragma unroll
     for (int j = 0; j < AS; ++j)
-      if (j < A) put<WAIT>(part + kAP_dW3 + j * kH + tid, UR::total(sums, stage + G::kStage / 2, tid, j));
-    put<WAIT>(part + kAP_db2 + tid, UR::total(sums, stage + G::kStage / 2, tid, AS));
+      if (j < A) put<WAIT>(part + kAP_dW3 + j * kH + tid, UR::total(sums, cross, tid, j));
+    put<WAIT>(part + kAP_db2 + tid, UR::total(sums, cross, tid, AS));
   }
+  if (kBothSlabs) __syncthreads();                   // the product writes the first one at once
   G::template input_grad_to_global<WAIT>(buf, an + d.actor.w2, wt, mask_a1, d.adZ1 + act_off, part + kAP_db1, wave, lane, stage);
   POP_MARK(14);
   if (WAIT) signal_count(d.done_a + parity_base(d, t, d.P) + agent, tid);

@@ -163,38 +163,67 @@ __device__ __forceinline__ void sac_target_chain(const PopDev& d, uint32_t t, in
 // buf: h2 in, dz2 out (LDS tile, row stride kLda); dz3: [R][kMaxHead], columns >= H2 hold zeros; W3: the
 // head's weights [256][H2] in global memory;
 // NC: head columns handled (a multiple of 4, >= H2).
-template <int R, int NC>
+template <class G, int NC>
 __device__ __forceinline__ void sac_head_backward(float* buf, const float* dz3, const float* __restrict__ W3, int H2,
-                                                  float* zg, float* part, int c) {
-  float w3[NC], gw3[NC];
+                                                  float* zg, float* part, float* cross, int tid) {
+  using UR = UnitRows<G>;
+  const int c = tid & (kH - 1);
+  float w3[NC], sums[UR::kOwn][NC + 1];              // dW3 by column, db2
 #pragma unroll
-  for (int j = 0; j < NC; ++j) { w3[j] = W3[c * H2 + (j < H2 ? j : 0)]; gw3[j] = 0.0f; }
+  for (int j = 0; j < NC; ++j) w3[j] = W3[c * H2 + (j < H2 ? j : 0)];
 #pragma unroll
   for (int j = 0; j < NC; ++j) w3[j] = j < H2 ? w3[j] : 0.0f;
-  float gb2 = 0.0f;
+#pragma unroll
+  for (int o = 0; o < UR::kOwn; ++o)
+#pragma unroll
+    for (int j = 0; j <= NC; ++j) sums[o][j] = 0.0f;
   zg += c;
+  constexpr int RB = NC <= 16 ? 4 / UR::kOwn : 1;    // rows of a half in flight
 #pragma unroll 1
-  for (int r = 0; r < R; ++r) {
-    const float h = buf[r * kLda + c];
-    float dh = 0.0f;
+  for (int rb = 0; rb < UR::kRows; rb += RB) {
 #pragma unroll
-    for (int q = 0; q < NC / 4; ++q) {
-      const f32x4 g = *reinterpret_cast<const f32x4*>(&dz3[r * kMaxHead + 4 * q]);
+    for (int o = 0; o < UR::kOwn; ++o)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        gw3[4 * q + i] += h * g[i];
-        dh += g[i] * w3[4 * q + i];
+      for (int i = 0; i < RB; ++i) {
+        const int r = UR::row0(o, tid) + rb + i;
+        const float h = buf[r * kLda + c];
+        float dh = 0.0f;
+#pragma unroll
+        for (int q = 0; q < NC / 4; ++q) {
+          const f32x4 g = *reinterpret_cast<const f32x4*>(&dz3[r * kMaxHead + 4 * q]);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            sums[o][4 * q + k] += h * g[k];
+            dh += g[k] * w3[4 * q + k];
+          }
+        }
+        const float z = h > 0.0f ? dh : 0.0f;
+        buf[r * kLda + c] = z;
+        zg[r * kH] = z;
+        sums[o][NC] += z;
+      }
+  }
+  // the halves' sums meet, as many columns at a time as the slabs hold
+  constexpr int CH = UR::kCross ? (G::kStage / kH < NC + 1 ? G::kStage / kH : NC + 1) : NC + 1;
+#pragma unroll
+  for (int j0 = 0; j0 <= NC; j0 += CH) {
+    if (UR::kCross) {
+      if (j0) __syncthreads();
+      if (tid >= kH) {
+#pragma unroll
+        for (int j = j0; j <= NC && j < j0 + CH; ++j) cross[(j - j0) * kH + c] = sums[0][j];
+      }
+      __syncthreads();
+    }
+    if (tid < kH) {
+#pragma unroll
+      for (int j = j0; j <= NC && j < j0 + CH; ++j) {
+        const float v = UR::kCross ? sums[0][j] + cross[(j - j0) * kH + c] : UR::kHalves == 1 ? sums[0][j] : sums[0][j] + sums[UR::kOwn - 1][j];
+        if (j == NC) part[kAP_db2 + c] = v;
+        else if (j < H2) part[kAP_dW3 + j * kH + c] = v;
       }
     }
-    const float z = h > 0.0f ? dh : 0.0f;
-    buf[r * kLda + c] = z;
-    zg[r * kH] = z;
-    gb2 += z;
   }
-#pragma unroll
-  for (int j = 0; j < NC; ++j)
-    if (j < H2) part[kAP_dW3 + j * kH + c] = gw3[j];
-  part[kAP_db2 + c] = gb2;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -238,7 +267,7 @@ __device__ __forceinline__ void sac_actor_chain(const PopDev& d, uint32_t t, int
   POP_MARK(20);
   if (d.D <= kMaxIn) {                               // one trip to memory for all of the prologue
     SmallVec ab3, cw3a, cw3b;
-    InputTile<R> xin;
+    InputTile<R, G::kThr> xin;
     ab3.fetch(an + d.actor.b3, H2, tid);
     cw3a.fetch(cn[0] + d.critic.w3, kH, tid);
     cw3b.fetch(cn[1] + d.critic.w3, kH, tid);
@@ -250,8 +279,8 @@ __device__ __forceinline__ void sac_actor_chain(const PopDev& d, uint32_t t, int
     if (tid < 2) v_cb3[tid] = cb3;
     xin.put(Xs, L.xld, tid);
   } else {
-    stage_vector(v_ab3, an + d.actor.b3, H2, tid);
-    for (int k = 0; k < 2; ++k) stage_vector(v_cw3 + k * kH, cn[k] + d.critic.w3, kH, tid);
+    stage_vector<G::kThr>(v_ab3, an + d.actor.b3, H2, tid);
+    for (int k = 0; k < 2; ++k) stage_vector<G::kThr>(v_cw3 + k * kH, cn[k] + d.critic.w3, kH, tid);
     if (tid < 2) v_cb3[tid] = cn[tid][d.critic.b3];
     G::load_input(Xs, L.xld, rows, d.row, 0, d.O, R, tid);
   }
@@ -264,10 +293,10 @@ __device__ __forceinline__ void sac_actor_chain(const PopDev& d, uint32_t t, int
                                   [&]() { pre.load(cn[0], d.critic, wave, lane); }, stage);
   __syncthreads();
   POP_MARK(22);
-  if (R <= 32 && H2 <= 16) head_mfma_split<R <= 32 ? R : 16, false>(buf, an + d.actor.w3, H2, hd, kMaxHead, wave, lane, stage);
-  else head_mfma<R>(buf, an + d.actor.w3, H2, hd, kMaxHead, wave, lane);
+  if (G::kStage > 0 && H2 <= 16) head_split<G, false>(buf, an + d.actor.w3, H2, hd, kMaxHead, wave, lane, stage);
+  else head_mfma<R, G::kThr>(buf, an + d.actor.w3, H2, hd, kMaxHead, wave, lane);
   __syncthreads();
-  for (int e = tid; e < R * A; e += kThreads) {
+  for (int e = tid; e < R * A; e += G::kThr) {
     const int r = e / A, j = e - r * A, o = r * kSs + j, om = r * kMaxHead + j, ol = om + A;
     const float mu = hd[om] + v_ab3[j];
     const float ls_raw = hd[ol] + v_ab3[A + j];
@@ -324,7 +353,8 @@ __device__ __forceinline__ void sac_actor_chain(const PopDev& d, uint32_t t, int
   __syncthreads();
 
   // both critics backward to the action
-  f32x4 h2r[R / 4];                                  // this thread's share of the actor's parked h2 tile
+  constexpr int W = G::kThr / 64;                    // wavefronts
+  f32x4 h2r[R / W];                                  // this thread's share of the actor's parked h2 tile
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
     G::store_outer_masked(buf, mask2[k], qv + (2 + k) * R, v_cw3 + k * kH, wave, lane);     // dz2 of critic k
@@ -333,12 +363,12 @@ __device__ __forceinline__ void sac_actor_chain(const PopDev& d, uint32_t t, int
     G::input_grad_to_lds(buf, cn[k] + d.critic.w2, wt, mask1[k], wave, lane, [&]() {
       if (k == 0) return;
 #pragma unroll
-      for (int i = 0; i < R / 4; ++i)
-        h2r[i] = *reinterpret_cast<const f32x4*>(h2g + (4 * i + (tid >> 6)) * kH + 4 * (tid & 63));
+      for (int i = 0; i < R / W; ++i)
+        h2r[i] = *reinterpret_cast<const f32x4*>(h2g + (W * i + (tid >> 6)) * kH + 4 * (tid & 63));
     }, stage);                                       // buf = dz1 of critic k
     __syncthreads();
-    if (R <= 32 && A <= 16) head_mfma_split<R <= 32 ? R : 16, true>(buf, cn[k] + d.critic.w1 + d.O * kH, A, k == 0 ? da1 : da2, kSs, wave, lane, stage);
-    else head_mfma_t<R>(buf, cn[k] + d.critic.w1 + d.O * kH, A, k == 0 ? da1 : da2, kSs, wave, lane);
+    if (G::kStage > 0 && A <= 16) head_split<G, true>(buf, cn[k] + d.critic.w1 + d.O * kH, A, k == 0 ? da1 : da2, kSs, wave, lane, stage);
+    else head_mfma_t<R, G::kThr>(buf, cn[k] + d.critic.w1 + d.O * kH, A, k == 0 ? da1 : da2, kSs, wave, lane);
     if (k == 0) G::load_wt(wt, cn[1] + d.critic.w2, wave, lane);
     else G::load_wt(wt, an + d.actor.w2, wave, lane);
     __syncthreads();
@@ -347,7 +377,7 @@ __device__ __forceinline__ void sac_actor_chain(const PopDev& d, uint32_t t, int
 
   // through the sampling into the actor's head
   const float ab = alpha * invB;
-  for (int e = tid; e < R * kMaxHead; e += kThreads) {
+  for (int e = tid; e < R * kMaxHead; e += G::kThr) {
     const int r = e / kMaxHead, c = e - r * kMaxHead;
     float g = 0.0f;
     if (c < H2) {
@@ -359,8 +389,8 @@ __device__ __forceinline__ void sac_actor_chain(const PopDev& d, uint32_t t, int
     dz3[e] = g;                                      // unused columns are kept at zero
   }
 #pragma unroll
-  for (int i = 0; i < R / 4; ++i)                    // h2 of the actor back into the tile
-    *reinterpret_cast<f32x4*>(&buf[(4 * i + (tid >> 6)) * kLda + 4 * (tid & 63)]) = h2r[i];
+  for (int i = 0; i < R / W; ++i)                    // h2 of the actor back into the tile
+    *reinterpret_cast<f32x4*>(&buf[(W * i + (tid >> 6)) * kLda + 4 * (tid & 63)]) = h2r[i];
   __syncthreads();
   if (tid < H2) {
     float s = 0.0f;
@@ -369,8 +399,9 @@ __device__ __forceinline__ void sac_actor_chain(const PopDev& d, uint32_t t, int
   }
   POP_MARK(28);
   // actor head backward, one thread per hidden unit; the common small heads stay in 16 registers
-  if (H2 <= 16) sac_head_backward<R, 16>(buf, dz3, an + d.actor.w3, H2, d.adZ2 + act_off, part, tid);
-  else sac_head_backward<R, kMaxHead>(buf, dz3, an + d.actor.w3, H2, d.adZ2 + act_off, part, tid);
+  float* cross = stage;                              // the slabs are idle here
+  if (H2 <= 16) sac_head_backward<G, 16>(buf, dz3, an + d.actor.w3, H2, d.adZ2 + act_off, part, cross, tid);
+  else sac_head_backward<G, kMaxHead>(buf, dz3, an + d.actor.w3, H2, d.adZ2 + act_off, part, cross, tid);
   __syncthreads();
   POP_MARK(29);
   G::template input_grad_to_global<false>(buf, an + d.actor.w2, wt, mask_a1, d.adZ1 + act_off, part + kAP_db1, wave, lane, stage);

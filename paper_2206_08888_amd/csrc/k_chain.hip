@@ -162,7 +162,9 @@ hipError_t setup_kernels() {
   POP_SET_LDS(k_critic<Rows64>);
   POP_SET_LDS(k_critic<Rows32Deep<1, 4>>);
   POP_SET_LDS(k_actor<Rows16>);
-  POP_SET_LDS(k_actor<Rows32<1>>);
+  POP_SET_LDS(k_actor<Rows32x8>);
+  POP_SET_LDS(k_actor<Rows32Deep<1, 2, 1>>);
+  POP_SET_LDS(k_actor<Rows32Deep<1, 2, 1>, 2, false, kSacMaxAct>);
   POP_SET_LDS(k_actor<Rows32<1>, 2>);
   POP_SET_LDS(k_actor<Rows64>);
   POP_SET_LDS(k_target_critic<Rows16, Rows32<2>>);
@@ -261,11 +263,13 @@ hipError_t launch_actor(const PopDev& d, uint32_t t, hipStream_t s) {
   if (d.A > kMaxAct) {
     if (d.actor_ahead) return hipErrorInvalidValue;
     if (d.rows_a == 16) k_actor<Rows16Deep, 1, false, kSacMaxAct><<<grid, block, chain_bytes<Rows16>(d.D, vec_actor(d), Rows16::kStage, kWideScratch), s>>>(d, t);
+    else if (d.rows_a == 32 && (int)grid.x <= kCUs) k_actor<Rows32Deep<1, 2, 1>, 2, false, kSacMaxAct><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec_actor(d), Rows32<1>::kStage, kWideScratch), s>>>(d, t);
     else if (d.rows_a == 32) k_actor<Rows32Deep<1>, 1, false, kSacMaxAct><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec_actor(d), Rows32<1>::kStage, kWideScratch), s>>>(d, t);
     else return hipErrorInvalidValue;
   } else if (d.D > kMaxIn) {
     if (d.actor_ahead) return hipErrorInvalidValue;
     if (d.rows_a == 16) k_actor<Rows16Deep><<<grid, block, chain_bytes<Rows16>(d.D, vec_actor(d)), s>>>(d, t);
+    else if (d.rows_a == 32 && (int)grid.x <= kCUs) k_actor<Rows32Deep<1, 2, 1>><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec_actor(d)), s>>>(d, t);
     else if (d.rows_a == 32) k_actor<Rows32Deep<1>><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec_actor(d)), s>>>(d, t);
     else return hipErrorInvalidValue;
   } else if (d.actor_ahead) {
@@ -273,7 +277,7 @@ hipError_t launch_actor(const PopDev& d, uint32_t t, hipStream_t s) {
     k_actor<Rows16, 1, true><<<grid, block, chain_bytes<Rows16>(d.D, vec_actor(d)), s>>>(d, t);
   } else if (d.rows_a == 16) k_actor<Rows16><<<grid, block, chain_bytes<Rows16>(d.D, vec_actor(d)), s>>>(d, t);
   else if (d.rows_a == 32 && (int)grid.x > kCUs) k_actor<Rows32<1>, 2><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec_actor(d)), s>>>(d, t);
-  else if (d.rows_a == 32) k_actor<Rows32<1>><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec_actor(d)), s>>>(d, t);
+  else if (d.rows_a == 32) k_actor<Rows32x8><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec_actor(d)), s>>>(d, t);
   else k_actor<Rows64><<<grid, dim3(Rows64::kThr), chain_bytes<Rows32<2>>(d.D, vec_actor(d)), s>>>(d, t);
   return hipGetLastError();
 }

@@ -19,7 +19,7 @@ __global__ __launch_bounds__(kThreads, PER_CU) void k_sac_target(PopDev d, uint3
 }
 
 template <class G>
-__global__ __launch_bounds__(kThreads, 1) void k_sac_actor(PopDev d, uint32_t t) {
+__global__ __launch_bounds__(G::kThr, G::kThr / kThreads) void k_sac_actor(PopDev d, uint32_t t) {
   extern __shared__ float lds[];
   int agent, chunk;
   POP_BLOCK_TIME(kTraceActor, 0);
@@ -57,6 +57,8 @@ hipError_t setup_sac_kernels() {
   POP_SET_LDS(k_sac_actor<SacRows64>);
   POP_SET_LDS(k_sac_actor<Rows16Deep>);
   POP_SET_LDS(k_sac_actor<Rows32Deep<1>>);
+  POP_SET_LDS(k_sac_actor<Rows32x8>);
+  POP_SET_LDS(k_sac_actor<Rows32Deep<1, 2, 1>>);
   POP_SET_LDS(k_sac_target_critic<Rows16, Rows32<2>>);
   POP_SET_LDS(k_sac_target_critic<Rows16, Rows32<1>>);
   POP_SET_LDS(k_sac_target_critic<Rows32<1>, Rows32<1>>);
@@ -114,9 +116,11 @@ hipError_t launch_sac_actor(const PopDev& d, uint32_t t, hipStream_t s) {
   const int vec = vec_sac_actor(d);
   if (d.D > kMaxIn) {
     if (d.rows_a == 16) k_sac_actor<Rows16Deep><<<grid, block, chain_bytes<Rows16>(d.D, vec, Rows16::kStage, kSacScratch), s>>>(d, t);
+    else if (d.rows_a == 32 && (int)grid.x <= kCUs) k_sac_actor<Rows32Deep<1, 2, 1>><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec, Rows32<1>::kStage, kSacScratch), s>>>(d, t);
     else if (d.rows_a == 32) k_sac_actor<Rows32Deep<1>><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec, Rows32<1>::kStage, kSacScratch), s>>>(d, t);
     else return hipErrorInvalidValue;
   } else if (d.rows_a == 16) k_sac_actor<Rows16><<<grid, block, chain_bytes<Rows16>(d.D, vec, Rows16::kStage, kSacScratch), s>>>(d, t);
+  else if (d.rows_a == 32 && (int)grid.x <= kCUs) k_sac_actor<Rows32x8><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec, Rows32<1>::kStage, kSacScratch), s>>>(d, t);
   else if (d.rows_a == 32) k_sac_actor<Rows32<1>><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec, Rows32<1>::kStage, kSacScratch), s>>>(d, t);
   else k_sac_actor<SacRows64><<<grid, block, chain_bytes<SacRows64>(d.D, vec, SacRows64::kStage, kSacScratch), s>>>(d, t);
   return hipGetLastError();

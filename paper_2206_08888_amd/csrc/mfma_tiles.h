@@ -60,6 +60,7 @@ __device__ inline f32x16 mfma32(float a, float b, f32x16 c) {
 // 2^-134.  A product's absolute error grows by 2^-134 (sum |x| + sum |y|) at most; with operands of 1e-31 nothing shows,
 // of 1e-34 the error is 2.8e-7 where the fp32 instructions have 2.0e-7, of 1e-37 2.7e-4.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 struct Split8 {                            // eight consecutive contraction elements of one lane: high, middle and low parts
@@ -272,23 +273,23 @@ __device__ inline void gemm_xw_small(const float* __restrict__ Xl, int ldx, int 
 // 3.1e-8 / 3.4e-8, one 2.5e-8 / 3.5e-8.  Inputs and weights below 2^-110 lose low parts, as in the hidden products (above).
 // X: as above; columns of the tile beyond K hold zeros (load_input_wide), and a block that would reach past the tile's
 // row reads its last four columns instead, where the weights are zero.
-template <int MT, int PF>
+template <int MT, int PF, int NT = 2>
 __device__ inline void gemm_xw_deep(const float* __restrict__ Xl, int ldx, int K, const float* __restrict__ W,
-                                    const SmallW<2>& pre, int wave, int lane, Acc<MT>& acc) {
+                                    const SmallW<NT>& pre, int wave, int lane, Acc<MT, NT>& acc) {
   const int half = lane >> 5, l32 = lane & 31;
   const int nb = (K + 15) >> 4;
-  uint32_t off = 4u * (uint32_t)(4 * half * kH + tile_col(wave, 0, lane));
-  Acc<MT> low;
+  uint32_t off = 4u * (uint32_t)(4 * half * kH + tile_col<NT>(wave, 0, lane));
+  Acc<MT, NT> low;
   low.zero();
-  float b[PF][2][8];
-  auto request = [&](float (&dst)[2][8], int blk) {
+  float b[PF][NT][8];
+  auto request = [&](float (&dst)[NT][8], int blk) {
     const WeightsRsrc Wr = weights_rsrc(W + 16 * blk * kH, (K - 16 * blk) * kH);      // rows at or beyond K are zero
     asm("" : "+v"(off));                              // or copies of it are kept for each block in flight
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const f32x2 v = rsrc_load2(Wr, off + 4 * (8 * (e >> 2) + (e & 3)) * kH, 0);
-      dst[0][e] = v[0];
-      dst[1][e] = v[1];
+      const auto v = rsrc_load_cols<NT>(Wr, off + 4 * (8 * (e >> 2) + (e & 3)) * kH, 0);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) dst[nt][e] = col_of(v, nt);
     }
   };
   f32x4 xn[MT][2];                                   // the LDS operand runs one block ahead
@@ -302,12 +303,12 @@ __device__ inline void gemm_xw_deep(const float* __restrict__ Xl, int ldx, int K
       }
   };
   // block i with weights w; the LDS operand of block i + 1 and the loads of next() go out ahead of the matrix work
-  auto block = [&](const float (&w)[2][8], int i, auto next) {
-    Split8 x[MT], ws[2];
+  auto block = [&](const float (&w)[NT][8], int i, auto next) {
+    Split8 x[MT], ws[NT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) split8(xn[mt][0], xn[mt][1], x[mt]);
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) split8(w[nt], ws[nt]);
+    for (int nt = 0; nt < NT; ++nt) split8(w[nt], ws[nt]);
     lds_block(i + 1);
     next();
     __builtin_amdgcn_sched_barrier(0);
@@ -316,7 +317,7 @@ __device__ inline void gemm_xw_deep(const float* __restrict__ Xl, int ldx, int K
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
+        for (int nt = 0; nt < NT; ++nt) {
           f32x16& c = q == kSplitTerms - 1 ? acc.t[mt][nt] : low.t[mt][nt];
           c = mfma32_bf16(x[mt].t[kTermX[q]], ws[nt].t[kTermW[q]], c);
         }
@@ -328,9 +329,9 @@ __device__ inline void gemm_xw_deep(const float* __restrict__ Xl, int ldx, int K
 #pragma unroll
   for (int i = 0; i < 2; ++i)
     if (i < nb) {
-      float w[2][8];
+      float w[NT][8];
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
+      for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
         for (int e = 0; e < 8; ++e) w[nt][e] = pre.w[2 * i + (e >> 2)][nt][e & 3];
       block(w, i, [] {});
@@ -543,20 +544,24 @@ constexpr int kSlabLd = 72;
 template <int MT>
 constexpr int slab_floats() { return 3 * 32 * MT * kSlabLd / 2; }
 template <int MT, int NT>
-struct SlabItem {                          // this thread's share of a slab: Q times eight neighbours of a row
-  static constexpr int Q = MT * NT / 2;
-  f32x4 x[Q][2];
+struct SlabItem {                          // this thread's share of a slab: Q times E neighbours of a row
+  static constexpr int E = MT * NT == 1 ? 4 : 8, Q = MT * NT == 4 ? 2 : 1, kPerRow = 64 / E;
+  f32x4 x[Q][E / 4];
   __device__ inline void read(const float* __restrict__ Xl, int s, int tid, int q) {
-    const float* p = Xl + (32 * q + (tid >> 3)) * kLda + 64 * s + 8 * (tid & 7);
-    x[q][0] = *reinterpret_cast<const f32x4*>(p);
-    x[q][1] = *reinterpret_cast<const f32x4*>(p + 4);
+    const float* p = Xl + (32 * q + tid / kPerRow) * kLda + 64 * s + E * (tid % kPerRow);
+#pragma unroll
+    for (int i = 0; i < E / 4; ++i) x[q][i] = *reinterpret_cast<const f32x4*>(p + 4 * i);
   }
   __device__ inline void put(float* __restrict__ slab, int tid, int q) const {
     Split8 v;
-    split8(x[q][0], x[q][1], v);
-    __bf16* b = reinterpret_cast<__bf16*>(slab) + (32 * q + (tid >> 3)) * kSlabLd + 8 * (tid & 7);
 #pragma unroll
-    for (int p = 0; p < 3; ++p) *reinterpret_cast<bf16x8*>(b + p * 32 * MT * kSlabLd) = v.t[p];
+    for (int i = 0; i < E / 2; ++i) split_pair(x[q][i / 2][2 * (i & 1)], x[q][i / 2][2 * (i & 1) + 1], i, v);
+    __bf16* b = reinterpret_cast<__bf16*>(slab) + (32 * q + tid / kPerRow) * kSlabLd + E * (tid % kPerRow);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      if constexpr (E == 8) *reinterpret_cast<bf16x8*>(b + p * 32 * MT * kSlabLd) = v.t[p];
+      else *reinterpret_cast<bf16x4*>(b + p * 32 * MT * kSlabLd) = __builtin_shufflevector(v.t[p], v.t[p], 0, 1, 2, 3);
+    }
   }
 };
 
@@ -565,7 +570,7 @@ struct SlabItem {                          // this thread's share of a slab: Q t
 template <int MT, bool TRANSPOSED, bool SLABS, int NT>
 struct SplitProduct {
   using Raw = WeightRaw<TRANSPOSED, NT>;
-  static_assert(NT == 2 || (SLABS && MT == 2), "eight wavefronts: 64 rows");
+  static_assert(NT == 2 || SLABS, "eight wavefronts read the left operand from the slabs");
   Split8 x[2][MT], w[2];                   // the LDS operand of this block and the next, the weights of the two column tiles (NT = 1: of this block and the next)
   SlabItem<MT, NT> item;
   Acc<MT, NT> low;
@@ -625,8 +630,8 @@ struct SplitProduct {
       for (int m = 0; m < M; ++m) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         if (NEXT) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        if (loads1 * m < 8 * M && loads1) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, ((NEXT ? 44 : 0) + (put ? 44 : 0) + M - 1) / M + 1, 0);
+        if (loads1 * m < 8 * M && loads1) __builtin_amdgcn_sched_group_barrier(0x020, (loads1 + M - 1) / M, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, ((NEXT ? 44 : 0) + (put ? 5 * SlabItem<MT, NT>::E + 4 : 0) + M - 1) / M + 1, 0);
       }
       __builtin_amdgcn_sched_barrier(0);
     } else {
@@ -779,7 +784,8 @@ template <int R, int THREADS = kThreads>
 __device__ inline void thin_dot(const float* __restrict__ Xl, const float* __restrict__ V, int J,
                                 float* __restrict__ outl, int tid, int stride = kMaxAct) {
   const int p = tid & 7;
-  for (int i = 0; i < 8 * R / THREADS; ++i) {
+  for (int i = 0; i < (8 * R + THREADS - 1) / THREADS; ++i) {
+    if (8 * R < THREADS && tid >= 8 * R) break;
     const int r = (tid >> 3) + THREADS / 8 * i;
     float s[kMaxAct];
 #pragma unroll

@@ -326,18 +326,18 @@ __device__ inline uint64_t relu_store16(const Acc16& acc, const f32x4& bb, float
 //   head_mfma:   out[r*stride + j] = sum_{c<256} X[r][c] W[c*J + j]      (W: [256][J], a network's head)
 //   head_mfma_t: out[r*stride + j] = sum_{c<256} X[r][c] W[j*256 + c]    (W: J rows of 256)
 // r < R (a multiple of 16), j < J; X in LDS with row stride kLda.  The output is cut into 16x16 tiles,
-// dealt round-robin to the 4 wavefronts; a tile's 256-deep product is 64 v_mfma_f32_16x16x4_f32, its
+// dealt round-robin to the wavefronts; a tile's 256-deep product is 64 v_mfma_f32_16x16x4_f32, its
 // weights requested in one go (head_mfma: in two halves) ahead of the products.  Columns at or beyond J are neither read nor
 // written.  The tile loop is controlled by a scalar (readfirstlane of the wavefront index): written on
 // the per-lane value, the compiler wraps the matrix instructions in an EXEC-masked loop, and one build of
 // that form produced wrong sums.
-template <int R>
+template <int R, int THREADS = kThreads>
 __device__ inline void head_mfma(const float* __restrict__ Xl, const float* __restrict__ W, int J, float* __restrict__ outl,
                                  int stride, int wave, int lane) {
   constexpr int RT = R / 16;
   const int c = lane & 15, kq = lane >> 4;
   const int tiles = RT * ((J + 15) >> 4);
-  for (int tile = __builtin_amdgcn_readfirstlane(wave); tile < tiles; tile += kThreads / 64) {
+  for (int tile = __builtin_amdgcn_readfirstlane(wave); tile < tiles; tile += THREADS / 64) {
     const int rt = tile % RT, col = 16 * (tile / RT) + c;
     const bool ok = col < J;
     const float* wp = W + (ok ? col : 0) + (size_t)(4 * kq) * J;
@@ -363,13 +363,13 @@ __device__ inline void head_mfma(const float* __restrict__ Xl, const float* __re
   }
 }
 
-template <int R>
+template <int R, int THREADS = kThreads>
 __device__ inline void head_mfma_t(const float* __restrict__ Xl, const float* __restrict__ W, int J, float* __restrict__ outl,
                                    int stride, int wave, int lane) {
   constexpr int RT = R / 16;
   const int c = lane & 15, kq = lane >> 4;
   const int tiles = RT * ((J + 15) >> 4);
-  for (int tile = __builtin_amdgcn_readfirstlane(wave); tile < tiles; tile += kThreads / 64) {
+  for (int tile = __builtin_amdgcn_readfirstlane(wave); tile < tiles; tile += THREADS / 64) {
     const int rt = tile % RT, col = 16 * (tile / RT) + c;
     const bool ok = col < J;
     const float* wp = W + (size_t)(ok ? col : 0) * kH + 4 * kq;

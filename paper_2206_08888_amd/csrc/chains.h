@@ -264,7 +264,7 @@ struct Rows32 {                                      // 32 MT rows on 32x32 tile
   }
   template <bool THROUGH>
   __device__ static inline uint64_t first_layer(const float* Xs, int xld, const float* net, const NetLayout& L,
-                                                const Pre& pre, float* Yl, float* Yg, int wave, int lane) {
+                                                const Pre& pre, float* Yl, float* Yg, int wave, int lane, float*) {
     return pop::first_layer<MT, THROUGH, NT>(Xs, xld, net, L, pre, Yl, Yg, wave, lane);
   }
   template <bool THROUGH, class Tail>
@@ -327,7 +327,8 @@ struct Rows32 {                                      // 32 MT rows on 32x32 tile
 using Rows64 = Rows32<2, true, 1>;
 // The same for 32 rows, for launches in which a workgroup has a CU to itself (with two to a CU there are two wavefronts on a SIMD
 // anyway, and eight would leave no registers): actor chain of 20 TD3 agents 45.1 -> 43.0 us on a slower card, per step 20 agents
-// 120 -> 117 (training rounds), 20 agents of 376 / 17 267 -> 263, 23 agents of 11 / 3 174 -> 168, 32 SAC agents 225 -> 214, of 376 / 17 455 -> 451.
+// 120 -> 117 (training rounds), 20 agents of 376 / 17 267 -> 263, 23 agents of 11 / 3 174 -> 168, 32 SAC agents 225 -> 214, of 376 / 17 455 -> 451.  Target chains with the input tile through the slabs
+// (gemm_xw_slabs): 20 agents of 376 / 17 263 -> 248, 32 SAC agents of 376 / 17 443 -> 432 (target chain 86 -> 70 us, a first layer 14.5 -> 12.5).
 using Rows32x8 = Rows32<1, true, 1>;
 
 struct Rows16 {                                      // 16 rows on v_mfma_f32_16x16x4_f32 (mfma_tiles16.h)
@@ -353,7 +354,7 @@ struct Rows16 {                                      // 16 rows on v_mfma_f32_16
   }
   template <bool THROUGH>
   __device__ static inline uint64_t first_layer(const float* Xs, int xld, const float* net, const NetLayout& L,
-                                                const Pre& pre, float* Yl, float* Yg, int wave, int lane) {
+                                                const Pre& pre, float* Yl, float* Yg, int wave, int lane, float*) {
     Acc16 acc;
     acc.zero();
     gemm_xw_small16(Xs, xld, L.in, net + L.w1, pre.w1, wave, lane, acc);
@@ -453,7 +454,8 @@ struct Rows16 {                                      // 16 rows on v_mfma_f32_16
 // The same tiles for first layers with a fan-in of several hundred (the SAC Humanoid shapes): only the
 // first-layer product differs (software-pipelined beyond the prefetched rows).
 // PF: weight blocks of 16 rows in flight; 4 where the registers allow it (the critic chain), else 2.
-template <int MT, int PF = 2, int NT = 2>
+// INPUT_SLABS: the input tile is split through the slabs -- not where they lie over it (critic chains).
+template <int MT, int PF = 2, int NT = 2, bool INPUT_SLABS = PF == 2>
 struct Rows32Deep : Rows32<MT, true, NT> {
   static constexpr bool kStageOnInput = true;
   using Pre = typename Rows32<MT, true, NT>::Pre;
@@ -463,10 +465,11 @@ struct Rows32Deep : Rows32<MT, true, NT> {
   }
   template <bool THROUGH>
   __device__ static inline uint64_t first_layer(const float* Xs, int xld, const float* net, const NetLayout& L,
-                                                const Pre& pre, float* Yl, float* Yg, int wave, int lane) {
+                                                const Pre& pre, float* Yl, float* Yg, int wave, int lane, float* stage) {
     Acc<MT, NT> acc;
     acc.zero();
-    gemm_xw_deep<MT, PF, NT>(Xs, xld, L.in, net + L.w1, pre.w1, wave, lane, acc);
+    if (INPUT_SLABS) gemm_xw_slabs<MT, NT>(Xs, xld, L.in, net + L.w1, pre.w1, stage, wave, lane, acc);
+    else gemm_xw_deep<MT, PF, NT>(Xs, xld, L.in, net + L.w1, pre.w1, wave, lane, acc);
     return relu_store<MT, THROUGH, NT>(acc, pre.b1, Yl, Yg, wave, lane);
   }
 };
@@ -478,7 +481,7 @@ struct Rows16Deep : Rows16 {
   }
   template <bool THROUGH>
   __device__ static inline uint64_t first_layer(const float* Xs, int xld, const float* net, const NetLayout& L,
-                                                const Pre& pre, float* Yl, float* Yg, int wave, int lane) {
+                                                const Pre& pre, float* Yl, float* Yg, int wave, int lane, float*) {
     Acc16 acc;
     acc.zero();
     gemm_xw_deep16(Xs, xld, L.in, net + L.w1, pre.w1, wave, lane, acc);
@@ -672,7 +675,7 @@ __device__ __forceinline__ void target_chain(const PopDev& d, uint32_t t, int ag
   __syncthreads();
   POP_MARK(31);
 
-  G::template first_layer<false>(Xs, L.xld, ta, d.actor, pre, buf, nullptr, wave, lane);
+  G::template first_layer<false>(Xs, L.xld, ta, d.actor, pre, buf, nullptr, wave, lane, stage);
   __syncthreads();
   POP_MARK(32);
   G::template hidden_layer<false>(buf, ta, d.actor, pre, nullptr, wave, lane, [&]() { pre.load(tc0, d.critic, wave, lane); }, stage);
@@ -699,7 +702,7 @@ __device__ __forceinline__ void target_chain(const PopDev& d, uint32_t t, int ag
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
     const float* tc = k == 0 ? tc0 : tc1;
-    G::template first_layer<false>(Xs, L.xld, tc, d.critic, pre, buf, nullptr, wave, lane);
+    G::template first_layer<false>(Xs, L.xld, tc, d.critic, pre, buf, nullptr, wave, lane, stage);
     __syncthreads();
     POP_MARK(36 + 4 * k);
     G::template hidden_layer<false>(buf, tc, d.critic, pre, nullptr, wave, lane,
@@ -747,7 +750,7 @@ __device__ __forceinline__ void actor_forward_ahead(const PopDev& d, int agent, 
   POP_MARK(56);
   pa.load(an, d.actor, wave, lane);
   const size_t act_off = ((size_t)agent * d.B + r0) * kH;
-  G::template first_layer<false>(Xs, xld, an, d.actor, pa, buf2, d.aH1 + act_off, wave, lane);
+  G::template first_layer<false>(Xs, xld, an, d.actor, pa, buf2, d.aH1 + act_off, wave, lane, stage);
   __syncthreads();
   POP_MARK(57);
   G::template hidden_layer<false>(buf2, an, d.actor, pa, d.aH2 + act_off, wave, lane, NoTail(), stage);
@@ -837,7 +840,7 @@ __device__ __forceinline__ void critic_chain(const PopDev& d, uint32_t t, int ne
   __syncthreads();
   POP_MARK(1);
 
-  const uint64_t mask1 = G::template first_layer<SIGNAL>(Xs, L.xld, cn, d.critic, pre, buf, d.cH1 + act_off, wave, lane);
+  const uint64_t mask1 = G::template first_layer<SIGNAL>(Xs, L.xld, cn, d.critic, pre, buf, d.cH1 + act_off, wave, lane, stage);
   __syncthreads();
   POP_MARK(2);
   typename G::WtBlock wt;                          // block 0 of W2 for the input-gradient product
@@ -1018,7 +1021,7 @@ __device__ __forceinline__ void actor_chain(const PopDev& d, uint32_t t, int age
   }
   __syncthreads();
 
-  mask_a1 = G::template first_layer<WAIT>(Xs, L.xld, an, d.actor, pre, buf, d.aH1 + act_off, wave, lane);
+  mask_a1 = G::template first_layer<WAIT>(Xs, L.xld, an, d.actor, pre, buf, d.aH1 + act_off, wave, lane, stage);
   __syncthreads();
   G::template hidden_layer<false>(buf, an, d.actor, pre, d.aH2 + act_off, wave, lane,
                          [&]() { if (!WAIT) pre.load(cn, d.critic, wave, lane); }, stage);
@@ -1045,7 +1048,7 @@ __device__ __forceinline__ void actor_chain(const PopDev& d, uint32_t t, int age
     __syncthreads();
   }
   POP_MARK(10);
-  const uint64_t mask_c1 = G::template first_layer<false>(Xs, L.xld, cn, d.critic, pre, buf, nullptr, wave, lane);
+  const uint64_t mask_c1 = G::template first_layer<false>(Xs, L.xld, cn, d.critic, pre, buf, nullptr, wave, lane, stage);
   __syncthreads();
   typename G::WtBlock wt;
   G::template hidden_layer<false>(buf, cn, d.critic, pre, nullptr, wave, lane, [&]() { G::load_wt(wt, cn + d.critic.w2, wave, lane); }, stage);

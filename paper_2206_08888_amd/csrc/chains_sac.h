@@ -81,7 +81,7 @@ __device__ __forceinline__ void sac_target_chain(const PopDev& d, uint32_t t, in
   POP_MARK(0);
   if (d.D <= kMaxIn) {                               // one trip to memory for all of the prologue
     SmallVec ab3, cw3a, cw3b;
-    InputTile<R> xin;
+    InputTile<R, G::kThr> xin;
     ab3.fetch(an + d.actor.b3, 2 * A, tid);
     cw3a.fetch(tc0 + d.critic.w3, kH, tid);
     cw3b.fetch(tc1 + d.critic.w3, kH, tid);
@@ -93,26 +93,26 @@ __device__ __forceinline__ void sac_target_chain(const PopDev& d, uint32_t t, in
     if (tid < 2) v_cb3[tid] = cb3;
     xin.put(Xs, L.xld, tid);
   } else {
-    stage_vector(v_ab3, an + d.actor.b3, 2 * A, tid);
-    stage_vector(v_cw3, tc0 + d.critic.w3, kH, tid);
-    stage_vector(v_cw3 + kH, tc1 + d.critic.w3, kH, tid);
+    stage_vector<G::kThr>(v_ab3, an + d.actor.b3, 2 * A, tid);
+    stage_vector<G::kThr>(v_cw3, tc0 + d.critic.w3, kH, tid);
+    stage_vector<G::kThr>(v_cw3 + kH, tc1 + d.critic.w3, kH, tid);
     if (tid < 2) v_cb3[tid] = (tid == 0 ? tc0 : tc1)[d.critic.b3];
     G::load_input(Xs, L.xld, rows, d.row, d.D + 2, d.O, R, tid);
   }
   __syncthreads();
   POP_MARK(1);
 
-  G::template first_layer<false>(Xs, L.xld, an, d.actor, pre, buf, nullptr, wave, lane);
+  G::template first_layer<false>(Xs, L.xld, an, d.actor, pre, buf, nullptr, wave, lane, stage);
   __syncthreads();
   POP_MARK(2);
   G::template hidden_layer<false>(buf, an, d.actor, pre, nullptr, wave, lane, [&]() { pre.load(tc0, d.critic, wave, lane); }, stage);
   __syncthreads();
   POP_MARK(3);
-  if (R <= 32 && 2 * A <= 16) head_mfma_split<R <= 32 ? R : 16, false>(buf, an + d.actor.w3, 2 * A, hd, kMaxHead, wave, lane, stage);
-  else head_mfma<R>(buf, an + d.actor.w3, 2 * A, hd, kMaxHead, wave, lane);
+  if (G::kStage > 0 && 2 * A <= 16) head_split<G, false>(buf, an + d.actor.w3, 2 * A, hd, kMaxHead, wave, lane, stage);
+  else head_mfma<R, G::kThr>(buf, an + d.actor.w3, 2 * A, hd, kMaxHead, wave, lane);
   __syncthreads();
   POP_MARK(4);
-  for (int e = tid; e < R * A; e += kThreads) {
+  for (int e = tid; e < R * A; e += G::kThr) {
     const int r = e / A, j = e - r * A;
     const float mu = hd[r * kMaxHead + j] + v_ab3[j];
     const float ls = fminf(fmaxf(hd[r * kMaxHead + A + j] + v_ab3[A + j], kLogStdMin), kLogStdMax);
@@ -132,7 +132,7 @@ __device__ __forceinline__ void sac_target_chain(const PopDev& d, uint32_t t, in
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
     const float* tc = k == 0 ? tc0 : tc1;
-    G::template first_layer<false>(Xs, L.xld, tc, d.critic, pre, buf, nullptr, wave, lane);
+    G::template first_layer<false>(Xs, L.xld, tc, d.critic, pre, buf, nullptr, wave, lane, stage);
     __syncthreads();
     POP_MARK(6 + 3 * k);
     G::template hidden_layer<false>(buf, tc, d.critic, pre, nullptr, wave, lane,
@@ -287,7 +287,7 @@ __device__ __forceinline__ void sac_actor_chain(const PopDev& d, uint32_t t, int
   __syncthreads();
   POP_MARK(21);
 
-  const uint64_t mask_a1 = G::template first_layer<false>(Xs, L.xld, an, d.actor, pre, buf, d.aH1 + act_off, wave, lane);
+  const uint64_t mask_a1 = G::template first_layer<false>(Xs, L.xld, an, d.actor, pre, buf, d.aH1 + act_off, wave, lane, stage);
   __syncthreads();
   G::template hidden_layer<false>(buf, an, d.actor, pre, d.aH2 + act_off, wave, lane,
                                   [&]() { pre.load(cn[0], d.critic, wave, lane); }, stage);
@@ -324,7 +324,7 @@ __device__ __forceinline__ void sac_actor_chain(const PopDev& d, uint32_t t, int
   typename G::WtBlock wt;
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
-    mask1[k] = G::template first_layer<false>(Xs, L.xld, cn[k], d.critic, pre, buf, nullptr, wave, lane);
+    mask1[k] = G::template first_layer<false>(Xs, L.xld, cn[k], d.critic, pre, buf, nullptr, wave, lane, stage);
     __syncthreads();
     mask2[k] = G::template hidden_layer<false>(buf, cn[k], d.critic, pre, nullptr, wave, lane, [&]() {
       if (k == 0) pre.load(cn[1], d.critic, wave, lane);

@@ -8,9 +8,9 @@ namespace pop {
 // 64 rows: the nine scratch blocks leave no room for the slabs of the target and actor products
 using SacRows64 = Rows32<2, false>;
 
-// PER_CU: workgroups that share a CU (registers to match): two of the narrow 16-row chains from 17 agents on
+// PER_CU: workgroups that share a CU (registers to match): two of the narrow 16-row chains, for tuning beyond 16 agents
 template <class G, int PER_CU = 1>
-__global__ __launch_bounds__(kThreads, PER_CU) void k_sac_target(PopDev d, uint32_t t) {
+__global__ __launch_bounds__(G::kThr, PER_CU * G::kThr / kThreads) void k_sac_target(PopDev d, uint32_t t) {
   extern __shared__ float lds[];
   int agent, chunk;
   POP_BLOCK_TIME(kTraceTarget, 0);
@@ -52,6 +52,8 @@ hipError_t setup_sac_kernels() {
   POP_SET_LDS(k_sac_target<SacRows64>);
   POP_SET_LDS(k_sac_target<Rows16Deep>);
   POP_SET_LDS(k_sac_target<Rows32Deep<1>>);
+  POP_SET_LDS(k_sac_target<Rows32x8>);
+  POP_SET_LDS(k_sac_target<Rows32Deep<1, 2, 1>>);
   POP_SET_LDS(k_sac_actor<Rows16>);
   POP_SET_LDS(k_sac_actor<Rows32<1>>);
   POP_SET_LDS(k_sac_actor<SacRows64>);
@@ -83,9 +85,11 @@ hipError_t launch_sac_target(const PopDev& d, uint32_t t, hipStream_t s) {
   const int vec = vec_sac_target(d);
   if (d.D > kMaxIn) {                                // wide inputs: 16 rows, pipelined first layers
     if (d.rows_t == 16) k_sac_target<Rows16Deep><<<grid, block, chain_bytes<Rows16>(d.D, vec, Rows16::kStageForward, kSacScratch), s>>>(d, t);
+    else if (d.rows_t == 32 && (int)grid.x <= kCUs) k_sac_target<Rows32Deep<1, 2, 1>><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec, Rows32<1>::kStage, kSacScratch), s>>>(d, t);
     else if (d.rows_t == 32) k_sac_target<Rows32Deep<1>><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec, Rows32<1>::kStage, kSacScratch), s>>>(d, t);
     else return hipErrorInvalidValue;
   } else if (d.rows_t == 16) k_sac_target<Rows16, 2><<<grid, block, chain_bytes<Rows16>(d.D, vec, Rows16::kStageForward, kSacScratch), s>>>(d, t);
+  else if (d.rows_t == 32 && (int)grid.x <= kCUs) k_sac_target<Rows32x8><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec, Rows32<1>::kStage, kSacScratch), s>>>(d, t);
   else if (d.rows_t == 32) k_sac_target<Rows32<1>><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec, Rows32<1>::kStage, kSacScratch), s>>>(d, t);
   else k_sac_target<SacRows64><<<grid, block, chain_bytes<SacRows64>(d.D, vec, SacRows64::kStage, kSacScratch), s>>>(d, t);
   return hipGetLastError();

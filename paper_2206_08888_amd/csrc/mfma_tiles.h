@@ -483,6 +483,7 @@ __device__ inline void gemm256_dz2(const float* __restrict__ Xl, int ldx, const 
   }
 }
 
+template <int N> struct IntC { static constexpr int value = N; };
 struct NoTail { __device__ inline void operator()() const {} };
 
 // ---------------------------------------------------------------------------------------------
@@ -551,6 +552,13 @@ struct SlabItem {                          // this thread's share of a slab: Q t
     const float* p = Xl + (32 * q + tid / kPerRow) * kLda + 64 * s + E * (tid % kPerRow);
 #pragma unroll
     for (int i = 0; i < E / 4; ++i) x[q][i] = *reinterpret_cast<const f32x4*>(p + 4 * i);
+  }
+  // of a tile with rows of ldx floats, the last four of which hold zeros: they stand in for what lies beyond
+  __device__ inline void read_to(const float* __restrict__ Xl, int ldx, int s, int tid, int q) {
+    const float* p = Xl + (32 * q + tid / kPerRow) * ldx;
+    const int c = 64 * s + E * (tid % kPerRow);
+#pragma unroll
+    for (int i = 0; i < E / 4; ++i) x[q][i] = *reinterpret_cast<const f32x4*>(p + (c + 4 * i < ldx - 4 ? c + 4 * i : ldx - 4));
   }
   __device__ inline void put(float* __restrict__ slab, int tid, int q) const {
     Split8 v;
@@ -731,6 +739,103 @@ struct SplitProduct {
     POP_MARK(24);
   }
 };
+
+// gemm_xw_deep's product (the same instructions in the same order, so the same bits) with the input tile split once per
+// workgroup, a slab of 64 columns at a time, instead of by every wavefront: per wavefront and block of 16 rows of W 44 NT + 11 vector
+// instructions beside 6 NT matrix instructions (32 rows), where there were 44 NT + 44.  Four weight blocks in registers, the two of `pre` the first;
+// blocks beyond K (a request ahead) read as zero.  slabs: as for gemm256, idle when the function is called and, after the next barrier, again.
+template <int MT, int NT>
+__device__ inline void gemm_xw_slabs(const float* __restrict__ Xl, int ldx, int K, const float* __restrict__ W,
+                                     const SmallW<NT>& pre, float* __restrict__ slabs, int wave, int lane, Acc<MT, NT>& acc) {
+  using Item = SlabItem<MT, NT>;
+  const int half = lane >> 5, l32 = lane & 31, tid = 64 * wave + lane;
+  const int nb = (K + 15) >> 4;
+  uint32_t off = 4u * (uint32_t)(4 * half * kH + tile_col<NT>(wave, 0, lane));
+  Acc<MT, NT> low;
+  low.zero();
+  float b[4][NT][8];
+  auto request = [&](float (&dst)[NT][8], int blk) {
+    const WeightsRsrc Wr = weights_rsrc(W + 16 * blk * kH, (K - 16 * blk) * kH);      // rows at or beyond K are zero
+    asm("" : "+v"(off));                              // or copies of it are kept for each block in flight
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const auto v = rsrc_load_cols<NT>(Wr, off + 4 * (8 * (e >> 2) + (e & 3)) * kH, 0);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) dst[nt][e] = col_of(v, nt);
+    }
+  };
+  Item item;
+  float* cur = slabs;
+  float* nxt = slabs + slab_floats<MT>();
+  Split8 x[2][MT];
+  auto read_x = [&](Split8 (&dst)[MT], const float* slab, int blk) {                  // columns 16 blk + 8 s + 4 half of the slab
+    const __bf16* p = reinterpret_cast<const __bf16*>(slab) + l32 * kSlabLd + 16 * blk + 4 * half;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        const __bf16* r = p + (q * 32 * MT + 32 * mt) * kSlabLd;
+        const bf16x4 lo = *reinterpret_cast<const bf16x4*>(r), hi = *reinterpret_cast<const bf16x4*>(r + 8);
+        dst[mt].t[q] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+      }
+  };
+  // block B of the slab; FULL: the slab has four and this thread's share of the next one is staged beside them
+  auto block = [&](auto B_, auto FULL_, int s, bool next) {
+    constexpr int B = decltype(B_)::value;
+    constexpr bool FULL = decltype(FULL_)::value, stage = FULL && B == 0, put = FULL && B >= 1 && B <= Item::Q;
+    constexpr int M = kSplitTerms * MT * NT;
+    Split8 ws[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) split8(b[B][nt], ws[nt]);
+    request(b[B], 4 * s + B + 4);
+    if (FULL && B == 3) __syncthreads();             // the next slab is complete
+    if (next) read_x(x[(B + 1) & 1], B == 3 ? nxt : cur, (B + 1) & 3);
+    if (stage) {
+#pragma unroll
+      for (int q = 0; q < Item::Q; ++q) item.read_to(Xl, ldx, s + 1, tid, q);
+    }
+    if (put) item.put(nxt, tid, B - 1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < kSplitTerms; ++q)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          f32x16& c = q == kSplitTerms - 1 ? acc.t[mt][nt] : low.t[mt][nt];
+          c = mfma32_bf16(x[B & 1][mt].t[kTermX[q]], ws[nt].t[kTermW[q]], c);
+        }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) b[i][nt][e] = pre.w[2 * i + (e >> 2)][nt][e & 3];
+  request(b[2], 2);
+  request(b[3], 3);
+#pragma unroll
+  for (int q = 0; q < Item::Q; ++q) item.read_to(Xl, ldx, 0, tid, q);
+#pragma unroll
+  for (int q = 0; q < Item::Q; ++q) item.put(cur, tid, q);
+  __syncthreads();
+  read_x(x[0], cur, 0);
+  int s = 0;
+#pragma unroll 1
+  for (; 4 * s + 4 <= nb; ++s) {                     // whole slabs: no branch inside
+    block(IntC<0>(), IntC<1>(), s, true);
+    block(IntC<1>(), IntC<1>(), s, true);
+    block(IntC<2>(), IntC<1>(), s, true);
+    block(IntC<3>(), IntC<1>(), s, true);
+    float* q = cur; cur = nxt; nxt = q;
+  }
+  const int rem = nb - 4 * s;
+  if (rem > 0) block(IntC<0>(), IntC<0>(), s, rem > 1);
+  if (rem > 1) block(IntC<1>(), IntC<0>(), s, rem > 2);
+  if (rem > 2) block(IntC<2>(), IntC<0>(), s, false);
+  acc.add_finite(low);
+}
 
 template <int MT, bool TRANSPOSED, bool SLABS = true, int NT = 2, class Tail>
 __device__ inline void gemm256(const float* __restrict__ Xl, const float* __restrict__ W, WeightRaw<TRANSPOSED, NT>& b0,

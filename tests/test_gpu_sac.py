@@ -153,8 +153,8 @@ def test_agent_in_population_equals_agent_alone_bit_for_bit():
 
 @pytest.mark.parametrize("P", [20, 36])
 def test_mid_size_populations_use_the_wider_chains_and_still_match(P):
-    """Past the 16-row class every chain has its own rows per workgroup: P = 20 runs 16-row target, 64-row critic
-    and 32-row actor chains, P = 36 32-row chains throughout.  First and last agent against the oracle, two free
+    """Past the 16-row class every chain has its own rows per workgroup: P = 20 runs 64-row critic
+    and 32-row target and actor chains, P = 36 32-row chains throughout.  First and last agent against the oracle, two free
     steps."""
     hps = sac_hparams(P)
     gpu, orc, agents = make_sac_pair(P=P, capacity=600, hps=hps, agents=[0, P - 1])

@@ -1090,6 +1090,12 @@ __device__ __forceinline__ void actor_chain(const PopDev& d, uint32_t t, int age
   if (AS == kMaxAct || A <= 16) head_split<G, true>(buf, cn + d.critic.w1 + d.O * kH, A, head, AS, wave, lane, stage);   // da
   else head_mfma_t<R, G::kThr>(buf, cn + d.critic.w1 + d.O * kH, A, head, AS, wave, lane);
   G::load_wt(wt, an + d.actor.w2, wave, lane);       // block 0 of the actor's input-gradient product
+  float w3[AS];                                      // and the head's weights of this thread's hidden unit
+#pragma unroll
+  for (int j = 0; j < AS; ++j) {
+    w3[j] = 0.0f;
+    if (j < A) w3[j] = (an + d.actor.w3)[unit * A + j];
+  }
   __syncthreads();
   for (int e = tid; e < R * AS; e += G::kThr) {
     const int j = e % AS;
@@ -1102,6 +1108,7 @@ __device__ __forceinline__ void actor_chain(const PopDev& d, uint32_t t, int age
   __syncthreads();
   if (tid < A) {
     float s = 0.0f;
+#pragma unroll 16
     for (int r = 0; r < R; ++r) s += dz3[r * AS + tid];
     put<WAIT>(part + kAP_db3 + tid, s);
   }
@@ -1113,11 +1120,6 @@ __device__ __forceinline__ void actor_chain(const PopDev& d, uint32_t t, int age
   {                                                 // actor head backward, one thread per hidden unit
     const int c = unit;
     constexpr int RB = (AS == kMaxAct ? 4 : 2) / UR::kOwn;   // rows of a half in flight (the wide rows cost three times the registers)
-    float w3[AS];
-#pragma unroll
-    for (int j = 0; j < AS; ++j) w3[j] = (an + d.actor.w3)[c * A + (j < A ? j : 0)];
-#pragma unroll
-    for (int j = 0; j < AS; ++j) w3[j] = j < A ? w3[j] : 0.0f;
 #pragma unroll
     for (int o = 0; o < UR::kOwn; ++o)
 #pragma unroll

@@ -161,18 +161,24 @@ __device__ __forceinline__ void sac_target_chain(const PopDev& d, uint32_t t, in
 // Backward through the actor's head for one chunk, thread c = hidden unit c:
 //   gW3[c][j] = sum_r h2[r][c] dz3[r][j];  dz2[r][c] = [h2[r][c] > 0] sum_j dz3[r][j] W3[c][j]
 // buf: h2 in, dz2 out (LDS tile, row stride kLda); dz3: [R][kMaxHead], columns >= H2 hold zeros; W3: the
-// head's weights [256][H2] in global memory;
+// head's weights [256][H2];
 // NC: head columns handled (a multiple of 4, >= H2).
+// w3: the unit's row of the head's weights, requested ahead by sac_head_row in pairs (H2 is even, a row 8-byte aligned): a lane's
+// row lies H2 floats from its neighbour's, so that a load touches up to 64 cache lines whatever its width.
+template <int NC>
+__device__ __forceinline__ void sac_head_row(f32x2 (&w3)[NC / 2], const float* __restrict__ W3, int H2, int c) {
+#pragma unroll
+  for (int j = 0; j < NC / 2; ++j) {
+    w3[j] = f32x2{0.0f, 0.0f};
+    if (2 * j < H2) w3[j] = *reinterpret_cast<const f32x2*>(W3 + c * H2 + 2 * j);
+  }
+}
 template <class G, int NC>
-__device__ __forceinline__ void sac_head_backward(float* buf, const float* dz3, const float* __restrict__ W3, int H2,
+__device__ __forceinline__ void sac_head_backward(float* buf, const float* dz3, const f32x2 (&w3)[NC / 2], int H2,
                                                   float* zg, float* part, float* cross, int tid) {
   using UR = UnitRows<G>;
   const int c = tid & (kH - 1);
-  float w3[NC], sums[UR::kOwn][NC + 1];              // dW3 by column, db2
-#pragma unroll
-  for (int j = 0; j < NC; ++j) w3[j] = W3[c * H2 + (j < H2 ? j : 0)];
-#pragma unroll
-  for (int j = 0; j < NC; ++j) w3[j] = j < H2 ? w3[j] : 0.0f;
+  float sums[UR::kOwn][NC + 1];                      // dW3 by column, db2
 #pragma unroll
   for (int o = 0; o < UR::kOwn; ++o)
 #pragma unroll
@@ -194,7 +200,7 @@ __device__ __forceinline__ void sac_head_backward(float* buf, const float* dz3, 
 #pragma unroll
           for (int k = 0; k < 4; ++k) {
             sums[o][4 * q + k] += h * g[k];
-            dh += g[k] * w3[4 * q + k];
+            dh += g[k] * w3[2 * q + (k >> 1)][k & 1];
           }
         }
         const float z = h > 0.0f ? dh : 0.0f;
@@ -375,33 +381,40 @@ __device__ __forceinline__ void sac_actor_chain(const PopDev& d, uint32_t t, int
     POP_MARK(26 + k);
   }
 
-  // through the sampling into the actor's head
+  // through the sampling into the actor's head and back through it, a thread per hidden unit; NC columns in registers
   const float ab = alpha * invB;
-  for (int e = tid; e < R * kMaxHead; e += G::kThr) {
-    const int r = e / kMaxHead, c = e - r * kMaxHead;
-    float g = 0.0f;
-    if (c < H2) {
-      const int j = c < A ? c : c - A, o = r * kSs + j;
-      const float a = ap[o];
-      const float du = (da1[o] + da2[o]) * (1.0f - a * a) + ab * 2.0f * a;
-      g = c < A ? du : (du * hd[r * kMaxHead + A + j] - ab) * ins[o];
-    }
-    dz3[e] = g;                                      // unused columns are kept at zero
-  }
-#pragma unroll
-  for (int i = 0; i < R / W; ++i)                    // h2 of the actor back into the tile
-    *reinterpret_cast<f32x4*>(&buf[(W * i + (tid >> 6)) * kLda + 4 * (tid & 63)]) = h2r[i];
-  __syncthreads();
-  if (tid < H2) {
-    float s = 0.0f;
-    for (int r = 0; r < R; ++r) s += dz3[r * kMaxHead + tid];
-    part[kAP_db3 + tid] = s;
-  }
-  POP_MARK(28);
-  // actor head backward, one thread per hidden unit; the common small heads stay in 16 registers
   float* cross = stage;                              // the slabs are idle here
-  if (H2 <= 16) sac_head_backward<G, 16>(buf, dz3, an + d.actor.w3, H2, d.adZ2 + act_off, part, cross, tid);
-  else sac_head_backward<G, kMaxHead>(buf, dz3, an + d.actor.w3, H2, d.adZ2 + act_off, part, cross, tid);
+  auto head_back = [&](auto NC_) {
+    constexpr int NC = decltype(NC_)::value;
+    f32x2 w3[NC / 2];
+    sac_head_row<NC>(w3, an + d.actor.w3, H2, tid & (kH - 1));
+    for (int e = tid; e < R * kMaxHead; e += G::kThr) {
+      const int r = e / kMaxHead, c = e - r * kMaxHead;
+      float g = 0.0f;
+      if (c < H2) {
+        const int j = c < A ? c : c - A, o = r * kSs + j;
+        const float a = ap[o];
+        const float du = (da1[o] + da2[o]) * (1.0f - a * a) + ab * 2.0f * a;
+        g = c < A ? du : (du * hd[r * kMaxHead + A + j] - ab) * ins[o];
+      }
+      dz3[e] = g;                                      // unused columns are kept at zero
+    }
+#pragma unroll
+    for (int i = 0; i < R / W; ++i)                    // h2 of the actor back into the tile
+      *reinterpret_cast<f32x4*>(&buf[(W * i + (tid >> 6)) * kLda + 4 * (tid & 63)]) = h2r[i];
+    __syncthreads();
+    if (tid < H2) {
+      float s = 0.0f;
+#pragma unroll 16
+      for (int r = 0; r < R; ++r) s += dz3[r * kMaxHead + tid];
+      part[kAP_db3 + tid] = s;
+    }
+    POP_MARK(28);
+    sac_head_backward<G, NC>(buf, dz3, w3, H2, d.adZ2 + act_off, part, cross, tid);
+  };
+  if (H2 <= 16) head_back(IntC<16>());
+  else if (H2 <= 36) head_back(IntC<36>());
+  else head_back(IntC<kMaxHead>());
   __syncthreads();
   POP_MARK(29);
   G::template input_grad_to_global<false>(buf, an + d.actor.w2, wt, mask_a1, d.adZ1 + act_off, part + kAP_db1, wave, lane, stage);

@@ -474,6 +474,13 @@ struct Rows32Deep : Rows32<MT, true, NT> {
   }
 };
 
+// Critic chains that have a CU to themselves even with the slabs over the input tile (from 337 inputs on, or few workgroups): slabs
+// beside it and eight wavefronts.  us/step at 376 / 17, before / so: 20 TD3 agents 247 / 238, 32 SAC agents 430 / 419, 40 TD3 agents
+// 495 / 485; 8 TD3 agents of 111 / 8 113.6 / 109.8.
+struct Rows32Wide : Rows32Deep<1, 2, 1> {
+  static constexpr bool kStageOnInput = false;
+};
+
 struct Rows16Deep : Rows16 {
   __device__ static inline void load_input(float* Xl, int xld, const float* rows, int row_stride, int c0, int n, int valid,
                                            int tid) {
@@ -906,10 +913,12 @@ __device__ __forceinline__ void critic_chain(const PopDev& d, uint32_t t, int ne
     }
     uint32_t* mg = d.cmask + ((size_t)net * (d.B / 32) + r0 / 32) * kH + c;
     static_assert(R >= 32 || !SIGNAL, "16-row critic chains hand nothing on inside their launch");
-    static_assert(R == 64 || !UR::kCross, "half a pattern word to a thread");
+    static_assert(R == 64 || !UR::kCross || !SIGNAL, "pattern words handed on inside a launch go out whole");
     if (R == 64) {
 #pragma unroll
       for (int o = 0; o < UR::kOwn; ++o) put_word<SIGNAL>(mg + (UR::row0(o, tid) / 32) * kH, active[o]);
+    } else if (UR::kCross) {                         // 32 rows: half of the word
+      reinterpret_cast<uint16_t*>(mg)[tid >> 8] = (uint16_t)active[0];
     } else if (R == 32) {
       put_word<SIGNAL>(mg, active[0] | active[UR::kOwn - 1] << 16);
     } else {

@@ -162,6 +162,8 @@ hipError_t setup_kernels() {
   POP_SET_LDS(k_target<Rows32<1>>);
   POP_SET_LDS(k_target<Rows64>);
   POP_SET_LDS(k_critic<Rows32<1>>);
+  POP_SET_LDS(k_critic<Rows32x8>);
+  POP_SET_LDS(k_critic<Rows32Wide>);
   POP_SET_LDS(k_critic<Rows64>);
   POP_SET_LDS(k_critic<Rows32Deep<1, 4>>);
   POP_SET_LDS(k_actor<Rows16>);
@@ -225,8 +227,12 @@ hipError_t launch_critic(const PopDev& d, uint32_t t, hipStream_t s) {
   const dim3 grid(xcd_grid(2 * d.P, d.B / d.rows_c)), block(kThreads);
   if (d.D > kMaxIn) {                                // wide inputs (SAC): 32 rows, pipelined first layer
     if (d.rows_c != 32) return hipErrorInvalidValue;
-    k_critic<Rows32Deep<1, 4>><<<grid, block, CriticMap<Rows32Deep<1, 4>>(d.D).bytes(), s>>>(d, t);
-  } else if (d.rows_c == 32) k_critic<Rows32<1>><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec_critic(d)), s>>>(d, t);
+    const size_t over = CriticMap<Rows32Deep<1, 4>>(d.D).bytes(), beside = CriticMap<Rows32Wide>(d.D).bytes();
+    if (beside <= (size_t)kLdsPerCU && (2 * over > (size_t)kLdsPerCU || (int)grid.x <= kCUs))
+      k_critic<Rows32Wide><<<grid, dim3(Rows32Wide::kThr), beside, s>>>(d, t);
+    else k_critic<Rows32Deep<1, 4>><<<grid, block, over, s>>>(d, t);
+  } else if (d.rows_c == 32 && (int)grid.x <= kCUs) k_critic<Rows32x8><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec_critic(d)), s>>>(d, t);
+  else if (d.rows_c == 32) k_critic<Rows32<1>><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec_critic(d)), s>>>(d, t);
   else k_critic<Rows64><<<grid, dim3(Rows64::kThr), chain_bytes<Rows32<2>>(d.D, vec_critic(d)), s>>>(d, t);
   return hipGetLastError();
 }

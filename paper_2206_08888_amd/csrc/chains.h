@@ -329,6 +329,10 @@ using Rows64 = Rows32<2, true, 1>;
 // anyway, and eight would leave no registers): actor chain of 20 TD3 agents 45.1 -> 43.0 us on a slower card, per step 20 agents
 // 120 -> 117 (training rounds), 20 agents of 376 / 17 267 -> 263, 23 agents of 11 / 3 174 -> 168, 32 SAC agents 225 -> 214, of 376 / 17 455 -> 451.  Target chains with the input tile through the slabs
 // (gemm_xw_slabs): 20 agents of 376 / 17 263 -> 248, 32 SAC agents of 376 / 17 443 -> 432 (target chain 86 -> 70 us, a first layer 14.5 -> 12.5).
+// Likewise wherever LDS or registers keep a CU to one workgroup in any case, however many there are: SAC's target and actor chains,
+// wide actor chains, wide target chains from some 250 inputs on.  us/step, four / eight wavefronts: SAC at 17 / 6 310.9 / 277.6 with 33 agents,
+// 416.5 / 381.9 with 64, 1593 / 1463 with 256, at 376 / 17 857.6 / 792.7 with 64; TD3 at 376 / 17 481.8 / 442.5 with 40, at 111 / 8 646.3 / 603.5 with 100;
+// shared critics at 376 / 17 559.5 / 525.8 with 64.
 using Rows32x8 = Rows32<1, true, 1>;
 
 struct Rows16 {                                      // 16 rows on v_mfma_f32_16x16x4_f32 (mfma_tiles16.h)

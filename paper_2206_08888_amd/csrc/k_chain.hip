@@ -150,14 +150,12 @@ hipError_t setup_kernels() {
   POP_SET_LDS(k_target<Rows16Deep, 1, kSacMaxAct>);
   POP_SET_LDS(k_target<Rows32Deep<1>, 2, kSacMaxAct>);
   POP_SET_LDS(k_actor<Rows16Deep, 1, false, kSacMaxAct>);
-  POP_SET_LDS(k_actor<Rows32Deep<1>, 1, false, kSacMaxAct>);
   POP_SET_LDS(k_target<Rows16Deep>);
   POP_SET_LDS(k_target<Rows32Deep<1>, 2>);
   POP_SET_LDS(k_target<Rows32x8>);
   POP_SET_LDS(k_target<Rows32Deep<1, 2, 1>>);
   POP_SET_LDS(k_target<Rows32Deep<1, 2, 1>, 2, kSacMaxAct>);
   POP_SET_LDS(k_actor<Rows16Deep>);
-  POP_SET_LDS(k_actor<Rows32Deep<1>>);
   POP_SET_LDS(k_target<Rows16>);
   POP_SET_LDS(k_target<Rows32<1>>);
   POP_SET_LDS(k_target<Rows64>);
@@ -205,20 +203,21 @@ size_t act_lds_bytes(const PopDev& d) { return ActMap(d.O).bytes(); }
 
 hipError_t launch_target(const PopDev& d, uint32_t t, hipStream_t s) {
   const dim3 grid(xcd_grid(d.P, d.B / d.rows_t)), block(kThreads);
+  const bool alone = (int)grid.x <= kCUs;            // a CU to each workgroup; the LDS may leave no other choice
   if (d.A > kMaxAct) {                               // wide actions: scratch rows of kSacMaxAct floats, first layers as for wide inputs
     const size_t b32 = chain_bytes<Rows32<1>>(d.D, vec_target(d), Rows32<1>::kStage, kWideScratch);
     if (d.rows_t == 16) k_target<Rows16Deep, 1, kSacMaxAct><<<grid, block, chain_bytes<Rows16>(d.D, vec_target(d), Rows16::kStageForward, kWideScratch), s>>>(d, t);
-    else if (d.rows_t == 32 && (int)grid.x <= kCUs) k_target<Rows32Deep<1, 2, 1>, 2, kSacMaxAct><<<grid, dim3(Rows32x8::kThr), b32, s>>>(d, t);
+    else if (d.rows_t == 32 && (alone || 2 * b32 > (size_t)kLdsPerCU)) k_target<Rows32Deep<1, 2, 1>, 2, kSacMaxAct><<<grid, dim3(Rows32x8::kThr), b32, s>>>(d, t);
     else if (d.rows_t == 32) k_target<Rows32Deep<1>, 2, kSacMaxAct><<<grid, block, b32, s>>>(d, t);
     else return hipErrorInvalidValue;
   } else if (d.D > kMaxIn) {                         // wide inputs: pipelined first layers, 16 or 32 rows
     const size_t b32 = chain_bytes<Rows32<1>>(d.D, vec_target(d));
     if (d.rows_t == 16) k_target<Rows16Deep><<<grid, block, chain_bytes<Rows16>(d.D, vec_target(d), Rows16::kStageForward), s>>>(d, t);
-    else if (d.rows_t == 32 && (int)grid.x <= kCUs) k_target<Rows32Deep<1, 2, 1>><<<grid, dim3(Rows32x8::kThr), b32, s>>>(d, t);
+    else if (d.rows_t == 32 && (alone || 2 * b32 > (size_t)kLdsPerCU)) k_target<Rows32Deep<1, 2, 1>><<<grid, dim3(Rows32x8::kThr), b32, s>>>(d, t);
     else if (d.rows_t == 32) k_target<Rows32Deep<1>, 2><<<grid, block, b32, s>>>(d, t);
     else return hipErrorInvalidValue;
   } else if (d.rows_t == 16) k_target<Rows16><<<grid, block, chain_bytes<Rows16>(d.D, vec_target(d), Rows16::kStageForward), s>>>(d, t);
-  else if (d.rows_t == 32 && (int)grid.x <= kCUs) k_target<Rows32x8><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec_target(d)), s>>>(d, t);
+  else if (d.rows_t == 32 && alone) k_target<Rows32x8><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec_target(d)), s>>>(d, t);
   else if (d.rows_t == 32) k_target<Rows32<1>><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec_target(d)), s>>>(d, t);
   else k_target<Rows64><<<grid, dim3(Rows64::kThr), chain_bytes<Rows32<2>>(d.D, vec_target(d)), s>>>(d, t);
   return hipGetLastError();
@@ -275,14 +274,12 @@ hipError_t launch_actor(const PopDev& d, uint32_t t, hipStream_t s) {
   if (d.A > kMaxAct) {
     if (d.actor_ahead) return hipErrorInvalidValue;
     if (d.rows_a == 16) k_actor<Rows16Deep, 1, false, kSacMaxAct><<<grid, block, chain_bytes<Rows16>(d.D, vec_actor(d), Rows16::kStage, kWideScratch), s>>>(d, t);
-    else if (d.rows_a == 32 && (int)grid.x <= kCUs) k_actor<Rows32Deep<1, 2, 1>, 2, false, kSacMaxAct><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec_actor(d), Rows32<1>::kStage, kWideScratch), s>>>(d, t);
-    else if (d.rows_a == 32) k_actor<Rows32Deep<1>, 1, false, kSacMaxAct><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec_actor(d), Rows32<1>::kStage, kWideScratch), s>>>(d, t);
+    else if (d.rows_a == 32) k_actor<Rows32Deep<1, 2, 1>, 2, false, kSacMaxAct><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec_actor(d), Rows32<1>::kStage, kWideScratch), s>>>(d, t);
     else return hipErrorInvalidValue;
   } else if (d.D > kMaxIn) {
     if (d.actor_ahead) return hipErrorInvalidValue;
     if (d.rows_a == 16) k_actor<Rows16Deep><<<grid, block, chain_bytes<Rows16>(d.D, vec_actor(d)), s>>>(d, t);
-    else if (d.rows_a == 32 && (int)grid.x <= kCUs) k_actor<Rows32Deep<1, 2, 1>><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec_actor(d)), s>>>(d, t);
-    else if (d.rows_a == 32) k_actor<Rows32Deep<1>><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec_actor(d)), s>>>(d, t);
+    else if (d.rows_a == 32) k_actor<Rows32Deep<1, 2, 1>><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec_actor(d)), s>>>(d, t);
     else return hipErrorInvalidValue;
   } else if (d.actor_ahead) {
     if (d.rows_a != 16) return hipErrorInvalidValue;

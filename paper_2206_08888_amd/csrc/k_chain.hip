@@ -185,7 +185,7 @@ hipError_t setup_kernels() {
 }
 
 // Rows per workgroup (pop_dev.h): (target, critic, actor) = (16, 32 or 64, 16) for small
-// populations, else (32, 32, 32), from 128 agents on (64, 64, 64).
+// populations, else (32, 32, 32), from 104 agents on (64, 64, 64); shared critics from 56 on (64, 64, 32).
 // LDS of the largest chain workgroup of a TD3 step at these shapes (the launches below ask for what each needs)
 size_t td3_lds_bytes(const PopDev& d) {
   auto chain = [&](int rows, int vec, bool back, int regions) {

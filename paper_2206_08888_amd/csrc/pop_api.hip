@@ -188,14 +188,19 @@ void fill_dims(const pop_config& c, PopDev& d) {
   // Rows per workgroup of the layer chains.  16 for the target and actor chains of small
   // populations: those parts have only 8 P workgroups at 32 rows, well under the 256 CUs, and
   // their latency is what a step waits for; 16-row tiles halve the matrix time of every
-  // product by spreading it over twice the CUs.  Else 32, two workgroups per CU; 64, one per CU, once the 32-row target
-  // chains alone fill the chip's 512 places twice over (P >= 128): a weight is then read and split for twice the rows,
-  // which pays as soon as there is enough work for the other rounds to hide the tails -- 558 -> 535 us/step at P = 128, 1103 -> 1043
-  // at P = 256, shared critics 613 -> 610 at P = 160, 972 -> 935 at P = 256; equal at P = 96, 331 -> 349 at P = 72.
+  // product by spreading it over twice the CUs.  Else 32, two workgroups per CU; 64, one per CU on
+  // eight wavefronts, for large populations: a weight is then read and split for twice the rows.  TD3 from 104 agents on, where the rounds
+  // hide the coarser tails (us/step, 32 / 64 rows: 359.9 / 372.8 at P = 88, 388.6 / 392.6 at 96, 428.3 / 423.3 at 104, 457.2 / 446.8 at 112, 488.7 / 478.8 at
+  // 120, 773.4 / 737.1 at 192, 1007 / 925 at 256).  Shared critics from 56 agents on for the target and critic chains, which always share a
+  // launch there, with actor chains of 32 rows (us/step, all 32 / all 64 / 64, 64, 32: 207.5 / 210.5 / 207.1 at P = 52, 224.6 / 219.8 / 214.0 at 56, 282.5 /
+  // 303.1 / 280.3 at 72, 304.0 / 311.3 / 290.2 at 80, 458.1 / 458.0 / 433.6 at 128, 562.9 / 583.4 / 546.1 at 160, 893.5 / 896.2 / 874.8 at 256).
   const int cls = (int64_t)c.P * (c.batch / 16) <= kCUs ? 0 : 1;   // 16-row chains of a part get a CU each
   const pop_tuning& u = c.tuning;
-  const bool many = c.algo != POP_ALGO_SAC && !u.rows_target && !u.rows_critic && !u.rows_actor && !u.rows_critic1 && (int64_t)c.P * (c.batch / 32) >= 4 * kCUs;
-  d.rows_t = d.rows_a = cls == 0 ? 16 : many ? 64 : 32;
+  const bool shared = c.algo == POP_ALGO_TD3_SHARED;
+  const bool many = c.algo != POP_ALGO_SAC && !u.rows_target && !u.rows_critic && !u.rows_actor && !u.rows_critic1 &&
+                    4 * (int64_t)c.P * (c.batch / 32) >= (shared ? 7 : 13) * (int64_t)kCUs;
+  d.rows_t = cls == 0 ? 16 : many ? 64 : 32;
+  d.rows_a = many && shared ? 32 : d.rows_t;
   // Beside 16 P target workgroups of 16 rows, 64-row critic chains (8 P workgroups) keep the fused
   // target/critic launch of a small population within one workgroup per CU.
   d.rows_c = cls == 1 && !many ? 32 : 64;

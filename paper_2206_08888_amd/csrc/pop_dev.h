@@ -87,7 +87,7 @@ struct PopDev {
   float* sloss;                // shared critics: [2][groups] partial losses
   int P, O, A, D, B, row;      // D = O + A; row = 2 O + A + 2 floats
   int rows_t, rows_c, rows_a;  // batch rows per workgroup of the target / critic / actor chain: (16, 32 or 64, 16) for
-                               // small populations, else (32, 32, 32), from 128 agents on (64, 64, 64)
+                               // small populations, else (32, 32, 32), from 104 agents on (64, 64, 64); shared critics from 56 on (64, 64, 32)
   int rows_c1;                 // rows per workgroup of critic 1's chain: rows_c, or 16 where the target workgroups run it (k_chain.hip)
   int cstride;                 // chunk slots per network in cpart: B / min(rows_c1, rows_c)
   int half_tiles;              // the stand-alone weight-gradient launch runs tiles of half the width (k_wgrad_adam.hip)

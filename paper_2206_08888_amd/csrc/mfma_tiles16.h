@@ -38,7 +38,9 @@ struct Acc16 {
 __device__ inline f32x4 mfma16(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
 // the weights one lane needs for a 16-deep block
-//   forward  (TRANSPOSED = false): w[j][nt] = W[16 i + 4 kq + j][64 wave + 4 c + nt]
+//   forward  (TRANSPOSED = false): w[j][nt] = W[16 i + k16(kq, j)][64 wave + 4 c + nt], k16 = 8 (kq >> 1) + 4 (j >> 1) + 2 (kq & 1) + (j & 1):
+//     lane groups kq and kq + 1 then read the two rows, two apart, that share a line of W2 (w2_index), and a load takes 8 whole lines; as
+//     rows 4 kq + j it took 16 half lines (10 agents 75.0 us/step with row-major matrices, 76.5 with half lines here and in WeightStage16)
 //   backward (TRANSPOSED = true):  w[nt][j] = W[64 wave + 4 c + nt][16 i + 4 kq + j]
 template <bool TRANSPOSED>
 struct WeightBlock16 {
@@ -47,9 +49,10 @@ struct WeightBlock16 {
   __device__ inline void load(const float* __restrict__ W, int i, int wave, int lane) {
     static_assert(!TRANSPOSED, "read from memory as WeightStage16");
     const WeightsRsrc r = weights_rsrc(W, kH * kH);
-    const uint32_t off = 4u * (uint32_t)w2_index(4 * (lane >> 4), 64 * wave + 4 * (lane & 15));
+    const int kq = lane >> 4;
+    const uint32_t off = 4u * (uint32_t)w2_index(8 * (kq >> 1) + 2 * (kq & 1), 64 * wave + 4 * (lane & 15));
 #pragma unroll
-    for (int j = 0; j < 4; ++j) w[j] = rsrc_load4(r, off + 4 * w2_index(j, 0), w2_index(16 * i, 0));
+    for (int j = 0; j < 4; ++j) w[j] = rsrc_load4(r, off + 4 * w2_index(j & 1, 0), w2_index(16 * i + 4 * (j >> 1), 0));
   }
 };
 
@@ -57,6 +60,12 @@ struct LdsBlock16 {                                  // the LDS operand of one b
   f32x4 a;
   __device__ inline void load(const float* __restrict__ Xl, int ldx, int k0, int lane) {
     a = *reinterpret_cast<const f32x4*>(&Xl[(lane & 15) * ldx + k0 + 4 * (lane >> 4)]);
+  }
+  __device__ inline void load_k16(const float* __restrict__ Xl, int ldx, int k0, int lane) {   // in the order of a forward block
+    const int kq = lane >> 4;
+    const float* p = &Xl[(lane & 15) * ldx + k0 + 8 * (kq >> 1) + 2 * (kq & 1)];
+    const f32x2 lo = *reinterpret_cast<const f32x2*>(p), hi = *reinterpret_cast<const f32x2*>(p + 4);
+    a = f32x4{lo[0], lo[1], hi[0], hi[1]};
   }
 };
 
@@ -82,12 +91,12 @@ __device__ inline void gemm256_16(const float* __restrict__ Xl, int ldx, const f
   wb[0] = b0;
   wb[1].load(W, 1, wave, lane);
   wb[2].load(W, 2, wave, lane);
-  xb[0].load(Xl, ldx, 0, lane);
+  xb[0].load_k16(Xl, ldx, 0, lane);
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     if (i + 3 < 16) wb[(i + 3) & 3].load(W, i + 3, wave, lane);
     if (i == 13) tail();
-    if (i + 1 < 16) xb[(i + 1) & 1].load(Xl, ldx, 16 * (i + 1), lane);
+    if (i + 1 < 16) xb[(i + 1) & 1].load_k16(Xl, ldx, 16 * (i + 1), lane);
     __builtin_amdgcn_sched_barrier(0);
     mfma_block16<false>(xb[i & 1], wb[i & 3], acc);
     __builtin_amdgcn_sched_barrier(0);
@@ -98,40 +107,41 @@ __device__ inline void gemm256_16(const float* __restrict__ Xl, int ldx, const f
 // Read straight from memory, that operand is 16 rows of W per quarter of a load instruction, 16 bytes of each: every
 // 128-byte line comes through the CU's L1 twice, half used, and a 16-row product, which already asks the L1 for half
 // of its bandwidth in the forward direction, takes 7.7 us instead of 4.9.  Here a wavefront fetches its 64 rows of W
-// in double blocks of 32 n as whole lines (8 lanes x 16 bytes per row, 8 rows per instruction), parks them in an LDS
+// in double blocks of 32 n as whole lines (4 lanes x 16 bytes of each of the two rows in a line, 8 lines per instruction), parks them in an LDS
 // area of its own and reads them back in the MFMA layout.  No barrier: a wavefront reads only what it wrote itself,
 // and the LDS serves a wavefront's accesses in order.
 //   LDS layout of a double block (two of them per wavefront, kStage16 floats per workgroup): row p = c + 16 nt
-//   (holding W[64 wave + 4 c + nt][32 D ..]) at p * 32 floats, its eight 16-byte pieces rotated by p >> 1 -- the 16
-//   lanes of a quarter wavefront then hit 64 different banks in the writes (two rows of opposite parity) and in the
+//   (holding W[64 wave + 4 c + nt][32 D ..]) at p * 32 floats, its eight 16-byte pieces rotated by (p >> 1) + 4 (nt >> 1) -- the 16
+//   lanes of a quarter wavefront then hit 64 different banks in the writes (four half rows) and in the
 //   reads (sixteen rows, one piece each).
 constexpr int kStage16Wave = 2 * 64 * 32;            // floats per wavefront: two double blocks
 constexpr int kStage16 = 4 * kStage16Wave;           // floats per workgroup (64 KB)
 struct WeightStage16 {                               // one double block on its way from memory to LDS
-  f32x4 g[8];
+  f32x4 g[8];                                        // lane 8 s + h, [q]: row c = 8 (q & 1) + s, nt = (q >> 1 & 1) + 2 (h >> 2), piece 4 (q >> 2) + (h & 3)
   __device__ inline void load(const float* __restrict__ W, int D, int wave, int lane) {
     const int s = lane >> 3, h = lane & 7;
     const WeightsRsrc r = weights_rsrc(W, kH * kH);
-    const uint32_t off = 4u * (uint32_t)w2_index(64 * wave + 4 * s, 4 * h);
+    const uint32_t off = 4u * (uint32_t)w2_index(64 * wave + 4 * s + 2 * (h >> 2), 4 * (h & 3));
 #pragma unroll
-    for (int q = 0; q < 8; ++q)                      // rows p = 8 q + s: c = 8 (q & 1) + s, nt = q >> 1
-      g[q] = rsrc_load4(r, off + 4 * w2_index(q >> 1, 0), w2_index(32 * (q & 1), 32 * D));
+    for (int q = 0; q < 8; ++q)
+      g[q] = rsrc_load4(r, off + 4 * w2_index((q >> 1) & 1, 16 * (q >> 2)), w2_index(32 * (q & 1), 32 * D));
   }
   __device__ inline void put(float* __restrict__ stage_wave, int D, int lane) const {
     const int s = lane >> 3, h = lane & 7;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-      const int p = 8 * q + s;
-      *reinterpret_cast<f32x4*>(stage_wave + (D & 1) * 2048 + p * 32 + 4 * ((h + (p >> 1)) & 7)) = g[q];
+      const int p = 8 * (q & 1) + s + 16 * ((q >> 1) & 1) + 32 * (h >> 2), piece = 4 * (q >> 2) + (h & 3) + (p >> 1) + 4 * (h >> 2);
+      *reinterpret_cast<f32x4*>(stage_wave + (D & 1) * 2048 + p * 32 + 4 * (piece & 7)) = g[q];
     }
   }
 };
 // block i (16 n) of the staged operand in the MFMA layout: w[nt][j] = W[64 wave + 4 c + nt][16 i + 4 kq + j]
 __device__ inline void staged_block16(WeightBlock16<true>& b, const float* __restrict__ stage_wave, int i, int lane) {
   const int c = lane & 15, kq = lane >> 4;
-  const float* base = stage_wave + ((i >> 1) & 1) * 2048 + c * 32 + 4 * ((4 * (i & 1) + kq + (c >> 1)) & 7);
+  const float* rows = stage_wave + ((i >> 1) & 1) * 2048 + c * 32;
+  const int piece = 4 * (i & 1) + kq + (c >> 1);
 #pragma unroll
-  for (int nt = 0; nt < 4; ++nt) b.w[nt] = *reinterpret_cast<const f32x4*>(base + 16 * 32 * nt);
+  for (int nt = 0; nt < 4; ++nt) b.w[nt] = *reinterpret_cast<const f32x4*>(rows + 16 * 32 * nt + 4 * ((piece + 4 * (nt >> 1)) & 7));
 }
 // g0: double block 0, requested by the caller as early as it can (with double block 1 as well the chains measured
 // slower: 64 more registers held across the product before); `stage`: the workgroup's kStage16 floats; tail() runs

@@ -478,7 +478,7 @@ struct Rows32Deep : Rows32<MT, true, NT> {
   }
 };
 
-// Critic chains that have a CU to themselves even with the slabs over the input tile (from 337 inputs on, or few workgroups): slabs
+// Wide target chains with a CU to themselves, and critic chains that have one even with the slabs over the input tile (from 337 inputs on, or few workgroups): slabs
 // beside it and eight wavefronts.  us/step at 376 / 17, before / so: 20 TD3 agents 247 / 238, 32 SAC agents 430 / 419, 40 TD3 agents
 // 495 / 485; 8 TD3 agents of 111 / 8 113.6 / 109.8.
 struct Rows32Wide : Rows32Deep<1, 2, 1> {

@@ -153,8 +153,8 @@ hipError_t setup_kernels() {
   POP_SET_LDS(k_target<Rows16Deep>);
   POP_SET_LDS(k_target<Rows32Deep<1>, 2>);
   POP_SET_LDS(k_target<Rows32x8>);
-  POP_SET_LDS(k_target<Rows32Deep<1, 2, 1>>);
-  POP_SET_LDS(k_target<Rows32Deep<1, 2, 1>, 2, kSacMaxAct>);
+  POP_SET_LDS(k_target<Rows32Wide>);
+  POP_SET_LDS(k_target<Rows32Wide, 2, kSacMaxAct>);
   POP_SET_LDS(k_actor<Rows16Deep>);
   POP_SET_LDS(k_target<Rows16>);
   POP_SET_LDS(k_target<Rows32<1>>);
@@ -207,13 +207,13 @@ hipError_t launch_target(const PopDev& d, uint32_t t, hipStream_t s) {
   if (d.A > kMaxAct) {                               // wide actions: scratch rows of kSacMaxAct floats, first layers as for wide inputs
     const size_t b32 = chain_bytes<Rows32<1>>(d.D, vec_target(d), Rows32<1>::kStage, kWideScratch);
     if (d.rows_t == 16) k_target<Rows16Deep, 1, kSacMaxAct><<<grid, block, chain_bytes<Rows16>(d.D, vec_target(d), Rows16::kStageForward, kWideScratch), s>>>(d, t);
-    else if (d.rows_t == 32 && (alone || 2 * b32 > (size_t)kLdsPerCU)) k_target<Rows32Deep<1, 2, 1>, 2, kSacMaxAct><<<grid, dim3(Rows32x8::kThr), b32, s>>>(d, t);
+    else if (d.rows_t == 32 && (alone || 2 * b32 > (size_t)kLdsPerCU)) k_target<Rows32Wide, 2, kSacMaxAct><<<grid, dim3(Rows32x8::kThr), b32, s>>>(d, t);
     else if (d.rows_t == 32) k_target<Rows32Deep<1>, 2, kSacMaxAct><<<grid, block, b32, s>>>(d, t);
     else return hipErrorInvalidValue;
   } else if (d.D > kMaxIn) {                         // wide inputs: pipelined first layers, 16 or 32 rows
     const size_t b32 = chain_bytes<Rows32<1>>(d.D, vec_target(d));
     if (d.rows_t == 16) k_target<Rows16Deep><<<grid, block, chain_bytes<Rows16>(d.D, vec_target(d), Rows16::kStageForward), s>>>(d, t);
-    else if (d.rows_t == 32 && (alone || 2 * b32 > (size_t)kLdsPerCU)) k_target<Rows32Deep<1, 2, 1>><<<grid, dim3(Rows32x8::kThr), b32, s>>>(d, t);
+    else if (d.rows_t == 32 && (alone || 2 * b32 > (size_t)kLdsPerCU)) k_target<Rows32Wide><<<grid, dim3(Rows32x8::kThr), b32, s>>>(d, t);
     else if (d.rows_t == 32) k_target<Rows32Deep<1>, 2><<<grid, block, b32, s>>>(d, t);
     else return hipErrorInvalidValue;
   } else if (d.rows_t == 16) k_target<Rows16><<<grid, block, chain_bytes<Rows16>(d.D, vec_target(d), Rows16::kStageForward), s>>>(d, t);

@@ -226,8 +226,12 @@ void fill_dims(const pop_config& c, PopDev& d) {
   // SAC past the 16-row class, one launch per chain: 64-row critic chains while they get a CU each (up to 32 agents; 194 us/step at
   // P = 20, 220 at 32, all chains at 32 rows 193, 220 on four wavefronts).  Its target chains of 32 rows, on eight wavefronts
   // up to 32 agents, against 16 rows, two workgroups per CU: 17 / 6 159.2 -> 151.1 us/step at P = 17, 166.3 -> 158.3 at 20, 208.3 -> 201.1 at
-  // 32; 11 / 3 169.7 -> 166.0 at 24; 56 / 8 235.2 -> 229.3 at 32.
-  if (c.algo == POP_ALGO_SAC && cls == 1 && (int64_t)c.P * (c.batch / 64) * 2 <= kCUs) d.rows_c = 64;
+  // 32; 11 / 3 169.7 -> 166.0 at 24; 56 / 8 235.2 -> 229.3 at 32.  A caller's fused launch keeps the 16 rows: there is no kernel of 32-row
+  // target beside 64-row critic chains.
+  if (c.algo == POP_ALGO_SAC && cls == 1 && (int64_t)c.P * (c.batch / 64) * 2 <= kCUs) {
+    d.rows_c = 64;
+    if (u.launch > POP_LAUNCH_PER_PART) d.rows_t = 16;
+  }
   // the caller's choices (measurements, tests); naming any chain's rows drops the critic-1 class unless it is named too
   if (u.rows_target || u.rows_critic || u.rows_actor || u.rows_critic1) {
     if (u.rows_target) d.rows_t = u.rows_target;

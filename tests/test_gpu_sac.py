@@ -192,6 +192,22 @@ def test_fused_and_separate_target_critic_launches_agree_bit_for_bit():
         assert np.array_equal(states[0][key], states[1][key]), key
 
 
+@pytest.mark.parametrize("P", [17, 32])
+def test_a_fused_launch_of_a_mid_size_population_runs_with_the_rows_the_library_chooses(P):
+    """The first and the last population for which the separate launches take 32-row target beside 64-row critic chains, a pair
+    that has no fused kernel: a caller's fused launch gets rows that have one, and the states of separate launches on them."""
+    states = []
+    for kw in (dict(launch=pp.POP_LAUNCH_TARGET_CRITIC), dict(launch=pp.POP_LAUNCH_PER_PART, rows=(16, 64, 32)),
+               dict(launch=pp.POP_LAUNCH_TARGET_CRITIC, rows=(0, 64, 0))):
+        gpu, _, _ = make_sac_pair(P=P, capacity=400, oracle=False, hps=sac_hparams(P), **kw)
+        gpu.update(3)
+        states.append({(i, w): gpu.get_params(i, w) for i in (0, P - 1) for w in NETS5 + MOMS + ALPHA3})
+        gpu.close()
+    for other in states[1:]:
+        for key in states[0]:
+            assert np.array_equal(states[0][key], other[key]), key
+
+
 def test_copy_agent_carries_the_temperature():
     gpu, _, _ = make_sac_pair(P=3, capacity=600, oracle=False)
     gpu.update(3)

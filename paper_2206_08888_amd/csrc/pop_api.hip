@@ -194,11 +194,13 @@ void fill_dims(const pop_config& c, PopDev& d) {
   // 120, 773.4 / 737.1 at 192, 1007 / 925 at 256).  Shared critics from 56 agents on for the target and critic chains, which always share a
   // launch there, with actor chains of 32 rows (us/step, all 32 / all 64 / 64, 64, 32: 207.5 / 210.5 / 207.1 at P = 52, 224.6 / 219.8 / 214.0 at 56, 282.5 /
   // 303.1 / 280.3 at 72, 304.0 / 311.3 / 290.2 at 80, 458.1 / 458.0 / 433.6 at 128, 562.9 / 583.4 / 546.1 at 160, 893.5 / 896.2 / 874.8 at 256).
+  // A caller's single or tail launch of TD3 runs its 64-row parts on four wavefronts (k_step) and takes them from 128 agents on: 32 / 64
+  // rows, single 426.4 / 490.4 at P = 104, 493.1 / 564.3 at 120, 521.8 / 604.5 at 127; tail 418.3 / 428.2, 483.5 / 492.9, 510.9 / 518.6.
   const int cls = (int64_t)c.P * (c.batch / 16) <= kCUs ? 0 : 1;   // 16-row chains of a part get a CU each
   const pop_tuning& u = c.tuning;
   const bool shared = c.algo == POP_ALGO_TD3_SHARED;
   const bool many = c.algo != POP_ALGO_SAC && !u.rows_target && !u.rows_critic && !u.rows_actor && !u.rows_critic1 &&
-                    4 * (int64_t)c.P * (c.batch / 32) >= (shared ? 7 : 13) * (int64_t)kCUs;
+                    4 * (int64_t)c.P * (c.batch / 32) >= (shared ? 7 : u.launch >= POP_LAUNCH_SINGLE ? 16 : 13) * (int64_t)kCUs;
   d.rows_t = cls == 0 ? 16 : many ? 64 : 32;
   d.rows_a = many && shared ? 32 : d.rows_t;
   // Beside 16 P target workgroups of 16 rows, 64-row critic chains (8 P workgroups) keep the fused

@@ -169,6 +169,17 @@ def test_the_tuning_in_force_is_reported():
     assert tuning(pp.POP_ALGO_SAC, 32)["launch"] == pp.POP_LAUNCH_PER_PART
 
 
+@pytest.mark.parametrize("launch,first", [(pp.POP_LAUNCH_AUTO, 104), (pp.POP_LAUNCH_PER_PART, 104), (pp.POP_LAUNCH_TARGET_CRITIC, 104),
+                                          (pp.POP_LAUNCH_SINGLE, 128), (pp.POP_LAUNCH_TAIL, 128)])
+def test_the_first_population_with_64_row_chains(launch, first):
+    """The separate launches run them on eight wavefronts and take them earlier than the single launch, which has four."""
+    for P, want in ((first - 1, 32), (first, 64)):
+        gpu = pp.Population(pp.make_config(P, 17, 6, (256, 256), 256, 64, launch=launch), workloads.hparams(2, P))
+        t = gpu.tuning()
+        gpu.close()
+        assert (t["rows_target"], t["rows_critic"], t["rows_actor"]) == (want,) * 3, (P, t)
+
+
 @pytest.mark.parametrize("launch,rows", [(pp.POP_LAUNCH_TARGET_CRITIC, None), (pp.POP_LAUNCH_SINGLE, (16, 64, 16))])
 def test_a_wait_between_workgroups_that_runs_out_is_reported_once_and_the_context_recovers(launch, rows):
     """Workgroups of a fused launch wait for results of other workgroups of the same launch, each wait bounded by

@@ -521,7 +521,10 @@ __device__ inline void head_split(const float* __restrict__ Xl, const float* __r
 
 // Passes with a thread per hidden unit sum a geometry's rows in two halves (16 rows: in one go), and the halves' sums are
 // added.  With four wavefronts a thread takes both halves side by side; with eight each half has 256 threads of its own (hidden
-// unit tid & 255, half tid >> 8), and the second half's sums cross over through LDS (unit_cross).
+// unit tid & 255, half tid >> 8), and the second half's sums cross over through LDS.
+// Where nothing crosses over, the sums are stored before the barrier that follows the pass: behind it the stores stand in front of
+// the next product's loads, and the launch ends with them (10 agents, us per launch, behind / before: k_target_critic1 40.5 / 40.2,
+// critic tiles 19.5 / 19.1).
 template <class G>
 struct UnitRows {
   static constexpr bool kCross = G::kThr == 2 * kThreads;
@@ -885,7 +888,7 @@ __device__ __forceinline__ void critic_chain(const PopDev& d, uint32_t t, int ne
   {                                                 // one thread per hidden unit, 8 rows at a time
     const int c = unit;
     const float w3 = v_w3[c];
-    if (chunk == 0 && tid < kH) put<SIGNAL>(d.cw3 + (size_t)net * kH + c, w3);
+    if (chunk == 0 && (!UR::kCross || tid < kH)) put<SIGNAL>(d.cw3 + (size_t)net * kH + c, w3);
     uint32_t active[UR::kOwn];                       // rows of a half in which this unit is
 #pragma unroll
     for (int o = 0; o < UR::kOwn; ++o) { sums[o][0] = 0.0f; sums[o][1] = 0.0f; active[o] = 0u; }
@@ -928,12 +931,17 @@ __device__ __forceinline__ void critic_chain(const PopDev& d, uint32_t t, int ne
     } else {
       reinterpret_cast<uint16_t*>(mg)[(r0 >> 4) & 1] = (uint16_t)active[0];
     }
-    UR::put(sums, stage + G::kStage / 2, tid);       // in the second slab: the next product writes it after a barrier of its own
+    if (UR::kCross) {
+      UR::put(sums, stage + G::kStage / 2, tid);     // in the second slab: the next product writes it after a barrier of its own
+    } else {                                         // stored here, ahead of the barrier (UnitRows)
+      put<SIGNAL>(part + kCP_dW3 + c, UR::total(sums, stage, c, 0));
+      put<SIGNAL>(part + kCP_db2 + c, UR::total(sums, stage, c, 1));
+    }
   }
   POP_MARK(5);
   __syncthreads();
   POP_MARK(6);
-  if (tid < kH) {
+  if (UR::kCross && tid < kH) {
     put<SIGNAL>(part + kCP_dW3 + tid, UR::total(sums, stage + G::kStage / 2, tid, 0));
     put<SIGNAL>(part + kCP_db2 + tid, UR::total(sums, stage + G::kStage / 2, tid, 1));
   }
@@ -1171,14 +1179,16 @@ __device__ __forceinline__ void actor_chain(const PopDev& d, uint32_t t, int age
     }
     UR::put(sums, cross, tid);
   }
-  __syncthreads();
-  POP_MARK(13);
-  if (tid < kH) {
+  auto store_sums = [&]() {
 #pragma unroll
     for (int j = 0; j < AS; ++j)
       if (j < A) put<WAIT>(part + kAP_dW3 + j * kH + tid, UR::total(sums, cross, tid, j));
     put<WAIT>(part + kAP_db2 + tid, UR::total(sums, cross, tid, AS));
-  }
+  };
+  if (!UR::kCross) store_sums();
+  __syncthreads();
+  POP_MARK(13);
+  if (UR::kCross && tid < kH) store_sums();
   if (kBothSlabs) __syncthreads();                   // the product writes the first one at once
   G::template input_grad_to_global<WAIT>(buf, an + d.actor.w2, wt, mask_a1, d.adZ1 + act_off, part + kAP_db1, wave, lane, stage);
   POP_MARK(14);

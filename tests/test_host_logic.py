@@ -4,6 +4,8 @@ import os
 import re
 import subprocess
 
+import pytest
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
@@ -28,13 +30,24 @@ def test_workgroups_per_cu(tmp_path):
     assert out.returncode == 0 and "bad 0" in out.stdout, out.stdout[-2000:]
 
 
-def test_wide_chains_that_have_a_cu_to_themselves_do_not_spill(tmp_path):
-    """The wide-input kernels of k_chain.hip bounded to one workgroup per CU keep everything in registers."""
+@pytest.fixture(scope="module")
+def k_chain_asm(tmp_path_factory):
     from paper_2206_08888_amd import build
-    asm = tmp_path / "k_chain.s"
+    asm = tmp_path_factory.mktemp("asm") / "k_chain.s"
     subprocess.run([build._hipcc(), *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, "k_chain.hip"), "-o", str(asm)],
                    check=True, capture_output=True)
-    spills = dict(re.findall(r"\.name: +(_ZN3pop\S*Rows\d+Deep\S*).*?\.vgpr_spill_count: +(\d+)", asm.read_text(), re.S))
+    return asm.read_text()
+
+
+def test_critic_1_inside_the_target_workgroups_spills_no_arguments(k_chain_asm):
+    """Arguments spilled at the kernel's start come in trips to memory one after the other."""
+    spills = dict(re.findall(r"\.name: +(_ZN3pop\S*k_target_critic1INS_\S*Rows32ILi1E\S*).*?\.sgpr_spill_count: +(\d+)", k_chain_asm, re.S))
+    assert len(spills) >= 2 and set(spills.values()) == {"0"}, spills
+
+
+def test_wide_chains_that_have_a_cu_to_themselves_do_not_spill(k_chain_asm):
+    """The wide-input kernels of k_chain.hip bounded to one workgroup per CU keep everything in registers."""
+    spills = dict(re.findall(r"\.name: +(_ZN3pop\S*Rows\d+Deep\S*).*?\.vgpr_spill_count: +(\d+)", k_chain_asm, re.S))
     two = [k for k in spills if "k_target" in k and "Rows32Deep" in k and "ELi2ELi" in k]      # bounded to two: registers for occupancy
     assert len(two) == 2 and len(spills) >= 9
     assert all(n == "0" for k, n in spills.items() if k not in two), spills

@@ -64,10 +64,10 @@ template <int MT>
 using Lds = LdsMap<32 * MT, 8>;
 
 // what a two-hidden-layer network needs from memory before its products can start
-template <int MT, int NT = 2>
+template <int MT, int NT = 2, bool PLAIN = false>
 struct LayerPre {
   SmallW<NT> w1;                   // first-layer weights
-  WeightRaw<false, NT> w2;         // block 0 of the hidden layer
+  WeightRaw<false, NT, PLAIN> w2;         // block 0 of the hidden layer
   float b1[NT], b2[NT];            // biases of this lane's columns
   __device__ inline void load(const float* __restrict__ net, const NetLayout& L, int wave, int lane) {
     w1.load(net + L.w1, L.in, wave, lane);
@@ -190,9 +190,9 @@ __device__ inline float wave_sum(float v) {
 }
 
 // First layer from the input tile into `Yl` (+ optional global copy); returns the ReLU pattern.
-template <int MT, bool THROUGH = false, int NT = 2>
+template <int MT, bool THROUGH, int NT, bool PLAIN>
 __device__ inline uint64_t first_layer(const float* Xs, int xld, const float* net, const NetLayout& L,
-                                       const LayerPre<MT, NT>& pre, float* Yl, float* Yg, int wave, int lane) {
+                                       const LayerPre<MT, NT, PLAIN>& pre, float* Yl, float* Yg, int wave, int lane) {
   Acc<MT, NT> acc;
   acc.zero();
   gemm_xw_small<MT, NT>(Xs, xld, L.in, net + L.w1, pre.w1, wave, lane, acc);
@@ -200,8 +200,8 @@ __device__ inline uint64_t first_layer(const float* Xs, int xld, const float* ne
 }
 
 // Hidden layer in place on `buf`; `stage` (LDS) and `tail` are handed to the product (see gemm256).
-template <int MT, bool THROUGH = false, bool SLABS = true, int NT = 2, class Tail>
-__device__ inline uint64_t hidden_layer(float* buf, const float* net, const NetLayout& L, LayerPre<MT, NT>& pre,
+template <int MT, bool THROUGH, bool SLABS, int NT, bool PLAIN, class Tail>
+__device__ inline uint64_t hidden_layer(float* buf, const float* net, const NetLayout& L, LayerPre<MT, NT, PLAIN>& pre,
                                         float* Yg, int wave, int lane, Tail tail, float* stage) {
   Acc<MT, NT> acc;
   acc.zero();
@@ -214,8 +214,8 @@ __device__ inline uint64_t hidden_layer(float* buf, const float* net, const NetL
 
 // dX = (dZ W^T) * mask written to global [rows][256]; column sums of the result
 // (over this workgroup's rows) go to colsum_out[256].
-template <int MT, bool THROUGH = false, bool SLABS = true, int NT = 2>
-__device__ inline void input_grad_to_global(const float* Zl, const float* W, WeightRaw<true, NT>& w0, uint64_t mask,
+template <int MT, bool THROUGH, bool SLABS, int NT, bool PLAIN>
+__device__ inline void input_grad_to_global(const float* Zl, const float* W, WeightRaw<true, NT, PLAIN>& w0, uint64_t mask,
                                             float* __restrict__ dXg, float* __restrict__ colsum_out, int wave,
                                             int lane, float* stage) {
   Acc<MT, NT> acc;
@@ -249,12 +249,14 @@ __device__ inline void input_grad_to_global(const float* Zl, const float* W, Wei
 //   input_grad_to_lds, thin (thin products on the vector ALU).
 // kStageForward / kStage: floats of LDS behind a chain's vectors that its products and the split heads (head_mfma_split)
 // share as `stage` -- a chain of forward products only, any chain.
-template <int MT, bool SLABS = true, int NT = 2>
+// PLAIN: hidden matrices row-major (w2_index).
+template <int MT, bool SLABS = true, int NT = 2, bool PLAIN = false>
 struct Rows32 {                                      // 32 MT rows on 32x32 tiles (mfma_tiles.h), 8 / NT wavefronts
   static constexpr int R = 32 * MT, kPad = 8, kThr = 64 * (8 / NT);   // kThr: threads of a workgroup
   static constexpr int kPerSimd = MT * NT == 4 ? 1 : 2;   // wavefronts of its chains on a SIMD
-  using Pre = LayerPre<MT, NT>;
-  using WtBlock = WeightRaw<true, NT>;
+  static constexpr bool kPlain = PLAIN;
+  using Pre = LayerPre<MT, NT, PLAIN>;
+  using WtBlock = WeightRaw<true, NT, PLAIN>;
   static constexpr int kStage = SLABS ? 2 * slab_floats<MT>() : 0, kStageForward = kStage;
   static constexpr bool kStageOnInput = false;       // critic chains: CriticMap
   __device__ static inline void load_wt(WtBlock& wt, const float* W, int wave, int lane) { wt.load(W, 0, wave, lane); }
@@ -335,11 +337,12 @@ using Rows64 = Rows32<2, true, 1>;
 // shared critics at 376 / 17 559.5 / 525.8 with 64.
 using Rows32x8 = Rows32<1, true, 1>;
 
-struct Rows16 {                                      // 16 rows on v_mfma_f32_16x16x4_f32 (mfma_tiles16.h)
+template <bool PLAIN>
+struct Rows16In {                                    // 16 rows on v_mfma_f32_16x16x4_f32 (mfma_tiles16.h)
   static constexpr int R = 16, kPad = 16, kThr = kThreads, kPerSimd = 1;
   struct Pre {
     SmallW16 w1;
-    WeightBlock16<false> w2;
+    WeightBlock16<false, PLAIN> w2;
     f32x4 b1, b2;                                    // biases of this lane's 4 columns
     __device__ inline void load(const float* __restrict__ net, const NetLayout& L, int wave, int lane) {
       w1.load(net + L.w1, L.in, wave, lane);
@@ -348,7 +351,7 @@ struct Rows16 {                                      // 16 rows on v_mfma_f32_16
       b2 = *reinterpret_cast<const f32x4*>(net + L.b2 + 64 * wave + 4 * (lane & 15));
     }
   };
-  using WtBlock = WeightStage16;                     // the transposed products stage their weights through LDS
+  using WtBlock = WeightStage16<PLAIN>;                     // the transposed products stage their weights through LDS
   static constexpr int kStage = kStage16, kStageForward = kHeadRed;   // floats of LDS they need for that
   static constexpr bool kStageOnInput = false;
   __device__ static inline void load_wt(WtBlock& wt, const float* W, int wave, int lane) { wt.load(W, 0, wave, lane); }
@@ -454,6 +457,8 @@ struct Rows16 {                                      // 16 rows on v_mfma_f32_16
     }
   }
 };
+
+using Rows16 = Rows16In<false>;
 
 // The same tiles for first layers with a fan-in of several hundred (the SAC Humanoid shapes): only the
 // first-layer product differs (software-pipelined beyond the prefetched rows).

@@ -48,7 +48,7 @@ __global__ __launch_bounds__(GT::kThr, GT::kPerSimd < GC::kPerSimd ? GT::kPerSim
 
 // The same for populations whose 16-row target workgroups and 32-row critic workgroups do not all get a CU at
 // once: a target workgroup goes on into critic 1 for its own 16 rows (its targets are its own, nothing waits),
-// and only critic 2 has workgroups of its own.
+// and only critic 2 has workgroups of its own.  GC: its geometry; the target workgroups read the hidden matrices in the same order.
 //
 // Its chains read more of the kernel's arguments than there are scalar registers.  Left to itself, the compiler requests all of them at the
 // start and spills them as they arrive, up to three trips to memory one after the other; here the target chains' arguments are requested
@@ -71,12 +71,13 @@ __global__ __launch_bounds__(kThreads, 1) void k_target_critic1(PopDev d, uint32
   request_together(d);
   request_together(d.actor);
   request_together(d.critic);
+  using GT = Rows16In<GC::kPlain>;
   POP_BLOCK_TIME(kTraceTargetCritic, 0);
   if ((int)blockIdx.x < target_blocks) {
     if (decode_block(blockIdx.x, d.P, d.B / 16, agent, chunk)) {
-      target_chain<Rows16>(d, t, agent, chunk, lds);
+      target_chain<GT>(d, t, agent, chunk, lds);
       __syncthreads();                               // the chain is done with its LDS; a lane reads back the targets it wrote
-      critic_chain<Rows16, false, false>(late_args(), t, 2 * agent, chunk, lds);
+      critic_chain<GT, false, false>(late_args(), t, 2 * agent, chunk, lds);
     }
   } else if (decode_block(blockIdx.x - target_blocks, d.P, d.B / GC::R, agent, chunk)) {
     critic_chain<GC, true, false, AHEAD>(late_args(), t, 2 * agent + 1, chunk, lds);
@@ -99,6 +100,7 @@ __global__ __launch_bounds__(G::kThr, PER_CU) void k_actor(PopDev d, uint32_t t)
 // sigma != nullptr: Gaussian exploration noise, a = clip(pi + sigma[agent] eps, -1, 1) with eps =
 // unit normal number (row_base + r) A + j of the agent's exploration stream at counter `step`
 // (row_base: index of row 0 of this call within the caller's whole request).
+template <bool PLAIN>
 __global__ __launch_bounds__(kThreads) void k_act(PopDev d, const float* __restrict__ obs, int n,
                                                   float* __restrict__ act, const float* __restrict__ sigma,
                                                   uint32_t step, uint32_t row_base) {
@@ -115,7 +117,7 @@ __global__ __launch_bounds__(kThreads) void k_act(PopDev d, const float* __restr
   const int agent = blockIdx.y, r0 = blockIdx.x * R;
   const int valid = n - r0 < R ? n - r0 : R;
   const float* an = net_ptr(d, d.theta, agent, 0);
-  LayerPre<1> pre;
+  LayerPre<1, 2, PLAIN> pre;
   pre.load(an, d.actor, wave, lane);
   const float* rows = obs + ((size_t)agent * n + r0) * d.O;
   if (d.O <= kMaxIn) {                               // one trip to memory for all of the prologue
@@ -130,9 +132,9 @@ __global__ __launch_bounds__(kThreads) void k_act(PopDev d, const float* __restr
     load_input_wide<R>(Xs, L.xld, rows, d.O, 0, d.O, valid, tid);
   }
   __syncthreads();
-  first_layer<1>(Xs, L.xld, an, d.actor, pre, buf, nullptr, wave, lane);
+  first_layer<1, false>(Xs, L.xld, an, d.actor, pre, buf, nullptr, wave, lane);
   __syncthreads();
-  hidden_layer<1>(buf, an, d.actor, pre, nullptr, wave, lane, NoTail(), stage);
+  hidden_layer<1, false, true>(buf, an, d.actor, pre, nullptr, wave, lane, NoTail(), stage);
   __syncthreads();
   head_mfma<R>(buf, an + d.actor.w3, d.actor.out, head, kHs, wave, lane);   // SAC: 2A outputs, the means come first
   const float sg = sigma ? sigma[agent] : 0.0f;
@@ -193,11 +195,17 @@ hipError_t setup_kernels() {
   POP_SET_LDS(k_target_critic1<Rows32<1>>);
   POP_SET_LDS(k_target_critic1<Rows32<2>>);
   POP_SET_LDS(k_target_critic1<Rows32<1>, true>);
+  POP_SET_LDS(k_target_critic1<Rows32<1, true, 2, true>>);
+  POP_SET_LDS(k_target_critic1<Rows32<2, true, 2, true>>);
+  POP_SET_LDS(k_target_critic1<Rows32<1, true, 2, true>, true>);
+  POP_SET_LDS(k_actor<Rows16In<true>>);
+  POP_SET_LDS(k_actor<Rows16In<true>, 1, true>);
   POP_SET_LDS(k_target_critic<Rows16, Rows32<1>, true>);
   POP_SET_LDS(k_actor<Rows16, 1, true>);
   POP_SET_LDS(k_target_critic<Rows32<1>, Rows32<1>>);
   POP_SET_LDS(k_target_critic<Rows64, Rows64>);
-  POP_SET_LDS(k_act);
+  POP_SET_LDS(k_act<false>);
+  POP_SET_LDS(k_act<true>);
 #undef POP_SET_LDS
   return hipSuccess;
 }
@@ -264,9 +272,16 @@ hipError_t launch_target_critic(const PopDev& d, uint32_t t, hipStream_t s) {
     if (d.actor_ahead) {
       if (d.rows_c != 32) return hipErrorInvalidValue;
       const size_t c = Lds<1>(d.D).bytes(kAheadBase + ahead_floats<32>());
-      k_target_critic1<Rows32<1>, true><<<grid, block, a > c ? a : c, s>>>(d, t, nt);
-    } else if (d.rows_c == 32) k_target_critic1<Rows32<1>><<<grid, block, a > b ? a : b, s>>>(d, t, nt);
-    else k_target_critic1<Rows32<2>><<<grid, block, a > b ? a : b, s>>>(d, t, nt);
+      if (d.w2_plain) k_target_critic1<Rows32<1, true, 2, true>, true><<<grid, block, a > c ? a : c, s>>>(d, t, nt);
+      else k_target_critic1<Rows32<1>, true><<<grid, block, a > c ? a : c, s>>>(d, t, nt);
+    } else if (d.rows_c == 32) {
+      if (d.w2_plain) k_target_critic1<Rows32<1, true, 2, true>><<<grid, block, a > b ? a : b, s>>>(d, t, nt);
+      else k_target_critic1<Rows32<1>><<<grid, block, a > b ? a : b, s>>>(d, t, nt);
+    } else if (d.w2_plain) {
+      k_target_critic1<Rows32<2, true, 2, true>><<<grid, block, a > b ? a : b, s>>>(d, t, nt);
+    } else {
+      k_target_critic1<Rows32<2>><<<grid, block, a > b ? a : b, s>>>(d, t, nt);
+    }
     return hipGetLastError();
   }
   const dim3 grid(nt + nc), block(kThreads);
@@ -301,8 +316,10 @@ hipError_t launch_actor(const PopDev& d, uint32_t t, hipStream_t s) {
     else return hipErrorInvalidValue;
   } else if (d.actor_ahead) {
     if (d.rows_a != 16) return hipErrorInvalidValue;
-    k_actor<Rows16, 1, true><<<grid, block, chain_bytes<Rows16>(d.D, vec_actor(d)), s>>>(d, t);
-  } else if (d.rows_a == 16) k_actor<Rows16><<<grid, block, chain_bytes<Rows16>(d.D, vec_actor(d)), s>>>(d, t);
+    if (d.w2_plain) k_actor<Rows16In<true>, 1, true><<<grid, block, chain_bytes<Rows16>(d.D, vec_actor(d)), s>>>(d, t);
+    else k_actor<Rows16, 1, true><<<grid, block, chain_bytes<Rows16>(d.D, vec_actor(d)), s>>>(d, t);
+  } else if (d.rows_a == 16 && d.w2_plain) k_actor<Rows16In<true>><<<grid, block, chain_bytes<Rows16>(d.D, vec_actor(d)), s>>>(d, t);
+  else if (d.rows_a == 16) k_actor<Rows16><<<grid, block, chain_bytes<Rows16>(d.D, vec_actor(d)), s>>>(d, t);
   else if (d.rows_a == 32 && (int)grid.x > kCUs) k_actor<Rows32<1>, 2><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec_actor(d)), s>>>(d, t);
   else if (d.rows_a == 32) k_actor<Rows32x8><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec_actor(d)), s>>>(d, t);
   else k_actor<Rows64><<<grid, dim3(Rows64::kThr), chain_bytes<Rows32<2>>(d.D, vec_actor(d)), s>>>(d, t);
@@ -310,8 +327,8 @@ hipError_t launch_actor(const PopDev& d, uint32_t t, hipStream_t s) {
 }
 hipError_t launch_act(const PopDev& d, const float* obs, int n, float* act, const float* sigma, uint32_t step,
                       uint32_t row_base, hipStream_t s) {
-  k_act<<<dim3((n + 31) / 32, d.P), dim3(kThreads), act_lds_bytes(d), s>>>(d, obs, n, act, sigma, step,
-                                                                                        row_base);
+  auto* kernel = d.w2_plain ? k_act<true> : k_act<false>;
+  kernel<<<dim3((n + 31) / 32, d.P), dim3(kThreads), act_lds_bytes(d), s>>>(d, obs, n, act, sigma, step, row_base);
   return hipGetLastError();
 }
 

@@ -29,7 +29,7 @@ __global__ __launch_bounds__(256) void k_init(PopDev d, InitLimits lim) {
   const float u = (float)(pick(blk, (uint32_t)e & 3u) >> 8) * 5.9604644775390625e-8f;
   const float centred = 2.0f * u - 1.0f;          // exact
   const float w = __fmul_rn(centred, limit);      // a single rounding, never fused
-  const int at = off + (layer == 1 ? w2_index(e / kH, e % kH) : e);
+  const int at = off + (layer == 1 && !d.w2_plain ? w2_index(e / kH, e % kH) : e);
   net_ptr(d, d.theta, agent, net)[at] = w;
   net_ptr(d, d.target, agent, net)[at] = w;
 }

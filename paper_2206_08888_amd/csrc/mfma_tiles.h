@@ -490,7 +490,7 @@ struct NoTail { __device__ inline void operator()() const {} };
 // 256-deep product of an LDS operand (fp32 tile, row stride kLda) with a global weight operand on the bf16 pipe:
 //   forward  (TRANSPOSED = false): acc[r][c] += sum_k X[r][k] W[k][c], c in this wave's 64 columns
 //   backward (TRANSPOSED = true):  acc[r][k] += sum_n Z[r][n] W[k][n], k in this wave's 64 columns
-// W is a [256][256] hidden matrix in the order of w2_index in both cases.  Matrix and vector instructions share the issue port (measured: about five
+// W is a [256][256] hidden matrix in the order of w2_index<PLAIN> in both cases.  Matrix and vector instructions share the issue port (measured: about five
 // cycles for either beside the other; a matrix instruction keeps its pipe for 32), and a pair of elements costs eleven
 // vector instructions to split, so the number of splits decides: a weight is used by one wavefront and split in its
 // registers, once per 32 MT rows; the LDS operand is used by all four wavefronts and split once per workgroup, 64
@@ -504,28 +504,29 @@ struct NoTail { __device__ inline void operator()() const {} };
 
 // The weights one lane needs for a 16-deep block i = 2 D + o: contraction indices 32 D + 16 half + 8 o + e, e < 8.  Two
 // blocks cover whole 128-byte lines of the transposed operand (a lane reads 64 bytes of one row of W).
-template <bool TRANSPOSED, int NT = 2>
+template <bool TRANSPOSED, int NT = 2, bool PLAIN = false>
 struct WeightRaw {
+  __device__ static constexpr int at(int k, int n) { return w2_index<PLAIN>(k, n); }
   float w[NT][8];                           // [column tile][e]
   static constexpr int kPieces = TRANSPOSED ? 2 * NT : 8;           // load instructions per block
-  static constexpr int kGroup = TRANSPOSED ? w2_index(0, 64) : w2_index(64, 0);   // floats from one group of four blocks to the next
+  static constexpr int kGroup = TRANSPOSED ? w2_index<PLAIN>(0, 64) : w2_index<PLAIN>(64, 0);   // floats from one group of four blocks to the next
   __device__ static constexpr int offset(int i) {
-    const int at = 32 * (i >> 1) + 8 * (i & 1);
-    return TRANSPOSED ? w2_index(0, at) : w2_index(at, 0);
+    const int k = 32 * (i >> 1) + 8 * (i & 1);
+    return TRANSPOSED ? at(0, k) : at(k, 0);
   }
   __device__ static inline WeightsRsrc rsrc(const float* W) { return weights_rsrc(W, kH * kH); }
   __device__ static inline uint32_t lane_bytes(int wave, int lane) {
     const int half = lane >> 5, col = tile_col<NT>(wave, 0, lane);
-    return 4u * (uint32_t)(TRANSPOSED ? w2_index(col, 16 * half) : w2_index(16 * half, col));
+    return 4u * (uint32_t)(TRANSPOSED ? at(col, 16 * half) : at(16 * half, col));
   }
   __device__ inline void load_piece(WeightsRsrc W, uint32_t lane_off, int blk, int p) {
     if (TRANSPOSED) {
       const int nt = p >> 1, s = p & 1;              // two columns are neighbouring rows of W, the first one even
-      const f32x4 v = rsrc_load4(W, lane_off + 4 * w2_index(nt, 4 * s), blk);
+      const f32x4 v = rsrc_load4(W, lane_off + 4 * at(nt, 4 * s), blk);
 #pragma unroll
       for (int j = 0; j < 4; ++j) w[nt][4 * s + j] = v[j];
     } else {
-      const auto v = rsrc_load_cols<NT>(W, lane_off + 4 * w2_index(p & 3, 0), blk + w2_index(p & ~3, 0));
+      const auto v = rsrc_load_cols<NT>(W, lane_off + 4 * at(p & 3, 0), blk + at(p & ~3, 0));
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) w[nt][p] = col_of(v, nt);
     }
@@ -575,9 +576,9 @@ struct SlabItem {                          // this thread's share of a slab: Q t
 
 // SLABS: as above; otherwise every wavefront splits the LDS operand itself, for chains whose scratch leaves no room for
 // the slabs (SAC with 64 rows).
-template <int MT, bool TRANSPOSED, bool SLABS, int NT>
+template <int MT, bool TRANSPOSED, bool SLABS, int NT, bool PLAIN>
 struct SplitProduct {
-  using Raw = WeightRaw<TRANSPOSED, NT>;
+  using Raw = WeightRaw<TRANSPOSED, NT, PLAIN>;
   static_assert(NT == 2 || SLABS, "eight wavefronts read the left operand from the slabs");
   Split8 x[2][MT], w[2];                   // the LDS operand of this block and the next, the weights of the two column tiles (NT = 1: of this block and the next)
   SlabItem<MT, NT> item;
@@ -837,10 +838,10 @@ __device__ inline void gemm_xw_slabs(const float* __restrict__ Xl, int ldx, int 
   acc.add_finite(low);
 }
 
-template <int MT, bool TRANSPOSED, bool SLABS = true, int NT = 2, class Tail>
-__device__ inline void gemm256(const float* __restrict__ Xl, const float* __restrict__ W, WeightRaw<TRANSPOSED, NT>& b0,
+template <int MT, bool TRANSPOSED, bool SLABS, int NT, bool PLAIN, class Tail>
+__device__ inline void gemm256(const float* __restrict__ Xl, const float* __restrict__ W, WeightRaw<TRANSPOSED, NT, PLAIN>& b0,
                                float* __restrict__ slabs, int wave, int lane, Acc<MT, NT>& acc, Tail tail) {
-  SplitProduct<MT, TRANSPOSED, SLABS, NT> p;
+  SplitProduct<MT, TRANSPOSED, SLABS, NT, PLAIN> p;
   p.run(Xl, W, b0, slabs, wave, lane, acc, tail);
   if (!SLABS) __syncthreads();                       // every wavefront has read the tile
 }

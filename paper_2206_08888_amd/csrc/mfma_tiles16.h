@@ -42,7 +42,8 @@ __device__ inline f32x4 mfma16(float a, float b, f32x4 c) { return __builtin_amd
 //     lane groups kq and kq + 1 then read the two rows, two apart, that share a line of W2 (w2_index), and a load takes 8 whole lines; as
 //     rows 4 kq + j it took 16 half lines (10 agents 75.0 us/step with row-major matrices, 76.5 with half lines here and in WeightStage16)
 //   backward (TRANSPOSED = true):  w[nt][j] = W[64 wave + 4 c + nt][16 i + 4 kq + j]
-template <bool TRANSPOSED>
+// PLAIN: rows 4 kq + j of a row-major W, whole lines as well.
+template <bool TRANSPOSED, bool PLAIN = false>
 struct WeightBlock16 {
   f32x4 w[4];
   // forward only: transposed blocks come out of LDS (staged_block16)
@@ -50,9 +51,10 @@ struct WeightBlock16 {
     static_assert(!TRANSPOSED, "read from memory as WeightStage16");
     const WeightsRsrc r = weights_rsrc(W, kH * kH);
     const int kq = lane >> 4;
-    const uint32_t off = 4u * (uint32_t)w2_index(8 * (kq >> 1) + 2 * (kq & 1), 64 * wave + 4 * (lane & 15));
+    const uint32_t off = 4u * (uint32_t)w2_index<PLAIN>(PLAIN ? 4 * kq : 8 * (kq >> 1) + 2 * (kq & 1), 64 * wave + 4 * (lane & 15));
 #pragma unroll
-    for (int j = 0; j < 4; ++j) w[j] = rsrc_load4(r, off + 4 * w2_index(j & 1, 0), w2_index(16 * i + 4 * (j >> 1), 0));
+    for (int j = 0; j < 4; ++j)
+      w[j] = PLAIN ? rsrc_load4(r, off + 4 * j * kH, 16 * i * kH) : rsrc_load4(r, off + 4 * w2_index(j & 1, 0), w2_index(16 * i + 4 * (j >> 1), 0));
   }
 };
 
@@ -61,7 +63,9 @@ struct LdsBlock16 {                                  // the LDS operand of one b
   __device__ inline void load(const float* __restrict__ Xl, int ldx, int k0, int lane) {
     a = *reinterpret_cast<const f32x4*>(&Xl[(lane & 15) * ldx + k0 + 4 * (lane >> 4)]);
   }
+  template <bool PLAIN>
   __device__ inline void load_k16(const float* __restrict__ Xl, int ldx, int k0, int lane) {   // in the order of a forward block
+    if (PLAIN) { load(Xl, ldx, k0, lane); return; }
     const int kq = lane >> 4;
     const float* p = &Xl[(lane & 15) * ldx + k0 + 8 * (kq >> 1) + 2 * (kq & 1)];
     const f32x2 lo = *reinterpret_cast<const f32x2*>(p), hi = *reinterpret_cast<const f32x2*>(p + 4);
@@ -69,8 +73,8 @@ struct LdsBlock16 {                                  // the LDS operand of one b
   }
 };
 
-template <bool TRANSPOSED>
-__device__ inline void mfma_block16(const LdsBlock16& x, const WeightBlock16<TRANSPOSED>& b, Acc16& acc) {
+template <bool TRANSPOSED, bool PLAIN>
+__device__ inline void mfma_block16(const LdsBlock16& x, const WeightBlock16<TRANSPOSED, PLAIN>& b, Acc16& acc) {
 #pragma unroll
   for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -83,22 +87,22 @@ __device__ inline void mfma_block16(const LdsBlock16& x, const WeightBlock16<TRA
 // before the MFMAs of block i, about 1500 cycles of matrix work ahead), the LDS operand one
 // block ahead.  Block 0 comes from the caller; `tail()` runs once the last weight block has
 // been requested, so the caller can start the next layer's loads under the last blocks.
-template <class Tail>
+template <bool PLAIN, class Tail>
 __device__ inline void gemm256_16(const float* __restrict__ Xl, int ldx, const float* __restrict__ W,
-                                  const WeightBlock16<false>& b0, int wave, int lane, Acc16& acc, Tail tail) {
-  WeightBlock16<false> wb[4];
+                                  const WeightBlock16<false, PLAIN>& b0, int wave, int lane, Acc16& acc, Tail tail) {
+  WeightBlock16<false, PLAIN> wb[4];
   LdsBlock16 xb[2];
   wb[0] = b0;
   wb[1].load(W, 1, wave, lane);
   wb[2].load(W, 2, wave, lane);
-  xb[0].load_k16(Xl, ldx, 0, lane);
+  xb[0].template load_k16<PLAIN>(Xl, ldx, 0, lane);
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     if (i + 3 < 16) wb[(i + 3) & 3].load(W, i + 3, wave, lane);
     if (i == 13) tail();
-    if (i + 1 < 16) xb[(i + 1) & 1].load_k16(Xl, ldx, 16 * (i + 1), lane);
+    if (i + 1 < 16) xb[(i + 1) & 1].template load_k16<PLAIN>(Xl, ldx, 16 * (i + 1), lane);
     __builtin_amdgcn_sched_barrier(0);
-    mfma_block16<false>(xb[i & 1], wb[i & 3], acc);
+    mfma_block16(xb[i & 1], wb[i & 3], acc);
     __builtin_amdgcn_sched_barrier(0);
   }
 }
@@ -107,30 +111,33 @@ __device__ inline void gemm256_16(const float* __restrict__ Xl, int ldx, const f
 // Read straight from memory, that operand is 16 rows of W per quarter of a load instruction, 16 bytes of each: every
 // 128-byte line comes through the CU's L1 twice, half used, and a 16-row product, which already asks the L1 for half
 // of its bandwidth in the forward direction, takes 7.7 us instead of 4.9.  Here a wavefront fetches its 64 rows of W
-// in double blocks of 32 n as whole lines (4 lanes x 16 bytes of each of the two rows in a line, 8 lines per instruction), parks them in an LDS
+// in double blocks of 32 n as whole lines (4 lanes x 16 bytes of each of the two rows in a line, PLAIN: 8 of one row; 8 lines per instruction), parks them in an LDS
 // area of its own and reads them back in the MFMA layout.  No barrier: a wavefront reads only what it wrote itself,
 // and the LDS serves a wavefront's accesses in order.
 //   LDS layout of a double block (two of them per wavefront, kStage16 floats per workgroup): row p = c + 16 nt
 //   (holding W[64 wave + 4 c + nt][32 D ..]) at p * 32 floats, its eight 16-byte pieces rotated by (p >> 1) + 4 (nt >> 1) -- the 16
-//   lanes of a quarter wavefront then hit 64 different banks in the writes (four half rows) and in the
+//   lanes of a quarter wavefront then hit 64 different banks in the writes (four half rows; PLAIN: two whole ones) and in the
 //   reads (sixteen rows, one piece each).
 constexpr int kStage16Wave = 2 * 64 * 32;            // floats per wavefront: two double blocks
 constexpr int kStage16 = 4 * kStage16Wave;           // floats per workgroup (64 KB)
+template <bool PLAIN = false>
 struct WeightStage16 {                               // one double block on its way from memory to LDS
-  f32x4 g[8];                                        // lane 8 s + h, [q]: row c = 8 (q & 1) + s, nt = (q >> 1 & 1) + 2 (h >> 2), piece 4 (q >> 2) + (h & 3)
+  f32x4 g[8];                                        // lane 8 s + h, [q]: row c = 8 (q & 1) + s; nt = (q >> 1 & 1) + 2 (h >> 2), piece 4 (q >> 2) + (h & 3)
+                                                     // (PLAIN: nt = q >> 1, piece h)
   __device__ inline void load(const float* __restrict__ W, int D, int wave, int lane) {
     const int s = lane >> 3, h = lane & 7;
     const WeightsRsrc r = weights_rsrc(W, kH * kH);
-    const uint32_t off = 4u * (uint32_t)w2_index(64 * wave + 4 * s + 2 * (h >> 2), 4 * (h & 3));
+    const uint32_t off = 4u * (uint32_t)(PLAIN ? w2_index<true>(64 * wave + 4 * s, 4 * h) : w2_index(64 * wave + 4 * s + 2 * (h >> 2), 4 * (h & 3)));
 #pragma unroll
     for (int q = 0; q < 8; ++q)
-      g[q] = rsrc_load4(r, off + 4 * w2_index((q >> 1) & 1, 16 * (q >> 2)), w2_index(32 * (q & 1), 32 * D));
+      g[q] = rsrc_load4(r, off + 4 * (PLAIN ? (q >> 1) * kH : w2_index((q >> 1) & 1, 16 * (q >> 2))), w2_index<PLAIN>(32 * (q & 1), 32 * D));
   }
   __device__ inline void put(float* __restrict__ stage_wave, int D, int lane) const {
     const int s = lane >> 3, h = lane & 7;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-      const int p = 8 * (q & 1) + s + 16 * ((q >> 1) & 1) + 32 * (h >> 2), piece = 4 * (q >> 2) + (h & 3) + (p >> 1) + 4 * (h >> 2);
+      const int nt = PLAIN ? q >> 1 : ((q >> 1) & 1) + 2 * (h >> 2), p = 8 * (q & 1) + s + 16 * nt;
+      const int piece = (PLAIN ? h : 4 * (q >> 2) + (h & 3)) + (p >> 1) + 4 * (nt >> 1);
       *reinterpret_cast<f32x4*>(stage_wave + (D & 1) * 2048 + p * 32 + 4 * (piece & 7)) = g[q];
     }
   }
@@ -146,12 +153,12 @@ __device__ inline void staged_block16(WeightBlock16<true>& b, const float* __res
 // g0: double block 0, requested by the caller as early as it can (with double block 1 as well the chains measured
 // slower: 64 more registers held across the product before); `stage`: the workgroup's kStage16 floats; tail() runs
 // once the last double block has been requested.
-template <class Tail>
+template <bool PLAIN, class Tail>
 __device__ inline void gemm256_16_staged(const float* __restrict__ Xl, int ldx, const float* __restrict__ W,
-                                         const WeightStage16& g0, float* __restrict__ stage, int wave, int lane, Acc16& acc,
+                                         const WeightStage16<PLAIN>& g0, float* __restrict__ stage, int wave, int lane, Acc16& acc,
                                          Tail tail) {
   float* sw = stage + wave * kStage16Wave;
-  WeightStage16 g[3];                                // double blocks D + 1 .. D + 3 in flight
+  WeightStage16<PLAIN> g[3];                                // double blocks D + 1 .. D + 3 in flight
   WeightBlock16<true> wb[2];
   LdsBlock16 xb[2];
   g[0] = g0;
@@ -167,7 +174,7 @@ __device__ inline void gemm256_16_staged(const float* __restrict__ Xl, int ldx, 
     staged_block16(wb[1], sw, 2 * D + 1, lane);
     xb[1].load(Xl, ldx, 16 * (2 * D + 1), lane);
     __builtin_amdgcn_sched_barrier(0);
-    mfma_block16<true>(xb[0], wb[0], acc);
+    mfma_block16(xb[0], wb[0], acc);
     __builtin_amdgcn_sched_barrier(0);
     if (D + 1 < 8) {
       g[(D + 1) % 3].put(sw, D + 1, lane);           // requested two rounds ago (the first two: at the start)
@@ -175,7 +182,7 @@ __device__ inline void gemm256_16_staged(const float* __restrict__ Xl, int ldx, 
       xb[0].load(Xl, ldx, 16 * (2 * D + 2), lane);
     }
     __builtin_amdgcn_sched_barrier(0);
-    mfma_block16<true>(xb[1], wb[1], acc);
+    mfma_block16(xb[1], wb[1], acc);
     __builtin_amdgcn_sched_barrier(0);
   }
 }

@@ -247,6 +247,9 @@ void fill_dims(const pop_config& c, PopDev& d) {
   if (d.D > kMaxIn || (c.algo != POP_ALGO_SAC && d.A > kMaxAct)) { d.rows_t = d.rows_a = (int64_t)c.P * (c.batch / 16) <= kCUs ? 16 : 32; d.rows_c = 32; d.rows_c1 = 0; }
   if (d.rows_c1 == 0) d.rows_c1 = d.rows_c;
   d.cstride = d.B / (d.rows_c1 < d.rows_c ? d.rows_c1 : d.rows_c);
+  // Row-major hidden matrices (w2_index): critic 1 in the target workgroups, so that target, critic 1 and actor chains have 16 rows and only critic 2,
+  // which those outlast, has more.  9 to 12 agents where the library chooses.
+  d.w2_plain = d.rows_c1 != d.rows_c && d.rows_a == 16;
   // Stand-alone weight-gradient launches: the last round of 32 x 128 tiles leaves most places empty for as long as a
   // tile lasts; tiles of half the width end sooner and spread more evenly.  That pays while the launch is a few rounds
   // of the 768 places (three per CU): us/step, full / half tiles: 85.7 / 83.3 at P = 12, 101.9 / 96.0 at P = 16, 116.7 / 114.6 at
@@ -889,12 +892,14 @@ int64_t pop_get_params(pop_ctx* ctx, int32_t agent, int32_t which, float* out, i
   if (out_len < L->size) return fail(ctx, POP_EINVAL, "out_len %lld < %d", (long long)out_len, L->size);
   if (ctx->d.share > 1 && net >= 1) agent = 0;         // the shared critics live in agent 0's blocks
   const float* src = (const float*)(ctx->ws + region + (int64_t)agent * ctx->d.agent_sz * 4 + off);
-  const bool direct = on_device && kernel_reaches(ctx, out);
+  const bool plain = ctx->d.w2_plain, direct = on_device && !plain && kernel_reaches(ctx, out);
   float* canon = direct ? out : (float*)(ctx->ws + ctx->lay.staging);
-  k_read_net<<<dim3((L->size + 255) / 256), dim3(256), 0, ctx->stream>>>(canon, src, L->size, L->w2);
-  HIP_TRY(ctx, hipGetLastError());
+  if (!plain) {
+    k_read_net<<<dim3((L->size + 255) / 256), dim3(256), 0, ctx->stream>>>(canon, src, L->size, L->w2);
+    HIP_TRY(ctx, hipGetLastError());
+  }
   if (!direct)
-    HIP_TRY(ctx, hipMemcpyAsync(out, canon, (size_t)L->size * 4, on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, ctx->stream));
+    HIP_TRY(ctx, hipMemcpyAsync(out, plain ? src : canon, (size_t)L->size * 4, on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, ctx->stream));
   if (!on_device) {
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     const int rc = check_fault(ctx);
@@ -922,12 +927,14 @@ int pop_set_params(pop_ctx* ctx, int32_t agent, int32_t which, const float* in, 
   if (in_len != L->size) return fail(ctx, POP_EINVAL, "in_len %lld != %d", (long long)in_len, L->size);
   if (ctx->d.share > 1 && net >= 1) agent = 0;
   float* dst = (float*)(ctx->ws + region + (int64_t)agent * ctx->d.agent_sz * 4 + off);
-  const bool direct = on_device && kernel_reaches(ctx, in);
+  const bool plain = ctx->d.w2_plain, direct = on_device && !plain && kernel_reaches(ctx, in);
   float* staged = (float*)(ctx->ws + ctx->lay.staging);
   if (!direct)
-    HIP_TRY(ctx, hipMemcpyAsync(staged, in, (size_t)L->size * 4, on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, ctx->stream));
-  k_write_net<<<dim3((L->size + 255) / 256), dim3(256), 0, ctx->stream>>>(dst, direct ? in : staged, L->size, L->w2);
-  HIP_TRY(ctx, hipGetLastError());
+    HIP_TRY(ctx, hipMemcpyAsync(plain ? dst : staged, in, (size_t)L->size * 4, on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, ctx->stream));
+  if (!plain) {
+    k_write_net<<<dim3((L->size + 255) / 256), dim3(256), 0, ctx->stream>>>(dst, direct ? in : staged, L->size, L->w2);
+    HIP_TRY(ctx, hipGetLastError());
+  }
   if (!on_device) HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
   return POP_OK;
 }

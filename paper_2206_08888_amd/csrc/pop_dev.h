@@ -74,8 +74,13 @@ __host__ __device__ inline NetLayout make_layout(int in, int out) {
 // clock from this order and 16 from plain rows, and lanes that read neighbouring columns the same from both (loads alone, cycles
 // per 256 KB, one / two 4-wavefront workgroups on a CU: a row per lane 16,390 / 28,060 plain, 8,200 / 14,410 here; 8 bytes
 // per lane along a row 8,200 / 12,300 and 8,200 / 13,540).  pop_get_params and pop_set_params speak row-major.
+// PLAIN: row-major inside as well (PopDev::w2_plain), for populations whose steps wait for 16-row chains alone.  Those read W2 16 bytes per lane along
+// a row, forward, and through LDS in whole lines, transposed, so the blocks gain them nothing; and a forward load asks the L1 for 16 half lines
+// where row-major it asks for 8 whole ones, which shows on weights the L2 does not have yet (blocks / row-major: k_target_critic1, four forward products
+// in a row, 39.7 / 39.25 us with 10 agents; us/step 73.2 / 72.7 with 10, 79.25 / 78.7 with 11, 79.9 / 79.1 with 12).
+template <bool PLAIN = false>
 __host__ __device__ constexpr int w2_index(int k, int n) {
-  return (k >> 2) * 4 * kH + (n >> 4) * 64 + (k & 1) * 32 + ((k >> 1) & 1) * 16 + (n & 15);
+  return PLAIN ? k * kH + n : (k >> 2) * 4 * kH + (n >> 4) * 64 + (k & 1) * 32 + ((k >> 1) & 1) * 16 + (n & 15);
 }
 
 struct PopDev {
@@ -89,6 +94,7 @@ struct PopDev {
   int rows_t, rows_c, rows_a;  // batch rows per workgroup of the target / critic / actor chain: (16, 32 or 64, 16) for
                                // small populations, else (32, 32, 32), from 104 agents on (64, 64, 64); shared critics from 56 on (64, 64, 32)
   int rows_c1;                 // rows per workgroup of critic 1's chain: rows_c, or 16 where the target workgroups run it (k_chain.hip)
+  int w2_plain;                // hidden matrices lie row-major (w2_index<true>): critic 1 inside the target workgroups and 16-row actor chains
   int cstride;                 // chunk slots per network in cpart: B / min(rows_c1, rows_c)
   int half_tiles;              // the stand-alone weight-gradient launch runs tiles of half the width (k_wgrad_adam.hip)
   NetLayout actor, critic;

@@ -140,7 +140,7 @@ struct XSlice {
 // One 32 x 128 tile of a weight matrix [M][256]: rows m0 .. m0+31 (rows >= M masked),
 // columns n0 .. n0+127, 32 per wavefront.
 //   x: [256][ldx] layer input, z: [256][256] pre-activation gradient, both global;
-//   base: offset of the matrix inside the network's parameter block; w2: its elements are in the order of w2_index.
+//   base: offset of the matrix inside the network's parameter block; blocked: its elements are in the order of w2_index, else row-major.
 // The tile's parameters, moments and targets do not depend on the product, so they are
 // requested first and arrive while the operands are staged and multiplied.  `setup()` fills
 // `sh` (thread 0 only; a few hundred cycles of double arithmetic): it runs once the loads are
@@ -150,23 +150,23 @@ template <bool WAIT, bool SLIM, bool HALF, bool DZ2, class Setup>
 __device__ __forceinline__ void weight_tile(const PopDev& d, const uint32_t* wait_on, uint32_t want, const Adam* sh,
                                             Setup setup, bool polyak, const float* __restrict__ x, int ldx, int M, int m0,
                                    int n0, const float* __restrict__ z, const uint32_t* __restrict__ zmask, const float* __restrict__ zdq,
-                                   const float* __restrict__ zw3, uint32_t base, bool w2, float* Xl,
+                                   const float* __restrict__ zw3, uint32_t base, bool blocked, float* Xl,
                                    float* __restrict__ th, float* __restrict__ mo, float* __restrict__ ve,
                                    float* __restrict__ tg, float* __restrict__ gr, int tid) {
   const int wave = tid >> 6, lane = tid & 63, l32 = lane & 31;
   POP_MARK(50);
   // The Adam step works on whole row pieces: thread `tid` owns, for q = 0 .. 3, four neighbouring parameters of row
-  // arow + 8 q of the tile (W1: arow = tid >> 5, columns 4 (tid & 31) ..) -- 16-byte operands, a quarter of the load and store
+  // arow + 8 q of the tile (row-major: arow = tid >> 5, columns 4 (tid & 31) ..) -- 16-byte operands, a quarter of the load and store
   // instructions of a one-float-per-lane layout (the CU's one load path is what the tile launches queue for).
   // The product leaves the gradients in the MFMA layout; they change over through LDS (the X slice is done with).
   // HALF: the tile is 64 columns wide; wavefront pairs take the two column groups for one half of the batch each
   // (kh), the halves are summed where the gradients change layout, and a thread owns two row pieces, 16 rows apart.
   constexpr int Q = HALF ? 2 : 4, QR = HALF ? 16 : 8;
   const int cw = HALF ? (wave & 1) : wave, kh = HALF ? (wave >> 1) : 0;
-  // W2: the threads follow the order of w2_index, four rows of 128 (64) columns per 128 (64) threads.
-  const int arow = w2 ? 4 * (tid >> (HALF ? 6 : 7)) + 2 * ((tid >> 2) & 1) + ((tid >> 3) & 1) : HALF ? tid >> 4 : tid >> 5;
-  const int acol = w2 ? 16 * ((tid >> 4) & (HALF ? 3 : 7)) + 4 * (tid & 3) : 4 * (tid & (HALF ? 15 : 31));
-  const uint32_t elem0 = base + (uint32_t)(w2 ? w2_index(m0 + arow, n0 + acol) : (m0 + arow) * kH + n0 + acol);      // q = 0; q adds QR rows
+  // Blocked: the threads follow the order of w2_index, four rows of 128 (64) columns per 128 (64) threads.
+  const int arow = blocked ? 4 * (tid >> (HALF ? 6 : 7)) + 2 * ((tid >> 2) & 1) + ((tid >> 3) & 1) : HALF ? tid >> 4 : tid >> 5;
+  const int acol = blocked ? 16 * ((tid >> 4) & (HALF ? 3 : 7)) + 4 * (tid & 3) : 4 * (tid & (HALF ? 15 : 31));
+  const uint32_t elem0 = base + (uint32_t)(blocked ? w2_index(m0 + arow, n0 + acol) : (m0 + arow) * kH + n0 + acol);      // q = 0; q adds QR rows
   AdamRegs4 regs[Q];
   auto load_adam = [&]() {
 #pragma unroll
@@ -304,10 +304,10 @@ __device__ __forceinline__ void wgrad_roles(const PopDev& d, uint32_t t, int act
     if (w2 && !actor_phase)
       weight_tile<WAIT, SLIM, HALF, true>(d, wait_on, (uint32_t)chunks, sh_adam, setup, polyak, x, kH, kH, m0, n0, nullptr,
                                           d.cmask + (size_t)unit * (d.B / 32) * kH, d.cdq + (size_t)unit * d.B, d.cw3 + (size_t)unit * kH,
-                                          (uint32_t)L.w2, true, xt_lds, th, mo, ve, tg, gr, tid);
+                                          (uint32_t)L.w2, !d.w2_plain, xt_lds, th, mo, ve, tg, gr, tid);
     else
       weight_tile<WAIT, SLIM, HALF, false>(d, wait_on, (uint32_t)chunks, sh_adam, setup, polyak, x, w2 ? kH : d.row, w2 ? kH : L.in, m0, n0, z,
-                                           nullptr, nullptr, nullptr, (uint32_t)(w2 ? L.w2 : L.w1), w2, xt_lds, th, mo, ve, tg, gr, tid);
+                                           nullptr, nullptr, nullptr, (uint32_t)(w2 ? L.w2 : L.w1), w2 && !d.w2_plain, xt_lds, th, mo, ve, tg, gr, tid);
   } else {
     // Small tensors from per-chunk partial sums; thread c owns hidden unit c.  Role `small` = 0: the hidden biases,
     // and for a critic its one head column, head bias and loss, for an actor its head bias and loss (SAC: the

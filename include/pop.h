@@ -17,8 +17,8 @@
  *   - "device pointer" = HIP device memory of the GPU that was current at
  *     pop_create; "host pointer" = ordinary host memory.  The caller owns every
  *     pointer it passes, including the workspace and the stream; the library
- *     allocates no device memory (a context holds 8 bytes of pinned host memory)
- *     and frees nothing of the caller's.
+ *     allocates no device memory (a context holds pinned host memory for two
+ *     words and one network, at most 0.8 MB) and frees nothing of the caller's.
  *   - All work is enqueued on the stream given to pop_create.  pop_update and
  *     calls with device pointers are asynchronous; calls that take or fill host
  *     pointers synchronise that stream before returning.

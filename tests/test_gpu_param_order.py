@@ -59,3 +59,32 @@ def test_row_major_matrices_change_rounding_only(rows_critic, ahead):
     assert all(np.array_equal(a, b) for a, b in zip(out[0][0], out[1][0]))
     worst = max(rel_l2(out[0][1][k], out[1][1][k]) for k in out[0][1] if out[1][1][k].any())
     assert worst <= 2e-5, worst
+
+
+@pytest.mark.parametrize("P", [2, 9])
+def test_networks_from_and_to_host_arrays_of_every_kind(P):
+    """Pageable and pinned, at the start of an allocation and inside it; each read back into the other kind and from the device."""
+    import torch
+    ensure_built()
+    cfg = pp.make_config(P, 17, 6, (256, 256), 256, 100)
+    pop = pp.Population(cfg, workloads.hparams(2, P))
+    rng = np.random.default_rng(7)
+
+    def arrays(n):
+        return {"pageable": torch.zeros(n), "pageable, inside": torch.zeros(n + 3)[3:], "pinned": torch.zeros(n, pin_memory=True),
+                "pinned, inside": torch.zeros(n + 3, pin_memory=True)[3:], "device": torch.zeros(n + 3, device="cuda")[3:]}
+    for code in (pp.PARAM_CODES["actor"], pp.PARAM_CODES["v_critic2"]):
+        n = pp.pop_net_size(cfg, code)
+        src, dst = arrays(n), arrays(n)
+        for kind in src:
+            a = torch.from_numpy(rng.standard_normal(n).astype(np.float32))
+            src[kind].copy_(a)
+            torch.cuda.synchronize()
+            pp.pop_set_params(pop.ctx, 1, code, src[kind])
+            for other in dst:
+                dst[other].zero_()
+                torch.cuda.synchronize()
+                pp.pop_get_params(pop.ctx, 1, code, dst[other])
+                pop.sync()
+                assert torch.equal(dst[other].cpu(), a), (code, kind, other)
+    pop.close()

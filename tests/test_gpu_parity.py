@@ -540,10 +540,10 @@ def test_wide_observations_in_a_mid_size_population(obs_dim, act_dim):
     gpu.close()
 
 
-@pytest.mark.parametrize("obs_dim,act_dim", [(59, 6), (110, 8), (40, 10)])
+@pytest.mark.parametrize("obs_dim,act_dim", [(59, 6), (104, 8), (105, 8), (110, 8), (40, 10)])
 def test_wide_target_chains_that_share_a_cu(obs_dim, act_dim):
-    """P = 33: more than one 32-row target workgroup per CU, and a fan-in (65, 118) whose LDS lets two share one (wide
-    scratch rows: 50); agents 0 and 32 against the oracle, the first step element by element."""
+    """P = 33: more than one 32-row target workgroup per CU, and a fan-in (65, 112) whose LDS lets two share one (wide
+    scratch rows: 50), the first that does not (113) and one beyond; agents 0 and 32 against the oracle, the first step element by element."""
     hps = workloads.hparams(2, 33)
     gpu, orc, agents = make_pair(2, P=33, capacity=300, hps=hps, agents=[0, 32], obs_dim=obs_dim, act_dim=act_dim)
     gpu.set_debug(1)

@@ -332,7 +332,7 @@ using Rows64 = Rows32<2, true, 1>;
 // 120 -> 117 (training rounds), 20 agents of 376 / 17 267 -> 263, 23 agents of 11 / 3 174 -> 168, 32 SAC agents 225 -> 214, of 376 / 17 455 -> 451.  Target chains with the input tile through the slabs
 // (gemm_xw_slabs): 20 agents of 376 / 17 263 -> 248, 32 SAC agents of 376 / 17 443 -> 432 (target chain 86 -> 70 us, a first layer 14.5 -> 12.5).
 // Likewise wherever LDS or registers keep a CU to one workgroup in any case, however many there are: SAC's target and actor chains,
-// wide actor chains, wide target chains from some 250 inputs on.  us/step, four / eight wavefronts: SAC at 17 / 6 310.9 / 277.6 with 33 agents,
+// wide actor chains, wide target chains from 113 inputs on (and of wide actions, from 65).  us/step, four / eight wavefronts: SAC at 17 / 6 310.9 / 277.6 with 33 agents,
 // 416.5 / 381.9 with 64, 1593 / 1463 with 256, at 376 / 17 857.6 / 792.7 with 64; TD3 at 376 / 17 481.8 / 442.5 with 40, at 111 / 8 646.3 / 603.5 with 100;
 // shared critics at 376 / 17 559.5 / 525.8 with 64.
 using Rows32x8 = Rows32<1, true, 1>;
@@ -462,33 +462,29 @@ using Rows16 = Rows16In<false>;
 
 // The same tiles for first layers with a fan-in of several hundred (the SAC Humanoid shapes): only the
 // first-layer product differs (software-pipelined beyond the prefetched rows).
-// PF: weight blocks of 16 rows in flight; 4 where the registers allow it (the critic chain), else 2.
-// INPUT_SLABS: the input tile is split through the slabs -- not where they lie over it (critic chains).
-template <int MT, int PF = 2, int NT = 2, bool INPUT_SLABS = PF == 2>
-struct Rows32Deep : Rows32<MT, true, NT> {
-  static constexpr bool kStageOnInput = true;
-  using Pre = typename Rows32<MT, true, NT>::Pre;
+// INPUT_SLABS: the input tile is split through the slabs -- not where they lie over it (critic chains of four wavefronts).
+// On eight wavefronts (NT = 1): target and critic chains with a CU to themselves (critic chains by LDS from 337 inputs on, slabs beside the tile or over
+// it), SAC's target chains and all actor chains.  us/step at 376 / 17 of the target and critic chains, four wavefronts and slabs over the
+// tile / so: 20 TD3 agents 247 / 238, 32 SAC agents 430 / 419, 40 TD3 agents 495 / 485; 8 TD3 agents of 111 / 8 113.6 / 109.8.
+template <int NT, bool INPUT_SLABS = true>
+struct Rows32Deep : Rows32<1, true, NT> {
+  static constexpr bool kStageOnInput = !INPUT_SLABS;
+  using Pre = typename Rows32<1, true, NT>::Pre;
   __device__ static inline void load_input(float* Xl, int xld, const float* rows, int row_stride, int c0, int n, int valid,
                                            int tid) {
-    load_input_wide<32 * MT, 64 * (8 / NT)>(Xl, xld, rows, row_stride, c0, n, valid, tid);
+    load_input_wide<32, 64 * (8 / NT)>(Xl, xld, rows, row_stride, c0, n, valid, tid);
   }
   template <bool THROUGH>
   __device__ static inline uint64_t first_layer(const float* Xs, int xld, const float* net, const NetLayout& L,
                                                 const Pre& pre, float* Yl, float* Yg, int wave, int lane, float* stage) {
-    Acc<MT, NT> acc;
+    Acc<1, NT> acc;
     acc.zero();
-    if (INPUT_SLABS) gemm_xw_slabs<MT, NT>(Xs, xld, L.in, net + L.w1, pre.w1, stage, wave, lane, acc);
-    else gemm_xw_deep<MT, PF, NT>(Xs, xld, L.in, net + L.w1, pre.w1, wave, lane, acc);
-    return relu_store<MT, THROUGH, NT>(acc, pre.b1, Yl, Yg, wave, lane);
+    if constexpr (INPUT_SLABS) gemm_xw_slabs<1, NT>(Xs, xld, L.in, net + L.w1, pre.w1, stage, wave, lane, acc);
+    else gemm_xw_deep(Xs, xld, L.in, net + L.w1, pre.w1, wave, lane, acc);
+    return relu_store<1, THROUGH, NT>(acc, pre.b1, Yl, Yg, wave, lane);
   }
 };
-
-// Wide target chains with a CU to themselves, and critic chains that have one even with the slabs over the input tile (from 337 inputs on, or few workgroups): slabs
-// beside it and eight wavefronts.  us/step at 376 / 17, before / so: 20 TD3 agents 247 / 238, 32 SAC agents 430 / 419, 40 TD3 agents
-// 495 / 485; 8 TD3 agents of 111 / 8 113.6 / 109.8.
-struct Rows32Wide : Rows32Deep<1, 2, 1> {
-  static constexpr bool kStageOnInput = false;
-};
+using Rows32Wide = Rows32Deep<1>;                    // eight wavefronts
 
 struct Rows16Deep : Rows16 {
   __device__ static inline void load_input(float* Xl, int xld, const float* rows, int row_stride, int c0, int n, int valid,

@@ -168,10 +168,10 @@ hipError_t setup_kernels() {
 #define POP_SET_LDS(...)                                                                                   \
   if ((e = hipFuncSetAttribute((const void*)__VA_ARGS__, hipFuncAttributeMaxDynamicSharedMemorySize, most)) != hipSuccess) return e
   POP_SET_LDS(k_target<Rows16Deep, 1, kSacMaxAct>);
-  POP_SET_LDS(k_target<Rows32Deep<1>, 2, kSacMaxAct>);
+  POP_SET_LDS(k_target<Rows32Deep<2>, 2, kSacMaxAct>);
   POP_SET_LDS(k_actor<Rows16Deep, 1, false, kSacMaxAct>);
   POP_SET_LDS(k_target<Rows16Deep>);
-  POP_SET_LDS(k_target<Rows32Deep<1>, 2>);
+  POP_SET_LDS(k_target<Rows32Deep<2>, 2>);
   POP_SET_LDS(k_target<Rows32x8>);
   POP_SET_LDS(k_target<Rows32Wide>);
   POP_SET_LDS(k_target<Rows32Wide, 2, kSacMaxAct>);
@@ -183,11 +183,11 @@ hipError_t setup_kernels() {
   POP_SET_LDS(k_critic<Rows32x8>);
   POP_SET_LDS(k_critic<Rows32Wide>);
   POP_SET_LDS(k_critic<Rows64>);
-  POP_SET_LDS(k_critic<Rows32Deep<1, 4>>);
+  POP_SET_LDS(k_critic<Rows32Deep<2, false>>);
   POP_SET_LDS(k_actor<Rows16>);
   POP_SET_LDS(k_actor<Rows32x8>);
-  POP_SET_LDS(k_actor<Rows32Deep<1, 2, 1>>);
-  POP_SET_LDS(k_actor<Rows32Deep<1, 2, 1>, 2, false, kSacMaxAct>);
+  POP_SET_LDS(k_actor<Rows32Wide>);
+  POP_SET_LDS(k_actor<Rows32Wide, 2, false, kSacMaxAct>);
   POP_SET_LDS(k_actor<Rows32<1>, 2>);
   POP_SET_LDS(k_actor<Rows64>);
   POP_SET_LDS(k_target_critic<Rows16, Rows32<2>>);
@@ -234,13 +234,13 @@ hipError_t launch_target(const PopDev& d, uint32_t t, hipStream_t s) {
     const size_t b32 = chain_bytes<Rows32<1>>(d.D, vec_target(d), Rows32<1>::kStage, kWideScratch);
     if (d.rows_t == 16) k_target<Rows16Deep, 1, kSacMaxAct><<<grid, block, chain_bytes<Rows16>(d.D, vec_target(d), Rows16::kStageForward, kWideScratch), s>>>(d, t);
     else if (d.rows_t == 32 && (alone || 2 * b32 > (size_t)kLdsPerCU)) k_target<Rows32Wide, 2, kSacMaxAct><<<grid, dim3(Rows32x8::kThr), b32, s>>>(d, t);
-    else if (d.rows_t == 32) k_target<Rows32Deep<1>, 2, kSacMaxAct><<<grid, block, b32, s>>>(d, t);
+    else if (d.rows_t == 32) k_target<Rows32Deep<2>, 2, kSacMaxAct><<<grid, block, b32, s>>>(d, t);
     else return hipErrorInvalidValue;
   } else if (d.D > kMaxIn) {                         // wide inputs: pipelined first layers, 16 or 32 rows
     const size_t b32 = chain_bytes<Rows32<1>>(d.D, vec_target(d));
     if (d.rows_t == 16) k_target<Rows16Deep><<<grid, block, chain_bytes<Rows16>(d.D, vec_target(d), Rows16::kStageForward), s>>>(d, t);
     else if (d.rows_t == 32 && (alone || 2 * b32 > (size_t)kLdsPerCU)) k_target<Rows32Wide><<<grid, dim3(Rows32x8::kThr), b32, s>>>(d, t);
-    else if (d.rows_t == 32) k_target<Rows32Deep<1>, 2><<<grid, block, b32, s>>>(d, t);
+    else if (d.rows_t == 32) k_target<Rows32Deep<2>, 2><<<grid, block, b32, s>>>(d, t);
     else return hipErrorInvalidValue;
   } else if (d.rows_t == 16) k_target<Rows16><<<grid, block, chain_bytes<Rows16>(d.D, vec_target(d), Rows16::kStageForward), s>>>(d, t);
   else if (d.rows_t == 32 && alone) k_target<Rows32x8><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec_target(d)), s>>>(d, t);
@@ -252,10 +252,10 @@ hipError_t launch_critic(const PopDev& d, uint32_t t, hipStream_t s) {
   const dim3 grid(xcd_grid(2 * d.P, d.B / d.rows_c)), block(kThreads);
   if (d.D > kMaxIn) {                                // wide inputs (SAC): 32 rows, pipelined first layer
     if (d.rows_c != 32) return hipErrorInvalidValue;
-    const size_t over = CriticMap<Rows32Deep<1, 4>>(d.D).bytes(), beside = CriticMap<Rows32Wide>(d.D).bytes();
-    if (beside <= (size_t)kLdsPerCU && (2 * over > (size_t)kLdsPerCU || (int)grid.x <= kCUs))
+    const size_t over = CriticMap<Rows32Deep<2, false>>(d.D).bytes(), beside = CriticMap<Rows32Wide>(d.D).bytes();
+    if (2 * over > (size_t)kLdsPerCU || (int)grid.x <= kCUs)         // a CU to itself in any case
       k_critic<Rows32Wide><<<grid, dim3(Rows32Wide::kThr), beside, s>>>(d, t);
-    else k_critic<Rows32Deep<1, 4>><<<grid, block, over, s>>>(d, t);
+    else k_critic<Rows32Deep<2, false>><<<grid, block, over, s>>>(d, t);
   } else if (d.rows_c == 32 && (int)grid.x <= kCUs) k_critic<Rows32x8><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec_critic(d)), s>>>(d, t);
   else if (d.rows_c == 32) k_critic<Rows32<1>><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec_critic(d)), s>>>(d, t);
   else k_critic<Rows64><<<grid, dim3(Rows64::kThr), chain_bytes<Rows32<2>>(d.D, vec_critic(d)), s>>>(d, t);
@@ -307,12 +307,12 @@ hipError_t launch_actor(const PopDev& d, uint32_t t, hipStream_t s) {
   if (d.A > kMaxAct) {
     if (d.actor_ahead) return hipErrorInvalidValue;
     if (d.rows_a == 16) k_actor<Rows16Deep, 1, false, kSacMaxAct><<<grid, block, chain_bytes<Rows16>(d.D, vec_actor(d), Rows16::kStage, kWideScratch), s>>>(d, t);
-    else if (d.rows_a == 32) k_actor<Rows32Deep<1, 2, 1>, 2, false, kSacMaxAct><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec_actor(d), Rows32<1>::kStage, kWideScratch), s>>>(d, t);
+    else if (d.rows_a == 32) k_actor<Rows32Wide, 2, false, kSacMaxAct><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec_actor(d), Rows32<1>::kStage, kWideScratch), s>>>(d, t);
     else return hipErrorInvalidValue;
   } else if (d.D > kMaxIn) {
     if (d.actor_ahead) return hipErrorInvalidValue;
     if (d.rows_a == 16) k_actor<Rows16Deep><<<grid, block, chain_bytes<Rows16>(d.D, vec_actor(d)), s>>>(d, t);
-    else if (d.rows_a == 32) k_actor<Rows32Deep<1, 2, 1>><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec_actor(d)), s>>>(d, t);
+    else if (d.rows_a == 32) k_actor<Rows32Wide><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec_actor(d)), s>>>(d, t);
     else return hipErrorInvalidValue;
   } else if (d.actor_ahead) {
     if (d.rows_a != 16) return hipErrorInvalidValue;

@@ -51,12 +51,12 @@ hipError_t setup_sac_kernels() {
   POP_SET_LDS(k_sac_target<SacRows64>);
   POP_SET_LDS(k_sac_target<Rows16Deep>);
   POP_SET_LDS(k_sac_target<Rows32x8>);
-  POP_SET_LDS(k_sac_target<Rows32Deep<1, 2, 1>>);
+  POP_SET_LDS(k_sac_target<Rows32Wide>);
   POP_SET_LDS(k_sac_actor<Rows16>);
   POP_SET_LDS(k_sac_actor<SacRows64>);
   POP_SET_LDS(k_sac_actor<Rows16Deep>);
   POP_SET_LDS(k_sac_actor<Rows32x8>);
-  POP_SET_LDS(k_sac_actor<Rows32Deep<1, 2, 1>>);
+  POP_SET_LDS(k_sac_actor<Rows32Wide>);
   POP_SET_LDS(k_sac_target_critic<Rows16, Rows32<2>>);
   POP_SET_LDS(k_sac_target_critic<Rows16, Rows32<1>>);
   POP_SET_LDS(k_sac_target_critic<Rows32<1>, Rows32<1>>);
@@ -81,7 +81,7 @@ hipError_t launch_sac_target(const PopDev& d, uint32_t t, hipStream_t s) {
   const int vec = vec_sac_target(d);
   if (d.D > kMaxIn) {                                // wide inputs: 16 rows, pipelined first layers
     if (d.rows_t == 16) k_sac_target<Rows16Deep><<<grid, block, chain_bytes<Rows16>(d.D, vec, Rows16::kStageForward, kSacScratch), s>>>(d, t);
-    else if (d.rows_t == 32) k_sac_target<Rows32Deep<1, 2, 1>><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec, Rows32<1>::kStage, kSacScratch), s>>>(d, t);
+    else if (d.rows_t == 32) k_sac_target<Rows32Wide><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec, Rows32<1>::kStage, kSacScratch), s>>>(d, t);
     else return hipErrorInvalidValue;
   } else if (d.rows_t == 16) k_sac_target<Rows16, 2><<<grid, block, chain_bytes<Rows16>(d.D, vec, Rows16::kStageForward, kSacScratch), s>>>(d, t);
   else if (d.rows_t == 32) k_sac_target<Rows32x8><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec, Rows32<1>::kStage, kSacScratch), s>>>(d, t);
@@ -114,7 +114,7 @@ hipError_t launch_sac_actor(const PopDev& d, uint32_t t, hipStream_t s) {
   const int vec = vec_sac_actor(d);
   if (d.D > kMaxIn) {
     if (d.rows_a == 16) k_sac_actor<Rows16Deep><<<grid, block, chain_bytes<Rows16>(d.D, vec, Rows16::kStage, kSacScratch), s>>>(d, t);
-    else if (d.rows_a == 32) k_sac_actor<Rows32Deep<1, 2, 1>><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec, Rows32<1>::kStage, kSacScratch), s>>>(d, t);
+    else if (d.rows_a == 32) k_sac_actor<Rows32Wide><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec, Rows32<1>::kStage, kSacScratch), s>>>(d, t);
     else return hipErrorInvalidValue;
   } else if (d.rows_a == 16) k_sac_actor<Rows16><<<grid, block, chain_bytes<Rows16>(d.D, vec, Rows16::kStage, kSacScratch), s>>>(d, t);
   else if (d.rows_a == 32) k_sac_actor<Rows32x8><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec, Rows32<1>::kStage, kSacScratch), s>>>(d, t);

@@ -11,11 +11,12 @@
 //   B: lane l supplies B[k = l >> 5][col = l & 31]
 //   D: register v of lane l is D[row = 8 (v >> 2) + 4 (l >> 5) + (v & 3)][col = l & 31]
 //
-// A workgroup is 4 wavefronts (8 where NT = 1, below); for a [R x 256] output each wavefront owns the
-// 64 columns [64 wave, 64 wave + 64) for all R = 32 MT rows, i.e. MT x 2 tiles.
-// Tile nt holds the columns of parity nt: lane l has columns 64 wave + 2 (l & 31) + nt
-// (tile_col), two neighbours, which it loads and stores as one 8-byte access.
-// The left operand (activations) lives in LDS and is shared by the 4
+// A workgroup is 8 / NT wavefronts; for a [R x 256] output each wavefront owns
+// 32 NT columns for all R = 32 MT rows, i.e. MT x NT tiles.  NT = 2, four wavefronts:
+// tile nt holds the columns of parity nt: lane l has columns 64 wave + 2 (l & 31) + nt
+// (tile_col), two neighbours, which it loads and stores as one 8-byte access.  NT = 1, eight wavefronts: column
+// 32 wave + (l & 31), 4-byte accesses.
+// The left operand (activations) lives in LDS and is shared by the
 // wavefronts; the right operand (weights) is read by each wavefront straight
 // from global memory/L2 into registers, because every weight element is used
 // by exactly one wavefront of the workgroup -- staging it in LDS would add
@@ -264,8 +265,9 @@ __device__ inline void gemm_xw_small(const float* __restrict__ Xl, int ldx, int 
 }
 
 // The same product for a fan-in of several hundred, on the bf16 pipe (SplitProduct's six products, above): blocks of 16,
-// contraction index 16 i + 8 s + 4 half + j at element 4 s + j of a lane, both operands split in registers, PF weight
-// blocks in flight beyond the two that `pre` holds.  With 376 inputs the first layers are three fifths of a chain's
+// contraction index 16 i + 8 s + 4 half + j at element 4 s + j of a lane, both operands split in registers, four weight
+// blocks in flight beyond the two that `pre` holds.  For the critic chains whose slabs lie over the input tile (32 rows, four wavefronts); all
+// others split the tile once per workgroup (gemm_xw_slabs, below).  With 376 inputs the first layers are three fifths of a chain's
 // matrix work, and the fp32 instructions take 1024 cycles per block of 32 rows and wavefront; the 12 bf16 instructions
 // and the splits of 12 pairs per lane some 700.  20 TD3 agents, obs 376 / act 17: 308 -> 271 us/step; 32 SAC agents 513 -> 464.
 // Error against 64 bits (2-norm; both emulated in numpy, normal inputs x Glorot weights), fp32 sums / here: 393 inputs 3.5e-7 /
@@ -273,54 +275,49 @@ __device__ inline void gemm_xw_small(const float* __restrict__ Xl, int ldx, int 
 // 3.1e-8 / 3.4e-8, one 2.5e-8 / 3.5e-8.  Inputs and weights below 2^-110 lose low parts, as in the hidden products (above).
 // X: as above; columns of the tile beyond K hold zeros (load_input_wide), and a block that would reach past the tile's
 // row reads its last four columns instead, where the weights are zero.
-template <int MT, int PF, int NT = 2>
-__device__ inline void gemm_xw_deep(const float* __restrict__ Xl, int ldx, int K, const float* __restrict__ W,
-                                    const SmallW<NT>& pre, int wave, int lane, Acc<MT, NT>& acc) {
+__device__ inline void gemm_xw_deep(const float* __restrict__ Xl, int ldx, int K, const float* __restrict__ W, const SmallW<2>& pre, int wave,
+                                    int lane, Acc<1, 2>& acc) {
+  constexpr int PF = 4;
   const int half = lane >> 5, l32 = lane & 31;
   const int nb = (K + 15) >> 4;
-  uint32_t off = 4u * (uint32_t)(4 * half * kH + tile_col<NT>(wave, 0, lane));
-  Acc<MT, NT> low;
+  uint32_t off = 4u * (uint32_t)(4 * half * kH + tile_col<2>(wave, 0, lane));
+  Acc<1, 2> low;
   low.zero();
-  float b[PF][NT][8];
-  auto request = [&](float (&dst)[NT][8], int blk) {
+  float b[PF][2][8];
+  auto request = [&](float (&dst)[2][8], int blk) {
     const WeightsRsrc Wr = weights_rsrc(W + 16 * blk * kH, (K - 16 * blk) * kH);      // rows at or beyond K are zero
     asm("" : "+v"(off));                              // or copies of it are kept for each block in flight
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const auto v = rsrc_load_cols<NT>(Wr, off + 4 * (8 * (e >> 2) + (e & 3)) * kH, 0);
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) dst[nt][e] = col_of(v, nt);
+      const f32x2 v = rsrc_load2(Wr, off + 4 * (8 * (e >> 2) + (e & 3)) * kH, 0);
+      dst[0][e] = v[0];
+      dst[1][e] = v[1];
     }
   };
-  f32x4 xn[MT][2];                                   // the LDS operand runs one block ahead
+  f32x4 xn[2];                                       // the LDS operand runs one block ahead
   auto lds_block = [&](int i) {
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        const int c = 16 * i + 8 * s + 4 * half;
-        xn[mt][s] = *reinterpret_cast<const f32x4*>(&Xl[(32 * mt + l32) * ldx + (c < ldx - 4 ? c : ldx - 4)]);
-      }
+    for (int s = 0; s < 2; ++s) {
+      const int c = 16 * i + 8 * s + 4 * half;
+      xn[s] = *reinterpret_cast<const f32x4*>(&Xl[l32 * ldx + (c < ldx - 4 ? c : ldx - 4)]);
+    }
   };
   // block i with weights w; the LDS operand of block i + 1 and the loads of next() go out ahead of the matrix work
-  auto block = [&](const float (&w)[NT][8], int i, auto next) {
-    Split8 x[MT], ws[NT];
+  auto block = [&](const float (&w)[2][8], int i, auto next) {
+    Split8 x, ws[2];
+    split8(xn[0], xn[1], x);
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) split8(xn[mt][0], xn[mt][1], x[mt]);
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) split8(w[nt], ws[nt]);
+    for (int nt = 0; nt < 2; ++nt) split8(w[nt], ws[nt]);
     lds_block(i + 1);
     next();
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int q = 0; q < kSplitTerms; ++q)
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-          f32x16& c = q == kSplitTerms - 1 ? acc.t[mt][nt] : low.t[mt][nt];
-          c = mfma32_bf16(x[mt].t[kTermX[q]], ws[nt].t[kTermW[q]], c);
-        }
+      for (int nt = 0; nt < 2; ++nt) {
+        f32x16& c = q == kSplitTerms - 1 ? acc.t[0][nt] : low.t[0][nt];
+        c = mfma32_bf16(x.t[kTermX[q]], ws[nt].t[kTermW[q]], c);
+      }
     __builtin_amdgcn_sched_barrier(0);
   };
 #pragma unroll
@@ -329,9 +326,9 @@ __device__ inline void gemm_xw_deep(const float* __restrict__ Xl, int ldx, int K
 #pragma unroll
   for (int i = 0; i < 2; ++i)
     if (i < nb) {
-      float w[NT][8];
+      float w[2][8];
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
+      for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
         for (int e = 0; e < 8; ++e) w[nt][e] = pre.w[2 * i + (e >> 2)][nt][e & 3];
       block(w, i, [] {});
@@ -488,14 +485,14 @@ struct NoTail { __device__ inline void operator()() const {} };
 
 // ---------------------------------------------------------------------------------------------
 // 256-deep product of an LDS operand (fp32 tile, row stride kLda) with a global weight operand on the bf16 pipe:
-//   forward  (TRANSPOSED = false): acc[r][c] += sum_k X[r][k] W[k][c], c in this wave's 64 columns
-//   backward (TRANSPOSED = true):  acc[r][k] += sum_n Z[r][n] W[k][n], k in this wave's 64 columns
+//   forward  (TRANSPOSED = false): acc[r][c] += sum_k X[r][k] W[k][c], c in this wave's 32 NT columns
+//   backward (TRANSPOSED = true):  acc[r][k] += sum_n Z[r][n] W[k][n], k in this wave's 32 NT columns
 // W is a [256][256] hidden matrix in the order of w2_index<PLAIN> in both cases.  Matrix and vector instructions share the issue port (measured: about five
 // cycles for either beside the other; a matrix instruction keeps its pipe for 32), and a pair of elements costs eleven
 // vector instructions to split, so the number of splits decides: a weight is used by one wavefront and split in its
-// registers, once per 32 MT rows; the LDS operand is used by all four wavefronts and split once per workgroup, 64
+// registers, once per 32 MT rows; the LDS operand is used by all wavefronts and split once per workgroup, 64
 // columns (a slab) at a time, into three bf16 planes in LDS from which the wavefronts read their operands ready for
-// use.  Per wavefront and 16-deep block: 12 MT matrix instructions, 88 + 11 MT vector instructions (88 + 44 MT where
+// use.  Per wavefront and 16-deep block: 6 MT NT matrix instructions, 44 NT + 11 MT NT / 2 vector instructions (44 NT + 44 MT where
 // every wavefront splits both operands itself).
 // 64 rows on one CU, us per product with the weights in L2: two 32-row workgroups on the fp32 instructions 16.9; here
 // 10.9 forward and 14.2 backward as two 32-row workgroups, 8.9 and 8.4 as one of 64 rows (zero weights; 13.3, 15.2,
@@ -848,8 +845,8 @@ __device__ inline void gemm256(const float* __restrict__ Xl, const float* __rest
 
 // ReLU epilogue of a hidden layer: Y = max(acc + b, 0) goes to LDS (row stride
 // kLda) and, when Yg != nullptr, to global memory as [rows][256].  Returns the
-// activation pattern of this lane's elements (bb = the two bias values of
-// this lane's columns 64 wave + 32 nt + (lane & 31), loaded by the caller ahead of the product), bit (2 mt + nt) 16 + v, so that
+// activation pattern of this lane's elements (bb = the bias values of
+// this lane's NT columns, tile_col, loaded by the caller ahead of the product), bit (NT mt + nt) 16 + v, so that
 // the backward pass can apply ReLU' without re-reading the activations: the
 // input-gradient product leaves element (row, col) in the same lane and
 // register as the forward product did.

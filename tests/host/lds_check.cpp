@@ -19,7 +19,7 @@ int main() {
         }
       }
   for (int in = pop::kMaxIn + 1; in <= pop::kSacMaxIn; ++in) {
-    const pop::CriticMap<pop::Rows32Deep<1, 4>> m(in);
+    const pop::CriticMap<pop::Rows32Deep<2, false>> m(in);
     const size_t without = pop::LdsMap<32, 8>(in).bytes(pop::vec_critic_floats), cu = pop::kLdsPerCU;
     const bool apart = m.buf + 32 * pop::kLda <= m.s0 && m.s0 + 32 * pop::kMaxAct <= m.s1 && m.s1 + 32 * pop::kMaxAct <= m.vec &&
                        m.vec + pop::vec_critic_floats <= m.input && m.input % 4 == 0 && m.stage == m.input &&

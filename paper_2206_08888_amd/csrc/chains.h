@@ -325,7 +325,8 @@ struct Rows32 {                                      // 32 MT rows on 32x32 tile
 // instructions of one wavefront run beside the matrix instructions of the other, and a trip to memory or to LDS outside the products
 // is waited for by half as much work per wavefront.  With four wavefronts a SIMD had one: 24 matrix and 110 vector instructions per block
 // at about five cycles of issue each left nothing to hide anything under.  us, four / eight wavefronts at 256 agents: product of 64 rows
-// 10.3 / 7.7, target chain 59 / 48, critic chain 36.4 / 30.5, actor chain 80 / 74, step 1007 / 925; SAC with 32 agents 214 / 209.
+// 10.3 / 7.7, target chain 59 / 48, critic chain 36.4 / 30.5; SAC's critics with 32 agents, step 214 / 209.  Actor chains stay on four: they hold the h2 tile
+// across a product, for which two wavefronts on a SIMD leave too few registers (54 spilled; launch of 256 agents 334 / 353 us, of 104 158 / 164).
 using Rows64 = Rows32<2, true, 1>;
 // The same for 32 rows, for launches in which a workgroup has a CU to itself (with two to a CU there are two wavefronts on a SIMD
 // anyway, and eight would leave no registers): actor chain of 20 TD3 agents 45.1 -> 43.0 us on a slower card, per step 20 agents

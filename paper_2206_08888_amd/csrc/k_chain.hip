@@ -189,7 +189,7 @@ hipError_t setup_kernels() {
   POP_SET_LDS(k_actor<Rows32Wide>);
   POP_SET_LDS(k_actor<Rows32Wide, 2, false, kSacMaxAct>);
   POP_SET_LDS(k_actor<Rows32<1>, 2>);
-  POP_SET_LDS(k_actor<Rows64>);
+  POP_SET_LDS(k_actor<Rows32<2>>);
   POP_SET_LDS(k_target_critic<Rows16, Rows32<2>>);
   POP_SET_LDS(k_target_critic<Rows16, Rows32<1>>);
   POP_SET_LDS(k_target_critic1<Rows32<1>>);
@@ -322,7 +322,7 @@ hipError_t launch_actor(const PopDev& d, uint32_t t, hipStream_t s) {
   else if (d.rows_a == 16) k_actor<Rows16><<<grid, block, chain_bytes<Rows16>(d.D, vec_actor(d)), s>>>(d, t);
   else if (d.rows_a == 32 && (int)grid.x > kCUs) k_actor<Rows32<1>, 2><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec_actor(d)), s>>>(d, t);
   else if (d.rows_a == 32) k_actor<Rows32x8><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec_actor(d)), s>>>(d, t);
-  else k_actor<Rows64><<<grid, dim3(Rows64::kThr), chain_bytes<Rows32<2>>(d.D, vec_actor(d)), s>>>(d, t);
+  else k_actor<Rows32<2>><<<grid, block, chain_bytes<Rows32<2>>(d.D, vec_actor(d)), s>>>(d, t);
   return hipGetLastError();
 }
 hipError_t launch_act(const PopDev& d, const float* obs, int n, float* act, const float* sigma, uint32_t step,

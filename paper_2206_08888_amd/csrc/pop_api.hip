@@ -189,12 +189,12 @@ void fill_dims(const pop_config& c, PopDev& d) {
   // Rows per workgroup of the layer chains.  16 for the target and actor chains of small
   // populations: those parts have only 8 P workgroups at 32 rows, well under the 256 CUs, and
   // their latency is what a step waits for; 16-row tiles halve the matrix time of every
-  // product by spreading it over twice the CUs.  Else 32, two workgroups per CU; 64, one per CU on
-  // eight wavefronts, for large populations: a weight is then read and split for twice the rows.  TD3 from 104 agents on, where the rounds
-  // hide the coarser tails (us/step, 32 / 64 rows: 359.9 / 372.8 at P = 88, 388.6 / 392.6 at 96, 428.3 / 423.3 at 104, 457.2 / 446.8 at 112, 488.7 / 478.8 at
-  // 120, 773.4 / 737.1 at 192, 1007 / 925 at 256).  Shared critics from 56 agents on for the target and critic chains, which always share a
-  // launch there, with actor chains of 32 rows (us/step, all 32 / all 64 / 64, 64, 32: 207.5 / 210.5 / 207.1 at P = 52, 224.6 / 219.8 / 214.0 at 56, 282.5 /
-  // 303.1 / 280.3 at 72, 304.0 / 311.3 / 290.2 at 80, 458.1 / 458.0 / 433.6 at 128, 562.9 / 583.4 / 546.1 at 160, 893.5 / 896.2 / 874.8 at 256).
+  // product by spreading it over twice the CUs.  Else 32, two workgroups per CU; 64, one per CU, target and critic chains
+  // on eight wavefronts, for large populations: a weight is then read and split for twice the rows.  TD3 from 104 agents on, where the rounds
+  // hide the coarser tails (us/step, 32 / 64 rows: 386 / 391 at P = 88, 413 / 410 at 96, 455 / 434 at 104, 484 / 458 at 112, 516 / 493 at
+  // 120, 807 / 752 at 192, 1066 / 995 at 256).  Shared critics from 56 agents on for the target and critic chains, which always share a
+  // launch there, with actor chains of 32 rows, the finer last round (us/step, all 32 / all 64 / 64, 64, 32: 222 / 222 / 225 at P = 52, 239 / 230 / 233 at 56,
+  // 308 / 314 / 304 at 72, 326 / 328 / 320 at 80, 489 / 473 / 480 at 128, 613 / 601 / 595 at 160, 962 / 921 / 927 at 256).
   // A caller's single or tail launch of TD3 runs its 64-row parts on four wavefronts (k_step) and takes them from 128 agents on: 32 / 64
   // rows, single 426.4 / 490.4 at P = 104, 493.1 / 564.3 at 120, 521.8 / 604.5 at 127; tail 418.3 / 428.2, 483.5 / 492.9, 510.9 / 518.6.
   const int cls = (int64_t)c.P * (c.batch / 16) <= kCUs ? 0 : 1;   // 16-row chains of a part get a CU each

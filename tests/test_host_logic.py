@@ -53,9 +53,9 @@ def test_wide_chains_that_have_a_cu_to_themselves_do_not_spill(k_chain_asm):
 
 
 def test_the_other_chains_spill_no_more_than_they_did(k_chain_asm):
-    """The narrow actor chains that share a SIMD hold the actor's h2 tile across a product: their spills are known, the others have none."""
+    """Narrow actor chains, two workgroups to a CU, hold the actor's h2 tile across a product: their spills are known, the others have none."""
     spills = dict(re.findall(r"\.name: +(_ZN3pop\S*k_(?:target|critic|actor|act)\S*).*?\.vgpr_spill_count: +(\d+)", k_chain_asm, re.S))
-    known = {"k_actorINS_12_GLOBAL__N_16Rows32ILi1ELb1ELi2ELb0EEELi2E": 40, "k_actorINS_12_GLOBAL__N_16Rows32ILi2ELb1ELi1ELb0EEELi2E": 54}
+    known = {"k_actorINS_12_GLOBAL__N_16Rows32ILi1ELb1ELi2ELb0EEELi2E": 40}
     for k, n in spills.items():
         assert int(n) <= max((m for name, m in known.items() if name in k), default=0), (k, n)
     assert all(any(name in k for k in spills) for name in known), sorted(spills)

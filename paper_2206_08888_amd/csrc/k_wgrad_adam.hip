@@ -7,8 +7,8 @@
 
 namespace pop {
 
-// HALF: tiles of half the width, for populations whose full tiles would leave CUs with one or two of them.
-template <bool HALF>
+// HALF: tiles of half the width, for populations whose full tiles would leave CUs with one or two of them.  PLAIN: wgrad_roles'.
+template <bool HALF, bool PLAIN>
 __global__ __launch_bounds__(kThreads, 3) void k_wgrad_adam(PopDev d, uint32_t t, int actor_phase, int main_blocks,
                                                           int roles, int prefetch) {
   __shared__ Adam sh_adam;
@@ -25,7 +25,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_wgrad_adam(PopDev d, uint32_t t
   }
   int unit, role;
   if (decode_block(blockIdx.x, actor_phase ? d.P : 2 * d.P, roles, unit, role))
-    wgrad_roles<false, true, HALF>(d, t, actor_phase, unit, role, xt_lds, &sh_adam);
+    wgrad_roles<false, true, HALF, PLAIN>(d, t, actor_phase, unit, role, xt_lds, &sh_adam);
   POP_BLOCK_TIME(actor_phase ? kTraceWgradActor : kTraceWgradCritic, 1);
 }
 
@@ -45,8 +45,9 @@ hipError_t launch_wgrad_adam(const PopDev& d, uint32_t t, int actor_phase, int p
   const int main_blocks = xcd_grid(actor_phase ? d.P : 2 * d.P, roles);
   const int extra = prefetch_next ? d.P * gather_blocks_per_agent(d) : 0;
   const dim3 grid(main_blocks + extra), block(kThreads);
-  if (d.half_tiles) k_wgrad_adam<true><<<grid, block, 0, s>>>(d, t, actor_phase, main_blocks, roles, prefetch_next);
-  else k_wgrad_adam<false><<<grid, block, 0, s>>>(d, t, actor_phase, main_blocks, roles, prefetch_next);
+  auto* kernel = d.w2_plain ? (d.half_tiles ? k_wgrad_adam<true, true> : k_wgrad_adam<false, true>)
+                            : (d.half_tiles ? k_wgrad_adam<true, false> : k_wgrad_adam<false, false>);
+  kernel<<<grid, block, 0, s>>>(d, t, actor_phase, main_blocks, roles, prefetch_next);
   return hipGetLastError();
 }
 

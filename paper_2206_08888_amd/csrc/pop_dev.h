@@ -94,7 +94,6 @@ struct PopDev {
   int rows_t, rows_c, rows_a;  // batch rows per workgroup of the target / critic / actor chain: (16, 32 or 64, 16) for
                                // small populations, else (32, 32, 32), from 104 agents on (64, 64, 64); shared critics from 56 on (64, 64, 32)
   int rows_c1;                 // rows per workgroup of critic 1's chain: rows_c, or 16 where the target workgroups run it (k_chain.hip)
-  int w2_plain;                // hidden matrices lie row-major (w2_index<true>): critic 1 inside the target workgroups and 16-row actor chains
   int cstride;                 // chunk slots per network in cpart: B / min(rows_c1, rows_c)
   int half_tiles;              // the stand-alone weight-gradient launch runs tiles of half the width (k_wgrad_adam.hip)
   NetLayout actor, critic;
@@ -137,6 +136,8 @@ struct PopDev {
   uint32_t* fault;             // [2] in pinned host memory: [0] != 0: a wait for y ran out, [1] != 0: a wait for a count
   unsigned long long wait_limit;   // longest wait of one workgroup for another of the same launch, in 10 ns ticks of the
                                // constant-rate clock (default 50 ms; a healthy wait is a fraction of a millisecond)
+  // (At the end: the fields before keep their places.  Four bytes on, the layouts' fields come to the kernels in smaller loads, 0.5 us a launch.)
+  int w2_plain;                // hidden matrices lie row-major (w2_index<true>): critic 1 inside the target workgroups and 16-row actor chains
 };
 
 // critic partial record: dW3[256] db3[1] pad[3] db2[256] db1[256] loss[1] pad[3]

@@ -245,7 +245,8 @@ constexpr int kSmallHeadBlock = 8;   // head columns of an actor that one small-
 // chain of this network) run in the same launch -- hold before the first read of chain
 // output, count in at the end.
 // SLIM: the register budget of three workgroups per CU (four dZ buffers, head columns eight at a time).
-template <bool WAIT, bool SLIM = false, bool HALF = false>
+// PLAIN: hidden matrices lie row-major.
+template <bool WAIT, bool SLIM = false, bool HALF = false, bool PLAIN = false>
 __device__ __forceinline__ void wgrad_roles(const PopDev& d, uint32_t t, int actor_phase, int unit, int role,
                                             float* xt_lds, Adam* sh_adam, bool producer_in_launch = true) {
   const int tid = threadIdx.x;
@@ -304,10 +305,10 @@ __device__ __forceinline__ void wgrad_roles(const PopDev& d, uint32_t t, int act
     if (w2 && !actor_phase)
       weight_tile<WAIT, SLIM, HALF, true>(d, wait_on, (uint32_t)chunks, sh_adam, setup, polyak, x, kH, kH, m0, n0, nullptr,
                                           d.cmask + (size_t)unit * (d.B / 32) * kH, d.cdq + (size_t)unit * d.B, d.cw3 + (size_t)unit * kH,
-                                          (uint32_t)L.w2, !d.w2_plain, xt_lds, th, mo, ve, tg, gr, tid);
+                                          (uint32_t)L.w2, !PLAIN, xt_lds, th, mo, ve, tg, gr, tid);
     else
       weight_tile<WAIT, SLIM, HALF, false>(d, wait_on, (uint32_t)chunks, sh_adam, setup, polyak, x, w2 ? kH : d.row, w2 ? kH : L.in, m0, n0, z,
-                                           nullptr, nullptr, nullptr, (uint32_t)(w2 ? L.w2 : L.w1), w2 && !d.w2_plain, xt_lds, th, mo, ve, tg, gr, tid);
+                                           nullptr, nullptr, nullptr, (uint32_t)(w2 ? L.w2 : L.w1), w2 && !PLAIN, xt_lds, th, mo, ve, tg, gr, tid);
   } else {
     // Small tensors from per-chunk partial sums; thread c owns hidden unit c.  Role `small` = 0: the hidden biases,
     // and for a critic its one head column, head bias and loss, for an actor its head bias and loss (SAC: the

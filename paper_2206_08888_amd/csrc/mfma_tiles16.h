@@ -40,9 +40,9 @@ __device__ inline f32x4 mfma16(float a, float b, f32x4 c) { return __builtin_amd
 // the weights one lane needs for a 16-deep block
 //   forward  (TRANSPOSED = false): w[j][nt] = W[16 i + k16(kq, j)][64 wave + 4 c + nt], k16 = 8 (kq >> 1) + 4 (j >> 1) + 2 (kq & 1) + (j & 1):
 //     lane groups kq and kq + 1 then read the two rows, two apart, that share a line of W2 (w2_index), and a load takes 8 whole lines; as
-//     rows 4 kq + j it took 16 half lines (10 agents 75.0 us/step with row-major matrices, 76.5 with half lines here and in WeightStage16)
+//     rows 4 kq + j it would take 16 half lines (50 steps of 10 agents in this order, with half lines here and in WeightStage16 3832 us, with whole ones 3807)
 //   backward (TRANSPOSED = true):  w[nt][j] = W[64 wave + 4 c + nt][16 i + 4 kq + j]
-// PLAIN: rows 4 kq + j of a row-major W, whole lines as well.
+// PLAIN: rows 4 kq + j of a row-major W, whole lines as well (the 9 to 12 agents that have it: w2_index).
 template <bool TRANSPOSED, bool PLAIN = false>
 struct WeightBlock16 {
   f32x4 w[4];

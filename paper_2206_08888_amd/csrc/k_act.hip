@@ -1,0 +1,228 @@
+// Acting on a few observations per agent (one environment step, evaluation with a handful of environments):
+// obs -> actor, one workgroup of sixteen wavefronts per agent and RR observations.
+//
+// One row is 66,000 multiply-adds per agent against 256 KB of W2, so the kernel is the trip of those weights to the CU and what
+// stands before and behind it.  The whole of W2 is requested at the start into registers (64 per lane: wavefront w has the rows
+// 16 w .. 16 w + 15, lane l the columns 4 l ..), and the first layer runs under that trip.  Each wavefront contracts over its
+// own 16 rows on the vector ALU (256 instructions per lane and observation row; 4x4x1 matrix instructions would take the time of four rows for one),
+// and the sixteen partial sums meet in LDS: rounding steps per sum 16 + 16 where a 256-deep chain has 256.
+// The 32-row workgroups of k_act spend 8 us on the same, most of it on rows that are not there.
+#include "chains.h"
+
+namespace pop {
+
+constexpr int kFewWaves = 16, kFewThr = 64 * kFewWaves;
+
+template <int RR>
+struct FewMap {                            // LDS (floats): observations | partial sums | hidden layer | head sums
+  static constexpr int kObsLd = kSacMaxIn;
+  static constexpr int obs = 0, part = RR * kObsLd, hidden = part + kFewWaves * RR * kH, head = hidden + RR * kH,
+                       floats = head + RR * kMaxHead;
+};
+
+// WIDE: more than 64 inputs.  Below that the first-layer weights are one batch of loads per lane.
+template <int RR, bool PLAIN, bool WIDE>
+__global__ __launch_bounds__(kFewThr) void k_act_few(PopDev d, const float* __restrict__ obs, int n, float* __restrict__ act,
+                                                     const float* __restrict__ sigma, SigmaArgs sigma_args, uint32_t step, uint32_t row_base) {
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  using L = FewMap<RR>;
+  float* xs = lds + L::obs;
+  float* part = lds + L::part;
+  float* hid = lds + L::hidden;
+  float* head = lds + L::head;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int agent, chunk;
+  if (!decode_block(blockIdx.x, d.P, (n + RR - 1) / RR, agent, chunk)) return;
+  const int r0 = chunk * RR, valid = n - r0 < RR ? n - r0 : RR;
+  const int K = d.O, A = d.A, J = d.actor.out;       // SAC: 2 A outputs, the means come first
+  const float* an = net_ptr(d, d.theta, agent, 0);
+  // observations first, then the first layer's weights, then W2: a wavefront's loads come back in the order they went out
+  const float* rows = obs + ((size_t)agent * n + r0) * K;
+  constexpr int XI = (RR * L::kObsLd + kFewThr - 1) / kFewThr;
+  float xv[XI];
+#pragma unroll
+  for (int i = 0; i < XI; ++i) {
+    const int e = tid + i * kFewThr;
+    xv[i] = 0.0f;
+    if (e < valid * K) xv[i] = rows[e];
+  }
+  constexpr int U = 4;                               // rows of W1 per wavefront and batch: k = 64 b + 16 u + wave
+  auto load_w1 = [&](f32x4 (&w)[U], int b) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = 64 * b + 16 * u + wave;
+      w[u] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      if (k < K) w[u] = *reinterpret_cast<const f32x4*>(an + d.actor.w1 + (size_t)k * kH + 4 * lane);
+    }
+  };
+  f32x4 w1[U];
+  load_w1(w1, 0);
+  f32x4 w2[16];
+  auto load_w2 = [&]() {
+    const float* p = an + d.actor.w2 + w2_index<PLAIN>(16 * wave, 0) + w2_index<PLAIN>(0, 4 * lane);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) w2[i] = *reinterpret_cast<const f32x4*>(p + w2_index<PLAIN>(i, 0));
+  };
+  const int nb = (K + 63) / 64;
+  // The head's columns wave, wave + 16, wave + 32 of the hidden units 4 lane ..; biases of the sums this thread adds up
+  constexpr int JQ = kMaxHead / kFewWaves;
+  float w3[JQ][4];
+#pragma unroll
+  for (int q = 0; q < JQ; ++q)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      w3[q][e] = 0.0f;
+      if (wave + kFewWaves * q < J) w3[q][e] = an[d.actor.w3 + (4 * lane + e) * J + wave + kFewWaves * q];
+    }
+  const float b1 = an[d.actor.b1 + (tid & (kH - 1))], b2 = an[d.actor.b2 + (tid & (kH - 1))];
+  // what the last step needs: thread e has action j of row r, its head biases and its noise
+  const int r_out = tid / A, j_out = tid - r_out * A;
+  const bool last = tid < valid * A;
+  const float ab3 = last ? an[d.actor.b3 + j_out] : 0.0f;
+  const bool sac = d.algo == 1;
+  const float lb3 = last && sac ? an[d.actor.b3 + A + j_out] : 0.0f;
+  const float sg = sigma ? sigma[agent] : sigma_args.s[agent < kStaticMaxP ? agent : 0];
+  if (!WIDE) load_w2();
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < XI; ++i) {                     // rows of K floats lie one behind the other here as well; rows past the last hold zeros
+    const int e = tid + i * kFewThr;
+    if (e < RR * L::kObsLd) xs[e] = xv[i];
+  }
+  __syncthreads();
+
+  f32x4 acc[RR];
+  auto sum_w1 = [&](const f32x4 (&w)[U], int b) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = 64 * b + 16 * u + wave;
+      if (k < K) {
+#pragma unroll
+        for (int r = 0; r < RR; ++r) acc[r] += xs[r * K + k] * w[u];
+      }
+    }
+  };
+  // the partial sums of the wavefronts, in their order, and the layer's bias and ReLU
+  auto meet = [&](float bias) {
+#pragma unroll
+    for (int r = 0; r < RR; ++r) *reinterpret_cast<f32x4*>(part + (wave * RR + r) * kH + 4 * lane) = acc[r];
+    __syncthreads();
+    if (tid < RR * kH) {
+      float s[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        s[q] = part[4 * q * RR * kH + tid];
+#pragma unroll
+        for (int i = 1; i < 4; ++i) s[q] += part[(4 * q + i) * RR * kH + tid];
+      }
+      hid[tid] = fmaxf(((s[0] + s[1]) + (s[2] + s[3])) + bias, 0.0f);
+    }
+    __syncthreads();
+  };
+#pragma unroll
+  for (int r = 0; r < RR; ++r) acc[r] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  if (WIDE) {
+#pragma unroll 1
+    for (int b = 0; b + 1 < nb; ++b) {
+      f32x4 next[U];
+      load_w1(next, b + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      sum_w1(w1, b);
+#pragma unroll
+      for (int u = 0; u < U; ++u) w1[u] = next[u];
+    }
+    load_w2();
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  sum_w1(w1, nb - 1);
+  meet(b1);
+
+  float nz = 0.0f;                                   // drawn while W2 arrives
+  if (sg > 0.0f && last) {
+    const HpDev hp = d.hp[agent];
+    const uint32_t el = (row_base + (uint32_t)(r0 + r_out)) * (uint32_t)A + (uint32_t)j_out;
+    const U4 blk = philox4x32_10(hp.seed_lo, hp.seed_hi, el >> 2, step, kStreamExplore, 0u);
+    float n4[4];
+    normals4(blk, n4);
+    nz = (el & 2u) ? ((el & 1u) ? n4[3] : n4[2]) : ((el & 1u) ? n4[1] : n4[0]);
+  }
+#pragma unroll
+  for (int r = 0; r < RR; ++r) {
+    acc[r] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const f32x4 h = *reinterpret_cast<const f32x4*>(hid + r * kH + 16 * wave + 4 * q);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[r] += h[e] * w2[4 * q + e];
+    }
+  }
+  meet(b2);
+#pragma unroll
+  for (int q = 0; q < JQ; ++q) {
+    if (wave + kFewWaves * q < J) {
+#pragma unroll
+      for (int r = 0; r < RR; ++r) {
+        const f32x4 h = *reinterpret_cast<const f32x4*>(hid + r * kH + 4 * lane);
+        const float s = wave_sum((h[0] * w3[q][0] + h[1] * w3[q][1]) + (h[2] * w3[q][2] + h[3] * w3[q][3]));
+        if (lane == 0) head[r * kMaxHead + wave + kFewWaves * q] = s;
+      }
+    }
+  }
+  __syncthreads();
+  if (last) {
+    const float pre_act = head[r_out * kMaxHead + j_out] + ab3;
+    float a = tanhf(pre_act);
+    if (sg > 0.0f) {
+      if (sac) {                                     // a sample of the policy itself, its std scaled by sigma
+        const float ls = fminf(fmaxf(head[r_out * kMaxHead + A + j_out] + lb3, -20.0f), 2.0f);
+        a = tanhf(pre_act + sg * expf(ls) * nz);
+      } else {
+        a = fminf(fmaxf(a + sg * nz, -1.0f), 1.0f);
+      }
+    }
+    act[((size_t)agent * n + r0 + r_out) * A + j_out] = a;
+  }
+}
+
+namespace {
+template <int RR>
+hipError_t setup_few() {
+  hipError_t e = hipSuccess;
+  const int bytes = FewMap<RR>::floats * (int)sizeof(float);
+  for (const void* k : {(const void*)k_act_few<RR, false, false>, (const void*)k_act_few<RR, false, true>,
+                        (const void*)k_act_few<RR, true, false>, (const void*)k_act_few<RR, true, true>})
+    if ((e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes)) != hipSuccess) return e;
+  return e;
+}
+template <int RR>
+hipError_t launch_few(const PopDev& d, const float* obs, int n, float* act, const float* sigma, const SigmaArgs& args, uint32_t step,
+                      uint32_t row_base, hipStream_t s) {
+  const bool wide = d.O > 64;
+  auto* kernel = d.w2_plain ? (wide ? k_act_few<RR, true, true> : k_act_few<RR, true, false>)
+                            : (wide ? k_act_few<RR, false, true> : k_act_few<RR, false, false>);
+  kernel<<<dim3(xcd_grid(d.P, (n + RR - 1) / RR)), dim3(kFewThr), FewMap<RR>::floats * sizeof(float), s>>>(d, obs, n, act, sigma, args, step, row_base);
+  return hipGetLastError();
+}
+}  // namespace
+
+hipError_t setup_act_kernels() {
+  hipError_t e;
+  if ((e = setup_few<1>()) != hipSuccess || (e = setup_few<2>()) != hipSuccess) return e;
+  return setup_few<4>();
+}
+
+// One workgroup of sixteen wavefronts fills a CU's registers.  As long as every RR rows get a CU to themselves the fewest rows per
+// workgroup end soonest; up to four rows per agent they are ahead of k_act's 32-row workgroups with any number of agents.
+// us per call with exploration noise, k_act behind a launch for the noise scales / here: 10 agents 1 row 14.6 / 8.0 (the host's share: 8), 50 rows 14.7 / 8.1,
+// 256 agents 1 row 18.5 / 13.5, 4 rows 18.6 / 15.5, 80 agents 8 rows 15.2 / 10.6; 376 inputs: 10 agents 1 row 33.2 / 10.9, 40 rows 37.3 / 12.4, 80
+// agents 1 row 42.0 / 15.1.
+hipError_t launch_act(const PopDev& d, const float* obs, int n, float* act, const float* sigma, const SigmaArgs& args, uint32_t step,
+                      uint32_t row_base, int whole, hipStream_t s) {
+  const int64_t P = d.P, N = whole;
+  if (N == 1 || P * N <= kCUs) return launch_few<1>(d, obs, n, act, sigma, args, step, row_base, s);
+  if (N == 2 || P * ((N + 1) / 2) <= kCUs) return launch_few<2>(d, obs, n, act, sigma, args, step, row_base, s);
+  if (N <= 4 || P * ((N + 3) / 4) <= kCUs) return launch_few<4>(d, obs, n, act, sigma, args, step, row_base, s);
+  return launch_act_rows(d, obs, n, act, sigma, args, step, row_base, s);
+}
+
+}  // namespace pop

@@ -97,12 +97,12 @@ __global__ __launch_bounds__(G::kThr, PER_CU) void k_actor(PopDev d, uint32_t t)
 
 // ---------------------------------------------------------------------------------------------
 // Acting: act[agent][r] = pi_agent(obs[agent][r]).  grid (ceil(n / 32), P).
-// sigma != nullptr: Gaussian exploration noise, a = clip(pi + sigma[agent] eps, -1, 1) with eps =
+// Noise scale sigma[agent] > 0: Gaussian exploration noise, a = clip(pi + sigma[agent] eps, -1, 1) with eps =
 // unit normal number (row_base + r) A + j of the agent's exploration stream at counter `step`
 // (row_base: index of row 0 of this call within the caller's whole request).
 template <bool PLAIN>
 __global__ __launch_bounds__(kThreads) void k_act(PopDev d, const float* __restrict__ obs, int n,
-                                                  float* __restrict__ act, const float* __restrict__ sigma,
+                                                  float* __restrict__ act, const float* __restrict__ sigma, SigmaArgs sigma_args,
                                                   uint32_t step, uint32_t row_base) {
   constexpr int R = 32;
   extern __shared__ float lds[];
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(kThreads) void k_act(PopDev d, const float* __restr
   hidden_layer<1, false, true>(buf, an, d.actor, pre, nullptr, wave, lane, NoTail(), stage);
   __syncthreads();
   head_mfma<R>(buf, an + d.actor.w3, d.actor.out, head, kHs, wave, lane);   // SAC: 2A outputs, the means come first
-  const float sg = sigma ? sigma[agent] : 0.0f;
+  const float sg = sigma ? sigma[agent] : sigma_args.s[agent < kStaticMaxP ? agent : 0];
   const bool sac = d.algo == 1;
   __syncthreads();
   const HpDev hp = d.hp[agent];
@@ -325,10 +325,10 @@ hipError_t launch_actor(const PopDev& d, uint32_t t, hipStream_t s) {
   else k_actor<Rows32<2>><<<grid, block, chain_bytes<Rows32<2>>(d.D, vec_actor(d)), s>>>(d, t);
   return hipGetLastError();
 }
-hipError_t launch_act(const PopDev& d, const float* obs, int n, float* act, const float* sigma, uint32_t step,
-                      uint32_t row_base, hipStream_t s) {
+hipError_t launch_act_rows(const PopDev& d, const float* obs, int n, float* act, const float* sigma, const SigmaArgs& args, uint32_t step,
+                           uint32_t row_base, hipStream_t s) {
   auto* kernel = d.w2_plain ? k_act<true> : k_act<false>;
-  kernel<<<dim3((n + 31) / 32, d.P), dim3(kThreads), act_lds_bytes(d), s>>>(d, obs, n, act, sigma, step, row_base);
+  kernel<<<dim3((n + 31) / 32, d.P), dim3(kThreads), act_lds_bytes(d), s>>>(d, obs, n, act, sigma, args, step, row_base);
   return hipGetLastError();
 }
 

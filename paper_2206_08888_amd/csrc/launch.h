@@ -45,10 +45,17 @@ hipError_t launch_step(const PopDev& d, uint32_t t, uint32_t launch_seq, int wit
 hipError_t setup_step_kernel();
 int wgrad_role_count(const PopDev& d, int actor_phase);
 
-// acting: obs[P][n][O] -> act[P][n][A] through the online actors; sigma (device, [P]) != nullptr adds
-// exploration noise drawn at counter `step`, rows numbered from row_base
-hipError_t launch_act(const PopDev& d, const float* obs, int n, float* act, const float* sigma, uint32_t step,
-                      uint32_t row_base, hipStream_t s);
+// acting: obs[P][n][O] -> act[P][n][A] through the online actors; a noise scale above zero adds exploration noise drawn at counter
+// `step`, rows numbered from row_base.  The scales: sigma (device, [P]), or where that is nullptr those of `args` (up to
+// kStaticMaxP agents; they travel as a kernel argument), for more agents without noise zeros.  `whole`: rows of the caller's request, of
+// which this launch may be a piece: it decides which kernel runs, so that a row comes out the same in one piece and in several.
+constexpr int kStaticMaxP = 256;
+struct SigmaArgs { float s[kStaticMaxP]; };
+hipError_t launch_act(const PopDev& d, const float* obs, int n, float* act, const float* sigma, const SigmaArgs& args, uint32_t step,
+                      uint32_t row_base, int whole, hipStream_t s);
+hipError_t launch_act_rows(const PopDev& d, const float* obs, int n, float* act, const float* sigma, const SigmaArgs& args, uint32_t step,
+                           uint32_t row_base, hipStream_t s);
+hipError_t setup_act_kernels();
 
 // one-time per-process kernel attribute setup (large dynamic LDS)
 hipError_t setup_kernels();

@@ -20,12 +20,9 @@ using namespace pop;
 // Scratch of pop_act_explore_noalloc: the per-agent noise scales of the call in flight.  One array per GPU for the
 // life of the process (1 KiB); host code reaches it only through the address hipGetSymbolAddress returns for the
 // device that is current (scratch_address below), never through this name.
-constexpr int kStaticMaxP = 256;
 static __device__ __align__(256) float scratch[kStaticMaxP];
 
 namespace {
-
-struct SigmaArgs { float s[kStaticMaxP]; };            // travels to the device as a kernel argument (1 KiB)
 
 // Hyperparameters of one agent, as a kernel argument: stream order keeps them from changing under launches in flight, where a
 // copy from host memory needs the stream idle before it as well (four agents copied and given new ones: 207 us, 134 now).
@@ -513,7 +510,8 @@ int pop_create(pop_ctx** out, const pop_config* cfg, const pop_hparams* hp, uint
     return rc;
   };
   hipError_t e;
-  if ((e = setup_kernels()) != hipSuccess || (e = setup_step_kernel()) != hipSuccess || (e = setup_sac_kernels()) != hipSuccess)
+  if ((e = setup_kernels()) != hipSuccess || (e = setup_step_kernel()) != hipSuccess || (e = setup_sac_kernels()) != hipSuccess ||
+      (e = setup_act_kernels()) != hipSuccess)
     return bail(e, "kernel attribute setup");
   if ((e = scratch_address(&ctx->static_scratch, &ctx->device)) != hipSuccess) return bail(e, "hipGetSymbolAddress(scratch)");
   // the two fault words, and room for a network whose order changes on its way: pinned host memory, mapped into the device's address space
@@ -782,8 +780,10 @@ int pop_update_timed(pop_ctx* ctx, int32_t n_steps, double* ms, int64_t* launche
 }
 
 namespace {
+const SigmaArgs kNoNoise{};
+
 int act_impl(pop_ctx* ctx, const float* obs, int32_t n, float* act_out, int32_t ptrs_on_device, const float* sigma_dev,
-             uint32_t step) {
+             const SigmaArgs& args, uint32_t step) {
   if (n < 0) return fail(ctx, POP_EINVAL, "n is negative");
   if (n == 0) return POP_OK;
   if (!obs || !act_out) return fail(ctx, POP_EINVAL, "NULL array");
@@ -791,7 +791,7 @@ int act_impl(pop_ctx* ctx, const float* obs, int32_t n, float* act_out, int32_t 
   if ((int64_t)n * d.A > 0xFFFFFFFFll) return fail(ctx, POP_EINVAL, "n * act_dim exceeds 2^32");
   hipStream_t s = ctx->stream;
   if (ptrs_on_device) {
-    HIP_TRY(ctx, launch_act(d, obs, n, act_out, sigma_dev, step, 0u, s));
+    HIP_TRY(ctx, launch_act(d, obs, n, act_out, sigma_dev, args, step, 0u, n, s));
     return POP_OK;
   }
   float* st = (float*)(ctx->ws + ctx->lay.staging);
@@ -807,7 +807,7 @@ int act_impl(pop_ctx* ctx, const float* obs, int32_t n, float* act_out, int32_t 
     if (whole) HIP_TRY(ctx, hipMemcpyAsync(s_obs, obs, (size_t)d.P * n * d.O * 4, hipMemcpyHostToDevice, s));
     else HIP_TRY(ctx, hipMemcpy2DAsync(s_obs, (size_t)k * d.O * 4, obs + off * d.O, (size_t)n * d.O * 4, (size_t)k * d.O * 4,
                                        d.P, hipMemcpyHostToDevice, s));
-    HIP_TRY(ctx, launch_act(d, s_obs, k, s_act, sigma_dev, step, (uint32_t)off, s));
+    HIP_TRY(ctx, launch_act(d, s_obs, k, s_act, sigma_dev, args, step, (uint32_t)off, n, s));
     if (whole) HIP_TRY(ctx, hipMemcpyAsync(act_out, s_act, (size_t)d.P * n * d.A * 4, hipMemcpyDeviceToHost, s));
     else HIP_TRY(ctx, hipMemcpy2DAsync(act_out + off * d.A, (size_t)n * d.A * 4, s_act, (size_t)k * d.A * 4,
                                        (size_t)k * d.A * 4, d.P, hipMemcpyDeviceToHost, s));
@@ -819,7 +819,7 @@ int act_impl(pop_ctx* ctx, const float* obs, int32_t n, float* act_out, int32_t 
 
 int pop_act(pop_ctx* ctx, const float* obs, int32_t n, float* act_out, int32_t ptrs_on_device) {
   if (!ctx) return POP_EINVAL;
-  return act_impl(ctx, obs, n, act_out, ptrs_on_device, nullptr, 0u);
+  return act_impl(ctx, obs, n, act_out, ptrs_on_device, nullptr, kNoNoise, 0u);
 }
 
 int pop_act_explore(pop_ctx* ctx, const float* obs, int32_t n, float* act_out, int32_t ptrs_on_device,
@@ -828,18 +828,23 @@ int pop_act_explore(pop_ctx* ctx, const float* obs, int32_t n, float* act_out, i
   if (!sigma) return fail(ctx, POP_EINVAL, "sigma is NULL");
   for (int a = 0; a < ctx->d.P; ++a)
     if (!(sigma[a] >= 0.0f)) return fail(ctx, POP_EINVAL, "agent %d: sigma must be >= 0", a);
-  // The noise scales travel as kernel arguments into this context's array: stream order keeps them from changing under
-  // an earlier call still in flight, so nothing here waits for the device (a copy from the caller's array needs the
-  // stream idle before it and after it: 36 -> 17 us per call with 10 agents and one row each).
+  // The noise scales travel as a kernel argument: stream order keeps them from changing under an earlier call still in flight, so
+  // nothing here waits for the device (a copy from the caller's array needs the stream idle before it and after it: 36 -> 17 us
+  // per call with 10 agents and one row each), and nothing is launched ahead of the acting kernel (17 -> 14.5 us staged first).
+  SigmaArgs args{};
+  if (ctx->d.P <= kStaticMaxP) {
+    std::memcpy(args.s, sigma, sizeof(float) * ctx->d.P);
+    return act_impl(ctx, obs, n, act_out, ptrs_on_device, nullptr, args, step);
+  }
+  // More agents than the argument holds: piecewise into this context's array, by a kernel each.
   float* sigma_dev = (float*)(ctx->ws + ctx->lay.sigma);
   for (int a0 = 0; a0 < ctx->d.P; a0 += kStaticMaxP) {
     const int k = std::min(kStaticMaxP, ctx->d.P - a0);
-    SigmaArgs args;
     std::memcpy(args.s, sigma + a0, sizeof(float) * k);
     k_stage_sigma<<<dim3((k + 63) / 64), dim3(64), 0, ctx->stream>>>(sigma_dev + a0, args, k);
     HIP_TRY(ctx, hipGetLastError());
   }
-  return act_impl(ctx, obs, n, act_out, ptrs_on_device, sigma_dev, step);
+  return act_impl(ctx, obs, n, act_out, ptrs_on_device, sigma_dev, args, step);
 }
 
 int pop_act_explore_noalloc(pop_ctx* ctx, const float* obs, int32_t n, float* act_out, const float* sigma, uint32_t step) {
@@ -861,7 +866,7 @@ int pop_act_explore_noalloc(pop_ctx* ctx, const float* obs, int32_t n, float* ac
   // argument, the acting kernel reads them from there
   k_stage_sigma<<<dim3((d.P + 63) / 64), dim3(64), 0, ctx->stream>>>(ctx->static_scratch, args, d.P);
   HIP_TRY(ctx, hipGetLastError());
-  HIP_TRY(ctx, launch_act(d, obs, n, act_out, ctx->static_scratch, step, 0u, ctx->stream));
+  HIP_TRY(ctx, launch_act(d, obs, n, act_out, ctx->static_scratch, args, step, 0u, n, ctx->stream));
   return POP_OK;
 }
 

@@ -1,0 +1,70 @@
+"""Acting on a few rows per agent (k_act_few): against the actor's forward pass in 64 bits, at the ends of its range."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2206_08888_amd as pp
+import workloads
+from gpu_common import ensure_built
+
+pytestmark = pytest.mark.gpu
+H = 256
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _lib():
+    ensure_built()
+
+
+def _actor64(pop, agent, O, out):
+    th, off, parts = pop.get_params(agent, "actor").astype(np.float64), 0, []
+    for shape in ((O, H), (H,), (H, H), (H,), (H, out), (out,)):
+        n = int(np.prod(shape))
+        parts.append(th[off:off + n].reshape(shape))
+        off += n
+    return parts
+
+
+def _forward64(net, x):
+    """Head sums, and a bound on what 32-bit sums may be off: u per operation, at most 64 operations one after the other in a
+    sum (28 + 16 for the widest first layer, 32 for the others, and the dot product over lanes), errors of a layer carried through the next."""
+    u = 64 * 2.0 ** -24
+    h, e = x, np.zeros_like(x)
+    for k in (0, 2, 4):
+        W, b = net[k], net[k + 1]
+        e = (e + u * np.abs(h)) @ np.abs(W) + u * np.abs(b)
+        h = h @ W + b
+        if k < 4:
+            h = np.maximum(h, 0.0)
+    return h, e
+
+
+@pytest.mark.parametrize("algo, P, O, A", [("td3", 1, 1, 1), ("td3", 3, 17, 6), ("td3", 10, 64, 8), ("td3", 2, 65, 24),
+                                           ("sac", 2, 128, 3), ("sac", 5, 424, 24), ("td3_shared", 3, 447, 1), ("td3", 70, 33, 5)])
+def test_a_few_rows_per_agent(algo, P, O, A):
+    code = {"td3": pp.POP_ALGO_TD3, "sac": pp.POP_ALGO_SAC, "td3_shared": pp.POP_ALGO_TD3_SHARED}[algo]
+    pop = pp.Population(pp.make_config(P, O, A, (H, H), 256, 64, algo=code), workloads.hparams(0, P))
+    rng = np.random.default_rng(100 * O + A)
+    for i in range(P):                                   # biases too
+        pop.set_params(i, "actor", pop.get_params(i, "actor") + 0.02 * rng.standard_normal(pop.actor_size).astype(np.float32))
+    nets = [_actor64(pop, i, O, 2 * A if algo == "sac" else A) for i in range(P)]
+    most = (256 // P) * 4                                # rows per agent up to which the kernel is taken whatever P is
+    first = None
+    for n in sorted({1, 2, 3, 4, 5, min(7, most), min(most, 41)}):
+        obs = rng.standard_normal((P, n, O)).astype(np.float32)
+        if first is not None:
+            obs[:, :1] = first
+        first = obs[:, :1]
+        got = pop.act(torch.from_numpy(obs).cuda()).cpu().numpy()
+        for i in range(P):
+            z, e = _forward64(nets[i], obs[i].astype(np.float64))
+            assert np.all(np.abs(got[i] - np.tanh(z[:, :A])) <= e[:, :A] + 2.0 ** -21), (n, i)
+        if n <= 4 or P * ((n + 3) // 4) <= 256:          # a row does not depend on how many there are
+            if n > 1:
+                assert np.array_equal(got[:, :1], alone)
+            alone = got[:, :1]
+        assert np.array_equal(got, pop.act(obs))         # host arrays
+        sigma = np.linspace(0.0, 0.3, P).astype(np.float32)
+        noisy = pop.act(torch.from_numpy(obs).cuda(), sigma, step=9).cpu().numpy()
+        assert np.array_equal(noisy[0], got[0]) and (P == 1 or not np.array_equal(noisy[-1], got[-1]))
+    pop.close()

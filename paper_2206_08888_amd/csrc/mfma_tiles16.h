@@ -84,8 +84,11 @@ __device__ inline void mfma_block16(const LdsBlock16& x, const WeightBlock16<TRA
 
 // 256-deep product of a 16-row LDS operand with a global weight operand, 16 blocks of 16,
 // fully unrolled; weight registers rotate through four buffers (block i+3 is requested
-// before the MFMAs of block i, about 1500 cycles of matrix work ahead), the LDS operand one
-// block ahead.  Block 0 comes from the caller; `tail()` runs once the last weight block has
+// under the MFMAs of block i, about 1500 cycles of matrix work ahead), the LDS operand one
+// block ahead.  A SIMD has one wavefront here: what does not issue between its MFMAs keeps the matrix pipe waiting, so loads and
+// LDS reads are dealt out between them (us per layer, ahead of each block / dealt out: 4.16 / 4.07 with a workgroup on every CU, 4.05 /
+// 3.80 on 16 CUs; 3.44 of matrix time).
+// Block 0 comes from the caller; `tail()` runs once the last weight block has
 // been requested, so the caller can start the next layer's loads under the last blocks.
 template <bool PLAIN, class Tail>
 __device__ inline void gemm256_16(const float* __restrict__ Xl, int ldx, const float* __restrict__ W,
@@ -101,8 +104,13 @@ __device__ inline void gemm256_16(const float* __restrict__ Xl, int ldx, const f
     if (i + 3 < 16) wb[(i + 3) & 3].load(W, i + 3, wave, lane);
     if (i == 13) tail();
     if (i + 1 < 16) xb[(i + 1) & 1].template load_k16<PLAIN>(Xl, ldx, 16 * (i + 1), lane);
-    __builtin_amdgcn_sched_barrier(0);
     mfma_block16(xb[i & 1], wb[i & 3], acc);
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      if (i + 1 < 16 && m < (PLAIN ? 1 : 2)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      else if (i + 3 < 16 && m >= 2 && m < 6) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+    }
     __builtin_amdgcn_sched_barrier(0);
   }
 }
@@ -114,6 +122,9 @@ __device__ inline void gemm256_16(const float* __restrict__ Xl, int ldx, const f
 // in double blocks of 32 n as whole lines (4 lanes x 16 bytes of each of the two rows in a line, PLAIN: 8 of one row; 8 lines per instruction), parks them in an LDS
 // area of its own and reads them back in the MFMA layout.  No barrier: a wavefront reads only what it wrote itself,
 // and the LDS serves a wavefront's accesses in order.
+// Reads, writes and loads are dealt out between the MFMAs as in the forward product: a double block is parked under the first
+// block of the one before, and its first operands are read under the second (us per layer, in bursts between the blocks / dealt
+// out: 5.7 / 4.3).
 //   LDS layout of a double block (two of them per wavefront, kStage16 floats per workgroup): row p = c + 16 nt
 //   (holding W[64 wave + 4 c + nt][32 D ..]) at p * 32 floats, its eight 16-byte pieces rotated by (p >> 1) + 4 (nt >> 1) -- the 16
 //   lanes of a quarter wavefront then hit 64 different banks in the writes (four half rows; PLAIN: two whole ones) and in the
@@ -158,7 +169,7 @@ __device__ inline void gemm256_16_staged(const float* __restrict__ Xl, int ldx, 
                                          const WeightStage16<PLAIN>& g0, float* __restrict__ stage, int wave, int lane, Acc16& acc,
                                          Tail tail) {
   float* sw = stage + wave * kStage16Wave;
-  WeightStage16<PLAIN> g[3];                                // double blocks D + 1 .. D + 3 in flight
+  WeightStage16<PLAIN> g[3];                         // double blocks on their way: D + 1 and D + 2 when round D begins
   WeightBlock16<true> wb[2];
   LdsBlock16 xb[2];
   g[0] = g0;
@@ -167,22 +178,35 @@ __device__ inline void gemm256_16_staged(const float* __restrict__ Xl, int ldx, 
   g[0].put(sw, 0, lane);
   staged_block16(wb[0], sw, 0, lane);
   xb[0].load(Xl, ldx, 0, lane);
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int D = 0; D < 8; ++D) {
-    if (D + 3 < 8) g[D % 3].load(W, D + 3, wave, lane);        // its registers were parked in LDS one round ago
-    if (D == 5) tail();
+    // under the first block's matrix instructions: the second block's operands, then the next double block into LDS
     staged_block16(wb[1], sw, 2 * D + 1, lane);
     xb[1].load(Xl, ldx, 16 * (2 * D + 1), lane);
-    __builtin_amdgcn_sched_barrier(0);
+    if (D + 1 < 8) g[(D + 1) % 3].put(sw, D + 1, lane);
     mfma_block16(xb[0], wb[0], acc);
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      if (m < 5) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      else if (D + 1 < 8 && m < 13) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+    }
     __builtin_amdgcn_sched_barrier(0);
+    // under the second's: the first operands of that double block, and the loads of the one three on
     if (D + 1 < 8) {
-      g[(D + 1) % 3].put(sw, D + 1, lane);           // requested two rounds ago (the first two: at the start)
       staged_block16(wb[0], sw, 2 * D + 2, lane);
       xb[0].load(Xl, ldx, 16 * (2 * D + 2), lane);
     }
-    __builtin_amdgcn_sched_barrier(0);
+    if (D + 3 < 8) g[D % 3].load(W, D + 3, wave, lane);        // its registers were parked in LDS one round ago
+    if (D == 5) tail();
     mfma_block16(xb[1], wb[1], acc);
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      if (D + 1 < 8 && m < 5) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      else if (D + 3 < 8 && m >= 5 && m < 13) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+    }
     __builtin_amdgcn_sched_barrier(0);
   }
 }

@@ -89,7 +89,8 @@ typedef struct {
 enum {
   POP_LAUNCH_AUTO = 0,
   POP_LAUNCH_PER_PART = 1,       /* one launch per part of the step: POP_K_TARGET .. POP_K_WGRAD_ACTOR */
-  POP_LAUNCH_TARGET_CRITIC = 2,  /* target and critic chains in one launch (POP_K_TARGET_CRITIC), the rest per part */
+  POP_LAUNCH_TARGET_CRITIC = 2,  /* target and critic chains in one launch (POP_K_TARGET_CRITIC), the rest per part; with wide inputs or
+                                    actions (obs + act > 64, act > 8) TD3 of up to 8 agents has it, others run PER_PART */
   POP_LAUNCH_SINGLE = 3,         /* the whole step in one launch (POP_K_STEP) */
   POP_LAUNCH_TAIL = 4            /* as TARGET_CRITIC, and on steps with an actor update the rest in one launch
                                     (POP_K_STEP_TAIL) */
@@ -112,7 +113,9 @@ typedef struct {
                             the actor launch starts at the critic: 0 = choose (on with rows_critic1 == 16 while every
                             workgroup of the launch has a CU of its own), 1 = off, 2 = on.  Exists for TD3 and shared critics with TARGET_CRITIC and
                             rows (16, 32, 16); POP_EINVAL for 2 elsewhere.  That pass then runs on 32-row instead of
-                            16-row tiles, another order of the fp32 sums: compare launch structures with this set to 1. */
+                            16-row tiles, another order of the fp32 sums: compare launch structures with this set to 1.
+                            Where up to 4 agents leave CUs idle in that launch, 0 has workgroups of their own run the pass, 16 rows
+                            each: the same sums as in the actor launch, and pop_get_tuning reports it as off. */
 } pop_tuning;
 
 typedef struct {

@@ -621,8 +621,10 @@ __device__ inline void wait_count(const PopDev& d, const uint32_t* count, uint32
 //   a~ = clip(pi'(s') + clip(sigma eps, -c, c), -1, 1), eps = normal e = b A + j of stream 1
 //   y  = r + gamma (1 - d) min(Q1'(s', a~), Q2'(s', a~))
 // AS: row stride of the head scratch (kMaxAct, or kSacMaxAct for action dimensions beyond kMaxAct).
-template <class G, int AS = kMaxAct>
-__device__ __forceinline__ void target_chain(const PopDev& d, uint32_t t, int agent, int chunk, float* lds) {
+// ONE: of the two target critics this workgroup runs number `one` only and publishes its value of each row; whoever reads the two
+// has the rest of y (critic_chain).
+template <class G, int AS = kMaxAct, bool ONE = false>
+__device__ __forceinline__ void target_chain(const PopDev& d, uint32_t t, int agent, int chunk, float* lds, int one = 0) {
   constexpr int R = G::R, RG = AS / kMaxAct;
   const LdsMap<G::R, G::kPad> L(d.D, AS == kMaxAct ? 3 : kWideScratch);
   float* Xs = lds;
@@ -636,8 +638,8 @@ __device__ __forceinline__ void target_chain(const PopDev& d, uint32_t t, int ag
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int r0 = chunk * R;
   const float* ta = net_ptr(d, d.target, agent, 0);
-  const float* tc0 = net_ptr(d, d.target, agent, 1);
-  const float* tc1 = net_ptr(d, d.target, agent, 2);
+  const float* tc0 = net_ptr(d, d.target, agent, 1 + (ONE ? one : 0));
+  const float* tc1 = ONE ? tc0 : net_ptr(d, d.target, agent, 2);
   POP_MARK(29);
   typename G::Pre pre;
   pre.load(ta, d.actor, wave, lane);
@@ -709,20 +711,20 @@ __device__ __forceinline__ void target_chain(const PopDev& d, uint32_t t, int ag
       const float mu = tanhf(head[r * AS + j] + v_ab3[j]);
       const float at = fminf(fmaxf(mu + noise[i], -1.0f), 1.0f);
       Xs[r * L.xld + d.O + j] = at;
-      d.atilde[((size_t)agent * d.B + r0 + r) * d.A + j] = at;
+      if (!ONE || one == 0) d.atilde[((size_t)agent * d.B + r0 + r) * d.A + j] = at;
     }
   }
   __syncthreads();
   POP_MARK(35);
 
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {
+  for (int k = 0; k < (ONE ? 1 : 2); ++k) {
     const float* tc = k == 0 ? tc0 : tc1;
     G::template first_layer<false>(Xs, L.xld, tc, d.critic, pre, buf, nullptr, wave, lane, stage);
     __syncthreads();
     POP_MARK(36 + 4 * k);
     G::template hidden_layer<false>(buf, tc, d.critic, pre, nullptr, wave, lane,
-                           [&]() { if (k == 0) pre.load(tc1, d.critic, wave, lane); }, stage);
+                           [&]() { if (!ONE && k == 0) pre.load(tc1, d.critic, wave, lane); }, stage);
     __syncthreads();
     POP_MARK(37 + 4 * k);
     G::thin(buf, v_cw3 + k * kH, 1, head, tid);
@@ -734,7 +736,9 @@ __device__ __forceinline__ void target_chain(const PopDev& d, uint32_t t, int ag
     }
     __syncthreads();
   }
-  if (tid < R) {
+  if (ONE) {
+    if (tid < R) publish_y(d, ((size_t)one * d.P + agent) * d.B + r0 + tid, t, qmin[tid]);
+  } else if (tid < R) {
     const float rew = rows[(size_t)tid * d.row + d.D];
     const float done = rows[(size_t)tid * d.row + d.D + 1];
     const float yv = rew + hp.gamma * (1.0f - done) * qmin[tid];
@@ -782,6 +786,42 @@ __device__ __forceinline__ void actor_forward_ahead(const PopDev& d, int agent, 
   }
 }
 
+// The same pass as workgroups of their own, 16 rows each: a few agents leave CUs idle beside their target and critic chains
+// (kSpreadActor).  The same sums as in actor_chain.
+template <class G, int AS>
+__device__ __forceinline__ void actor_forward(const PopDev& d, uint32_t t, int agent, int chunk, float* lds) {
+  constexpr int R = G::R;
+  const LdsMap<G::R, G::kPad> L(d.D, AS == kMaxAct ? 3 : kWideScratch);
+  float* Xs = lds;
+  float* buf = lds + L.buf;
+  float* head = lds + L.s0;
+  float* v_ab3 = lds + L.vec;
+  float* stage = lds + L.vec + vec_actor_floats_for(AS);
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int r0 = chunk * R, A = d.A;
+  if (t % (uint32_t)d.hp[agent].policy_delay != 0u) return;
+  const float* an = net_ptr(d, d.theta, agent, 0);
+  typename G::Pre pre;
+  pre.load(an, d.actor, wave, lane);
+  const float* rows = batch_rows(d, t, agent) + (size_t)r0 * d.row;
+  const size_t act_off = ((size_t)agent * d.B + r0) * kH;
+  stage_vector<G::kThr>(v_ab3, an + d.actor.b3, A, tid);
+  G::load_input(Xs, L.xld, rows, d.row, 0, d.O, R, tid);
+  __syncthreads();
+  G::template first_layer<false>(Xs, L.xld, an, d.actor, pre, buf, d.aH1 + act_off, wave, lane, stage);
+  __syncthreads();
+  G::template hidden_layer<false>(buf, an, d.actor, pre, d.aH2 + act_off, wave, lane, NoTail(), stage);
+  __syncthreads();
+  if (AS == kMaxAct || A <= 16) head_split<G, false>(buf, an + d.actor.w3, A, head, AS, wave, lane, stage);
+  else head_mfma<R, G::kThr>(buf, an + d.actor.w3, A, head, AS, wave, lane);
+  __syncthreads();
+  float* out = d.api + ((size_t)agent * d.B + r0) * A;
+  for (int e = tid; e < R * A; e += G::kThr) {
+    const int r = e / A, j = e - r * A;
+    out[e] = tanhf(head[r * AS + j] + v_ab3[j]);
+  }
+}
+
 // LDS of a critic chain.  A wide input tile (kStageOnInput) is done with once the first layer has been, and the slabs of
 // the products take its place: from 121 to 336 inputs two workgroups share a CU like that, one with the two side by
 // side (us/step at 140 inputs: TD3 with 96 agents 741 against 679, SAC with 64 agents 676 against 637).
@@ -812,8 +852,9 @@ struct CriticMap : LdsMap<G::R, G::kPad> {
 // WAIT: the targets come from target workgroups of the same launch; the lanes that need
 // them poll for their rows right before the loss.  SIGNAL: count this chunk as finished
 // for the weight-gradient workgroups of the same launch.  AHEAD: the workgroups of critic 2 run the actor's forward
-// pass for their rows before they wait (d.actor_ahead, steps with an actor update).
-template <class G, bool WAIT, bool SIGNAL, bool AHEAD = false>
+// pass for their rows before they wait (d.actor_ahead, steps with an actor update).  TWO: what is waited for are the two target critics'
+// values (target_chain's ONE); the workgroups of critic 1 write y.
+template <class G, bool WAIT, bool SIGNAL, bool AHEAD = false, bool TWO = false>
 __device__ __forceinline__ void critic_chain(const PopDev& d, uint32_t t, int net, int chunk, float* lds) {
   constexpr int R = G::R;
   static_assert(!(AHEAD && G::kStageOnInput), "the forward pass ahead reads the input tile after the first product");
@@ -832,7 +873,11 @@ __device__ __forceinline__ void critic_chain(const PopDev& d, uint32_t t, int ne
   const float* rows = batch_rows(d, t, agent) + (size_t)r0 * d.row;
   const size_t act_off = ((size_t)net * d.B + r0) * kH;
   float* part = d.cpart + ((size_t)net * d.cstride + chunk) * kCPart;
-  float yv = 0.0f, b3 = 0.0f;
+  float yv = 0.0f, b3 = 0.0f, rew = 0.0f, done = 0.0f, gamma = 0.0f;
+  if (TWO) {
+    gamma = d.hp[agent].gamma;
+    if (tid < R) { rew = rows[(size_t)tid * d.row + d.D]; done = rows[(size_t)tid * d.row + d.D + 1]; }
+  }
   if (POP_ONE_TRIP && d.D <= kMaxIn) {               // one trip to memory for all of the prologue
     SmallVec w3;
     InputTile<R, G::kThr> xin;
@@ -868,7 +913,16 @@ __device__ __forceinline__ void critic_chain(const PopDev& d, uint32_t t, int ne
     if (k == 1 && d.actor_ahead && t % (uint32_t)d.hp[agent].policy_delay == 0u)
       actor_forward_ahead<G>(d, agent, r0, Xs, L.xld, lds + L.vec + kAheadBase, stage);
   }
-  if (WAIT && tid < R) yv = await_y(d, (size_t)agent * d.B + r0 + tid, t);   // same lane uses it below
+  if (TWO) {
+    if (tid < R) {                                   // same lane uses it below
+      const size_t row = (size_t)agent * d.B + r0 + tid;
+      const float q0 = await_y(d, row, t), q1 = await_y(d, (size_t)d.P * d.B + row, t);
+      yv = rew + gamma * (1.0f - done) * fminf(q0, q1);
+      if (k == 0) d.y[row] = yv;
+    }
+  } else if (WAIT && tid < R) {
+    yv = await_y(d, (size_t)agent * d.B + r0 + tid, t);   // same lane uses it below
+  }
   __syncthreads();
   POP_MARK(4);
   if (tid < 64) {                                   // R <= 64: one wavefront covers the chunk
@@ -1003,8 +1057,21 @@ __device__ __forceinline__ void actor_chain(const PopDev& d, uint32_t t, int age
     cb3 = cn[d.critic.b3];
   };
   uint64_t mask_a1 = 0;
-  if constexpr (AHEAD) {
-    static_assert(!WAIT && AS == kMaxAct, "the forward pass ahead belongs to the separate launches of the narrow shapes");
+  if (AHEAD && (AS != kMaxAct || d.D > kMaxIn)) {
+    stage_critic();
+    if constexpr (AHEAD) mask_a1 = G::mask_from_global(d.aH1 + act_off, wave, lane);
+    G::load_input(Xs, L.xld, rows, d.row, 0, d.O, R, tid);
+    __syncthreads();
+    const float* ag = d.api + ((size_t)agent * d.B + r0) * A;
+    for (int e = tid; e < R * A; e += G::kThr) {
+      const int r = e / A, j = e - r * A;
+      const float a = ag[e];
+      api[r * AS + j] = a;
+      Xs[r * L.xld + d.O + j] = a;
+    }
+    __syncthreads();
+  } else if constexpr (AHEAD) {
+    static_assert(!WAIT, "the forward pass ahead belongs to the separate launches");
     // one trip to memory: the critic's head, the input tile [s, a_pi] (a_pi from the forward pass ahead), h1's pattern
     constexpr int IT = InputTile<R, G::kThr>::IT;
     SmallVec cw3;

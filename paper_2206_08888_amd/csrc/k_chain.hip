@@ -85,6 +85,27 @@ __global__ __launch_bounds__(kThreads, 1) void k_target_critic1(PopDev d, uint32
   POP_BLOCK_TIME(kTraceTargetCritic, 1);
 }
 
+// The same for the few agents whose target (16 rows) and critic (32 rows) workgroups leave CUs idle, and for wide inputs or actions
+// as long as each workgroup gets a CU.  A step of so few agents is a chain of single-workgroup latencies, so the idle CUs take work out of
+// it: SPLIT runs the two target critics in workgroups of their own (each repeats the target actor), and `ahead_blocks`
+// workgroups run the actor's own forward pass.  Same sums, same bits.  Blocks: targets | forward passes | critics.
+template <class GT, class GC, int AS, bool SPLIT>
+__global__ __launch_bounds__(kThreads, 1) void k_target_critic_few(PopDev d, uint32_t t, int target_blocks, int ahead_blocks) {
+  static_assert(GT::kThr == kThreads && GC::kThr == kThreads, "one workgroup size");
+  extern __shared__ float lds[];
+  int unit, sub, b = (int)blockIdx.x;
+  POP_BLOCK_TIME(kTraceTargetCritic, 0);
+  if (b < target_blocks) {
+    if (decode_block(b, d.P, (SPLIT ? 2 : 1) * (d.B / GT::R), unit, sub))
+      target_chain<GT, AS, SPLIT>(d, t, unit, SPLIT ? sub >> 1 : sub, lds, sub & 1);
+  } else if ((b -= target_blocks) < ahead_blocks) {
+    if (decode_block(b, d.P, d.B / GT::R, unit, sub)) actor_forward<GT, AS>(d, t, unit, sub, lds);
+  } else if (decode_block(b - ahead_blocks, 2 * d.P, d.B / GC::R, unit, sub)) {
+    critic_chain<GC, true, false, false, SPLIT>(d, t, unit, sub, lds);
+  }
+  POP_BLOCK_TIME(kTraceTargetCritic, 1);
+}
+
 // PER_CU: wavefronts per SIMD the register budget is set for; AHEAD, AS: actor_chain's
 template <class G, int PER_CU = G::kThr / kThreads, bool AHEAD = false, int AS = kMaxAct>
 __global__ __launch_bounds__(G::kThr, PER_CU) void k_actor(PopDev d, uint32_t t) {
@@ -201,6 +222,15 @@ hipError_t setup_kernels() {
   POP_SET_LDS(k_actor<Rows16In<true>>);
   POP_SET_LDS(k_actor<Rows16In<true>, 1, true>);
   POP_SET_LDS(k_target_critic<Rows16, Rows32<1>, true>);
+  POP_SET_LDS(k_target_critic_few<Rows16, Rows32<1>, kMaxAct, true>);
+  POP_SET_LDS(k_target_critic_few<Rows16Deep, Rows32Deep<2, false>, kMaxAct, true>);
+  POP_SET_LDS(k_target_critic_few<Rows16Deep, Rows32Deep<2, false>, kMaxAct, false>);
+  POP_SET_LDS(k_target_critic_few<Rows16Deep, Rows32Deep<2, false>, kSacMaxAct, true>);
+  POP_SET_LDS(k_target_critic_few<Rows16Deep, Rows32Deep<2, false>, kSacMaxAct, false>);
+  POP_SET_LDS(k_target_critic_few<Rows16Deep, Rows32<1>, kSacMaxAct, true>);
+  POP_SET_LDS(k_target_critic_few<Rows16Deep, Rows32<1>, kSacMaxAct, false>);
+  POP_SET_LDS(k_actor<Rows16Deep, 1, true>);
+  POP_SET_LDS(k_actor<Rows16Deep, 1, true, kSacMaxAct>);
   POP_SET_LDS(k_actor<Rows16, 1, true>);
   POP_SET_LDS(k_target_critic<Rows32<1>, Rows32<1>>);
   POP_SET_LDS(k_target_critic<Rows64, Rows64>);
@@ -261,7 +291,31 @@ hipError_t launch_critic(const PopDev& d, uint32_t t, hipStream_t s) {
   else k_critic<Rows64><<<grid, dim3(Rows64::kThr), chain_bytes<Rows32<2>>(d.D, vec_critic(d)), s>>>(d, t);
   return hipGetLastError();
 }
+hipError_t launch_target_critic_few(const PopDev& d, uint32_t t, hipStream_t s) {
+  if (d.rows_t != 16 || d.rows_c != 32 || d.rows_c1 != 32 || d.w2_plain) return hipErrorInvalidValue;
+  const bool split = (d.spread & kSpreadTargets) != 0;
+  const int chunks = xcd_grid(d.P, d.B / 16), nt = split ? 2 * chunks : chunks, na = d.spread & kSpreadActor ? chunks : 0;
+  const dim3 grid(nt + na + xcd_grid(2 * d.P, d.B / 32)), block(kThreads);
+  const int vec = std::max(std::max(vec_target(d), vec_actor(d)), vec_critic(d));
+  if (d.D <= kMaxIn && d.A <= kMaxAct) {
+    if (!split) return hipErrorInvalidValue;         // k_target_critic has it
+    const size_t bytes = std::max(chain_bytes<Rows16>(d.D, vec, Rows16::kStageForward), chain_bytes<Rows32<1>>(d.D, vec));
+    k_target_critic_few<Rows16, Rows32<1>, kMaxAct, true><<<grid, block, bytes, s>>>(d, t, nt, na);
+    return hipGetLastError();
+  }
+  const size_t bytes = std::max(chain_bytes<Rows16>(d.D, vec, Rows16::kStageForward, d.A > kMaxAct ? kWideScratch : 3),
+                                d.D > kMaxIn ? CriticMap<Rows32Deep<2, false>>(d.D).bytes() : chain_bytes<Rows32<1>>(d.D, vec));
+  auto* kernel = d.D <= kMaxIn  ? (split ? k_target_critic_few<Rows16Deep, Rows32<1>, kSacMaxAct, true>     // wide actions alone: a critic's input is narrow
+                                         : k_target_critic_few<Rows16Deep, Rows32<1>, kSacMaxAct, false>)
+                 : d.A > kMaxAct ? (split ? k_target_critic_few<Rows16Deep, Rows32Deep<2, false>, kSacMaxAct, true>
+                                        : k_target_critic_few<Rows16Deep, Rows32Deep<2, false>, kSacMaxAct, false>)
+                               : (split ? k_target_critic_few<Rows16Deep, Rows32Deep<2, false>, kMaxAct, true>
+                                        : k_target_critic_few<Rows16Deep, Rows32Deep<2, false>, kMaxAct, false>);
+  kernel<<<grid, block, bytes, s>>>(d, t, nt, na);
+  return hipGetLastError();
+}
 hipError_t launch_target_critic(const PopDev& d, uint32_t t, hipStream_t s) {
+  if (d.spread || d.D > kMaxIn || d.A > kMaxAct) return launch_target_critic_few(d, t, s);
   const int nt = xcd_grid(d.P, d.B / d.rows_t), nc = xcd_grid(2 * d.P, d.B / d.rows_c);
   const int vec = vec_target(d) > vec_critic(d) ? vec_target(d) : vec_critic(d);
   if (d.rows_c1 != d.rows_c) {                       // critic 1 inside the target workgroups
@@ -304,18 +358,21 @@ hipError_t launch_target_critic(const PopDev& d, uint32_t t, hipStream_t s) {
 }
 hipError_t launch_actor(const PopDev& d, uint32_t t, hipStream_t s) {
   const dim3 grid(xcd_grid(d.P, d.B / d.rows_a)), block(kThreads);
+  const bool ahead = (d.spread & kSpreadActor) != 0;
+  if ((d.actor_ahead || ahead) && d.rows_a != 16) return hipErrorInvalidValue;
   if (d.A > kMaxAct) {
     if (d.actor_ahead) return hipErrorInvalidValue;
-    if (d.rows_a == 16) k_actor<Rows16Deep, 1, false, kSacMaxAct><<<grid, block, chain_bytes<Rows16>(d.D, vec_actor(d), Rows16::kStage, kWideScratch), s>>>(d, t);
+    if (ahead) k_actor<Rows16Deep, 1, true, kSacMaxAct><<<grid, block, chain_bytes<Rows16>(d.D, vec_actor(d), Rows16::kStage, kWideScratch), s>>>(d, t);
+    else if (d.rows_a == 16) k_actor<Rows16Deep, 1, false, kSacMaxAct><<<grid, block, chain_bytes<Rows16>(d.D, vec_actor(d), Rows16::kStage, kWideScratch), s>>>(d, t);
     else if (d.rows_a == 32) k_actor<Rows32Wide, 2, false, kSacMaxAct><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec_actor(d), Rows32<1>::kStage, kWideScratch), s>>>(d, t);
     else return hipErrorInvalidValue;
   } else if (d.D > kMaxIn) {
     if (d.actor_ahead) return hipErrorInvalidValue;
-    if (d.rows_a == 16) k_actor<Rows16Deep><<<grid, block, chain_bytes<Rows16>(d.D, vec_actor(d)), s>>>(d, t);
+    if (ahead) k_actor<Rows16Deep, 1, true><<<grid, block, chain_bytes<Rows16>(d.D, vec_actor(d)), s>>>(d, t);
+    else if (d.rows_a == 16) k_actor<Rows16Deep><<<grid, block, chain_bytes<Rows16>(d.D, vec_actor(d)), s>>>(d, t);
     else if (d.rows_a == 32) k_actor<Rows32Wide><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec_actor(d)), s>>>(d, t);
     else return hipErrorInvalidValue;
-  } else if (d.actor_ahead) {
-    if (d.rows_a != 16) return hipErrorInvalidValue;
+  } else if (d.actor_ahead || ahead) {
     if (d.w2_plain) k_actor<Rows16In<true>, 1, true><<<grid, block, chain_bytes<Rows16>(d.D, vec_actor(d)), s>>>(d, t);
     else k_actor<Rows16, 1, true><<<grid, block, chain_bytes<Rows16>(d.D, vec_actor(d)), s>>>(d, t);
   } else if (d.rows_a == 16 && d.w2_plain) k_actor<Rows16In<true>><<<grid, block, chain_bytes<Rows16>(d.D, vec_actor(d)), s>>>(d, t);

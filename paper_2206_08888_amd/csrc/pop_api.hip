@@ -300,7 +300,7 @@ Layout make_ws_layout(const PopDev& d) {
   L.cpart = take(P * 2 * (int64_t)d.cstride * kCPart * 4);
   L.apart = take(P * (int64_t)(d.B / d.rows_a) * kAPart * 4);
   L.losses = take(P * 4 * 4);
-  L.y_tagged = take(P * B * 8);
+  L.y_tagged = take(2 * P * B * 8);
   L.done_c = take(4 * P * 4); L.done_wc = take(4 * P * 4); L.done_a = take(2 * P * 4);
   L.spart = take(2 * (int64_t)d.groups * d.critic.padded * 4);
   L.sloss = take(2 * (int64_t)d.groups * 4);
@@ -444,7 +444,10 @@ int pop_create(pop_ctx** out, const pop_config* cfg, const pop_hparams* hp, uint
   if (cfg->algo == POP_ALGO_SAC) ctx->fuse = (d.rows_t == 16 && d.rows_c == 32 && tc_blocks <= kCUs) ? 1 : 0;
   if (cfg->algo == POP_ALGO_TD3_SHARED) ctx->fuse = 1;   // target and critic chains together; the critic's weight step is a reduction of its own
   if (cfg->tuning.launch != POP_LAUNCH_AUTO) ctx->fuse = cfg->tuning.launch - POP_LAUNCH_PER_PART;   // 0 .. 3
-  if (d.D > kMaxIn || d.A > kMaxAct) ctx->fuse = 0; // wide inputs or actions: the chains exist as separate launches only
+  // Wide inputs or actions: the target and critic chains share a launch where each of their workgroups gets a CU (up to 8 TD3 agents), otherwise
+  // the chains exist as separate launches only.
+  const bool wide = d.D > kMaxIn || d.A > kMaxAct;
+  if (wide) ctx->fuse = cfg->algo != POP_ALGO_SAC && d.rows_t == 16 && tc_blocks <= kCUs && cfg->tuning.launch != POP_LAUNCH_PER_PART ? 1 : 0;
   if (cfg->algo == POP_ALGO_TD3_SHARED && ctx->fuse > 1) ctx->fuse = 1;
   if (d.rows_c1 != d.rows_c && (ctx->fuse != 1 || cfg->algo != POP_ALGO_TD3 || d.rows_t != 16 || d.rows_c1 != 16)) {
     delete ctx;
@@ -454,7 +457,7 @@ int pop_create(pop_ctx** out, const pop_config* cfg, const pop_hparams* hp, uint
   // beside 16-row target workgroups (their forward pass takes 12 us, the targets arrive after 27) and every workgroup
   // of the launch has a CU of its own.
   {
-    const bool exists = ctx->fuse == 1 && cfg->algo != POP_ALGO_SAC && d.rows_t == 16 && d.rows_c == 32 && d.rows_a == 16 && d.D <= kMaxIn;
+    const bool exists = ctx->fuse == 1 && !wide && cfg->algo != POP_ALGO_SAC && d.rows_t == 16 && d.rows_c == 32 && d.rows_a == 16 && d.D <= kMaxIn;
     if (cfg->tuning.actor_ahead == 2 && !exists) {
       delete ctx;
       return fail(nullptr, POP_EINVAL, "tuning.actor_ahead = 2 needs TD3 or shared critics, POP_LAUNCH_TARGET_CRITIC and rows (16, 32, 16)");
@@ -464,6 +467,17 @@ int pop_create(pop_ctx** out, const pop_config* cfg, const pop_hparams* hp, uint
     // most of what the actor launch saves -- except where the target workgroups, which run critic 1 as well
     // (rows_c1 == 16), are the longer ones anyway.
     d.actor_ahead = cfg->tuning.actor_ahead ? (cfg->tuning.actor_ahead == 2) : (exists && d.rows_c1 == 16 && tc_blocks <= kCUs);
+  }
+  // CUs left over beside the 32 workgroups per agent of 16-row target and 32-row critic chains: the target critics apart (16 more
+  // workgroups per agent, up to 5 agents), then the actor's forward pass (16 more, up to 4).  tuning.actor_ahead = 1 keeps that in the actor launch.
+  // us/step, without / with (delay 2): 17 / 6 55.5 / 47.4 with 1 agent, 59.6 / 51.6 with 4, 60.7 / 55.9 with 5.  Wide inputs or actions, launches of
+  // their own / fused and spread: 111 / 8 91.5 / 62.3 with 1 agent, 424 / 24 143.3 / 96.5 with 4, 447 / 1 143.1 / 105.0 with 5; fused alone: 111 / 8 109.0 /
+  // 96.5 with 8, 30 / 20 (delays 1 .. 3) 117.0 / 105.7 with 7.
+  d.spread = 0;
+  if (ctx->fuse == 1 && cfg->algo != POP_ALGO_SAC && d.rows_t == 16 && d.rows_c == 32 && d.rows_c1 == 32 && d.rows_a == 16 && !d.actor_ahead) {
+    const int64_t b16 = (int64_t)cfg->P * (cfg->batch / 16);
+    if (tc_blocks + b16 <= kCUs) d.spread |= kSpreadTargets;
+    if (tc_blocks + 2 * b16 <= kCUs && cfg->tuning.actor_ahead != 1) d.spread |= kSpreadActor;
   }
   if (ctx->fuse >= 2 && d.rows_t == 16 && d.rows_c != 64) {   // the single launch exists for the (16, 64, 16) small class only
     delete ctx;

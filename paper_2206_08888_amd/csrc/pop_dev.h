@@ -128,7 +128,8 @@ struct PopDev {
   float* losses;               // [P][4]: critic 1, critic 2, actor, unused
   float* log_alpha;            // SAC: [3][P] log temperature, its Adam m, its Adam v
   // cross-workgroup signalling inside a launch
-  uint64_t* y_tagged;          // [P][B]: (t + 1) << 32 | bits of y, for readers inside the launch that writes y
+  uint64_t* y_tagged;          // [2][P][B]: (t + 1) << 32 | bits of y, for readers inside the launch that writes y; kSpreadTargets: of the
+                               // two target critics' values
   int sync_half;               // which half of the counters below this launch counts in (set per launch)
   uint32_t* done_c;            // [2][2P] critic chunks finished per network
   uint32_t* done_wc;           // [2][2P] critic weight-gradient roles finished per network
@@ -137,8 +138,13 @@ struct PopDev {
   unsigned long long wait_limit;   // longest wait of one workgroup for another of the same launch, in 10 ns ticks of the
                                // constant-rate clock (default 50 ms; a healthy wait is a fraction of a millisecond)
   // (At the end: the fields before keep their places.  Four bytes on, the layouts' fields come to the kernels in smaller loads, 0.5 us a launch.)
+  int spread;                  // kSpread* below
   int w2_plain;                // hidden matrices lie row-major (w2_index<true>): critic 1 inside the target workgroups and 16-row actor chains
 };
+
+// What a few agents' target / critic launch runs on CUs that would stand idle (PopDev::spread, k_target_critic_few)
+constexpr int kSpreadTargets = 1;          // a workgroup per target critic: both run the target actor, each its own critic
+constexpr int kSpreadActor = 2;            // workgroups that run the actor's own forward pass, where the agent's policy is updated
 
 // critic partial record: dW3[256] db3[1] pad[3] db2[256] db1[256] loss[1] pad[3]
 constexpr int kCP_dW3 = 0, kCP_db3 = 256, kCP_db2 = 260, kCP_db1 = 516, kCP_loss = 772, kCPart = 776;

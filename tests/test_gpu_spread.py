@@ -1,0 +1,51 @@
+"""The target / critic launch of a few TD3 agents: target critics in workgroups of their own (up to 5 agents), the actor's forward
+pass beside them (up to 4), wide inputs or actions (up to 8 agents) -- all bit for bit what one launch per part computes."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2206_08888_amd as pp
+import workloads
+from gpu_common import STATE12, ensure_built
+
+pytestmark = pytest.mark.gpu
+
+
+def _states(algo, P, O, A, **kw):
+    hps = workloads.hparams(2, P)
+    for i, h in enumerate(hps):
+        h["policy_delay"] = 2 if algo == pp.POP_ALGO_TD3_SHARED else 1 + (i + 1) % 3
+    pop = pp.Population(pp.make_config(P, O, A, (256, 256), 256, 300, algo=algo, **kw), hps)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(O)
+    rnd = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    pop.insert(-1, obs=rnd(P, 300, O), act=rnd(P, 300, A).clamp(-1, 1), rew=rnd(P, 300), done=(rnd(P, 300) > 2).float(), next_obs=rnd(P, 300, O))
+    pop.update(2)
+    ms, cnt = pop.update_timed(5)
+    out = {(i, w): pop.get_params(i, w) for i in range(P) for w in STATE12}
+    out.update({w: pop.debug(w) for w in ("target_y", "target_action", "losses")})
+    pop.sync()
+    pop.close()
+    return out, cnt
+
+
+@pytest.mark.parametrize("algo, P, O, A", [
+    ("td3", 1, 17, 6), ("td3", 4, 60, 4), ("td3", 5, 1, 1), ("td3_shared", 3, 17, 6),          # narrow: both, both, targets only
+    ("td3", 1, 64, 1), ("td3", 4, 424, 24), ("td3", 5, 40, 9), ("td3_shared", 2, 9, 24),       # wide inputs, wide actions, both
+    ("td3", 6, 447, 1), ("td3", 8, 65, 8), ("td3", 8, 30, 20), ("td3_shared", 8, 111, 8)])     # fused only
+def test_against_one_launch_per_part(algo, P, O, A):
+    ensure_built()
+    code = {"td3": pp.POP_ALGO_TD3, "td3_shared": pp.POP_ALGO_TD3_SHARED}[algo]
+    want, apart = _states(code, P, O, A, launch=pp.POP_LAUNCH_PER_PART)
+    assert apart["target"] == apart["critic"] == 5 and apart["target_critic"] == 0
+    for ahead in (0, 1):
+        got, cnt = _states(code, P, O, A, actor_ahead=ahead)
+        assert cnt["target_critic"] == 5 and cnt["target"] == cnt["critic"] == 0
+        assert all(np.array_equal(got[k], want[k]) for k in want), [k for k in want if not np.array_equal(got[k], want[k])][:4]
+
+
+def test_the_first_population_whose_wide_chains_have_launches_of_their_own():
+    for P, launch in ((8, pp.POP_LAUNCH_TARGET_CRITIC), (9, pp.POP_LAUNCH_PER_PART)):
+        pop = pp.Population(pp.make_config(P, 111, 8, (256, 256), 256, 64), workloads.hparams(2, P))
+        assert pop.tuning()["launch"] == launch
+        pop.close()

@@ -85,27 +85,6 @@ __global__ __launch_bounds__(kThreads, 1) void k_target_critic1(PopDev d, uint32
   POP_BLOCK_TIME(kTraceTargetCritic, 1);
 }
 
-// The same for the few agents whose target (16 rows) and critic (32 rows) workgroups leave CUs idle, and for wide inputs or actions
-// as long as each workgroup gets a CU.  A step of so few agents is a chain of single-workgroup latencies, so the idle CUs take work out of
-// it: SPLIT runs the two target critics in workgroups of their own (each repeats the target actor), and `ahead_blocks`
-// workgroups run the actor's own forward pass.  Same sums, same bits.  Blocks: targets | forward passes | critics.
-template <class GT, class GC, int AS, bool SPLIT>
-__global__ __launch_bounds__(kThreads, 1) void k_target_critic_few(PopDev d, uint32_t t, int target_blocks, int ahead_blocks) {
-  static_assert(GT::kThr == kThreads && GC::kThr == kThreads, "one workgroup size");
-  extern __shared__ float lds[];
-  int unit, sub, b = (int)blockIdx.x;
-  POP_BLOCK_TIME(kTraceTargetCritic, 0);
-  if (b < target_blocks) {
-    if (decode_block(b, d.P, (SPLIT ? 2 : 1) * (d.B / GT::R), unit, sub))
-      target_chain<GT, AS, SPLIT>(d, t, unit, SPLIT ? sub >> 1 : sub, lds, sub & 1);
-  } else if ((b -= target_blocks) < ahead_blocks) {
-    if (decode_block(b, d.P, d.B / GT::R, unit, sub)) actor_forward<GT, AS>(d, t, unit, sub, lds);
-  } else if (decode_block(b - ahead_blocks, 2 * d.P, d.B / GC::R, unit, sub)) {
-    critic_chain<GC, true, false, false, SPLIT>(d, t, unit, sub, lds);
-  }
-  POP_BLOCK_TIME(kTraceTargetCritic, 1);
-}
-
 // PER_CU: wavefronts per SIMD the register budget is set for; AHEAD, AS: actor_chain's
 template <class G, int PER_CU = G::kThr / kThreads, bool AHEAD = false, int AS = kMaxAct>
 __global__ __launch_bounds__(G::kThr, PER_CU) void k_actor(PopDev d, uint32_t t) {
@@ -222,13 +201,6 @@ hipError_t setup_kernels() {
   POP_SET_LDS(k_actor<Rows16In<true>>);
   POP_SET_LDS(k_actor<Rows16In<true>, 1, true>);
   POP_SET_LDS(k_target_critic<Rows16, Rows32<1>, true>);
-  POP_SET_LDS(k_target_critic_few<Rows16, Rows32<1>, kMaxAct, true>);
-  POP_SET_LDS(k_target_critic_few<Rows16Deep, Rows32Deep<2, false>, kMaxAct, true>);
-  POP_SET_LDS(k_target_critic_few<Rows16Deep, Rows32Deep<2, false>, kMaxAct, false>);
-  POP_SET_LDS(k_target_critic_few<Rows16Deep, Rows32Deep<2, false>, kSacMaxAct, true>);
-  POP_SET_LDS(k_target_critic_few<Rows16Deep, Rows32Deep<2, false>, kSacMaxAct, false>);
-  POP_SET_LDS(k_target_critic_few<Rows16Deep, Rows32<1>, kSacMaxAct, true>);
-  POP_SET_LDS(k_target_critic_few<Rows16Deep, Rows32<1>, kSacMaxAct, false>);
   POP_SET_LDS(k_actor<Rows16Deep, 1, true>);
   POP_SET_LDS(k_actor<Rows16Deep, 1, true, kSacMaxAct>);
   POP_SET_LDS(k_actor<Rows16, 1, true>);
@@ -278,40 +250,18 @@ hipError_t launch_target(const PopDev& d, uint32_t t, hipStream_t s) {
   else k_target<Rows64><<<grid, dim3(Rows64::kThr), chain_bytes<Rows32<2>>(d.D, vec_target(d)), s>>>(d, t);
   return hipGetLastError();
 }
+bool wide_critics_alone(const PopDev& d) { return d.D > kMaxIn && 2 * CriticMap<Rows32Deep<2, false>>(d.D).bytes() > (size_t)kLdsPerCU; }
 hipError_t launch_critic(const PopDev& d, uint32_t t, hipStream_t s) {
   const dim3 grid(xcd_grid(2 * d.P, d.B / d.rows_c)), block(kThreads);
   if (d.D > kMaxIn) {                                // wide inputs (SAC): 32 rows, pipelined first layer
     if (d.rows_c != 32) return hipErrorInvalidValue;
     const size_t over = CriticMap<Rows32Deep<2, false>>(d.D).bytes(), beside = CriticMap<Rows32Wide>(d.D).bytes();
-    if (2 * over > (size_t)kLdsPerCU || (int)grid.x <= kCUs)         // a CU to itself in any case
+    if (wide_critics_alone(d) || (int)grid.x <= kCUs)                // a CU to itself in any case
       k_critic<Rows32Wide><<<grid, dim3(Rows32Wide::kThr), beside, s>>>(d, t);
     else k_critic<Rows32Deep<2, false>><<<grid, block, over, s>>>(d, t);
   } else if (d.rows_c == 32 && (int)grid.x <= kCUs) k_critic<Rows32x8><<<grid, dim3(Rows32x8::kThr), chain_bytes<Rows32<1>>(d.D, vec_critic(d)), s>>>(d, t);
   else if (d.rows_c == 32) k_critic<Rows32<1>><<<grid, block, chain_bytes<Rows32<1>>(d.D, vec_critic(d)), s>>>(d, t);
   else k_critic<Rows64><<<grid, dim3(Rows64::kThr), chain_bytes<Rows32<2>>(d.D, vec_critic(d)), s>>>(d, t);
-  return hipGetLastError();
-}
-hipError_t launch_target_critic_few(const PopDev& d, uint32_t t, hipStream_t s) {
-  if (d.rows_t != 16 || d.rows_c != 32 || d.rows_c1 != 32 || d.w2_plain) return hipErrorInvalidValue;
-  const bool split = (d.spread & kSpreadTargets) != 0;
-  const int chunks = xcd_grid(d.P, d.B / 16), nt = split ? 2 * chunks : chunks, na = d.spread & kSpreadActor ? chunks : 0;
-  const dim3 grid(nt + na + xcd_grid(2 * d.P, d.B / 32)), block(kThreads);
-  const int vec = std::max(std::max(vec_target(d), vec_actor(d)), vec_critic(d));
-  if (d.D <= kMaxIn && d.A <= kMaxAct) {
-    if (!split) return hipErrorInvalidValue;         // k_target_critic has it
-    const size_t bytes = std::max(chain_bytes<Rows16>(d.D, vec, Rows16::kStageForward), chain_bytes<Rows32<1>>(d.D, vec));
-    k_target_critic_few<Rows16, Rows32<1>, kMaxAct, true><<<grid, block, bytes, s>>>(d, t, nt, na);
-    return hipGetLastError();
-  }
-  const size_t bytes = std::max(chain_bytes<Rows16>(d.D, vec, Rows16::kStageForward, d.A > kMaxAct ? kWideScratch : 3),
-                                d.D > kMaxIn ? CriticMap<Rows32Deep<2, false>>(d.D).bytes() : chain_bytes<Rows32<1>>(d.D, vec));
-  auto* kernel = d.D <= kMaxIn  ? (split ? k_target_critic_few<Rows16Deep, Rows32<1>, kSacMaxAct, true>     // wide actions alone: a critic's input is narrow
-                                         : k_target_critic_few<Rows16Deep, Rows32<1>, kSacMaxAct, false>)
-                 : d.A > kMaxAct ? (split ? k_target_critic_few<Rows16Deep, Rows32Deep<2, false>, kSacMaxAct, true>
-                                        : k_target_critic_few<Rows16Deep, Rows32Deep<2, false>, kSacMaxAct, false>)
-                               : (split ? k_target_critic_few<Rows16Deep, Rows32Deep<2, false>, kMaxAct, true>
-                                        : k_target_critic_few<Rows16Deep, Rows32Deep<2, false>, kMaxAct, false>);
-  kernel<<<grid, block, bytes, s>>>(d, t, nt, na);
   return hipGetLastError();
 }
 hipError_t launch_target_critic(const PopDev& d, uint32_t t, hipStream_t s) {

@@ -20,6 +20,9 @@ hipError_t launch_sample_gather(const PopDev& d, uint32_t t, hipStream_t s);
 hipError_t launch_target(const PopDev& d, uint32_t t, hipStream_t s);
 hipError_t launch_critic(const PopDev& d, uint32_t t, hipStream_t s);
 hipError_t launch_target_critic(const PopDev& d, uint32_t t, hipStream_t s);   // both of the above in one launch
+hipError_t launch_target_critic_few(const PopDev& d, uint32_t t, hipStream_t s);   // the same for a few agents and wide shapes (k_few.hip)
+hipError_t setup_few_kernels();
+bool wide_critics_alone(const PopDev& d);   // wide inputs: a critic workgroup's LDS leaves no room for a second one on its CU
 hipError_t launch_actor(const PopDev& d, uint32_t t, hipStream_t s);
 // prefetch_next != 0: extra workgroups also gather the replay rows of step t + 1
 hipError_t launch_wgrad_adam(const PopDev& d, uint32_t t, int actor_phase, int prefetch_next, hipStream_t s);

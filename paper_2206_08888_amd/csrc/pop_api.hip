@@ -444,10 +444,19 @@ int pop_create(pop_ctx** out, const pop_config* cfg, const pop_hparams* hp, uint
   if (cfg->algo == POP_ALGO_SAC) ctx->fuse = (d.rows_t == 16 && d.rows_c == 32 && tc_blocks <= kCUs) ? 1 : 0;
   if (cfg->algo == POP_ALGO_TD3_SHARED) ctx->fuse = 1;   // target and critic chains together; the critic's weight step is a reduction of its own
   if (cfg->tuning.launch != POP_LAUNCH_AUTO) ctx->fuse = cfg->tuning.launch - POP_LAUNCH_PER_PART;   // 0 .. 3
-  // Wide inputs or actions: the target and critic chains share a launch where each of their workgroups gets a CU (up to 8 TD3 agents), otherwise
-  // the chains exist as separate launches only.
+  // Wide inputs or actions, TD3: the target and critic chains share a launch where each of their workgroups gets a CU (16-row target chains, up to 8
+  // agents), and with 32-row target chains, where critic workgroups then start in the CUs that the last round of target workgroups leaves,
+  // if those are three eighths of the chip or more and the rounds few (80 agents).  Critics that have a CU to themselves by their LDS gain in any case; others would run two to a CU
+  // by themselves.  us/step, launches of their own / fused: 376 / 17 228 / 206 with 20 agents, 248 / 244 with 24, 300 / 296 with 32, 421 / 362 with 36, 519 / 483
+  // with 52, 1152 / 1143 with 128; 111 / 8 142 / 133 with 20, 146 / 148 with 22, 165 / 167 with 28, 248 / 216 with 33, 310 / 299 with 52, 339 / 342 with 60,
+  // 354 / 357 with 64, 446 / 436 with 76, 1003 / 1006 with 180; 30 / 20 131 / 123 with 20, 146 / 149 with 28, 220 / 205 with 36, 384 / 382 with 76, 501 / 503 with 100; shared critics 111 / 8 253 / 223 with 40, 307 / 312 with 60.
   const bool wide = d.D > kMaxIn || d.A > kMaxAct;
-  if (wide) ctx->fuse = cfg->algo != POP_ALGO_SAC && d.rows_t == 16 && tc_blocks <= kCUs && cfg->tuning.launch != POP_LAUNCH_PER_PART ? 1 : 0;
+  if (wide) {
+    const int last = (int)((int64_t)cfg->P * (cfg->batch / 32) % kCUs);     // 32-row target workgroups in their last round
+    const bool pays = d.rows_t == 16 ? tc_blocks <= kCUs : (wide_critics_alone(d) || (last > 0 && 8 * last <= 5 * kCUs && 2 * (int64_t)cfg->P * (cfg->batch / 32) <= 5 * kCUs));
+    const bool can = cfg->algo != POP_ALGO_SAC && cfg->tuning.launch != POP_LAUNCH_PER_PART && (d.rows_t == 32 || tc_blocks <= kCUs);
+    ctx->fuse = can && (pays || cfg->tuning.launch == POP_LAUNCH_TARGET_CRITIC) ? 1 : 0;
+  }
   if (cfg->algo == POP_ALGO_TD3_SHARED && ctx->fuse > 1) ctx->fuse = 1;
   if (d.rows_c1 != d.rows_c && (ctx->fuse != 1 || cfg->algo != POP_ALGO_TD3 || d.rows_t != 16 || d.rows_c1 != 16)) {
     delete ctx;
@@ -525,7 +534,7 @@ int pop_create(pop_ctx** out, const pop_config* cfg, const pop_hparams* hp, uint
   };
   hipError_t e;
   if ((e = setup_kernels()) != hipSuccess || (e = setup_step_kernel()) != hipSuccess || (e = setup_sac_kernels()) != hipSuccess ||
-      (e = setup_act_kernels()) != hipSuccess)
+      (e = setup_act_kernels()) != hipSuccess || (e = setup_few_kernels()) != hipSuccess)
     return bail(e, "kernel attribute setup");
   if ((e = scratch_address(&ctx->static_scratch, &ctx->device)) != hipSuccess) return bail(e, "hipGetSymbolAddress(scratch)");
   // the two fault words, and room for a network whose order changes on its way: pinned host memory, mapped into the device's address space

@@ -14,6 +14,7 @@ __device__ unsigned long long g_pop_block_time[kTraceKinds][2][kTraceBlocks];
 #include "k_replay.hip"
 #include "k_init.hip"
 #include "k_chain.hip"
+#include "k_few.hip"
 #include "k_act.hip"
 #include "k_wgrad_adam.hip"
 #include "k_step.hip"

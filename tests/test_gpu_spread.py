@@ -1,5 +1,5 @@
-"""The target / critic launch of a few TD3 agents: target critics in workgroups of their own (up to 5 agents), the actor's forward
-pass beside them (up to 4), wide inputs or actions (up to 8 agents) -- all bit for bit what one launch per part computes."""
+"""The target / critic launch of a few TD3 agents (target critics in workgroups of their own up to 5 agents, the actor's forward
+pass beside them up to 4) and of wide inputs or actions -- all bit for bit what one launch per part computes."""
 import numpy as np
 import pytest
 import torch
@@ -15,6 +15,7 @@ def _states(algo, P, O, A, **kw):
     hps = workloads.hparams(2, P)
     for i, h in enumerate(hps):
         h["policy_delay"] = 2 if algo == pp.POP_ALGO_TD3_SHARED else 1 + (i + 1) % 3
+    kw.setdefault("launch", pp.POP_LAUNCH_TARGET_CRITIC)
     pop = pp.Population(pp.make_config(P, O, A, (256, 256), 256, 300, algo=algo, **kw), hps)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(O)
@@ -30,6 +31,7 @@ def _states(algo, P, O, A, **kw):
 
 
 @pytest.mark.parametrize("algo, P, O, A", [
+    ("td3", 17, 376, 17), ("td3", 20, 111, 8), ("td3", 33, 30, 20), ("td3_shared", 18, 336, 1), ("td3", 24, 424, 24),  # 32-row chains
     ("td3", 1, 17, 6), ("td3", 4, 60, 4), ("td3", 5, 1, 1), ("td3_shared", 3, 17, 6),          # narrow: both, both, targets only
     ("td3", 1, 64, 1), ("td3", 4, 424, 24), ("td3", 5, 40, 9), ("td3_shared", 2, 9, 24),       # wide inputs, wide actions, both
     ("td3", 6, 447, 1), ("td3", 8, 65, 8), ("td3", 8, 30, 20), ("td3_shared", 8, 111, 8)])     # fused only
@@ -45,7 +47,9 @@ def test_against_one_launch_per_part(algo, P, O, A):
 
 
 def test_the_first_population_whose_wide_chains_have_launches_of_their_own():
-    for P, launch in ((8, pp.POP_LAUNCH_TARGET_CRITIC), (9, pp.POP_LAUNCH_PER_PART)):
-        pop = pp.Population(pp.make_config(P, 111, 8, (256, 256), 256, 64), workloads.hparams(2, P))
-        assert pop.tuning()["launch"] == launch
+    fused, apart = pp.POP_LAUNCH_TARGET_CRITIC, pp.POP_LAUNCH_PER_PART
+    for P, O, launch in ((8, 111, fused), (9, 111, apart), (16, 376, apart), (20, 111, fused), (21, 111, apart), (32, 111, apart), (33, 111, fused),
+                         (52, 111, fused), (53, 111, apart), (80, 111, fused), (81, 111, apart), (32, 328, apart), (32, 329, fused), (17, 376, fused)):
+        pop = pp.Population(pp.make_config(P, O, 8, (256, 256), 256, 64), workloads.hparams(2, P))
+        assert pop.tuning()["launch"] == launch, (P, O)
         pop.close()

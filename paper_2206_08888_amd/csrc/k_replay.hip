@@ -62,8 +62,9 @@ hipError_t launch_insert(const PopDev& d, int agent, int64_t n, const float* obs
 }
 
 __global__ __launch_bounds__(256) void k_sample_gather(PopDev d, uint32_t t) {
-  // grid: (gather_blocks_per_agent, P); a thread copies one float of the stacked batch (several for wide rows)
-  gather_block(d, t, blockIdx.y, blockIdx.x, threadIdx.x);
+  // grid: (gather_blocks_per_agent, P)
+  __shared__ uint32_t drawn[kGatherLds];
+  gather_block(d, t, blockIdx.y, blockIdx.x, threadIdx.x, drawn);
 }
 
 hipError_t launch_sample_gather(const PopDev& d, uint32_t t, hipStream_t s) {

@@ -91,7 +91,7 @@ __global__ __launch_bounds__(kThreads, GC::R == 64 ? 1 : 2) void k_step(PopDev d
   b -= g.wa;
   if (b < g.g) {
     const int per = gather_blocks_per_agent(d);
-    gather_block(d, t + 1u, b / per, b % per, threadIdx.x);
+    gather_block(d, t + 1u, b / per, b % per, threadIdx.x, lds);
   }
 }
 

@@ -18,7 +18,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_wgrad_adam(PopDev d, uint32_t t
   if ((int)blockIdx.x >= main_blocks) {              // gather role: rows of the next step
     if (prefetch) {
       const int g = blockIdx.x - main_blocks, per = gather_blocks_per_agent(d);
-      gather_block(d, t + 1u, g / per, g % per, threadIdx.x);
+      gather_block(d, t + 1u, g / per, g % per, threadIdx.x, xt_lds);
     }
     POP_BLOCK_TIME(actor_phase ? kTraceWgradActor : kTraceWgradCritic, 1);
     return;

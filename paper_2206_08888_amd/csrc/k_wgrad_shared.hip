@@ -22,7 +22,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_shared_partial(PopDev d, uint32
   if ((int)blockIdx.x >= main_blocks) {
     if (prefetch) {
       const int g = blockIdx.x - main_blocks, per = gather_blocks_per_agent(d);
-      gather_block(d, t + 1u, g / per, g % per, tid);
+      gather_block(d, t + 1u, g / per, g % per, tid, xt_lds);
     }
     return;
   }

@@ -24,6 +24,8 @@ struct FewMap {                            // LDS (floats): observations | parti
 template <int RR, bool PLAIN, bool WIDE>
 __global__ __launch_bounds__(kFewThr) void k_act_few(PopDev d, const float* __restrict__ obs, int n, float* __restrict__ act,
                                                      const float* __restrict__ sigma, SigmaArgs sigma_args, uint32_t step, uint32_t row_base) {
+  warm_args<sizeof(PopDev) + 32>();
+  asm volatile("" ::"s"(step), "s"(row_base));
   extern __shared__ __attribute__((aligned(16))) float lds[];
   using L = FewMap<RR>;
   float* xs = lds + L::obs;

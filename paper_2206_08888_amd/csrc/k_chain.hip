@@ -10,6 +10,7 @@ namespace pop {
 // PER_CU: wavefronts that share a SIMD (registers to match), i.e. workgroups per CU where they have four.
 template <class G, int PER_CU = G::kPerSimd, int AS = kMaxAct>
 __global__ __launch_bounds__(G::kThr, PER_CU) void k_target(PopDev d, uint32_t t) {
+  warm_args<sizeof(PopDev) + 16>();
   extern __shared__ float lds[];
   int agent, chunk;
   POP_BLOCK_TIME(kTraceTarget, 0);
@@ -19,6 +20,7 @@ __global__ __launch_bounds__(G::kThr, PER_CU) void k_target(PopDev d, uint32_t t
 
 template <class G>
 __global__ __launch_bounds__(G::kThr, G::kPerSimd) void k_critic(PopDev d, uint32_t t) {
+  warm_args<sizeof(PopDev) + 16>();
   extern __shared__ float lds[];
   int net, chunk;
   POP_BLOCK_TIME(kTraceCritic, 0);
@@ -34,6 +36,7 @@ __global__ __launch_bounds__(G::kThr, G::kPerSimd) void k_critic(PopDev d, uint3
 // GT, GC: tile geometries of the two chains.  AHEAD: critic_chain's.
 template <class GT, class GC, bool AHEAD = false>
 __global__ __launch_bounds__(GT::kThr, GT::kPerSimd < GC::kPerSimd ? GT::kPerSimd : GC::kPerSimd) void k_target_critic(PopDev d, uint32_t t, int target_blocks) {
+  warm_args<sizeof(PopDev) + 16>();
   static_assert(GT::kThr == GC::kThr, "one workgroup size");
   extern __shared__ float lds[];
   int unit, chunk;
@@ -88,6 +91,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_target_critic1(PopDev d, uint32
 // PER_CU: wavefronts per SIMD the register budget is set for; AHEAD, AS: actor_chain's
 template <class G, int PER_CU = G::kThr / kThreads, bool AHEAD = false, int AS = kMaxAct>
 __global__ __launch_bounds__(G::kThr, PER_CU) void k_actor(PopDev d, uint32_t t) {
+  if constexpr (G::kThr != kThreads || PER_CU == 1) warm_args<sizeof(PopDev) + 16>();       // (the other is short of registers: 2 more spilled)
   extern __shared__ float lds[];
   int agent, chunk;
   POP_BLOCK_TIME(kTraceActor, 0);

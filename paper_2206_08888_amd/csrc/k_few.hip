@@ -11,6 +11,7 @@ namespace pop {
 // wide inputs or actions (eight wavefronts) have neither of the two.
 template <class GT, class GC, int AS, bool SPLIT>
 __global__ __launch_bounds__(GT::kThr, GT::kThr / kThreads) void k_target_critic_few(PopDev d, uint32_t t, int target_blocks, int ahead_blocks) {
+  warm_args<sizeof(PopDev) + 16>();
   static_assert(GT::kThr == GC::kThr, "one workgroup size");
   extern __shared__ float lds[];
   int unit, sub, b = (int)blockIdx.x;

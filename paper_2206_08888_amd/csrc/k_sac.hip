@@ -11,6 +11,7 @@ using SacRows64 = Rows32<2, false>;
 // PER_CU: workgroups that share a CU (registers to match): two of the narrow 16-row chains, for tuning beyond 16 agents
 template <class G, int PER_CU = 1>
 __global__ __launch_bounds__(G::kThr, PER_CU * G::kThr / kThreads) void k_sac_target(PopDev d, uint32_t t) {
+  warm_args<sizeof(PopDev) + 16>();
   extern __shared__ float lds[];
   int agent, chunk;
   POP_BLOCK_TIME(kTraceTarget, 0);
@@ -20,6 +21,7 @@ __global__ __launch_bounds__(G::kThr, PER_CU * G::kThr / kThreads) void k_sac_ta
 
 template <class G>
 __global__ __launch_bounds__(G::kThr, G::kThr / kThreads) void k_sac_actor(PopDev d, uint32_t t) {
+  warm_args<sizeof(PopDev) + 16>();
   extern __shared__ float lds[];
   int agent, chunk;
   POP_BLOCK_TIME(kTraceActor, 0);
@@ -31,6 +33,7 @@ __global__ __launch_bounds__(G::kThr, G::kThr / kThreads) void k_sac_actor(PopDe
 // the target workgroups and only the loss waits for the targets of its own rows.
 template <class GT, class GC>
 __global__ __launch_bounds__(kThreads, 1) void k_sac_target_critic(PopDev d, uint32_t t, int target_blocks) {
+  warm_args<sizeof(PopDev) + 16>();
   extern __shared__ float lds[];
   int unit, chunk;
   POP_BLOCK_TIME(kTraceTargetCritic, 0);

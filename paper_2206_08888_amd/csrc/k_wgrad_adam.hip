@@ -11,6 +11,7 @@ namespace pop {
 template <bool HALF, bool PLAIN>
 __global__ __launch_bounds__(kThreads, 3) void k_wgrad_adam(PopDev d, uint32_t t, int actor_phase, int main_blocks,
                                                           int roles, int prefetch) {
+  warm_args<sizeof(PopDev) + 16>();
   __shared__ Adam sh_adam;
   __shared__ __attribute__((aligned(16))) float xt_lds[kTileLds];
   POP_MARK(49);

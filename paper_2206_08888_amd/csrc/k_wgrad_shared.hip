@@ -17,6 +17,7 @@ namespace pop {
 // Blocks at and beyond main_blocks gather the replay rows of step t + 1 into the other half of the batch buffer
 // (prefetch != 0), as the tail of the per-agent weight-gradient launch does.
 __global__ __launch_bounds__(kThreads, 3) void k_shared_partial(PopDev d, uint32_t t, int roles, int main_blocks, int prefetch) {
+  warm_args<sizeof(PopDev) + 16>();
   __shared__ __attribute__((aligned(16))) float xt_lds[kTileLds];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   if ((int)blockIdx.x >= main_blocks) {

@@ -58,7 +58,7 @@ __global__ void k_stage_sigma(float* dst, SigmaArgs a, int P) {
 
 constexpr int kMaxDevices = 64;
 float* g_scratch_ptr[kMaxDevices];                     // address of `scratch` on each device, once looked up
-std::mutex g_scratch_mutex;
+std::mutex g_scratch_mutex;                            // for it and setup_device
 
 // Address of the static scratch array on the device that is current (looked up once per device).
 hipError_t scratch_address(float** out, int* device) {
@@ -76,6 +76,21 @@ hipError_t scratch_address(float** out, int* device) {
   }
   *out = g_scratch_ptr[dev];
   *device = dev;
+  return hipSuccess;
+}
+
+// Attributes of the kernels on the device that is current: set once per device (some sixty calls, 0.1 ms of a pop_create).
+hipError_t setup_device() {
+  static bool done[kMaxDevices];
+  int dev = -1;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
+  std::lock_guard<std::mutex> lock(g_scratch_mutex);
+  if (done[dev]) return hipSuccess;
+  for (hipError_t (*setup)() : {setup_kernels, setup_step_kernel, setup_sac_kernels, setup_act_kernels, setup_few_kernels})
+    if ((e = setup()) != hipSuccess) return e;
+  done[dev] = true;
   return hipSuccess;
 }
 
@@ -533,9 +548,7 @@ int pop_create(pop_ctx** out, const pop_config* cfg, const pop_hparams* hp, uint
     return rc;
   };
   hipError_t e;
-  if ((e = setup_kernels()) != hipSuccess || (e = setup_step_kernel()) != hipSuccess || (e = setup_sac_kernels()) != hipSuccess ||
-      (e = setup_act_kernels()) != hipSuccess || (e = setup_few_kernels()) != hipSuccess)
-    return bail(e, "kernel attribute setup");
+  if ((e = setup_device()) != hipSuccess) return bail(e, "kernel attribute setup");
   if ((e = scratch_address(&ctx->static_scratch, &ctx->device)) != hipSuccess) return bail(e, "hipGetSymbolAddress(scratch)");
   // the two fault words, and room for a network whose order changes on its way: pinned host memory, mapped into the device's address space
   void* fh = nullptr;

@@ -90,7 +90,7 @@ enum {
   POP_LAUNCH_AUTO = 0,
   POP_LAUNCH_PER_PART = 1,       /* one launch per part of the step: POP_K_TARGET .. POP_K_WGRAD_ACTOR */
   POP_LAUNCH_TARGET_CRITIC = 2,  /* target and critic chains in one launch (POP_K_TARGET_CRITIC), the rest per part; with wide inputs or
-                                    actions (obs + act > 64, act > 8) TD3 and shared critics have it but for 9 to 16 agents, SAC runs PER_PART */
+                                    actions (obs + act > 64, act > 8) they have it but for 9 to 16 agents */
   POP_LAUNCH_SINGLE = 3,         /* the whole step in one launch (POP_K_STEP) */
   POP_LAUNCH_TAIL = 4            /* as TARGET_CRITIC, and on steps with an actor update the rest in one launch
                                     (POP_K_STEP_TAIL) */

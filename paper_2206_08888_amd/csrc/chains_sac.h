@@ -55,8 +55,10 @@ inline int vec_sac_actor(const PopDev&) { return vec_sac_actor_floats; }
 
 // ---------------------------------------------------------------------------------------------
 // Target chain.  One workgroup per (agent, chunk).
-template <class G>
-__device__ __forceinline__ void sac_target_chain(const PopDev& d, uint32_t t, int agent, int chunk, float* lds) {
+// ONE: of the two target critics this workgroup runs number `one` only and publishes Q' - alpha log pi of each row (target_chain); the
+// smaller of the two is that of the smaller Q', rounding included.
+template <class G, bool ONE = false>
+__device__ __forceinline__ void sac_target_chain(const PopDev& d, uint32_t t, int agent, int chunk, float* lds, int one = 0) {
   constexpr int R = G::R;
   const LdsMap<G::R, G::kPad> L(d.D, kSacScratch);
   const int A = d.A;
@@ -71,8 +73,8 @@ __device__ __forceinline__ void sac_target_chain(const PopDev& d, uint32_t t, in
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int r0 = chunk * R;
   const float* an = net_ptr(d, d.theta, agent, 0);   // the online actor: SAC has no target actor
-  const float* tc0 = net_ptr(d, d.target, agent, 1);
-  const float* tc1 = net_ptr(d, d.target, agent, 2);
+  const float* tc0 = net_ptr(d, d.target, agent, 1 + (ONE ? one : 0));
+  const float* tc1 = ONE ? tc0 : net_ptr(d, d.target, agent, 2);
   typename G::Pre pre;
   pre.load(an, d.actor, wave, lane);
   const HpDev hp = d.hp[agent];
@@ -130,13 +132,13 @@ __device__ __forceinline__ void sac_target_chain(const PopDev& d, uint32_t t, in
   POP_MARK(5);
 
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {
+  for (int k = 0; k < (ONE ? 1 : 2); ++k) {
     const float* tc = k == 0 ? tc0 : tc1;
     G::template first_layer<false>(Xs, L.xld, tc, d.critic, pre, buf, nullptr, wave, lane, stage);
     __syncthreads();
     POP_MARK(6 + 3 * k);
     G::template hidden_layer<false>(buf, tc, d.critic, pre, nullptr, wave, lane,
-                                    [&]() { if (k == 0) pre.load(tc1, d.critic, wave, lane); }, stage);
+                                    [&]() { if (!ONE && k == 0) pre.load(tc1, d.critic, wave, lane); }, stage);
     __syncthreads();
     POP_MARK(7 + 3 * k);
     G::thin(buf, v_cw3 + k * kH, 1, hd, tid, kMaxHead);
@@ -148,7 +150,9 @@ __device__ __forceinline__ void sac_target_chain(const PopDev& d, uint32_t t, in
     __syncthreads();
     POP_MARK(8 + 3 * k);
   }
-  if (tid < R) {
+  if (ONE) {
+    if (tid < R) publish_y(d, ((size_t)one * d.P + agent) * d.B + r0 + tid, t, qmin[tid] - alpha * qmin[R + tid]);
+  } else if (tid < R) {
     const float rew = rows[(size_t)tid * d.row + d.D];
     const float done = rows[(size_t)tid * d.row + d.D + 1];
     const float yv = rew + hp.gamma * (1.0f - done) * (qmin[tid] - alpha * qmin[R + tid]);

@@ -45,6 +45,23 @@ __global__ __launch_bounds__(kThreads, 1) void k_sac_target_critic(PopDev d, uin
   POP_BLOCK_TIME(kTraceTargetCritic, 1);
 }
 
+// The same for a few agents and for wide inputs (k_target_critic_few, k_few.hip).  SPLIT: a workgroup per target critic.
+template <class GT, class GC, bool SPLIT>
+__global__ __launch_bounds__(GT::kThr, GT::kThr / kThreads) void k_sac_target_critic_few(PopDev d, uint32_t t, int target_blocks) {
+  static_assert(GT::kThr == GC::kThr, "one workgroup size");
+  warm_args<sizeof(PopDev) + 16>();
+  extern __shared__ float lds[];
+  int unit, sub;
+  POP_BLOCK_TIME(kTraceTargetCritic, 0);
+  if ((int)blockIdx.x < target_blocks) {
+    if (decode_block(blockIdx.x, d.P, (SPLIT ? 2 : 1) * (d.B / GT::R), unit, sub))
+      sac_target_chain<GT, SPLIT>(d, t, unit, SPLIT ? sub >> 1 : sub, lds, sub & 1);
+  } else if (decode_block(blockIdx.x - target_blocks, 2 * d.P, d.B / GC::R, unit, sub)) {
+    critic_chain<GC, true, false, false, SPLIT>(d, t, unit, sub, lds);
+  }
+  POP_BLOCK_TIME(kTraceTargetCritic, 1);
+}
+
 hipError_t setup_sac_kernels() {
   hipError_t e;
   const int most = 160 * 1024;
@@ -63,6 +80,10 @@ hipError_t setup_sac_kernels() {
   POP_SET_LDS(k_sac_target_critic<Rows16, Rows32<2>>);
   POP_SET_LDS(k_sac_target_critic<Rows16, Rows32<1>>);
   POP_SET_LDS(k_sac_target_critic<Rows32<1>, Rows32<1>>);
+  POP_SET_LDS(k_sac_target_critic_few<Rows16, Rows32<1>, true>);
+  POP_SET_LDS(k_sac_target_critic_few<Rows16Deep, Rows32Deep<2, false>, true>);
+  POP_SET_LDS(k_sac_target_critic_few<Rows16Deep, Rows32Deep<2, false>, false>);
+  POP_SET_LDS(k_sac_target_critic_few<Rows32Wide, Rows32Wide, false>);
 #undef POP_SET_LDS
   return hipSuccess;
 }
@@ -92,11 +113,28 @@ hipError_t launch_sac_target(const PopDev& d, uint32_t t, hipStream_t s) {
   return hipGetLastError();
 }
 
+static hipError_t launch_sac_target_critic_few(const PopDev& d, uint32_t t, hipStream_t s) {
+  const bool split = (d.spread & kSpreadTargets) != 0, wide = d.D > kMaxIn;
+  if (d.rows_c != 32 || d.rows_c1 != 32 || (d.rows_t != 16 && (d.rows_t != 32 || split || !wide)) || (!wide && !split)) return hipErrorInvalidValue;
+  const int nt = (split ? 2 : 1) * xcd_grid(d.P, d.B / d.rows_t), vec = vec_sac_target(d);
+  const dim3 grid(nt + xcd_grid(2 * d.P, d.B / 32));
+  if (d.rows_t == 32) {
+    const size_t bytes = std::max(chain_bytes<Rows32<1>>(d.D, vec, Rows32<1>::kStage, kSacScratch), CriticMap<Rows32Wide>(d.D).bytes());
+    k_sac_target_critic_few<Rows32Wide, Rows32Wide, false><<<grid, dim3(Rows32Wide::kThr), bytes, s>>>(d, t, nt);
+    return hipGetLastError();
+  }
+  const size_t bytes = std::max(chain_bytes<Rows16>(d.D, vec, Rows16::kStageForward, kSacScratch),
+                                wide ? CriticMap<Rows32Deep<2, false>>(d.D).bytes() : chain_bytes<Rows32<1>>(d.D, vec_critic(d)));
+  auto* kernel = !wide ? k_sac_target_critic_few<Rows16, Rows32<1>, true>
+                 : split ? k_sac_target_critic_few<Rows16Deep, Rows32Deep<2, false>, true> : k_sac_target_critic_few<Rows16Deep, Rows32Deep<2, false>, false>;
+  kernel<<<grid, dim3(kThreads), bytes, s>>>(d, t, nt);
+  return hipGetLastError();
+}
 hipError_t launch_sac_target_critic(const PopDev& d, uint32_t t, hipStream_t s) {
+  if (d.spread || d.D > kMaxIn) return launch_sac_target_critic_few(d, t, s);
   const int nt = xcd_grid(d.P, d.B / d.rows_t), nc = xcd_grid(2 * d.P, d.B / d.rows_c);
   const dim3 grid(nt + nc), block(kThreads);
   const int vec = vec_sac_target(d);                 // larger than the critic chain's
-  if (d.D > kMaxIn) return hipErrorInvalidValue;     // wide inputs run the two chains as separate launches
   if (d.rows_t == 16 && d.rows_c == 64) {
     const size_t a = chain_bytes<Rows16>(d.D, vec, Rows16::kStageForward, kSacScratch), b = chain_bytes<Rows32<2>>(d.D, vec_critic(d));
     k_sac_target_critic<Rows16, Rows32<2>><<<grid, block, a > b ? a : b, s>>>(d, t, nt);

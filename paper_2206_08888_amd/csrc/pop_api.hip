@@ -459,17 +459,18 @@ int pop_create(pop_ctx** out, const pop_config* cfg, const pop_hparams* hp, uint
   if (cfg->algo == POP_ALGO_SAC) ctx->fuse = (d.rows_t == 16 && d.rows_c == 32 && tc_blocks <= kCUs) ? 1 : 0;
   if (cfg->algo == POP_ALGO_TD3_SHARED) ctx->fuse = 1;   // target and critic chains together; the critic's weight step is a reduction of its own
   if (cfg->tuning.launch != POP_LAUNCH_AUTO) ctx->fuse = cfg->tuning.launch - POP_LAUNCH_PER_PART;   // 0 .. 3
-  // Wide inputs or actions, TD3: the target and critic chains share a launch where each of their workgroups gets a CU (16-row target chains, up to 8
+  // Wide inputs or (but for SAC) actions: the target and critic chains share a launch where each of their workgroups gets a CU (16-row target chains, up to 8
   // agents), and with 32-row target chains, where critic workgroups then start in the CUs that the last round of target workgroups leaves,
   // if those are three eighths of the chip or more and the rounds few (80 agents).  Critics that have a CU to themselves by their LDS gain in any case; others would run two to a CU
   // by themselves.  us/step, launches of their own / fused: 376 / 17 228 / 206 with 20 agents, 248 / 244 with 24, 300 / 296 with 32, 421 / 362 with 36, 519 / 483
   // with 52, 1152 / 1143 with 128; 111 / 8 142 / 133 with 20, 146 / 148 with 22, 165 / 167 with 28, 248 / 216 with 33, 310 / 299 with 52, 339 / 342 with 60,
-  // 354 / 357 with 64, 446 / 436 with 76, 1003 / 1006 with 180; 30 / 20 131 / 123 with 20, 146 / 149 with 28, 220 / 205 with 36, 384 / 382 with 76, 501 / 503 with 100; shared critics 111 / 8 253 / 223 with 40, 307 / 312 with 60.
-  const bool wide = d.D > kMaxIn || d.A > kMaxAct;
+  // 354 / 357 with 64, 446 / 436 with 76, 1003 / 1006 with 180; 30 / 20 131 / 123 with 20, 146 / 149 with 28, 220 / 205 with 36, 384 / 382 with 76, 501 / 503 with 100; shared critics 111 / 8 253 / 223 with 40, 307 / 312 with 60;
+  // SAC 111 / 8 194 / 183 with 20, 203 / 204 with 24, 344 / 313 with 33, 442 / 447 with 60, 376 / 17 294 / 275 with 20, 371 / 370 with 32, 535 / 477 with 33.
+  const bool wide = d.D > kMaxIn || (cfg->algo != POP_ALGO_SAC && d.A > kMaxAct);
   if (wide) {
     const int last = (int)((int64_t)cfg->P * (cfg->batch / 32) % kCUs);     // 32-row target workgroups in their last round
     const bool pays = d.rows_t == 16 ? tc_blocks <= kCUs : (wide_critics_alone(d) || (last > 0 && 8 * last <= 5 * kCUs && 2 * (int64_t)cfg->P * (cfg->batch / 32) <= 5 * kCUs));
-    const bool can = cfg->algo != POP_ALGO_SAC && cfg->tuning.launch != POP_LAUNCH_PER_PART && (d.rows_t == 32 || tc_blocks <= kCUs);
+    const bool can = cfg->tuning.launch != POP_LAUNCH_PER_PART && (d.rows_t == 32 || tc_blocks <= kCUs);
     ctx->fuse = can && (pays || cfg->tuning.launch == POP_LAUNCH_TARGET_CRITIC) ? 1 : 0;
   }
   if (cfg->algo == POP_ALGO_TD3_SHARED && ctx->fuse > 1) ctx->fuse = 1;
@@ -496,12 +497,13 @@ int pop_create(pop_ctx** out, const pop_config* cfg, const pop_hparams* hp, uint
   // workgroups per agent, up to 5 agents), then the actor's forward pass (16 more, up to 4).  tuning.actor_ahead = 1 keeps that in the actor launch.
   // us/step, without / with (delay 2): 17 / 6 55.5 / 47.4 with 1 agent, 59.6 / 51.6 with 4, 60.7 / 55.9 with 5.  Wide inputs or actions, launches of
   // their own / fused and spread: 111 / 8 91.5 / 62.3 with 1 agent, 424 / 24 143.3 / 96.5 with 4, 447 / 1 143.1 / 105.0 with 5; fused alone: 111 / 8 109.0 /
-  // 96.5 with 8, 30 / 20 (delays 1 .. 3) 117.0 / 105.7 with 7.
+  // 96.5 with 8, 30 / 20 (delays 1 .. 3) 117.0 / 105.7 with 7.  SAC (the target critics alone): 17 / 6 fused 89.0 / 82.2 with 1 agent, 97.5 / 90.9 with 5, 111 / 8 136 / 113 with 1, 147 / 121 with 5,
+  // 157 / 145 with 8 (fused alone).
   d.spread = 0;
-  if (ctx->fuse == 1 && cfg->algo != POP_ALGO_SAC && d.rows_t == 16 && d.rows_c == 32 && d.rows_c1 == 32 && d.rows_a == 16 && !d.actor_ahead) {
+  if (ctx->fuse == 1 && d.rows_t == 16 && d.rows_c == 32 && d.rows_c1 == 32 && d.rows_a == 16 && !d.actor_ahead) {
     const int64_t b16 = (int64_t)cfg->P * (cfg->batch / 16);
     if (tc_blocks + b16 <= kCUs) d.spread |= kSpreadTargets;
-    if (tc_blocks + 2 * b16 <= kCUs && cfg->tuning.actor_ahead != 1) d.spread |= kSpreadActor;
+    if (cfg->algo != POP_ALGO_SAC && tc_blocks + 2 * b16 <= kCUs && cfg->tuning.actor_ahead != 1) d.spread |= kSpreadActor;
   }
   if (ctx->fuse >= 2 && d.rows_t == 16 && d.rows_c != 64) {   // the single launch exists for the (16, 64, 16) small class only
     delete ctx;

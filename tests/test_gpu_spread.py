@@ -1,4 +1,4 @@
-"""The target / critic launch of a few TD3 agents (target critics in workgroups of their own up to 5 agents, the actor's forward
+"""The target / critic launch of a few agents (target critics in workgroups of their own up to 5 agents, the actor's forward
 pass beside them up to 4) and of wide inputs or actions -- all bit for bit what one launch per part computes."""
 import numpy as np
 import pytest
@@ -23,7 +23,9 @@ def _states(algo, P, O, A, **kw):
     pop.insert(-1, obs=rnd(P, 300, O), act=rnd(P, 300, A).clamp(-1, 1), rew=rnd(P, 300), done=(rnd(P, 300) > 2).float(), next_obs=rnd(P, 300, O))
     pop.update(2)
     ms, cnt = pop.update_timed(5)
-    out = {(i, w): pop.get_params(i, w) for i in range(P) for w in STATE12}
+    sac = algo == pp.POP_ALGO_SAC
+    codes = [w for w in STATE12 if not (sac and w == "t_actor")] + (["log_alpha"] if sac else [])
+    out = {(i, w): pop.get_params(i, w) for i in range(P) for w in codes}
     out.update({w: pop.debug(w) for w in ("target_y", "target_action", "losses")})
     pop.sync()
     pop.close()
@@ -32,12 +34,14 @@ def _states(algo, P, O, A, **kw):
 
 @pytest.mark.parametrize("algo, P, O, A", [
     ("td3", 17, 376, 17), ("td3", 20, 111, 8), ("td3", 33, 30, 20), ("td3_shared", 18, 336, 1), ("td3", 24, 424, 24),  # 32-row chains
+    ("sac", 1, 17, 6), ("sac", 5, 40, 24), ("sac", 6, 9, 9), ("sac", 3, 424, 24), ("sac", 5, 64, 1), ("sac", 8, 447, 1),
+    ("sac", 17, 376, 17), ("sac", 33, 65, 8),
     ("td3", 1, 17, 6), ("td3", 4, 60, 4), ("td3", 5, 1, 1), ("td3_shared", 3, 17, 6),          # narrow: both, both, targets only
     ("td3", 1, 64, 1), ("td3", 4, 424, 24), ("td3", 5, 40, 9), ("td3_shared", 2, 9, 24),       # wide inputs, wide actions, both
     ("td3", 6, 447, 1), ("td3", 8, 65, 8), ("td3", 8, 30, 20), ("td3_shared", 8, 111, 8)])     # fused only
 def test_against_one_launch_per_part(algo, P, O, A):
     ensure_built()
-    code = {"td3": pp.POP_ALGO_TD3, "td3_shared": pp.POP_ALGO_TD3_SHARED}[algo]
+    code = {"td3": pp.POP_ALGO_TD3, "td3_shared": pp.POP_ALGO_TD3_SHARED, "sac": pp.POP_ALGO_SAC}[algo]
     want, apart = _states(code, P, O, A, launch=pp.POP_LAUNCH_PER_PART)
     assert apart["target"] == apart["critic"] == 5 and apart["target_critic"] == 0
     for ahead in (0, 1):
@@ -48,6 +52,9 @@ def test_against_one_launch_per_part(algo, P, O, A):
 
 def test_the_first_population_whose_wide_chains_have_launches_of_their_own():
     fused, apart = pp.POP_LAUNCH_TARGET_CRITIC, pp.POP_LAUNCH_PER_PART
+    sac = pp.Population(pp.make_config(20, 111, 8, (256, 256), 256, 64, algo=pp.POP_ALGO_SAC), workloads.hparams(5, 20))
+    assert sac.tuning()["launch"] == fused
+    sac.close()
     for P, O, launch in ((8, 111, fused), (9, 111, apart), (16, 376, apart), (20, 111, fused), (21, 111, apart), (32, 111, apart), (33, 111, fused),
                          (52, 111, fused), (53, 111, apart), (80, 111, fused), (81, 111, apart), (32, 328, apart), (32, 329, fused), (17, 376, fused)):
         pop = pp.Population(pp.make_config(P, O, 8, (256, 256), 256, 64), workloads.hparams(2, P))

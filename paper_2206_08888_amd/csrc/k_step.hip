@@ -28,8 +28,8 @@ struct StepGrid {
   int roles_c, roles_a;            // weight-gradient roles per critic / actor network
 };
 
-// GT, GC, GA: tile geometries of the target, critic and actor chains.
-template <class GT, class GC, class GA>
+// GT, GC, GA: tile geometries of the target, critic and actor chains.  STREAM: wgrad_roles'.
+template <class GT, class GC, class GA, bool STREAM = false>
 __global__ __launch_bounds__(kThreads, GC::R == 64 ? 1 : 2) void k_step(PopDev d, uint32_t t, StepGrid g) {
   extern __shared__ __attribute__((aligned(16))) float lds[];
   int b = blockIdx.x;
@@ -65,14 +65,14 @@ __global__ __launch_bounds__(kThreads, GC::R == 64 ? 1 : 2) void k_step(PopDev d
     // workgroup per CU the actor chains of the first agents then start while later agents' tiles still run.
     const int tiles = 2 * g.roles_c, chunks = g.a / d.P;
     if (decode_block<true>(b, d.P, tiles + chunks, unit, sub)) {    // an agent's actor chains wait for its own tiles
-      if (sub < tiles) wgrad_roles<true>(d, t, 0, 2 * unit + sub / g.roles_c, sub % g.roles_c, lds, sh_adam, g.c != 0);
+      if (sub < tiles) wgrad_roles<true, false, false, false, STREAM>(d, t, 0, 2 * unit + sub / g.roles_c, sub % g.roles_c, lds, sh_adam, g.c != 0);
       else actor_chain<GA, true>(d, t, unit, sub - tiles, lds, g.roles_c);
     }
     POP_BLOCK_TIME(kTraceStep, 1);
     return;
   }
   if (b < g.wc) {
-    if (decode_block(b, 2 * d.P, g.roles_c, unit, sub)) wgrad_roles<true>(d, t, 0, unit, sub, lds, sh_adam, g.c != 0);
+    if (decode_block(b, 2 * d.P, g.roles_c, unit, sub)) wgrad_roles<true, false, false, false, STREAM>(d, t, 0, unit, sub, lds, sh_adam, g.c != 0);
     POP_BLOCK_TIME(kTraceStep, 1);
     return;
   }
@@ -84,7 +84,7 @@ __global__ __launch_bounds__(kThreads, GC::R == 64 ? 1 : 2) void k_step(PopDev d
   }
   b -= g.a;
   if (b < g.wa) {
-    if (decode_block(b, d.P, g.roles_a, unit, sub)) wgrad_roles<true>(d, t, 1, unit, sub, lds, sh_adam);
+    if (decode_block(b, d.P, g.roles_a, unit, sub)) wgrad_roles<true, false, false, false, STREAM>(d, t, 1, unit, sub, lds, sh_adam);
     POP_BLOCK_TIME(kTraceStep, 1);
     return;
   }
@@ -97,12 +97,14 @@ __global__ __launch_bounds__(kThreads, GC::R == 64 ? 1 : 2) void k_step(PopDev d
 
 #define POP_STEP_SMALL k_step<Rows16, Rows32<2>, Rows16>
 #define POP_STEP_MID k_step<Rows32<1>, Rows32<1>, Rows32<1>>
+#define POP_STEP_MID_STREAM k_step<Rows32<1>, Rows32<1>, Rows32<1>, true>
 #define POP_STEP_LARGE k_step<Rows32<2>, Rows32<2>, Rows32<2>>
 
 hipError_t setup_step_kernel() {
   hipError_t e;
   if ((e = hipFuncSetAttribute((const void*)POP_STEP_SMALL, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)) != hipSuccess) return e;
   if ((e = hipFuncSetAttribute((const void*)POP_STEP_MID, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)) != hipSuccess) return e;
+  if ((e = hipFuncSetAttribute((const void*)POP_STEP_MID_STREAM, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)) != hipSuccess) return e;
   return hipFuncSetAttribute((const void*)POP_STEP_LARGE, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
 }
 
@@ -140,7 +142,8 @@ hipError_t launch_step(const PopDev& dev, uint32_t t, uint32_t launch_seq, int w
     POP_STEP_SMALL<<<grid, block, bytes, s>>>(d, t, g);
   } else if (d.rows_a == 32) {
     need(chain_bytes<Rows32<1>>(d.D, vec));
-    POP_STEP_MID<<<grid, block, bytes, s>>>(d, t, g);
+    if (d.stream) POP_STEP_MID_STREAM<<<grid, block, bytes, s>>>(d, t, g);
+    else POP_STEP_MID<<<grid, block, bytes, s>>>(d, t, g);
   } else {
     need(chain_bytes<Rows32<2>>(d.D, vec));
     POP_STEP_LARGE<<<grid, block, bytes, s>>>(d, t, g);

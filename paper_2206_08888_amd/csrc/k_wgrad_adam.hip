@@ -7,8 +7,8 @@
 
 namespace pop {
 
-// HALF: tiles of half the width, for populations whose full tiles would leave CUs with one or two of them.  PLAIN: wgrad_roles'.
-template <bool HALF, bool PLAIN>
+// HALF: tiles of half the width, for populations whose full tiles would leave CUs with one or two of them.  PLAIN, STREAM: wgrad_roles'.
+template <bool HALF, bool PLAIN, bool STREAM = false>
 __global__ __launch_bounds__(kThreads, 3) void k_wgrad_adam(PopDev d, uint32_t t, int actor_phase, int main_blocks,
                                                           int roles, int prefetch) {
   warm_args<sizeof(PopDev) + 16>();
@@ -26,7 +26,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_wgrad_adam(PopDev d, uint32_t t
   }
   int unit, role;
   if (decode_block(blockIdx.x, actor_phase ? d.P : 2 * d.P, roles, unit, role))
-    wgrad_roles<false, true, HALF, PLAIN>(d, t, actor_phase, unit, role, xt_lds, &sh_adam);
+    wgrad_roles<false, true, HALF, PLAIN, STREAM>(d, t, actor_phase, unit, role, xt_lds, &sh_adam);
   POP_BLOCK_TIME(actor_phase ? kTraceWgradActor : kTraceWgradCritic, 1);
 }
 
@@ -47,7 +47,8 @@ hipError_t launch_wgrad_adam(const PopDev& d, uint32_t t, int actor_phase, int p
   const int extra = prefetch_next ? d.P * gather_blocks_per_agent(d) : 0;
   const dim3 grid(main_blocks + extra), block(kThreads);
   auto* kernel = d.w2_plain ? (d.half_tiles ? k_wgrad_adam<true, true> : k_wgrad_adam<false, true>)
-                            : (d.half_tiles ? k_wgrad_adam<true, false> : k_wgrad_adam<false, false>);
+                : d.half_tiles ? k_wgrad_adam<true, false>
+                : d.stream     ? k_wgrad_adam<false, false, true> : k_wgrad_adam<false, false>;
   kernel<<<grid, block, 0, s>>>(d, t, actor_phase, main_blocks, roles, prefetch_next);
   return hipGetLastError();
 }

@@ -275,6 +275,11 @@ void fill_dims(const pop_config& c, PopDev& d) {
   d.actor = make_layout(d.O, c.algo == POP_ALGO_SAC ? 2 * d.A : d.A);   // SAC: mean and log-std per action
   d.critic = make_layout(d.D, 1);
   d.agent_sz = d.actor.padded + 2 * d.critic.padded;
+  // Parameters, targets and moments of all agents against the 256 MB of the Infinity Cache, which the activations share: from three quarters of it on the
+  // moments, read and written once a step, only push out what the next launches read.  us/step, through the caches / past them: TD3 17 / 6 172.6 / 175.3
+  // with 40 agents (138 MB), 245 / 242 with 60 (208), 286 / 281 with 70, 324 / 320 with 80, 372 / 359 with 90, 492 / 485 with 128; 376 / 17 271 / 263 with 30
+  // (240 MB), 352 / 339 with 36; 111 / 8 354 / 343 with 64; SAC 378 / 375 with 64 (222 MB), 651 / 630 with 100; shared critics 893 / 886 with 256.
+  d.stream = 16 * ((int64_t)c.P * (shared ? d.actor.padded : d.agent_sz) + (shared ? 2 * d.critic.padded : 0)) > 192ll << 20;
   d.capacity = (uint64_t)c.capacity;
   d.actor_ahead = 0;                                   // pop_create decides, once the launch structure is known
   d.share = 1;

@@ -139,6 +139,7 @@ struct PopDev {
                                // constant-rate clock (default 50 ms; a healthy wait is a fraction of a millisecond)
   // (At the end: the fields before keep their places.  Four bytes on, the layouts' fields come to the kernels in smaller loads, 0.5 us a launch.)
   int spread;                  // kSpread* below
+  int stream;                  // the Adam moments are read and written past the caches: a population whose state the Infinity Cache does not hold
   int w2_plain;                // hidden matrices lie row-major (w2_index<true>): critic 1 inside the target workgroups and 16-row actor chains
 };
 

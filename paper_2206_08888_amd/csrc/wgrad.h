@@ -71,9 +71,19 @@ __device__ inline void adam_store(const Adam& a, const AdamRegs& r, float g, uin
 }
 
 // Four neighbouring parameters at once (16-byte operands; the updated parameters, when another workgroup of the
-// launch reads them, as two 8-byte write-through stores).
+// launch reads them, as two 8-byte write-through stores).  STREAM: the moments go past the caches (PopDev::stream; the rule and its figures are in fill_dims).
 struct AdamRegs4 { f32x4 th, m, v, tg; };
-template <bool THROUGH = false>
+template <bool STREAM>
+__device__ inline f32x4 load_moment(const float* p) {
+  if (STREAM) return __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
+  return *reinterpret_cast<const f32x4*>(p);
+}
+template <bool STREAM>
+__device__ inline void store_moment(float* p, const f32x4& x) {
+  if (STREAM) __builtin_nontemporal_store(x, reinterpret_cast<f32x4*>(p));
+  else *reinterpret_cast<f32x4*>(p) = x;
+}
+template <bool THROUGH, bool STREAM>
 __device__ inline void adam_store4(const Adam& a, const AdamRegs4& r, const f32x4& g, uint32_t i, float* __restrict__ th,
                                    float* __restrict__ m, float* __restrict__ v, float* __restrict__ tg,
                                    float* __restrict__ gr) {
@@ -86,8 +96,8 @@ __device__ inline void adam_store4(const Adam& a, const AdamRegs4& r, const f32x
     tn[e] = r.th[e] - a.lr * (mm[e] * a.inv_c1) * __builtin_amdgcn_rcpf(denom);
     tt[e] = (1.0f - a.tau) * r.tg[e] + a.tau * tn[e];
   }
-  *reinterpret_cast<f32x4*>(m + i) = mm;
-  *reinterpret_cast<f32x4*>(v + i) = vv;
+  store_moment<STREAM>(m + i, mm);
+  store_moment<STREAM>(v + i, vv);
   if (THROUGH && a.through) {
     put2<true>(th + i, tn[0], tn[1]);
     put2<true>(th + i + 2, tn[2], tn[3]);
@@ -146,7 +156,7 @@ struct XSlice {
 // `sh` (thread 0 only; a few hundred cycles of double arithmetic): it runs once the loads are
 // on their way, and `sh` is read after the barrier that follows.
 // DZ2: z is a critic's dZ2, given by its factors (Dz2Factors): zmask [8][256] words, zdq [256], zw3 [256].
-template <bool WAIT, bool SLIM, bool HALF, bool DZ2, class Setup>
+template <bool WAIT, bool SLIM, bool HALF, bool STREAM, bool DZ2, class Setup>
 __device__ __forceinline__ void weight_tile(const PopDev& d, const uint32_t* wait_on, uint32_t want, const Adam* sh,
                                             Setup setup, bool polyak, const float* __restrict__ x, int ldx, int M, int m0,
                                    int n0, const float* __restrict__ z, const uint32_t* __restrict__ zmask, const float* __restrict__ zdq,
@@ -174,8 +184,8 @@ __device__ __forceinline__ void weight_tile(const PopDev& d, const uint32_t* wai
       const bool ok = (m0 + arow + QR * q) < M;
       const uint32_t i = ok ? elem0 + (uint32_t)(QR * q * kH) : elem0 - (uint32_t)(arow * kH);   // else: row m0, always valid
       regs[q].th = *reinterpret_cast<const f32x4*>(th + i);
-      regs[q].m = *reinterpret_cast<const f32x4*>(mo + i);
-      regs[q].v = *reinterpret_cast<const f32x4*>(ve + i);
+      regs[q].m = load_moment<STREAM>(mo + i);
+      regs[q].v = load_moment<STREAM>(ve + i);
       regs[q].tg = polyak ? *reinterpret_cast<const f32x4*>(tg + i) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     }
   };
@@ -231,7 +241,7 @@ __device__ __forceinline__ void weight_tile(const PopDev& d, const uint32_t* wai
     if ((m0 + arow + QR * q) < M) {
       f32x4 g = *reinterpret_cast<const f32x4*>(&Xl[(arow + QR * q) * kLda + acol]);
       if (HALF) g += *reinterpret_cast<const f32x4*>(&Xl[(arow + QR * q) * kLda + 64 + acol]);
-      adam_store4<WAIT>(adam, regs[q], g, elem0 + (uint32_t)(QR * q * kH), th, mo, ve, tg, gr);
+      adam_store4<WAIT, STREAM>(adam, regs[q], g, elem0 + (uint32_t)(QR * q * kH), th, mo, ve, tg, gr);
     }
   }
   POP_MARK(54);
@@ -245,8 +255,8 @@ constexpr int kSmallHeadBlock = 8;   // head columns of an actor that one small-
 // chain of this network) run in the same launch -- hold before the first read of chain
 // output, count in at the end.
 // SLIM: the register budget of three workgroups per CU (four dZ buffers, head columns eight at a time).
-// PLAIN: hidden matrices lie row-major.
-template <bool WAIT, bool SLIM = false, bool HALF = false, bool PLAIN = false>
+// PLAIN: hidden matrices lie row-major.  STREAM: adam_store4's.
+template <bool WAIT, bool SLIM = false, bool HALF = false, bool PLAIN = false, bool STREAM = false>
 __device__ __forceinline__ void wgrad_roles(const PopDev& d, uint32_t t, int actor_phase, int unit, int role,
                                             float* xt_lds, Adam* sh_adam, bool producer_in_launch = true) {
   const int tid = threadIdx.x;
@@ -303,11 +313,11 @@ __device__ __forceinline__ void wgrad_roles(const PopDev& d, uint32_t t, int act
     const bool polyak = delayed_step && !(actor_phase && d.algo == 1);
     const int m0 = 32 * ((w2 ? role : role - 16) >> 1);
     if (w2 && !actor_phase)
-      weight_tile<WAIT, SLIM, HALF, true>(d, wait_on, (uint32_t)chunks, sh_adam, setup, polyak, x, kH, kH, m0, n0, nullptr,
+      weight_tile<WAIT, SLIM, HALF, STREAM, true>(d, wait_on, (uint32_t)chunks, sh_adam, setup, polyak, x, kH, kH, m0, n0, nullptr,
                                           d.cmask + (size_t)unit * (d.B / 32) * kH, d.cdq + (size_t)unit * d.B, d.cw3 + (size_t)unit * kH,
                                           (uint32_t)L.w2, !PLAIN, xt_lds, th, mo, ve, tg, gr, tid);
     else
-      weight_tile<WAIT, SLIM, HALF, false>(d, wait_on, (uint32_t)chunks, sh_adam, setup, polyak, x, w2 ? kH : d.row, w2 ? kH : L.in, m0, n0, z,
+      weight_tile<WAIT, SLIM, HALF, STREAM, false>(d, wait_on, (uint32_t)chunks, sh_adam, setup, polyak, x, w2 ? kH : d.row, w2 ? kH : L.in, m0, n0, z,
                                            nullptr, nullptr, nullptr, (uint32_t)(w2 ? L.w2 : L.w1), w2 && !PLAIN, xt_lds, th, mo, ve, tg, gr, tid);
   } else {
     // Small tensors from per-chunk partial sums; thread c owns hidden unit c.  Role `small` = 0: the hidden biases,

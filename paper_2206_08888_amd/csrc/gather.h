@@ -52,7 +52,7 @@ __device__ __forceinline__ void gather_run(const PopDev& d, uint32_t t, int agen
 #pragma unroll
   for (int k = 0; k < E; ++k) {
     const int e = base + k * 256 + tid, ec = e <= last ? e : last, b = row_of(ec);
-    v[k] = src[(size_t)drawn[b - b0] * row + (ec - b * row)];
+    v[k] = __builtin_nontemporal_load(src + (size_t)drawn[b - b0] * row + (ec - b * row));
   }
 #pragma unroll
   for (int k = 0; k < E; ++k) {

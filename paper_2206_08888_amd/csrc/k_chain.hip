@@ -105,11 +105,11 @@ __global__ __launch_bounds__(G::kThr, PER_CU) void k_actor(PopDev d, uint32_t t)
 // inputs 159 -> 137; the head on all four wavefronts is part of it).
 // Noise scale sigma[agent] > 0: Gaussian exploration noise, a = clip(pi + sigma[agent] eps, -1, 1) with eps =
 // unit normal number (row_base + r) A + j of the agent's exploration stream at counter `step`
-// (row_base: index of row 0 of this call within the caller's whole request).
+// (row_base: index of row 0 of this call within the caller's whole request).  Grid: act_grid.
 template <bool PLAIN>
 __global__ __launch_bounds__(kThreads) void k_act(PopDev d, const float* __restrict__ obs, int n,
                                                   float* __restrict__ act, const float* __restrict__ sigma, SigmaArgs sigma_args,
-                                                  uint32_t step, uint32_t row_base) {
+                                                  uint32_t step, uint32_t row_base, int chunks) {
   warm_args<sizeof(PopDev) + 32>();
   constexpr int R = 32;
   extern __shared__ float lds[];
@@ -122,7 +122,9 @@ __global__ __launch_bounds__(kThreads) void k_act(PopDev d, const float* __restr
   float* stage = Xs;                                 // the input tile is done with when the hidden layer starts
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   int agent, chunk;
-  if (!decode_block(blockIdx.x, d.P, (n + R - 1) / R, agent, chunk)) return;   // an agent's chunks share an XCD's L2 for its weights
+  if (!decode_block(blockIdx.x, d.P, chunks, agent, chunk)) return;   // an agent's chunks share an XCD's L2 for its weights
+  chunk += blockIdx.y * chunks;
+  if (chunk > (n - 1) / R) return;                   // past the end of the last piece
   const int r0 = chunk * R;
   const int valid = n - r0 < R ? n - r0 : R;
   const float* an = net_ptr(d, d.theta, agent, 0);
@@ -345,7 +347,8 @@ hipError_t launch_actor(const PopDev& d, uint32_t t, hipStream_t s) {
 hipError_t launch_act_rows(const PopDev& d, const float* obs, int n, float* act, const float* sigma, const SigmaArgs& args, uint32_t step,
                            uint32_t row_base, hipStream_t s) {
   auto* kernel = d.w2_plain ? k_act<true> : k_act<false>;
-  kernel<<<dim3(xcd_grid(d.P, (n + 31) / 32)), dim3(kThreads), act_lds_bytes(d), s>>>(d, obs, n, act, sigma, args, step, row_base);
+  const ActGrid g = act_grid(d.P, n);
+  kernel<<<dim3(xcd_grid(d.P, g.chunks), g.pieces), dim3(kThreads), act_lds_bytes(d), s>>>(d, obs, n, act, sigma, args, step, row_base, g.chunks);
   return hipGetLastError();
 }
 

@@ -56,6 +56,14 @@ constexpr int kStaticMaxP = 256;
 struct SigmaArgs { float s[kStaticMaxP]; };
 hipError_t launch_act(const PopDev& d, const float* obs, int n, float* act, const float* sigma, const SigmaArgs& args, uint32_t step,
                       uint32_t row_base, int whole, hipStream_t s);
+// Grid of k_act: x = `chunks` blocks of 32 rows per agent, y = pieces of that many.  A dimension of a grid holds fewer than 2^32 threads and what
+// is beyond is cut off without an error, so a request of more than 2^24 - 1 workgroups of 256 (537 million rows of all agents) takes several pieces.
+struct ActGrid { int chunks, pieces; };
+inline ActGrid act_grid(int P, int n) {
+  const int64_t all = ((int64_t)n + 31) / 32, most = ((1 << 24) - 1) / P;
+  const int64_t chunks = all < most ? all : most;
+  return {(int)chunks, (int)((all + chunks - 1) / chunks)};
+}
 hipError_t launch_act_rows(const PopDev& d, const float* obs, int n, float* act, const float* sigma, const SigmaArgs& args, uint32_t step,
                            uint32_t row_base, hipStream_t s);
 hipError_t setup_act_kernels();

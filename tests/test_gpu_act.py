@@ -68,3 +68,24 @@ def test_a_few_rows_per_agent(algo, P, O, A):
         noisy = pop.act(torch.from_numpy(obs).cuda(), sigma, step=9).cpu().numpy()
         assert np.array_equal(noisy[0], got[0]) and (P == 1 or not np.array_equal(noisy[-1], got[-1]))
     pop.close()
+
+
+def test_more_rows_than_one_grid_dimension_holds():
+    """537 million rows of two agents: their row blocks, 256 threads each, are more than the 2^32 - 1 threads of a grid dimension, past which a launch
+    loses workgroups without an error.  Rows at the ends and on both sides of the line between the pieces as in calls of their own."""
+    n, few = (1 << 28) + 33, 70_000
+    pop = pp.Population(pp.make_config(2, 1, 1, (H, H), 256, 64), workloads.hparams(0, 2))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1)
+    obs = torch.randn((2, n, 1), generator=gen, device="cuda")
+    sigma = np.array([0.0, 0.1], np.float32)
+    got = pop.act(obs, sigma, step=4)
+    line = 32 * (((1 << 24) - 1) // 2)                    # rows per agent in the first piece
+    for at in (0, line - few // 2, n - few):
+        want = pop.act(obs[:, at:at + few].contiguous(), sigma, step=4)
+        assert torch.equal(got[0, at:at + few], want[0]), at
+        assert (at == 0) == torch.equal(got[1, at:at + few], want[1]), at       # noise is numbered by the row of the call
+    still = pop.act(obs[:, line - few // 2:line + few // 2].contiguous())[1]
+    noise = got[1, line - few // 2:line + few // 2] - still
+    assert 0.05 < float(noise.std()) < 0.15
+    pop.close()

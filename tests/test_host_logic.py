@@ -30,6 +30,16 @@ def test_workgroups_per_cu(tmp_path):
     assert out.returncode == 0 and "bad 0" in out.stdout, out.stdout[-2000:]
 
 
+def test_grid_of_an_acting_launch(tmp_path):
+    exe = tmp_path / "act_grid_check"
+    hipcc = "/opt/rocm/bin/hipcc" if os.path.exists("/opt/rocm/bin/hipcc") else "hipcc"
+    subprocess.run([hipcc, "-O1", "-std=c++17", "--offload-arch=gfx950", "--cuda-host-only", "-Wno-unused-command-line-argument",
+                    "-I", os.path.join(ROOT, "paper_2206_08888_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "host", "act_grid_check.cpp"), "-o", str(exe)], check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert out.returncode == 0 and "bad 0" in out.stdout, out.stdout[-2000:]
+
+
 @pytest.fixture(scope="module")
 def k_chain_asm(tmp_path_factory):
     from paper_2206_08888_amd import build

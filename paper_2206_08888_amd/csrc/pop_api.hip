@@ -478,6 +478,9 @@ int pop_create(pop_ctx** out, const pop_config* cfg, const pop_hparams* hp, uint
     const bool can = cfg->tuning.launch != POP_LAUNCH_PER_PART && (d.rows_t == 32 || tc_blocks <= kCUs);
     ctx->fuse = can && (pays || cfg->tuning.launch == POP_LAUNCH_TARGET_CRITIC) ? 1 : 0;
   }
+  // SAC of more than kMaxAct actions and narrow inputs takes what a caller names as far as there is a fused kernel for it, else one launch per part.
+  if (cfg->algo == POP_ALGO_SAC && !wide && d.A > kMaxAct && ctx->fuse != 0)
+    ctx->fuse = cfg->tuning.launch <= POP_LAUNCH_TARGET_CRITIC && (d.rows_t == 16 || (d.rows_t == 32 && d.rows_c == 32)) ? 1 : 0;
   if (cfg->algo == POP_ALGO_TD3_SHARED && ctx->fuse > 1) ctx->fuse = 1;
   if (d.rows_c1 != d.rows_c && (ctx->fuse != 1 || cfg->algo != POP_ALGO_TD3 || d.rows_t != 16 || d.rows_c1 != 16)) {
     delete ctx;

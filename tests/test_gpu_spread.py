@@ -60,3 +60,26 @@ def test_the_first_population_whose_wide_chains_have_launches_of_their_own():
         pop = pp.Population(pp.make_config(P, O, 8, (256, 256), 256, 64), workloads.hparams(2, P))
         assert pop.tuning()["launch"] == launch, (P, O)
         pop.close()
+
+
+@pytest.mark.parametrize("P, launch, rows", [
+    (3, "POP_LAUNCH_SINGLE", None), (3, "POP_LAUNCH_TAIL", None), (20, "POP_LAUNCH_SINGLE", None), (3, "POP_LAUNCH_TARGET_CRITIC", (64, 64, 64)),
+    (3, "POP_LAUNCH_TARGET_CRITIC", (32, 64, 32)), (3, "POP_LAUNCH_TARGET_CRITIC", (64, 32, 16)), (20, "POP_LAUNCH_TARGET_CRITIC", None),
+    (3, "POP_LAUNCH_TARGET_CRITIC", (16, 64, 16)), (34, "POP_LAUNCH_TARGET_CRITIC", None)])
+def test_sac_with_more_than_eight_actions_takes_every_launch_and_rows(P, launch, rows):
+    """Structures or rows without a fused kernel run one launch per part."""
+    ensure_built()
+    states = []
+    for tuning in (dict(launch=pp.POP_LAUNCH_PER_PART), dict(launch=getattr(pp, launch))):
+        pop = pp.Population(pp.make_config(P, 30, 12, (256, 256), 256, 300, algo=pp.POP_ALGO_SAC, rows=rows, half_tiles=1, **tuning), workloads.hparams(5, P))
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(3)
+        rnd = lambda *s: torch.randn(s, generator=gen, device="cuda")
+        pop.insert(-1, obs=rnd(P, 300, 30), act=rnd(P, 300, 12).clamp(-1, 1), rew=rnd(P, 300), done=(rnd(P, 300) > 2).float(), next_obs=rnd(P, 300, 30))
+        if tuning["launch"] != pp.POP_LAUNCH_PER_PART:
+            assert pop.tuning()["launch"] in (pp.POP_LAUNCH_PER_PART, pp.POP_LAUNCH_TARGET_CRITIC)
+        pop.update(3)
+        states.append([pop.get_params(i, w) for i in range(P) for w in ("actor", "critic1", "critic2", "t_critic1", "log_alpha")])
+        pop.close()
+    if rows is not None or P != 20:                       # (20 agents: one launch per part has 32-row target chains, a fused launch 16)
+        assert all(np.array_equal(a, b) for a, b in zip(*states))

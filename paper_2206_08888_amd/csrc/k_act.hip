@@ -197,12 +197,13 @@ hipError_t setup_few() {
   return e;
 }
 template <int RR>
-hipError_t launch_few(const PopDev& d, const float* obs, int n, float* act, const float* sigma, const SigmaArgs& args, uint32_t step,
+hipError_t launch_few(const PopDev& d, const float* obs, int n, float* act, const float* sigma, const SigmaArgs* args, uint32_t step,
                       uint32_t row_base, hipStream_t s) {
   const bool wide = d.O > 64;
   auto* kernel = d.w2_plain ? (wide ? k_act_few<RR, true, true> : k_act_few<RR, true, false>)
                             : (wide ? k_act_few<RR, false, true> : k_act_few<RR, false, false>);
-  kernel<<<dim3(xcd_grid(d.P, (n + RR - 1) / RR)), dim3(kFewThr), FewMap<RR>::floats * sizeof(float), s>>>(d, obs, n, act, sigma, args, step, row_base);
+  kernel<<<dim3(xcd_grid(d.P, (n + RR - 1) / RR)), dim3(kFewThr), FewMap<RR>::floats * sizeof(float), s>>>(d, obs, n, act, sigma, args ? *args : kNoNoise, step,
+                                                                                                                        row_base);
   return hipGetLastError();
 }
 }  // namespace
@@ -218,7 +219,7 @@ hipError_t setup_act_kernels() {
 // us per call with exploration noise, k_act behind a launch for the noise scales / here: 10 agents 1 row 14.6 / 8.0 (the host's share: 8), 50 rows 14.7 / 8.1,
 // 256 agents 1 row 18.5 / 13.5, 4 rows 18.6 / 15.5, 80 agents 8 rows 15.2 / 10.6; 376 inputs: 10 agents 1 row 33.2 / 10.9, 40 rows 37.3 / 12.4, 80
 // agents 1 row 42.0 / 15.1.
-hipError_t launch_act(const PopDev& d, const float* obs, int n, float* act, const float* sigma, const SigmaArgs& args, uint32_t step,
+hipError_t launch_act(const PopDev& d, const float* obs, int n, float* act, const float* sigma, const SigmaArgs* args, uint32_t step,
                       uint32_t row_base, int whole, hipStream_t s) {
   const int64_t P = d.P, N = whole;
   if (N == 1 || P * N <= kCUs) return launch_few<1>(d, obs, n, act, sigma, args, step, row_base, s);

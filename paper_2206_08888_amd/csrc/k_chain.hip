@@ -108,9 +108,9 @@ __global__ __launch_bounds__(G::kThr, PER_CU) void k_actor(PopDev d, uint32_t t)
 // (row_base: index of row 0 of this call within the caller's whole request).  Grid: act_grid.
 template <bool PLAIN>
 __global__ __launch_bounds__(kThreads) void k_act(PopDev d, const float* __restrict__ obs, int n,
-                                                  float* __restrict__ act, const float* __restrict__ sigma, SigmaArgs sigma_args,
-                                                  uint32_t step, uint32_t row_base, int chunks) {
-  warm_args<sizeof(PopDev) + 32>();
+                                                  float* __restrict__ act, const float* __restrict__ sigma, uint32_t step,
+                                                  uint32_t row_base, int chunks, int noise, SigmaArgs sigma_args) {
+  warm_args<sizeof(PopDev) + 48>();
   constexpr int R = 32;
   extern __shared__ float lds[];
   constexpr int kHs = kMaxHead;                      // row stride of the head block
@@ -122,7 +122,8 @@ __global__ __launch_bounds__(kThreads) void k_act(PopDev d, const float* __restr
   float* stage = Xs;                                 // the input tile is done with when the hidden layer starts
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   int agent, chunk;
-  if (!decode_block(blockIdx.x, d.P, chunks, agent, chunk)) return;   // an agent's chunks share an XCD's L2 for its weights
+  if (chunks == 1) { agent = blockIdx.x; chunk = 0; }                      // what decode_block makes of it, without its divisions
+  else if (!decode_block(blockIdx.x, d.P, chunks, agent, chunk)) return;   // an agent's chunks share an XCD's L2 for its weights
   chunk += blockIdx.y * chunks;
   if (chunk > (n - 1) / R) return;                   // past the end of the last piece
   const int r0 = chunk * R;
@@ -131,6 +132,8 @@ __global__ __launch_bounds__(kThreads) void k_act(PopDev d, const float* __restr
   LayerPre<1, 2, PLAIN> pre;
   pre.load(an, d.actor, wave, lane);
   const float* rows = obs + ((size_t)agent * n + r0) * d.O;
+  float sg = 0.0f;
+  if (noise) sg = sigma ? sigma[agent] : sigma_args.s[agent < kStaticMaxP ? agent : 0];
   if (d.O <= kMaxIn) {                               // one trip to memory for all of the prologue
     SmallVec ab3;
     InputTile<R> xin;
@@ -142,6 +145,7 @@ __global__ __launch_bounds__(kThreads) void k_act(PopDev d, const float* __restr
     stage_vector(v_ab3, an + d.actor.b3, d.actor.out, tid);
     load_input_wide<R>(Xs, L.xld, rows, d.O, 0, d.O, valid, tid);
   }
+  asm volatile("" ::"v"(sg));                         // in the trip of the weights, not in one of its own behind the head
   __syncthreads();
   first_layer<1, false>(Xs, L.xld, an, d.actor, pre, buf, nullptr, wave, lane);
   __syncthreads();
@@ -149,15 +153,14 @@ __global__ __launch_bounds__(kThreads) void k_act(PopDev d, const float* __restr
   __syncthreads();
   if (d.actor.out <= 16) head_mfma_split<R, false>(buf, an + d.actor.w3, d.actor.out, head, kHs, wave, lane, stage);   // SAC: 2A outputs, the means come first
   else head_mfma<R>(buf, an + d.actor.w3, d.actor.out, head, kHs, wave, lane);
-  const float sg = sigma ? sigma[agent] : sigma_args.s[agent < kStaticMaxP ? agent : 0];
   const bool sac = d.algo == 1;
   __syncthreads();
-  const HpDev hp = d.hp[agent];
   for (int e = tid; e < valid * d.A; e += kThreads) {
     const int r = e / d.A, j = e - r * d.A;
     const float pre_act = head[r * kHs + j] + v_ab3[j];
     float a = tanhf(pre_act);
     if (sg > 0.0f) {
+      const HpDev hp = d.hp[agent];
       const uint32_t el = (row_base + (uint32_t)(r0 + r)) * (uint32_t)d.A + (uint32_t)j;
       const U4 blk = philox4x32_10(hp.seed_lo, hp.seed_hi, el >> 2, step, kStreamExplore, 0u);
       float n4[4];
@@ -344,11 +347,12 @@ hipError_t launch_actor(const PopDev& d, uint32_t t, hipStream_t s) {
   else k_actor<Rows32<2>><<<grid, block, chain_bytes<Rows32<2>>(d.D, vec_actor(d)), s>>>(d, t);
   return hipGetLastError();
 }
-hipError_t launch_act_rows(const PopDev& d, const float* obs, int n, float* act, const float* sigma, const SigmaArgs& args, uint32_t step,
+hipError_t launch_act_rows(const PopDev& d, const float* obs, int n, float* act, const float* sigma, const SigmaArgs* args, uint32_t step,
                            uint32_t row_base, hipStream_t s) {
   auto* kernel = d.w2_plain ? k_act<true> : k_act<false>;
   const ActGrid g = act_grid(d.P, n);
-  kernel<<<dim3(xcd_grid(d.P, g.chunks), g.pieces), dim3(kThreads), act_lds_bytes(d), s>>>(d, obs, n, act, sigma, args, step, row_base, g.chunks);
+  kernel<<<dim3(xcd_grid(d.P, g.chunks), g.pieces), dim3(kThreads), act_lds_bytes(d), s>>>(d, obs, n, act, sigma, step, row_base,
+                                                                                                        g.chunks, sigma || args, args ? *args : kNoNoise);
   return hipGetLastError();
 }
 

@@ -50,11 +50,12 @@ int wgrad_role_count(const PopDev& d, int actor_phase);
 
 // acting: obs[P][n][O] -> act[P][n][A] through the online actors; a noise scale above zero adds exploration noise drawn at counter
 // `step`, rows numbered from row_base.  The scales: sigma (device, [P]), or where that is nullptr those of `args` (up to
-// kStaticMaxP agents; they travel as a kernel argument), for more agents without noise zeros.  `whole`: rows of the caller's request, of
+// kStaticMaxP agents; they travel as a kernel argument); both nullptr: no noise.  `whole`: rows of the caller's request, of
 // which this launch may be a piece: it decides which kernel runs, so that a row comes out the same in one piece and in several.
 constexpr int kStaticMaxP = 256;
 struct SigmaArgs { float s[kStaticMaxP]; };
-hipError_t launch_act(const PopDev& d, const float* obs, int n, float* act, const float* sigma, const SigmaArgs& args, uint32_t step,
+constexpr SigmaArgs kNoNoise{};
+hipError_t launch_act(const PopDev& d, const float* obs, int n, float* act, const float* sigma, const SigmaArgs* args, uint32_t step,
                       uint32_t row_base, int whole, hipStream_t s);
 // Grid of k_act: x = `chunks` blocks of 32 rows per agent, y = pieces of that many.  A dimension of a grid holds fewer than 2^32 threads and what
 // is beyond is cut off without an error, so a request of more than 2^24 - 1 workgroups of 256 (537 million rows of all agents) takes several pieces.
@@ -64,7 +65,7 @@ inline ActGrid act_grid(int P, int n) {
   const int64_t chunks = all < most ? all : most;
   return {(int)chunks, (int)((all + chunks - 1) / chunks)};
 }
-hipError_t launch_act_rows(const PopDev& d, const float* obs, int n, float* act, const float* sigma, const SigmaArgs& args, uint32_t step,
+hipError_t launch_act_rows(const PopDev& d, const float* obs, int n, float* act, const float* sigma, const SigmaArgs* args, uint32_t step,
                            uint32_t row_base, hipStream_t s);
 hipError_t setup_act_kernels();
 

@@ -826,10 +826,8 @@ int pop_update_timed(pop_ctx* ctx, int32_t n_steps, double* ms, int64_t* launche
 }
 
 namespace {
-const SigmaArgs kNoNoise{};
-
 int act_impl(pop_ctx* ctx, const float* obs, int32_t n, float* act_out, int32_t ptrs_on_device, const float* sigma_dev,
-             const SigmaArgs& args, uint32_t step) {
+             const SigmaArgs* args, uint32_t step) {
   if (n < 0) return fail(ctx, POP_EINVAL, "n is negative");
   if (n == 0) return POP_OK;
   if (!obs || !act_out) return fail(ctx, POP_EINVAL, "NULL array");
@@ -865,7 +863,7 @@ int act_impl(pop_ctx* ctx, const float* obs, int32_t n, float* act_out, int32_t 
 
 int pop_act(pop_ctx* ctx, const float* obs, int32_t n, float* act_out, int32_t ptrs_on_device) {
   if (!ctx) return POP_EINVAL;
-  return act_impl(ctx, obs, n, act_out, ptrs_on_device, nullptr, kNoNoise, 0u);
+  return act_impl(ctx, obs, n, act_out, ptrs_on_device, nullptr, nullptr, 0u);
 }
 
 int pop_act_explore(pop_ctx* ctx, const float* obs, int32_t n, float* act_out, int32_t ptrs_on_device,
@@ -880,7 +878,7 @@ int pop_act_explore(pop_ctx* ctx, const float* obs, int32_t n, float* act_out, i
   SigmaArgs args{};
   if (ctx->d.P <= kStaticMaxP) {
     std::memcpy(args.s, sigma, sizeof(float) * ctx->d.P);
-    return act_impl(ctx, obs, n, act_out, ptrs_on_device, nullptr, args, step);
+    return act_impl(ctx, obs, n, act_out, ptrs_on_device, nullptr, &args, step);
   }
   // More agents than the argument holds: piecewise into this context's array, by a kernel each.
   float* sigma_dev = (float*)(ctx->ws + ctx->lay.sigma);
@@ -890,7 +888,7 @@ int pop_act_explore(pop_ctx* ctx, const float* obs, int32_t n, float* act_out, i
     k_stage_sigma<<<dim3((k + 63) / 64), dim3(64), 0, ctx->stream>>>(sigma_dev + a0, args, k);
     HIP_TRY(ctx, hipGetLastError());
   }
-  return act_impl(ctx, obs, n, act_out, ptrs_on_device, sigma_dev, args, step);
+  return act_impl(ctx, obs, n, act_out, ptrs_on_device, sigma_dev, nullptr, step);
 }
 
 int pop_act_explore_noalloc(pop_ctx* ctx, const float* obs, int32_t n, float* act_out, const float* sigma, uint32_t step) {
@@ -912,7 +910,7 @@ int pop_act_explore_noalloc(pop_ctx* ctx, const float* obs, int32_t n, float* ac
   // argument, the acting kernel reads them from there
   k_stage_sigma<<<dim3((d.P + 63) / 64), dim3(64), 0, ctx->stream>>>(ctx->static_scratch, args, d.P);
   HIP_TRY(ctx, hipGetLastError());
-  HIP_TRY(ctx, launch_act(d, obs, n, act_out, ctx->static_scratch, args, step, 0u, n, ctx->stream));
+  HIP_TRY(ctx, launch_act(d, obs, n, act_out, ctx->static_scratch, nullptr, step, 0u, n, ctx->stream));
   return POP_OK;
 }
 

@@ -151,7 +151,10 @@ __global__ __launch_bounds__(kThreads) void k_act(PopDev d, const float* __restr
   __syncthreads();
   hidden_layer<1, false, true>(buf, an, d.actor, pre, nullptr, wave, lane, NoTail(), stage);
   __syncthreads();
-  if (d.actor.out <= 16) head_mfma_split<R, false>(buf, an + d.actor.w3, d.actor.out, head, kHs, wave, lane, stage);   // SAC: 2A outputs, the means come first
+  // SAC: 2A outputs, the means come first.  Up to 16 outputs all four wavefronts share the head, unless rounds of workgroups each read another agent's
+  // weights, which then are on their way from memory four times (us, shared / not: 512 agents 33 rows, 3 inputs, 37.0 / 38.2; 768 agents 5 rows 40.3 / 36.5,
+  // SAC of 6 actions 45.8 / 41.4; 512 agents 27.6 / 27.4).
+  if (d.actor.out <= 16 && (chunks > 1 || d.P <= kCUs)) head_mfma_split<R, false>(buf, an + d.actor.w3, d.actor.out, head, kHs, wave, lane, stage);
   else head_mfma<R>(buf, an + d.actor.w3, d.actor.out, head, kHs, wave, lane);
   const bool sac = d.algo == 1;
   __syncthreads();

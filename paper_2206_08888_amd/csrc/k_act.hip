@@ -14,10 +14,12 @@ namespace pop {
 constexpr int kFewWaves = 16, kFewThr = 64 * kFewWaves;
 
 template <int RR>
-struct FewMap {                            // LDS (floats): observations | partial sums | hidden layer | head sums
+struct FewMap {                            // LDS (floats): observations | partial sums | hidden layer | head sums | head weights
   static constexpr int kObsLd = kSacMaxIn;
   static constexpr int obs = 0, part = RR * kObsLd, hidden = part + kFewWaves * RR * kH, head = hidden + RR * kH,
-                       floats = head + RR * kMaxHead;
+                       w3 = head + RR * kMaxHead;
+  __host__ __device__ static constexpr int w3_ld(int J) { return J | 1; }   // a hidden unit's weights: odd, four lanes to a bank at most
+  static constexpr size_t bytes(int J) { return sizeof(float) * (w3 + kH * w3_ld(J)); }
 };
 
 // WIDE: more than 64 inputs.  Below that the first-layer weights are one batch of loads per lane.
@@ -66,16 +68,29 @@ __global__ __launch_bounds__(kFewThr) void k_act_few(PopDev d, const float* __re
     for (int i = 0; i < 16; ++i) w2[i] = *reinterpret_cast<const f32x4*>(p + w2_index<PLAIN>(i, 0));
   };
   const int nb = (K + 63) / 64;
-  // The head's columns wave, wave + 16, wave + 32 of the hidden units 4 lane ..; biases of the sums this thread adds up
-  constexpr int JQ = kMaxHead / kFewWaves;
-  float w3[JQ][4];
+  // The head's weights.  Up to 16 outputs a wavefront requests its own column, hidden units 4 lane .., a line per lane; more columns like that
+  // keep the load path busy longer than the matrix pipe of k_act takes for all of it, so they come in whole lines instead, on their way to
+  // LDS.  us per call, 17 inputs 1 row, columns / lines: 48 outputs 11.1 / 7.9 with 80 agents, 16.6 / 13.8 with 200; 24 outputs 8.3 / 7.0 and 13.1 / 12.2;
+  // 6 outputs 6.6 / 6.6 with 64 agents, 11.4 / 11.6 with 200.  One or two columns beyond 16 (376 inputs, 17 outputs) 17.1 / 15.9 with 128 agents, 27.5 / 27.8 with 256.
+  constexpr int JQ = kMaxHead / kFewWaves, W3I = kMaxHead * kH / 4 / kFewThr;
+  f32x4 w3[W3I];
+  const bool stage3 = J >= kFewWaves + 4 || (J > kFewWaves && d.P <= kCUs / 2);
 #pragma unroll
-  for (int q = 0; q < JQ; ++q)
+  for (int i = 0; i < W3I; ++i) w3[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  if (stage3) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      w3[q][e] = 0.0f;
-      if (wave + kFewWaves * q < J) w3[q][e] = an[d.actor.w3 + (4 * lane + e) * J + wave + kFewWaves * q];
+    for (int i = 0; i < W3I; ++i) {
+      const int e = tid + i * kFewThr;
+      if (e < J * (kH / 4)) w3[i] = *reinterpret_cast<const f32x4*>(an + d.actor.w3 + 4 * e);
     }
+  } else {
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (wave + kFewWaves * q < J) w3[q][e] = an[d.actor.w3 + (4 * lane + e) * J + wave + kFewWaves * q];
+  }
+  // biases of the sums this thread adds up
   const float b1 = an[d.actor.b1 + (tid & (kH - 1))], b2 = an[d.actor.b2 + (tid & (kH - 1))];
   // what the last step needs: thread e has action j of row r, its head biases and its noise
   const int r_out = tid / A, j_out = tid - r_out * A;
@@ -139,7 +154,21 @@ __global__ __launch_bounds__(kFewThr) void k_act_few(PopDev d, const float* __re
   sum_w1(w1, nb - 1);
   meet(b1);
 
-  float nz = 0.0f;                                   // drawn while W2 arrives
+  // while W2 arrives: the head's weights to LDS (read behind the next barriers), and the noise
+  float* w3l = lds + L::w3;
+  const int ld3 = L::w3_ld(J);
+  if (stage3) {
+    const float inv = 1.0f / (float)J;
+#pragma unroll
+    for (int i = 0; i < W3I; ++i) {
+      const int e = 4 * (tid + i * kFewThr);
+      if (e < J * kH) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) w3l[e + k + (ld3 - J) * (int)(((float)(e + k) + 0.5f) * inv)] = w3[i][k];   // unit (e + k) / J, as in gather_run
+      }
+    }
+  }
+  float nz = 0.0f;
   if (sg > 0.0f && last) {
     const HpDev hp = d.hp[agent];
     const uint32_t el = (row_base + (uint32_t)(r0 + r_out)) * (uint32_t)A + (uint32_t)j_out;
@@ -162,10 +191,13 @@ __global__ __launch_bounds__(kFewThr) void k_act_few(PopDev d, const float* __re
 #pragma unroll
   for (int q = 0; q < JQ; ++q) {
     if (wave + kFewWaves * q < J) {
+      float w[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w[e] = stage3 ? w3l[(4 * lane + e) * ld3 + wave + kFewWaves * q] : w3[q][e];
 #pragma unroll
       for (int r = 0; r < RR; ++r) {
         const f32x4 h = *reinterpret_cast<const f32x4*>(hid + r * kH + 4 * lane);
-        const float s = wave_sum((h[0] * w3[q][0] + h[1] * w3[q][1]) + (h[2] * w3[q][2] + h[3] * w3[q][3]));
+        const float s = wave_sum((h[0] * w[0] + h[1] * w[1]) + (h[2] * w[2] + h[3] * w[3]));
         if (lane == 0) head[r * kMaxHead + wave + kFewWaves * q] = s;
       }
     }
@@ -190,7 +222,7 @@ namespace {
 template <int RR>
 hipError_t setup_few() {
   hipError_t e = hipSuccess;
-  const int bytes = FewMap<RR>::floats * (int)sizeof(float);
+  const int bytes = (int)FewMap<RR>::bytes(kMaxHead);
   for (const void* k : {(const void*)k_act_few<RR, false, false>, (const void*)k_act_few<RR, false, true>,
                         (const void*)k_act_few<RR, true, false>, (const void*)k_act_few<RR, true, true>})
     if ((e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes)) != hipSuccess) return e;
@@ -202,7 +234,7 @@ hipError_t launch_few(const PopDev& d, const float* obs, int n, float* act, cons
   const bool wide = d.O > 64;
   auto* kernel = d.w2_plain ? (wide ? k_act_few<RR, true, true> : k_act_few<RR, true, false>)
                             : (wide ? k_act_few<RR, false, true> : k_act_few<RR, false, false>);
-  kernel<<<dim3(xcd_grid(d.P, (n + RR - 1) / RR)), dim3(kFewThr), FewMap<RR>::floats * sizeof(float), s>>>(d, obs, n, act, sigma, args ? *args : kNoNoise, step,
+  kernel<<<dim3(xcd_grid(d.P, (n + RR - 1) / RR)), dim3(kFewThr), FewMap<RR>::bytes(d.actor.out), s>>>(d, obs, n, act, sigma, args ? *args : kNoNoise, step,
                                                                                                                         row_base);
   return hipGetLastError();
 }

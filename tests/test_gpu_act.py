@@ -40,7 +40,9 @@ def _forward64(net, x):
 
 
 @pytest.mark.parametrize("algo, P, O, A", [("td3", 1, 1, 1), ("td3", 3, 17, 6), ("td3", 10, 64, 8), ("td3", 2, 65, 24),
-                                           ("sac", 2, 128, 3), ("sac", 5, 424, 24), ("td3_shared", 3, 447, 1), ("td3", 70, 33, 5)])
+                                           ("sac", 2, 128, 3), ("sac", 5, 424, 24), ("td3_shared", 3, 447, 1), ("td3", 70, 33, 5),
+                                           # heads past 16 columns: even and odd rows in LDS, or two columns of a wavefront (many agents, 17 .. 19)
+                                           ("sac", 2, 17, 10), ("td3", 2, 9, 23), ("td3", 3, 40, 17), ("td3", 130, 70, 17), ("td3", 129, 66, 19)])
 def test_a_few_rows_per_agent(algo, P, O, A):
     code = {"td3": pp.POP_ALGO_TD3, "sac": pp.POP_ALGO_SAC, "td3_shared": pp.POP_ALGO_TD3_SHARED}[algo]
     pop = pp.Population(pp.make_config(P, O, A, (H, H), 256, 64, algo=code), workloads.hparams(0, P))

@@ -247,16 +247,37 @@ hipError_t setup_act_kernels() {
 }
 
 // One workgroup of sixteen wavefronts fills a CU's registers.  As long as every RR rows get a CU to themselves the fewest rows per
-// workgroup end soonest; up to four rows per agent they are ahead of k_act's 32-row workgroups with any number of agents.
+// workgroup end soonest; up to four rows per agent they are ahead of k_act's 32-row workgroups with more agents too (most_agents).
 // us per call with exploration noise, k_act behind a launch for the noise scales / here: 10 agents 1 row 14.6 / 8.0 (the host's share: 8), 50 rows 14.7 / 8.1,
 // 256 agents 1 row 18.5 / 13.5, 4 rows 18.6 / 15.5, 80 agents 8 rows 15.2 / 10.6; 376 inputs: 10 agents 1 row 33.2 / 10.9, 40 rows 37.3 / 12.4, 80
 // agents 1 row 42.0 / 15.1.
+namespace {
+// The most agents with which workgroups of RR rows are ahead of k_act, which reads an agent's weights once for all of its rows and has a head of
+// matrix instructions, but spends a row block's time on one row and reads the first layer's weights block after block: the fewer rows here, the fewer
+// outputs and the more inputs, the longer this kernel stays ahead.  us, k_act / here, without noise.  17 inputs, 6 outputs: 1 row 52.6 / 48.9 with 1024
+// agents, 3 % shorter with 4000 (16 outputs of 3 inputs 38.8 / 37.5 with 768, 49.0 / 50.4 with 1000); 2 rows 23.2 / 21.8 with 384, 26.3 / 26.5 with 512; 4 rows 16.3 / 15.4 with 256, 23.1 / 24.3 with 384.  48 outputs: 1 row 18.4 / 16.2
+// with 256, 30.8 / 31.0 with 512; 2 rows 18.4 / 17.8 with 256, 27.5 / 28.6 with 384; 4 rows 15.0 / 12.4 with 128, 15.3 / 15.6 with 136; 8 rows 15.0 / 14.7 with
+// 120, 15.2 / 15.5 with 128.  65 inputs, 48 outputs: 2 rows 4 % shorter here with 768, 1 % longer with 1024; 4 rows 2 % shorter with 256, 11 % longer with 320.
+// 128 inputs, 8 outputs, 4 rows: 3 % shorter with 4000; 256 inputs, 48 outputs: 4 %.
+int64_t most_agents(int RR, int rows, int inputs, int outputs) {
+  const bool heads = outputs > kFewWaves;
+  if (inputs > 64) {
+    if (RR == 1 || inputs >= 256 || (inputs >= 128 && (RR == 2 || !heads)) || (RR == 2 && outputs <= 32)) return 1 << 24;
+    return RR == 2 ? 3 * kCUs : kCUs;
+  }
+  if (RR == 1) return heads ? 448 : outputs > 8 ? 768 : 2048;
+  if (RR == 2) return heads ? kCUs : 448;
+  return !heads ? kCUs : rows <= 4 ? 128 : 120;
+}
+}  // namespace
 hipError_t launch_act(const PopDev& d, const float* obs, int n, float* act, const float* sigma, const SigmaArgs* args, uint32_t step,
                       uint32_t row_base, int whole, hipStream_t s) {
-  const int64_t P = d.P, N = whole;
-  if (N == 1 || P * N <= kCUs) return launch_few<1>(d, obs, n, act, sigma, args, step, row_base, s);
-  if (N == 2 || P * ((N + 1) / 2) <= kCUs) return launch_few<2>(d, obs, n, act, sigma, args, step, row_base, s);
-  if (N <= 4 || P * ((N + 3) / 4) <= kCUs) return launch_few<4>(d, obs, n, act, sigma, args, step, row_base, s);
+  const auto ahead = [&](int RR) {
+    return (whole <= RR || (int64_t)d.P * (((int64_t)whole + RR - 1) / RR) <= kCUs) && d.P <= most_agents(RR, whole, d.O, d.actor.out);
+  };
+  if (ahead(1)) return launch_few<1>(d, obs, n, act, sigma, args, step, row_base, s);
+  if (ahead(2)) return launch_few<2>(d, obs, n, act, sigma, args, step, row_base, s);
+  if (ahead(4)) return launch_few<4>(d, obs, n, act, sigma, args, step, row_base, s);
   return launch_act_rows(d, obs, n, act, sigma, args, step, row_base, s);
 }
 

@@ -17,11 +17,6 @@
 
 using namespace pop;
 
-// Scratch of pop_act_explore_noalloc: the per-agent noise scales of the call in flight.  One array per GPU for the
-// life of the process (1 KiB); host code reaches it only through the address hipGetSymbolAddress returns for the
-// device that is current (scratch_address below), never through this name.
-static __device__ __align__(256) float scratch[kStaticMaxP];
-
 namespace {
 
 // Hyperparameters of one agent, as a kernel argument: stream order keeps them from changing under launches in flight, where a
@@ -57,36 +52,17 @@ __global__ void k_stage_sigma(float* dst, SigmaArgs a, int P) {
 }
 
 constexpr int kMaxDevices = 64;
-float* g_scratch_ptr[kMaxDevices];                     // address of `scratch` on each device, once looked up
-std::mutex g_scratch_mutex;                            // for it and setup_device
-
-// Address of the static scratch array on the device that is current (looked up once per device).
-hipError_t scratch_address(float** out, int* device) {
-  int dev = -1;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-  std::lock_guard<std::mutex> lock(g_scratch_mutex);
-  if (!g_scratch_ptr[dev]) {
-    float* p = nullptr;
-    e = hipGetSymbolAddress((void**)&p, HIP_SYMBOL(scratch));
-    if (e != hipSuccess) return e;
-    if (!p) return hipErrorInvalidSymbol;
-    g_scratch_ptr[dev] = p;
-  }
-  *out = g_scratch_ptr[dev];
-  *device = dev;
-  return hipSuccess;
-}
+std::mutex g_setup_mutex;
 
 // Attributes of the kernels on the device that is current: set once per device (some sixty calls, 0.1 ms of a pop_create).
-hipError_t setup_device() {
+hipError_t setup_device(int* device) {
   static bool done[kMaxDevices];
   int dev = -1;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-  std::lock_guard<std::mutex> lock(g_scratch_mutex);
+  std::lock_guard<std::mutex> lock(g_setup_mutex);
+  *device = dev;
   if (done[dev]) return hipSuccess;
   for (hipError_t (*setup)() : {setup_kernels, setup_step_kernel, setup_sac_kernels, setup_act_kernels, setup_few_kernels})
     if ((e = setup()) != hipSuccess) return e;
@@ -124,7 +100,6 @@ struct pop_ctx {
   bool handover_pending;         // a launch with waits between its workgroups was enqueued since the fault words were last read
   uint32_t* fault_host;          // two words of pinned host memory the kernels mark when a wait runs out
   float *net_host, *net_dev;     // behind them, as the host and the device see it: a network on its way from or to a pageable host array
-  float* static_scratch;         // this device's copy of the static scratch array (pop_act_explore_noalloc)
   int device;                    // the device that was current at pop_create
   int fuse;                      // launch structure of a step, see POP_K_* in pop.h: 0 one launch per part, 1 target and
                                  // critic chains in one launch, 2 one launch per step, 3 as 1 plus the rest of a
@@ -558,8 +533,7 @@ int pop_create(pop_ctx** out, const pop_config* cfg, const pop_hparams* hp, uint
     return rc;
   };
   hipError_t e;
-  if ((e = setup_device()) != hipSuccess) return bail(e, "kernel attribute setup");
-  if ((e = scratch_address(&ctx->static_scratch, &ctx->device)) != hipSuccess) return bail(e, "hipGetSymbolAddress(scratch)");
+  if ((e = setup_device(&ctx->device)) != hipSuccess) return bail(e, "kernel attribute setup");
   // the two fault words, and room for a network whose order changes on its way: pinned host memory, mapped into the device's address space
   void* fh = nullptr;
   const size_t net_bytes = d.w2_plain ? 0 : sizeof(float) * (size_t)std::max(d.actor.padded, d.critic.padded);
@@ -895,22 +869,19 @@ int pop_act_explore_noalloc(pop_ctx* ctx, const float* obs, int32_t n, float* ac
   if (!ctx) return POP_EINVAL;
   const PopDev& d = ctx->d;
   if (d.P > kStaticMaxP)
-    return fail(ctx, POP_EUNSUPPORTED, "a population of %d agents exceeds the %d the static scratch array holds", d.P, kStaticMaxP);
+    return fail(ctx, POP_EUNSUPPORTED, "a population of %d agents exceeds the %d whose noise scales a kernel argument holds", d.P, kStaticMaxP);
   if (!sigma) return fail(ctx, POP_EINVAL, "sigma is NULL");
   if (n < 0) return fail(ctx, POP_EINVAL, "n is negative");
   if ((int64_t)n * d.A > 0xFFFFFFFFll) return fail(ctx, POP_EINVAL, "n * act_dim exceeds 2^32");
-  SigmaArgs args;
+  SigmaArgs args{};
   for (int a = 0; a < d.P; ++a) {
     if (!(sigma[a] >= 0.0f)) return fail(ctx, POP_EINVAL, "agent %d: sigma must be >= 0", a);
     args.s[a] = sigma[a];
   }
   if (n == 0) return POP_OK;
   if (!obs || !act_out) return fail(ctx, POP_EINVAL, "NULL array");
-  // two launches in stream order and nothing else: the noise scales go into this device's scratch array as a kernel
-  // argument, the acting kernel reads them from there
-  k_stage_sigma<<<dim3((d.P + 63) / 64), dim3(64), 0, ctx->stream>>>(ctx->static_scratch, args, d.P);
-  HIP_TRY(ctx, hipGetLastError());
-  HIP_TRY(ctx, launch_act(d, obs, n, act_out, ctx->static_scratch, nullptr, step, 0u, n, ctx->stream));
+  // one launch and nothing else: the noise scales travel with it, so calls on other streams and of other contexts cannot change them
+  HIP_TRY(ctx, launch_act(d, obs, n, act_out, nullptr, &args, step, 0u, n, ctx->stream));
   return POP_OK;
 }
 

@@ -1,7 +1,6 @@
 """pop_act_explore_noalloc, the entry point for callers that cannot allocate: through the C boundary against
 pop_act_explore (same kernels, so the results must be equal bit for bit), on two calls in a row, the second on a
-smaller population with fewer rows -- both use the one static scratch array of the GPU, which keeps the first
-call's contents."""
+smaller population with fewer rows, and on calls of two populations that overlap on two streams."""
 import numpy as np
 import pytest
 import torch
@@ -49,6 +48,30 @@ def test_noalloc_entry_point_equals_pop_act_explore_on_two_calls_in_a_row():
         pp.pop_act_explore_noalloc(big.ctx, outs[0][1], 70, outs[0][5], [0.1, -1.0, 0.1, 0.1, 0.1, 0.1], 0)
     assert e.value.code == pp.POP_EINVAL
     big.close(); small.close()
+
+
+@pytest.mark.parametrize("n", [3, 700])                   # k_act_few, k_act
+def test_overlapping_calls_keep_their_own_noise_scales(n):
+    ensure_built()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    calls = []
+    for k, s in enumerate(streams):
+        with torch.cuda.stream(s):
+            pop = _population((6, 3)[k], 2)
+            obs = torch.randn((pop.cfg.P, n, 17), generator=torch.Generator(device="cuda").manual_seed(k), device="cuda")
+            calls.append((pop, obs, [torch.empty((pop.cfg.P, n, 6), device="cuda") for _ in range(40)]))
+    torch.cuda.synchronize()
+    sigmas = [[[0.01 * (1 + (i + k + 7 * j) % 30) for i in range(pop.cfg.P)] for j in range(40)] for k, (pop, _, _) in enumerate(calls)]
+    for j in range(40):                                   # one after the other on the two streams, nothing waited for
+        for k, (pop, obs, outs) in enumerate(calls):
+            pp.pop_act_explore_noalloc(pop.ctx, obs, n, outs[j], sigmas[k][j], j)
+    for k, (pop, obs, outs) in enumerate(calls):
+        pop.sync()
+        for j in range(40):
+            want = pop.act(obs, sigma=sigmas[k][j], step=j)
+            pop.sync()
+            assert torch.equal(outs[j], want), (k, j)
+        pop.close()
 
 
 def test_noalloc_entry_point_refuses_populations_beyond_its_scratch():

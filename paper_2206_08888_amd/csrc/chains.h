@@ -583,6 +583,10 @@ __device__ inline float await_y(const PopDev& d, size_t row, uint32_t t) {
   return __uint_as_float((uint32_t)word);
 }
 
+// The NaN that a SAC target critic's workgroup publishes for Q' = alpha log pi = -inf (a diverged population): the smaller Q' of the row, whose
+// difference is the row's NaN, where fminf would take the other critic's finite or infinite difference instead.  No NaN that arithmetic makes.
+constexpr uint32_t kInfMinusInf = 0x7fe5a5a5u;
+
 // Bulk results (activation tiles, partial sums, updated weights) handed to later workgroups
 // of the same launch.  The producers of a unit write them with put<true> (written through
 // to memory), wait until the memory system has acknowledged all of their own stores
@@ -853,8 +857,8 @@ struct CriticMap : LdsMap<G::R, G::kPad> {
 // them poll for their rows right before the loss.  SIGNAL: count this chunk as finished
 // for the weight-gradient workgroups of the same launch.  AHEAD: the workgroups of critic 2 run the actor's forward
 // pass for their rows before they wait (d.actor_ahead, steps with an actor update).  TWO: what is waited for are the two target critics'
-// values (target_chain's ONE); the workgroups of critic 1 write y.
-template <class G, bool WAIT, bool SIGNAL, bool AHEAD = false, bool TWO = false>
+// values (target_chain's ONE; SAC: sac_target_chain's); the workgroups of critic 1 write y.
+template <class G, bool WAIT, bool SIGNAL, bool AHEAD = false, bool TWO = false, bool SAC = false>
 __device__ __forceinline__ void critic_chain(const PopDev& d, uint32_t t, int net, int chunk, float* lds) {
   constexpr int R = G::R;
   static_assert(!(AHEAD && G::kStageOnInput), "the forward pass ahead reads the input tile after the first product");
@@ -917,7 +921,8 @@ __device__ __forceinline__ void critic_chain(const PopDev& d, uint32_t t, int ne
     if (tid < R) {                                   // same lane uses it below
       const size_t row = (size_t)agent * d.B + r0 + tid;
       const float q0 = await_y(d, row, t), q1 = await_y(d, (size_t)d.P * d.B + row, t);
-      yv = rew + gamma * (1.0f - done) * fminf(q0, q1);
+      const bool undefined = SAC && (__float_as_uint(q0) == kInfMinusInf || __float_as_uint(q1) == kInfMinusInf);
+      yv = rew + gamma * (1.0f - done) * (undefined ? __uint_as_float(kInfMinusInf) : fminf(q0, q1));
       if (k == 0) d.y[row] = yv;
     }
   } else if (WAIT && tid < R) {

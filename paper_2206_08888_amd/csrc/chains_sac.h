@@ -56,7 +56,7 @@ inline int vec_sac_actor(const PopDev&) { return vec_sac_actor_floats; }
 // ---------------------------------------------------------------------------------------------
 // Target chain.  One workgroup per (agent, chunk).
 // ONE: of the two target critics this workgroup runs number `one` only and publishes Q' - alpha log pi of each row (target_chain); the
-// smaller of the two is that of the smaller Q', rounding included.
+// smaller of the two is that of the smaller Q', rounding included (and kInfMinusInf).
 template <class G, bool ONE = false>
 __device__ __forceinline__ void sac_target_chain(const PopDev& d, uint32_t t, int agent, int chunk, float* lds, int one = 0) {
   constexpr int R = G::R;
@@ -151,7 +151,10 @@ __device__ __forceinline__ void sac_target_chain(const PopDev& d, uint32_t t, in
     POP_MARK(8 + 3 * k);
   }
   if (ONE) {
-    if (tid < R) publish_y(d, ((size_t)one * d.P + agent) * d.B + r0 + tid, t, qmin[tid] - alpha * qmin[R + tid]);
+    if (tid < R) {
+      const float q = qmin[tid], v = q - alpha * qmin[R + tid];
+      publish_y(d, ((size_t)one * d.P + agent) * d.B + r0 + tid, t, q == -INFINITY && v != v ? __uint_as_float(kInfMinusInf) : v);
+    }
   } else if (tid < R) {
     const float rew = rows[(size_t)tid * d.row + d.D];
     const float done = rows[(size_t)tid * d.row + d.D + 1];

@@ -57,7 +57,7 @@ __global__ __launch_bounds__(GT::kThr, GT::kThr / kThreads) void k_sac_target_cr
     if (decode_block(blockIdx.x, d.P, (SPLIT ? 2 : 1) * (d.B / GT::R), unit, sub))
       sac_target_chain<GT, SPLIT>(d, t, unit, SPLIT ? sub >> 1 : sub, lds, sub & 1);
   } else if (decode_block(blockIdx.x - target_blocks, 2 * d.P, d.B / GC::R, unit, sub)) {
-    critic_chain<GC, true, false, false, SPLIT>(d, t, unit, sub, lds);
+    critic_chain<GC, true, false, false, SPLIT, SPLIT>(d, t, unit, sub, lds);
   }
   POP_BLOCK_TIME(kTraceTargetCritic, 1);
 }

@@ -83,3 +83,25 @@ def test_sac_with_more_than_eight_actions_takes_every_launch_and_rows(P, launch,
         pop.close()
     if rows is not None or P != 20:                       # (20 agents: one launch per part has 32-row target chains, a fused launch 16)
         assert all(np.array_equal(a, b) for a, b in zip(*states))
+
+
+@pytest.mark.parametrize("bias1, bias2", [(-np.inf, 0.0), (0.0, -np.inf), (np.inf, 0.0), (-np.inf, np.nan), (np.nan, 0.0), (np.inf, np.inf)])
+def test_sac_targets_of_a_diverged_population(bias1, bias2):
+    """An infinite temperature and infinite or NaN target critics: the two critics' values, handed over apart, give the y of min(Q1', Q2') - alpha log pi."""
+    ensure_built()
+    hps = workloads.hparams(5, 1)
+    hps[0]["init_log_alpha"] = 100.0                      # alpha = inf, alpha log pi = +-inf
+    got = []
+    for launch in (pp.POP_LAUNCH_PER_PART, pp.POP_LAUNCH_TARGET_CRITIC):
+        pop = pp.Population(pp.make_config(1, 17, 6, (256, 256), 256, 300, algo=pp.POP_ALGO_SAC, launch=launch), hps)
+        for net, bias in (("t_critic1", bias1), ("t_critic2", bias2)):
+            th = pop.get_params(0, net).copy()
+            th[-1] = bias
+            pop.set_params(0, net, th)
+        g = np.random.default_rng(5)
+        rows = lambda *s: g.standard_normal((1, 300) + s).astype(np.float32)
+        pop.insert(-1, obs=rows(17), act=np.clip(rows(6), -1, 1), rew=rows(), done=np.zeros((1, 300), np.float32), next_obs=rows(17))
+        pop.update(1)
+        got.append(pop.debug("target_y"))
+        pop.close()
+    assert not np.isfinite(got[0]).all() and np.array_equal(got[0], got[1], equal_nan=True), (got[0][0, :8], got[1][0, :8])

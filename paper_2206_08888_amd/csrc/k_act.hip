@@ -278,7 +278,7 @@ hipError_t launch_act(const PopDev& d, const float* obs, int n, float* act, cons
   if (ahead(1)) return launch_few<1>(d, obs, n, act, sigma, args, step, row_base, s);
   if (ahead(2)) return launch_few<2>(d, obs, n, act, sigma, args, step, row_base, s);
   if (ahead(4)) return launch_few<4>(d, obs, n, act, sigma, args, step, row_base, s);
-  return launch_act_rows(d, obs, n, act, sigma, args, step, row_base, s);
+  return launch_act_rows(d, obs, n, act, sigma, args, step, row_base, whole, s);
 }
 
 }  // namespace pop

@@ -109,8 +109,8 @@ __global__ __launch_bounds__(G::kThr, PER_CU) void k_actor(PopDev d, uint32_t t)
 template <bool PLAIN>
 __global__ __launch_bounds__(kThreads) void k_act(PopDev d, const float* __restrict__ obs, int n,
                                                   float* __restrict__ act, const float* __restrict__ sigma, uint32_t step,
-                                                  uint32_t row_base, int chunks, int noise, SigmaArgs sigma_args) {
-  warm_args<sizeof(PopDev) + 48>();
+                                                  uint32_t row_base, int chunks, int noise, int share_head, SigmaArgs sigma_args) {
+  warm_args<sizeof(PopDev) + 52>();
   constexpr int R = 32;
   extern __shared__ float lds[];
   constexpr int kHs = kMaxHead;                      // row stride of the head block
@@ -151,10 +151,8 @@ __global__ __launch_bounds__(kThreads) void k_act(PopDev d, const float* __restr
   __syncthreads();
   hidden_layer<1, false, true>(buf, an, d.actor, pre, nullptr, wave, lane, NoTail(), stage);
   __syncthreads();
-  // SAC: 2A outputs, the means come first.  Up to 16 outputs all four wavefronts share the head, unless rounds of workgroups each read another agent's
-  // weights, which then are on their way from memory four times (us, shared / not: 512 agents 33 rows, 3 inputs, 37.0 / 38.2; 768 agents 5 rows 40.3 / 36.5,
-  // SAC of 6 actions 45.8 / 41.4; 512 agents 27.6 / 27.4).
-  if (d.actor.out <= 16 && (chunks > 1 || d.P <= kCUs)) head_mfma_split<R, false>(buf, an + d.actor.w3, d.actor.out, head, kHs, wave, lane, stage);
+  // SAC: 2A outputs, the means come first
+  if (share_head) head_mfma_split<R, false>(buf, an + d.actor.w3, d.actor.out, head, kHs, wave, lane, stage);
   else head_mfma<R>(buf, an + d.actor.w3, d.actor.out, head, kHs, wave, lane);
   const bool sac = d.algo == 1;
   __syncthreads();
@@ -351,11 +349,15 @@ hipError_t launch_actor(const PopDev& d, uint32_t t, hipStream_t s) {
   return hipGetLastError();
 }
 hipError_t launch_act_rows(const PopDev& d, const float* obs, int n, float* act, const float* sigma, const SigmaArgs* args, uint32_t step,
-                           uint32_t row_base, hipStream_t s) {
+                           uint32_t row_base, int whole, hipStream_t s) {
   auto* kernel = d.w2_plain ? k_act<true> : k_act<false>;
   const ActGrid g = act_grid(d.P, n);
+  // Up to 16 outputs all four wavefronts share the head, unless rounds of workgroups each read another agent's weights, which then are on their way
+  // from memory four times (us, shared / not: 512 agents 33 rows, 3 inputs, 37.0 / 38.2; 768 agents 5 rows 40.3 / 36.5, SAC of 6 actions 45.8 / 41.4; 512
+  // agents 27.6 / 27.4).
+  const int share_head = d.actor.out <= 16 && (whole > 32 || d.P <= kCUs);
   kernel<<<dim3(xcd_grid(d.P, g.chunks), g.pieces), dim3(kThreads), act_lds_bytes(d), s>>>(d, obs, n, act, sigma, step, row_base,
-                                                                                                        g.chunks, sigma || args, args ? *args : kNoNoise);
+                                                                                                        g.chunks, sigma || args, share_head, args ? *args : kNoNoise);
   return hipGetLastError();
 }
 

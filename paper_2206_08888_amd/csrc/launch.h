@@ -51,7 +51,7 @@ int wgrad_role_count(const PopDev& d, int actor_phase);
 // acting: obs[P][n][O] -> act[P][n][A] through the online actors; a noise scale above zero adds exploration noise drawn at counter
 // `step`, rows numbered from row_base.  The scales: sigma (device, [P]), or where that is nullptr those of `args` (up to
 // kStaticMaxP agents; they travel as a kernel argument); both nullptr: no noise.  `whole`: rows of the caller's request, of
-// which this launch may be a piece: it decides which kernel runs, so that a row comes out the same in one piece and in several.
+// which this launch may be a piece: it decides which kernel and which form of its head runs, so that a row comes out the same in one piece and in several.
 constexpr int kStaticMaxP = 256;
 struct SigmaArgs { float s[kStaticMaxP]; };
 constexpr SigmaArgs kNoNoise{};
@@ -66,7 +66,7 @@ inline ActGrid act_grid(int P, int n) {
   return {(int)chunks, (int)((all + chunks - 1) / chunks)};
 }
 hipError_t launch_act_rows(const PopDev& d, const float* obs, int n, float* act, const float* sigma, const SigmaArgs* args, uint32_t step,
-                           uint32_t row_base, hipStream_t s);
+                           uint32_t row_base, int whole, hipStream_t s);
 hipError_t setup_act_kernels();
 
 // one-time per-process kernel attribute setup (large dynamic LDS)

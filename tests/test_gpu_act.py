@@ -91,3 +91,15 @@ def test_more_rows_than_one_grid_dimension_holds():
     noise = got[1, line - few // 2:line + few // 2] - still
     assert 0.05 < float(noise.std()) < 0.15
     pop.close()
+
+
+@pytest.mark.parametrize("P, O, n", [(300, 100, 151), (30, 376, 370), (257, 376, 45)])
+def test_the_last_piece_of_host_arrays_rounds_as_the_others(P, O, n):
+    """Host arrays go through a 16 MB staging area piece by piece; the rows of a short last piece come out as in a device call with all rows."""
+    A = 6
+    piece = (16 << 20) // (P * (O + A) * 4)
+    assert n > piece and 0 < n % piece <= 32
+    pop = pp.Population(pp.make_config(P, O, A, (H, H), 256, 64), workloads.hparams(0, P))
+    obs = np.random.default_rng(n).standard_normal((P, n, O)).astype(np.float32)
+    assert np.array_equal(pop.act(obs), pop.act(torch.from_numpy(obs).cuda()).cpu().numpy())
+    pop.close()

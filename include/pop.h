@@ -229,7 +229,11 @@ int pop_update_timed(pop_ctx* ctx, int32_t n_steps, double* ms, int64_t* launche
 /* Deterministic actions of every agent's current actor (for SAC: the tanh of
  * the mean): obs[P, n, obs_dim] -> act_out[P, n, act_dim] (agent i acts on
  * slice i).  This is the inference the paper's actor processes run on their copy of the parameters (App. A), here
- * for the whole population at once on the device that holds them. */
+ * for the whole population at once on the device that holds them.  Which kernel runs depends on P, n and the shapes
+ * (few rows per agent have one of their own), and the two sum in different orders: the same observation in calls of
+ * different n gives actions that may differ by fp32 rounding, a few 1e-7 where the action is not saturated (some
+ * 2e-5 at the most for inputs of several hundred components).  Calls of the same shape are bit-reproducible, and
+ * host arrays, which the library takes piece by piece, give the bits of a device call with all rows. */
 int pop_act(pop_ctx* ctx, const float* obs, int32_t n, float* act_out,
             int32_t ptrs_on_device);
 
@@ -238,8 +242,10 @@ int pop_act(pop_ctx* ctx, const float* obs, int32_t n, float* act_out,
  * sigma = host array of P non-negative values (0: no noise for that agent).
  * eps is unit normal number r * act_dim + j (r = row of the agent's slice, j =
  * action component) of the agent's exploration stream at counter `step`, so a
- * call is reproducible and independent of how it is split into pieces; callers
- * pass a fresh `step` per call (e.g. their environment-step counter).
+ * call is reproducible and independent of the pieces that the library takes
+ * host arrays in; callers pass a fresh `step` per call (e.g. their
+ * environment-step counter).  (A caller's own pieces number their rows from 0
+ * each, and round as pop_act says.)
  * For SAC the policy itself is sampled instead: a = tanh(mu + sigma[i] *
  * std * eps) with the policy's own std (sigma[i] = 1 is the policy).
  * sigma is read before the call returns; it reaches the device in stream order, as kernel arguments, so with device

@@ -19,11 +19,15 @@ struct FewMap {                            // LDS (floats): observations | parti
   static constexpr int obs = 0, part = RR * kObsLd, hidden = part + kFewWaves * RR * kH, head = hidden + RR * kH,
                        w3 = head + RR * kMaxHead;
   __host__ __device__ static constexpr int w3_ld(int J) { return J | 1; }   // a hidden unit's weights: odd, four lanes to a bank at most
-  static constexpr size_t bytes(int J) { return sizeof(float) * (w3 + kH * w3_ld(J)); }
+  static constexpr size_t bytes(int J) { return sizeof(float) * (w3 + (J ? kH * w3_ld(J) : 0)); }   // J = 0: no head weights
 };
 
 // WIDE: more than 64 inputs.  Below that the first-layer weights are one batch of loads per lane.
-template <int RR, bool PLAIN, bool WIDE>
+// LINES: a head of many columns.  A column requested by its wavefront is a line per lane, and more than one or two of those keep the load path busy longer
+// than k_act takes for all of it; whole lines take a detour through LDS.  us per call, 17 inputs 1 row, columns / lines: 48 outputs 11.1 / 7.9 with 80 agents,
+// 16.6 / 13.8 with 200; 24 outputs 8.3 / 7.0 and 13.1 / 12.2; 6 outputs 6.6 / 6.6 with 64, 11.4 / 11.6 with 200; 376 inputs, 17 outputs: 17.1 / 15.9 with 128, 27.5 /
+// 27.8 with 256.
+template <int RR, bool PLAIN, bool WIDE, bool LINES>
 __global__ __launch_bounds__(kFewThr) void k_act_few(PopDev d, const float* __restrict__ obs, int n, float* __restrict__ act,
                                                      const float* __restrict__ sigma, SigmaArgs sigma_args, uint32_t step, uint32_t row_base) {
   warm_args<sizeof(PopDev) + 32>();
@@ -68,27 +72,25 @@ __global__ __launch_bounds__(kFewThr) void k_act_few(PopDev d, const float* __re
     for (int i = 0; i < 16; ++i) w2[i] = *reinterpret_cast<const f32x4*>(p + w2_index<PLAIN>(i, 0));
   };
   const int nb = (K + 63) / 64;
-  // The head's weights.  Up to 16 outputs a wavefront requests its own column, hidden units 4 lane .., a line per lane; more columns like that
-  // keep the load path busy longer than the matrix pipe of k_act takes for all of it, so they come in whole lines instead, on their way to
-  // LDS.  us per call, 17 inputs 1 row, columns / lines: 48 outputs 11.1 / 7.9 with 80 agents, 16.6 / 13.8 with 200; 24 outputs 8.3 / 7.0 and 13.1 / 12.2;
-  // 6 outputs 6.6 / 6.6 with 64 agents, 11.4 / 11.6 with 200.  One or two columns beyond 16 (376 inputs, 17 outputs) 17.1 / 15.9 with 128 agents, 27.5 / 27.8 with 256.
+  // The head's weights: the wavefront's columns wave, wave + 16, wave + 32 of the hidden units 4 lane .., or (LINES) whole lines on their way to LDS
   constexpr int JQ = kMaxHead / kFewWaves, W3I = kMaxHead * kH / 4 / kFewThr;
-  f32x4 w3[W3I];
-  const bool stage3 = J >= kFewWaves + 4 || (J > kFewWaves && d.P <= kCUs / 2);
-#pragma unroll
-  for (int i = 0; i < W3I; ++i) w3[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  if (stage3) {
+  float w3[LINES ? 1 : JQ][4];
+  f32x4 w3_lines[LINES ? W3I : 1];
+  if constexpr (LINES) {
 #pragma unroll
     for (int i = 0; i < W3I; ++i) {
       const int e = tid + i * kFewThr;
-      if (e < J * (kH / 4)) w3[i] = *reinterpret_cast<const f32x4*>(an + d.actor.w3 + 4 * e);
+      w3_lines[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      if (e < J * (kH / 4)) w3_lines[i] = *reinterpret_cast<const f32x4*>(an + d.actor.w3 + 4 * e);
     }
   } else {
 #pragma unroll
-    for (int q = 0; q < 2; ++q)
+    for (int q = 0; q < JQ; ++q)
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
+      for (int e = 0; e < 4; ++e) {
+        w3[q][e] = 0.0f;
         if (wave + kFewWaves * q < J) w3[q][e] = an[d.actor.w3 + (4 * lane + e) * J + wave + kFewWaves * q];
+      }
   }
   // biases of the sums this thread adds up
   const float b1 = an[d.actor.b1 + (tid & (kH - 1))], b2 = an[d.actor.b2 + (tid & (kH - 1))];
@@ -154,21 +156,20 @@ __global__ __launch_bounds__(kFewThr) void k_act_few(PopDev d, const float* __re
   sum_w1(w1, nb - 1);
   meet(b1);
 
-  // while W2 arrives: the head's weights to LDS (read behind the next barriers), and the noise
   float* w3l = lds + L::w3;
   const int ld3 = L::w3_ld(J);
-  if (stage3) {
+  if constexpr (LINES) {                             // to LDS while W2 arrives, read behind the next barriers
     const float inv = 1.0f / (float)J;
 #pragma unroll
     for (int i = 0; i < W3I; ++i) {
       const int e = 4 * (tid + i * kFewThr);
       if (e < J * kH) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) w3l[e + k + (ld3 - J) * (int)(((float)(e + k) + 0.5f) * inv)] = w3[i][k];   // unit (e + k) / J, as in gather_run
+        for (int k = 0; k < 4; ++k) w3l[e + k + (ld3 - J) * (int)(((float)(e + k) + 0.5f) * inv)] = w3_lines[i][k];   // unit (e + k) / J, as in gather_run
       }
     }
   }
-  float nz = 0.0f;
+  float nz = 0.0f;                                   // drawn while W2 arrives
   if (sg > 0.0f && last) {
     const HpDev hp = d.hp[agent];
     const uint32_t el = (row_base + (uint32_t)(r0 + r_out)) * (uint32_t)A + (uint32_t)j_out;
@@ -193,7 +194,10 @@ __global__ __launch_bounds__(kFewThr) void k_act_few(PopDev d, const float* __re
     if (wave + kFewWaves * q < J) {
       float w[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) w[e] = stage3 ? w3l[(4 * lane + e) * ld3 + wave + kFewWaves * q] : w3[q][e];
+      for (int e = 0; e < 4; ++e) {
+        if constexpr (LINES) w[e] = w3l[(4 * lane + e) * ld3 + wave + kFewWaves * q];
+        else w[e] = w3[q][e];
+      }
 #pragma unroll
       for (int r = 0; r < RR; ++r) {
         const f32x4 h = *reinterpret_cast<const f32x4*>(hid + r * kH + 4 * lane);
@@ -219,23 +223,31 @@ __global__ __launch_bounds__(kFewThr) void k_act_few(PopDev d, const float* __re
 }
 
 namespace {
+template <int RR, bool PLAIN, bool WIDE>
+const void* few_kernel(bool lines) { return lines ? (const void*)k_act_few<RR, PLAIN, WIDE, true> : (const void*)k_act_few<RR, PLAIN, WIDE, false>; }
+template <int RR>
+const void* few_kernel(bool plain, bool wide, bool lines) {
+  return plain ? (wide ? few_kernel<RR, true, true>(lines) : few_kernel<RR, true, false>(lines))
+               : (wide ? few_kernel<RR, false, true>(lines) : few_kernel<RR, false, false>(lines));
+}
 template <int RR>
 hipError_t setup_few() {
-  hipError_t e = hipSuccess;
-  const int bytes = (int)FewMap<RR>::bytes(kMaxHead);
-  for (const void* k : {(const void*)k_act_few<RR, false, false>, (const void*)k_act_few<RR, false, true>,
-                        (const void*)k_act_few<RR, true, false>, (const void*)k_act_few<RR, true, true>})
-    if ((e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes)) != hipSuccess) return e;
-  return e;
+  for (int form = 0; form < 8; ++form) {
+    const hipError_t e = hipFuncSetAttribute(few_kernel<RR>(form & 1, form & 2, form & 4), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             (int)FewMap<RR>::bytes(form & 4 ? kMaxHead : 0));
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 template <int RR>
 hipError_t launch_few(const PopDev& d, const float* obs, int n, float* act, const float* sigma, const SigmaArgs* args, uint32_t step,
                       uint32_t row_base, hipStream_t s) {
-  const bool wide = d.O > 64;
-  auto* kernel = d.w2_plain ? (wide ? k_act_few<RR, true, true> : k_act_few<RR, true, false>)
-                            : (wide ? k_act_few<RR, false, true> : k_act_few<RR, false, false>);
-  kernel<<<dim3(xcd_grid(d.P, (n + RR - 1) / RR)), dim3(kFewThr), FewMap<RR>::bytes(d.actor.out), s>>>(d, obs, n, act, sigma, args ? *args : kNoNoise, step,
-                                                                                                                        row_base);
+  const int J = d.actor.out;
+  const bool lines = J >= kFewWaves + 4 || (J > kFewWaves && d.P <= kCUs / 2);
+  using Kernel = void (*)(PopDev, const float*, int, float*, const float*, SigmaArgs, uint32_t, uint32_t);
+  auto kernel = (Kernel)few_kernel<RR>(d.w2_plain != 0, d.O > 64, lines);
+  kernel<<<dim3(xcd_grid(d.P, (n + RR - 1) / RR)), dim3(kFewThr), FewMap<RR>::bytes(lines ? J : 0), s>>>(d, obs, n, act, sigma, args ? *args : kNoNoise, step,
+                                                                                                         row_base);
   return hipGetLastError();
 }
 }  // namespace
@@ -254,20 +266,25 @@ hipError_t setup_act_kernels() {
 namespace {
 // The most agents with which workgroups of RR rows are ahead of k_act, which reads an agent's weights once for all of its rows and has a head of
 // matrix instructions, but spends a row block's time on one row and reads the first layer's weights block after block: the fewer rows here, the fewer
-// outputs and the more inputs, the longer this kernel stays ahead.  us, k_act / here, without noise.  17 inputs, 6 outputs: 1 row 52.6 / 48.9 with 1024
-// agents, 3 % shorter with 4000 (16 outputs of 3 inputs 38.8 / 37.5 with 768, 49.0 / 50.4 with 1000); 2 rows 23.2 / 21.8 with 384, 26.3 / 26.5 with 512; 4 rows 16.3 / 15.4 with 256, 23.1 / 24.3 with 384.  48 outputs: 1 row 18.4 / 16.2
-// with 256, 30.8 / 31.0 with 512; 2 rows 18.4 / 17.8 with 256, 27.5 / 28.6 with 384; 4 rows 15.0 / 12.4 with 128, 15.3 / 15.6 with 136; 8 rows 15.0 / 14.7 with
-// 120, 15.2 / 15.5 with 128.  65 inputs, 48 outputs: 2 rows 4 % shorter here with 768, 1 % longer with 1024; 4 rows 2 % shorter with 256, 11 % longer with 320.
-// 128 inputs, 8 outputs, 4 rows: 3 % shorter with 4000; 256 inputs, 48 outputs: 4 %.
+// outputs and the more inputs, the longer this kernel stays ahead.  us, k_act / here, without noise:
+//   17 inputs, 6 outputs: 1 row 52.0 / 48.6 with 1024 agents, 110.5 / 107.8 with 2048; 2 rows 26.5 / 25.9 with 512, 52.5 / 52.7 with 1024; 3 rows 23.3 / 23.0 with
+//   304, 23.5 / 24.0 with 384
+//   12 and 16 outputs: 17 inputs 12 outputs, 3 rows, 22.7 / 23.4 with 257; 3 inputs 16 outputs, 1 row the same with 768, 4 % longer with 1024, 2 rows 1 % longer with 384
+//   17 inputs, 48 outputs: 1 row 18.4 / 16.2 with 256, 30.8 / 31.0 with 512; 2 rows 18.4 / 17.8 with 256, 27.5 / 28.6 with 384; 4 rows 15.0 / 12.4 with 128, 15.3 /
+//   15.6 with 136; 8 rows 15.0 / 14.7 with 120, 15.2 / 15.5 with 128
+//   65 inputs, 3 rows: 8 outputs 27.4 / 24.7 with 257, 137.5 / 136.4 with 2048; 12 outputs 28.2 / 28.0 with 384, 32.4 / 32.5 with 512; 16 outputs 27.1 / 27.2
+//   with 257; 48 outputs, 2 rows, 5 % shorter with 768, 1 % longer with 1024
 int64_t most_agents(int RR, int rows, int inputs, int outputs) {
-  const bool heads = outputs > kFewWaves;
+  constexpr int64_t any = 1 << 24;
   if (inputs > 64) {
-    if (RR == 1 || inputs >= 256 || (inputs >= 128 && (RR == 2 || !heads)) || (RR == 2 && outputs <= 32)) return 1 << 24;
-    return RR == 2 ? 3 * kCUs : kCUs;
+    if (RR == 1 || inputs >= 256) return any;
+    if (RR == 2) return outputs <= 32 || inputs >= 128 ? any : 768;
+    if (outputs <= 8 || (outputs <= 16 && inputs >= 96)) return any;
+    return outputs <= 12 ? 384 : 256;
   }
-  if (RR == 1) return heads ? 448 : outputs > 8 ? 768 : 2048;
-  if (RR == 2) return heads ? kCUs : 448;
-  return !heads ? kCUs : rows <= 4 ? 128 : 120;
+  if (outputs <= 8) return RR == 1 ? 2048 : RR == 2 ? 512 : 304;
+  if (outputs <= 16) return RR == 1 ? 768 : RR == 2 ? 384 : 256;
+  return RR == 1 ? 448 : RR == 2 ? 256 : rows <= 4 ? 128 : 120;
 }
 }  // namespace
 hipError_t launch_act(const PopDev& d, const float* obs, int n, float* act, const float* sigma, const SigmaArgs* args, uint32_t step,

@@ -18,6 +18,13 @@ def ensure_built():
     return pp.load_library()
 
 
+def many_rows(P):
+    """Rows per agent that the 32-row acting kernel takes: sixteen-wavefront workgroups of four rows each would need more than the 256
+    CUs.  The last block of 32 is ragged."""
+    n = 4 * (256 // P) + 13
+    return n if n % 32 else n + 1
+
+
 def rel_l2(a, b):
     a = np.asarray(a, dtype=np.float64); b = np.asarray(b, dtype=np.float64)
     return float(np.linalg.norm(a - b) / max(np.linalg.norm(b), 1e-300))

@@ -1,11 +1,12 @@
-"""Acting on a few rows per agent (k_act_few): against the actor's forward pass in 64 bits, at the ends of its range."""
+"""Acting on a few rows per agent (k_act_few): against the actor's forward pass in 64 bits, at the ends of its range, and the same rows among
+many (k_act)."""
 import numpy as np
 import pytest
 import torch
 
 import paper_2206_08888_amd as pp
 import workloads
-from gpu_common import ensure_built
+from gpu_common import ensure_built, many_rows
 
 pytestmark = pytest.mark.gpu
 H = 256
@@ -25,10 +26,11 @@ def _actor64(pop, agent, O, out):
     return parts
 
 
-def _forward64(net, x):
-    """Head sums, and a bound on what 32-bit sums may be off: u per operation, at most 64 operations one after the other in a
-    sum (28 + 16 for the widest first layer, 32 for the others, and the dot product over lanes), errors of a layer carried through the next."""
-    u = 64 * 2.0 ** -24
+def _forward64(net, x, chain=64):
+    """Head sums, and a bound on what 32-bit sums may be off: u per operation, at most `chain` operations one after the other in a
+    sum (k_act_few 64: 28 + 16 for the widest first layer, 32 for the others, and the dot product over lanes; k_act 448: the widest
+    first layer; six partial products of 16 instructions for the others), errors of a layer carried through the next."""
+    u = chain * 2.0 ** -24
     h, e = x, np.zeros_like(x)
     for k in (0, 2, 4):
         W, b = net[k], net[k + 1]
@@ -52,20 +54,24 @@ def test_a_few_rows_per_agent(algo, P, O, A):
     nets = [_actor64(pop, i, O, 2 * A if algo == "sac" else A) for i in range(P)]
     most = (256 // P) * 4                                # rows per agent up to which the kernel is taken whatever P is
     first = None
-    for n in sorted({1, 2, 3, 4, 5, min(7, most), min(most, 41)}):
+    for n in sorted({1, 2, 3, 4, 5, min(7, most), min(most, 41), many_rows(P)}):
         obs = rng.standard_normal((P, n, O)).astype(np.float32)
         if first is not None:
             obs[:, :1] = first
         first = obs[:, :1]
         got = pop.act(torch.from_numpy(obs).cuda()).cpu().numpy()
         for i in range(P):
-            z, e = _forward64(nets[i], obs[i].astype(np.float64))
+            z, e = _forward64(nets[i], obs[i].astype(np.float64), 64 if n <= most else 448)
             assert np.all(np.abs(got[i] - np.tanh(z[:, :A])) <= e[:, :A] + 2.0 ** -21), (n, i)
         if n <= 4 or P * ((n + 3) // 4) <= 256:          # a row does not depend on how many there are
             if n > 1:
                 assert np.array_equal(got[:, :1], alone)
             alone = got[:, :1]
         assert np.array_equal(got, pop.act(obs))         # host arrays
+        if n > most:                                     # the same row among many: both sums are within their bounds
+            z, few = _forward64(nets[0], obs[0, :1].astype(np.float64))
+            many = _forward64(nets[0], obs[0, :1].astype(np.float64), 448)[1]
+            assert np.all(np.abs(got[0, :1] - alone[0]) <= (few + many)[:, :A] + 2.0 ** -20)
         sigma = np.linspace(0.0, 0.3, P).astype(np.float32)
         noisy = pop.act(torch.from_numpy(obs).cuda(), sigma, step=9).cpu().numpy()
         assert np.array_equal(noisy[0], got[0]) and (P == 1 or not np.array_equal(noisy[-1], got[-1]))

@@ -5,7 +5,7 @@ import pytest
 
 import paper_2206_08888_amd as pp
 import workloads
-from gpu_common import NETS, STATE12, ensure_built, make_pair, rel_l2
+from gpu_common import NETS, STATE12, ensure_built, make_pair, many_rows, rel_l2
 
 pytestmark = pytest.mark.gpu
 
@@ -47,12 +47,12 @@ def test_row_major_matrices_change_rounding_only(rows_critic, ahead):
     initial networks and actions bit for bit as with 32-row actor chains, where they do not, and steps that differ in the order of
     fp32 sums only (the bound of the comparison between the row classes)."""
     import torch
-    obs = torch.randn((10, 40, 17), generator=torch.Generator().manual_seed(3)).cuda()
+    obs = [torch.randn((10, n, 17), generator=torch.Generator().manual_seed(3)).cuda() for n in (40, many_rows(10))]   # both acting kernels
     out = []
     for rows_actor in (16, 32):
         gpu, _, _ = make_pair(2, P=10, capacity=600, hps=workloads.hparams(2, 10), oracle=False, rows=(16, rows_critic, rows_actor),
                               rows_critic1=16, launch=pp.POP_LAUNCH_TARGET_CRITIC, half_tiles=1, actor_ahead=ahead if rows_actor == 16 else 1)
-        first = [gpu.get_params(i, w) for i in range(10) for w in NETS] + [gpu.act(obs).cpu().numpy()]
+        first = [gpu.get_params(i, w) for i in range(10) for w in NETS] + [gpu.act(o).cpu().numpy() for o in obs]
         gpu.update(3)
         out.append((first, {(i, w): gpu.get_params(i, w) for i in range(10) for w in STATE12}))
         gpu.close()

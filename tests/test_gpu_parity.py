@@ -17,7 +17,7 @@ import pytest
 import paper_2206_08888_amd as pp
 import workloads
 from gpu_common import (MOM_M, MOM_V, NETS, PARAMS6, STATE12, check_step_elementwise, check_tensors_all, describe_free_run,
-                        ensure_built, force_state, free_run_tie_aware, make_pair, rel_l2, snapshot)
+                        ensure_built, force_state, free_run_tie_aware, make_pair, rel_l2, snapshot, many_rows)
 
 pytestmark = pytest.mark.gpu
 
@@ -532,11 +532,12 @@ def test_wide_observations_in_a_mid_size_population(obs_dim, act_dim):
     check_tensors_all(gpu, orc, pairs, PARAMS6, 1e-3, "four steps at P = 20, obs %d, act %d" % (obs_dim, act_dim), steps=4)
     force_state(gpu, orc, pairs)                            # acting: the same actors on both sides
     rng = np.random.default_rng(9)
-    obs = rng.standard_normal((20, 45, obs_dim)).astype(np.float32)
-    got = gpu.act(obs)
-    for i, j in pairs:
-        want = orc.agents[j].act(obs[i].astype(np.float64))
-        assert float(np.abs(got[i] - want).max()) <= 2e-5
+    for rows in (45, many_rows(20)):
+        obs = rng.standard_normal((20, rows, obs_dim)).astype(np.float32)
+        got = gpu.act(obs)
+        for i, j in pairs:
+            want = orc.agents[j].act(obs[i].astype(np.float64))
+            assert float(np.abs(got[i] - want).max()) <= 2e-5
     gpu.close()
 
 

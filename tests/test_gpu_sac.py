@@ -8,7 +8,7 @@ import pytest
 
 import paper_2206_08888_amd as pp
 import workloads
-from gpu_common import check_step_elementwise, check_tensors_all, ensure_built, rel_l2, snapshot
+from gpu_common import check_step_elementwise, check_tensors_all, ensure_built, many_rows, rel_l2, snapshot
 from oracle import sac as oracle_sac
 
 pytestmark = pytest.mark.gpu
@@ -163,11 +163,12 @@ def test_mid_size_populations_use_the_wider_chains_and_still_match(P):
     gpu.close()
 
 
-def test_act_mean_and_sampled_actions_match_oracle():
+@pytest.mark.parametrize("n", [70, many_rows(2)])
+def test_act_mean_and_sampled_actions_match_oracle(n):
     gpu, orc, agents = make_sac_pair(capacity=600)
     gpu.update(2); orc.update(2)
     rng = np.random.default_rng(8)
-    obs = rng.standard_normal((2, 70, 17)).astype(np.float32)
+    obs = rng.standard_normal((2, n, 17)).astype(np.float32)
     ref = orc.act(obs.astype(np.float64))
     assert np.abs(gpu.act(obs) - ref).max() <= 5e-6
     got = gpu.act(obs, sigma=[1.0, 0.0], step=31)          # agent 0 samples its policy, agent 1 acts on the mean
@@ -280,11 +281,12 @@ def test_wide_shapes_in_a_mid_size_population(obs_dim, act_dim):
 
 
 @pytest.mark.parametrize("obs_dim,act_dim", WIDE)
-def test_wide_shapes_act_matches_oracle(obs_dim, act_dim):
+@pytest.mark.parametrize("n", [45, many_rows(2)])
+def test_wide_shapes_act_matches_oracle(obs_dim, act_dim, n):
     gpu, orc, agents = make_sac_pair(capacity=400, obs_dim=obs_dim, act_dim=act_dim)
     gpu.update(2); orc.update(2)
     rng = np.random.default_rng(9)
-    obs = rng.standard_normal((2, 45, obs_dim)).astype(np.float32)
+    obs = rng.standard_normal((2, n, obs_dim)).astype(np.float32)
     wide = obs_dim > 64                                   # fp32 rounding of the first layer grows with its fan-in
     err = float(np.abs(gpu.act(obs) - orc.act(obs.astype(np.float64))).max())
     assert err <= (2e-5 if wide else 5e-6), err

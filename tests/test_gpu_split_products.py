@@ -1,11 +1,11 @@
 """The 256-deep products on the bf16 pipe (three-way split operands): acting against 64-bit arithmetic at the edges of
-the row and contraction tiles and over a wide range of magnitudes, and the row geometries that split their operands
+the row and contraction tiles and over a wide range of magnitudes (with few rows on the vector ALU, with many on the bf16 pipe), and the row geometries that split their operands
 differently against each other."""
 import numpy as np
 import pytest
 
 import paper_2206_08888_amd as pp
-from gpu_common import ensure_built, rel_l2
+from gpu_common import ensure_built, many_rows, rel_l2
 from oracle import sac as oracle_sac, td3 as oracle_td3, td3_shared as oracle_shared
 
 pytestmark = pytest.mark.gpu
@@ -43,8 +43,8 @@ def _apart(a, ref, terms):
 
 
 @pytest.mark.parametrize("algo", [pp.POP_ALGO_TD3, pp.POP_ALGO_SAC])
-@pytest.mark.parametrize("O,A", [(1, 1), (8, 3), (9, 24), (33, 6), (376, 17), (424, 24)])
-@pytest.mark.parametrize("n", [1, 33])
+@pytest.mark.parametrize("O,A", [(1, 1), (8, 3), (9, 24), (33, 6), (376, 17), (424, 24), (64, 16), (65, 8), (17, 9)])
+@pytest.mark.parametrize("n", [1, 33, many_rows(2), 17 * 32])
 def test_acting_against_64_bits(algo, O, A, n):
     pop = _population(algo, 2, O, A)
     obs = np.random.default_rng(O + n).standard_normal((2, n, O)).astype(np.float32)
@@ -57,7 +57,8 @@ def test_acting_against_64_bits(algo, O, A, n):
 
 
 @pytest.mark.parametrize("scale", [1e-28, 1e-15, 1e15, 1e28])
-def test_acting_over_magnitudes(scale):
+@pytest.mark.parametrize("n", [64, many_rows(1)])
+def test_acting_over_magnitudes(scale, n):
     """Hidden activations of very different sizes: the layers are scaled against each other."""
     O, A = 17, 6
     pop = _population(pp.POP_ALGO_TD3, 1, O, A)
@@ -65,7 +66,7 @@ def test_acting_over_magnitudes(scale):
     th[:O * H + H] *= np.float32(scale)
     th[O * H + H:O * H + H + H * H] *= np.float32(1.0 / scale)
     pop.set_params(0, "actor", th)
-    obs = np.random.default_rng(3).standard_normal((1, 64, O)).astype(np.float32)
+    obs = np.random.default_rng(3).standard_normal((1, n, O)).astype(np.float32)
     assert _apart(pop.act(obs)[0], *_act64(th, obs[0], O, A, A)) < 6e-7
     pop.close()
 
@@ -93,17 +94,21 @@ PLANTS = {                     # what is put into a network's W1, b1, W2, b2, W3
 
 @pytest.mark.parametrize("plant", sorted(PLANTS))
 @pytest.mark.parametrize("algo", [pp.POP_ALGO_TD3, pp.POP_ALGO_SAC])
-def test_acting_with_infinities(algo, plant):
+@pytest.mark.parametrize("times", [1, 17])                # the same 64 rows over again: 1,088 go to the 32-row kernel
+def test_acting_with_infinities(algo, plant, times):
     """Infinite, NaN and the largest finite operands of a hidden product give what fp32 arithmetic gives."""
     O, A, n = 17, 6, 64
+    assert times == 1 or times * n >= many_rows(1)
     pop = _population(algo, 1, O, A)
     out = 2 * A if algo == pp.POP_ALGO_SAC else A
     th = pop.get_params(0, "actor").copy()
     PLANTS[plant](*_views(th, O, out))
     pop.set_params(0, "actor", th)
     obs = np.random.default_rng(4).standard_normal((1, n, O)).astype(np.float32)
-    got = pop.act(obs)[0].astype(np.float64)
+    got = pop.act(np.tile(obs, (1, times, 1)))[0].astype(np.float64)
     pop.close()
+    assert all(np.array_equal(got[:n], got[k * n:(k + 1) * n], equal_nan=True) for k in range(1, times))
+    got = got[:n]
     w1, b1, w2, b2, w3, b3 = (v.astype(np.float64) for v in _views(th, O, out))
     with np.errstate(all="ignore"):
         h = np.fmax(obs[0].astype(np.float64) @ w1 + b1, 0.0)      # max(NaN, 0) = 0, as the kernels' ReLU has it

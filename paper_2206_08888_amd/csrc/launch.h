@@ -22,6 +22,12 @@ hipError_t launch_critic(const PopDev& d, uint32_t t, hipStream_t s);
 hipError_t launch_target_critic(const PopDev& d, uint32_t t, hipStream_t s);   // both of the above in one launch
 hipError_t launch_target_critic_few(const PopDev& d, uint32_t t, hipStream_t s);   // the same for a few agents and wide shapes (k_few.hip)
 hipError_t setup_few_kernels();
+// What a fused target / critic launch of 16-row target and 32-row critic chains has CUs left for (kSpread*); `forward`: the actor's forward pass is wanted there.
+inline int spread_of(const PopDev& d, bool forward) {
+  if (d.rows_t != 16 || d.rows_c != 32 || d.rows_c1 != 32 || d.rows_a != 16 || d.actor_ahead) return 0;
+  const int64_t b16 = (int64_t)d.P * (d.B / 16), chains = b16 + 2 * (int64_t)d.P * (d.B / 32);
+  return (chains + b16 <= kCUs ? kSpreadTargets : 0) | (forward && chains + 2 * b16 <= kCUs ? kSpreadActor : 0);
+}
 bool wide_critics_alone(const PopDev& d);   // wide inputs: a critic workgroup's LDS leaves no room for a second one on its CU
 hipError_t launch_actor(const PopDev& d, uint32_t t, hipStream_t s);
 // prefetch_next != 0: extra workgroups also gather the replay rows of step t + 1

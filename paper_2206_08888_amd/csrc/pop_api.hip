@@ -482,12 +482,7 @@ int pop_create(pop_ctx** out, const pop_config* cfg, const pop_hparams* hp, uint
   // their own / fused and spread: 111 / 8 91.5 / 62.3 with 1 agent, 424 / 24 143.3 / 96.5 with 4, 447 / 1 143.1 / 105.0 with 5; fused alone: 111 / 8 109.0 /
   // 96.5 with 8, 30 / 20 (delays 1 .. 3) 117.0 / 105.7 with 7.  SAC (the target critics alone): 17 / 6 fused 89.0 / 82.2 with 1 agent, 97.5 / 90.9 with 5, 111 / 8 136 / 113 with 1, 147 / 121 with 5,
   // 157 / 145 with 8 (fused alone).
-  d.spread = 0;
-  if (ctx->fuse == 1 && d.rows_t == 16 && d.rows_c == 32 && d.rows_c1 == 32 && d.rows_a == 16 && !d.actor_ahead) {
-    const int64_t b16 = (int64_t)cfg->P * (cfg->batch / 16);
-    if (tc_blocks + b16 <= kCUs) d.spread |= kSpreadTargets;
-    if (cfg->algo != POP_ALGO_SAC && tc_blocks + 2 * b16 <= kCUs && cfg->tuning.actor_ahead != 1) d.spread |= kSpreadActor;
-  }
+  d.spread = ctx->fuse == 1 ? spread_of(d, cfg->algo != POP_ALGO_SAC && cfg->tuning.actor_ahead != 1) : 0;
   if (ctx->fuse >= 2 && d.rows_t == 16 && d.rows_c != 64) {   // the single launch exists for the (16, 64, 16) small class only
     delete ctx;
     return fail(nullptr, POP_EINVAL, "POP_LAUNCH_SINGLE and POP_LAUNCH_TAIL need rows (16, 64, 16) for a population this small");

@@ -50,6 +50,27 @@ def test_against_one_launch_per_part(algo, P, O, A):
         assert all(np.array_equal(got[k], want[k]) for k in want), [k for k in want if not np.array_equal(got[k], want[k])][:4]
 
 
+@pytest.mark.parametrize("algo, P, O, A, apart", [("td3", 1, 17, 6, True), ("td3", 5, 17, 6, True), ("td3", 6, 17, 6, False), ("td3", 5, 111, 8, True), ("td3", 6, 111, 8, False),
+                                                  ("sac", 5, 17, 6, True), ("sac", 6, 17, 6, False), ("sac", 2, 376, 17, True), ("td3_shared", 5, 40, 9, True)])
+def test_what_the_target_workgroups_publish(algo, P, O, A, apart):
+    """One value of each target critic where they have workgroups of their own, y where one workgroup runs both: of all words of the workspace, those with the
+    step's tag over the bits of y are there in the second case only."""
+    ensure_built()
+    code = {"td3": pp.POP_ALGO_TD3, "td3_shared": pp.POP_ALGO_TD3_SHARED, "sac": pp.POP_ALGO_SAC}[algo]
+    pop = pp.Population(pp.make_config(P, O, A, (256, 256), 256, 300, algo=code), workloads.hparams(2, P))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(O)
+    rnd = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    pop.insert(-1, obs=rnd(P, 300, O), act=rnd(P, 300, A).clamp(-1, 1), rew=rnd(P, 300), done=(rnd(P, 300) > 2).float(), next_obs=rnd(P, 300, O))
+    pop.update(400)
+    y = pop.debug("target_y")
+    words = (400 << 32) | torch.from_numpy(np.ascontiguousarray(y).view(np.uint32).astype(np.int64)).flatten()
+    ws = pop.workspace[:pop.workspace.numel() // 8 * 8].view(torch.int64)
+    found = int(torch.isin(words.cuda(), ws).sum())
+    assert (found <= 4) if apart else found == P * 256, found      # (a y that happens to be some critic's value)
+    pop.close()
+
+
 def test_the_first_population_whose_wide_chains_have_launches_of_their_own():
     fused, apart = pp.POP_LAUNCH_TARGET_CRITIC, pp.POP_LAUNCH_PER_PART
     sac = pp.Population(pp.make_config(20, 111, 8, (256, 256), 256, 64, algo=pp.POP_ALGO_SAC), workloads.hparams(5, 20))

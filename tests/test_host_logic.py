@@ -30,23 +30,39 @@ def test_workgroups_per_cu(tmp_path):
     assert out.returncode == 0 and "bad 0" in out.stdout, out.stdout[-2000:]
 
 
-def test_grid_of_an_acting_launch(tmp_path):
-    exe = tmp_path / "act_grid_check"
+@pytest.mark.parametrize("check", ["act_grid_check", "spread_check"])
+def test_rules_of_the_launches(tmp_path, check):
+    exe = tmp_path / check
     hipcc = "/opt/rocm/bin/hipcc" if os.path.exists("/opt/rocm/bin/hipcc") else "hipcc"
     subprocess.run([hipcc, "-O1", "-std=c++17", "--offload-arch=gfx950", "--cuda-host-only", "-Wno-unused-command-line-argument",
                     "-I", os.path.join(ROOT, "paper_2206_08888_amd", "csrc"),
-                    os.path.join(ROOT, "tests", "host", "act_grid_check.cpp"), "-o", str(exe)], check=True)
+                    os.path.join(ROOT, "tests", "host", check + ".cpp"), "-o", str(exe)], check=True)
     out = subprocess.run([str(exe)], capture_output=True, text=True)
     assert out.returncode == 0 and "bad 0" in out.stdout, out.stdout[-2000:]
 
 
-@pytest.fixture(scope="module")
-def k_chain_asm(tmp_path_factory):
+def _asm(tmp, source):
     from paper_2206_08888_amd import build
-    asm = tmp_path_factory.mktemp("asm") / "k_chain.s"
-    subprocess.run([build._hipcc(), *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, "k_chain.hip"), "-o", str(asm)],
+    asm = tmp / (source + ".s")
+    subprocess.run([build._hipcc(), *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, source), "-o", str(asm)],
                    check=True, capture_output=True)
     return asm.read_text()
+
+
+@pytest.fixture(scope="module")
+def k_chain_asm(tmp_path_factory):
+    return _asm(tmp_path_factory.mktemp("asm"), "k_chain.hip")
+
+
+# most SGPRs (arguments, mostly) and VGPRs spilled by the kernels of a file, where other than none: SAC's 64-row actor chains exist for tuning only
+@pytest.mark.parametrize("source, kernels, sgprs, vgprs", [("k_few.hip", 10, 34, {}), ("k_sac.hip", 17, 16, {"k_sac_actorINS_12_GLOBAL__N_16Rows32ILi2E": 152}),
+                                                            ("k_act.hip", 24, 0, {})])
+def test_the_kernels_of_few_agents_of_sac_and_of_acting_spill_no_more_than_they_did(tmp_path, source, kernels, sgprs, vgprs):
+    spills = {m[1]: (int(m[2]), int(m[3])) for m in re.finditer(r"\.name: +(_ZN3pop\S*).*?\.sgpr_spill_count: +(\d+).*?\.vgpr_spill_count: +(\d+)",
+                                                                 _asm(tmp_path, source), re.S)}
+    assert len(spills) == kernels, sorted(spills)
+    for name, (s, v) in spills.items():
+        assert s <= sgprs and v <= max((n for known, n in vgprs.items() if known in name), default=0), (name, s, v)
 
 
 def test_critic_1_inside_the_target_workgroups_spills_no_arguments(k_chain_asm):

@@ -329,8 +329,8 @@ int pop_set_option(pop_ctx* ctx, int32_t key, int64_t value);
 
 /* Block until everything enqueued by this context has finished (Sec. 4.1: the host takes part only between
  * device calls of many update steps each); reports asynchronous kernel errors as POP_EHIP.
- * A wait between workgroups of a fused launch that ran into its time limit (the launch still completes, its
- * results are invalid) is reported once, as POP_EHIP, by the first call that synchronises after it -- pop_sync,
+ * A wait between workgroups of a fused launch (every launch structure but POP_LAUNCH_PER_PART, those of wide shapes
+ * too) that ran into its time limit (the launch still completes, its results are invalid) is reported once, as POP_EHIP, by the first call that synchronises after it -- pop_sync,
  * pop_update_timed, and pop_get_params / pop_debug_get / pop_act with host pointers -- and then cleared: the
  * population's state is invalid from that step on until the caller restores it (pop_set_params). */
 int pop_sync(pop_ctx* ctx);

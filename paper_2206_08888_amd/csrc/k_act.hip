@@ -6,7 +6,8 @@
 // 16 w .. 16 w + 15, lane l the columns 4 l ..), and the first layer runs under that trip.  Each wavefront contracts over its
 // own 16 rows on the vector ALU (256 instructions per lane and observation row; 4x4x1 matrix instructions would take the time of four rows for one),
 // and the sixteen partial sums meet in LDS: rounding steps per sum 16 + 16 where a 256-deep chain has 256.
-// The 32-row workgroups of k_act spend 8 us on the same, most of it on rows that are not there.
+// The 32-row workgroups of k_act spend 8 us on the same, most of it on rows that are not there; with many agents, rows or outputs they are ahead
+// all the same (most_agents).
 #include "chains.h"
 
 namespace pop {

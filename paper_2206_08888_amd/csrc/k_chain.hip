@@ -269,7 +269,7 @@ hipError_t launch_target(const PopDev& d, uint32_t t, hipStream_t s) {
 bool wide_critics_alone(const PopDev& d) { return d.D > kMaxIn && 2 * CriticMap<Rows32Deep<2, false>>(d.D).bytes() > (size_t)kLdsPerCU; }
 hipError_t launch_critic(const PopDev& d, uint32_t t, hipStream_t s) {
   const dim3 grid(xcd_grid(2 * d.P, d.B / d.rows_c)), block(kThreads);
-  if (d.D > kMaxIn) {                                // wide inputs (SAC): 32 rows, pipelined first layer
+  if (d.D > kMaxIn) {                                // wide inputs: 32 rows, pipelined first layer
     if (d.rows_c != 32) return hipErrorInvalidValue;
     const size_t over = CriticMap<Rows32Deep<2, false>>(d.D).bytes(), beside = CriticMap<Rows32Wide>(d.D).bytes();
     if (wide_critics_alone(d) || (int)grid.x <= kCUs)                // a CU to itself in any case

@@ -426,8 +426,8 @@ int pop_create(pop_ctx** out, const pop_config* cfg, const pop_hparams* hp, uint
   // launch, two workgroups per CU; waiting weight-gradient workgroups would take the slots the actor chains could
   // start in.  From P = 34 the parts are each several times larger than the 512 workgroups the chip holds and the
   // tails of one part overlap the next inside a single launch; towards a hundred agents the separate launches are
-  // ahead again (bf16 products, single / target+critic: 164.7 / 175.5 at P = 34, 187.9 / 191.2 at 40, 283.3 / 281.5 at 64, 320.9 / 331.1 at 72,
-  // 354.2 / 361.1 at 80, 427.4 / 419.7 at 96) (their tile kernel runs three workgroups per CU, the tiles inside the single launch two).
+  // ahead again (bf16 products, moments past the caches, single / target+critic: 158.1 / 164.6 at P = 33, 159.8 / 164.6 at 34, 177.7 / 179.3 at 40,
+  // 209.0 / 209.7 at 48, 258.0 / 254.3 at 64, 287.0 / 293.1 at 72, 316.5 / 321.2 at 80, 333.4 / 341.5 at 83, 354.0 / 354.2 at 88, 387.7 / 379.6 at 96) (their tile kernel runs three workgroups per CU, the tiles inside the single launch two).
   const int64_t tc_blocks = (int64_t)cfg->P * (cfg->batch / d.rows_t) + (int64_t)cfg->P * (cfg->batch / d.rows_c) +
                             (d.rows_c1 == d.rows_c ? (int64_t)cfg->P * (cfg->batch / d.rows_c) : 0);
   const int64_t chain_blocks = (int64_t)cfg->P * (cfg->batch / 32) * 3;

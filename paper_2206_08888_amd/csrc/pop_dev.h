@@ -31,7 +31,7 @@ constexpr int kLda = kH + 4;   // LDS row stride of a 256-wide activation tile: 
                                // 8 lanes reading 16 B each from 8 consecutive rows hit all 32 banks
 constexpr int kThreads = 256;  // 4 wavefronts of 64 per workgroup in every compute kernel
 constexpr int kMaxIn = 64;     // narrow shapes: largest first-layer fan-in (obs_dim + act_dim) of the chains without a pipelined
-                               // first layer -- all fused launch structures are built for these
+                               // first layer -- the single and tail launches exist for these alone
 constexpr int kMaxAct = 8;     // narrow shapes: largest action dimension; also the row stride of the small LDS scratch blocks
 constexpr int kSacMaxIn = 448; // wide shapes (SAC and plain TD3): largest first-layer fan-in (the Humanoid shapes need 393)
 constexpr int kSacMaxAct = 24; // wide shapes: largest action dimension (Humanoid: 17) and row stride of their scratch blocks

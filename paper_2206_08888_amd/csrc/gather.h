@@ -22,13 +22,6 @@ __host__ __device__ inline int gather_blocks_per_agent(const PopDev& d) {
   const int per = 256 * gather_floats_per_thread(d);
   return (d.B * d.row + per - 1) / per;
 }
-// Replay rows go past the caches where the filled buffers of all agents (each as full as this one) are more than the L2s hold: a row is then read once,
-// and through the caches would push out weights and activations that the next launches read.  Smaller buffers draw the same rows again step after
-// step, out of those caches.  us/step, through / past them: 20 TD3 agents of 376 / 17 196.2 / 197.4 with 256 rows (16 MB), 201.9 / 199.9 with 1000 (62 MB),
-// 201.0 / 197.6 with 10,000; 8 of them 131.3 / 131.8 with 1000 rows (25 MB), 132.0 / 132.3 with 10,000; 32 SAC agents of 17 / 6 193.7 / 195.3 with 1000 rows
-// (5 MB); 80 agents with shared critics 297.7 / 295.3 with 10,000 (134 MB).
-constexpr uint64_t kL2Floats = (32ull << 20) / sizeof(float);
-__host__ __device__ inline bool past_caches(const PopDev& d, uint32_t count) { return (uint64_t)d.P * count * (uint32_t)d.row > kL2Floats; }
 constexpr int kGatherLds = 256;            // words of LDS: the drawn rows of a workgroup's part of the batch
 
 // Workgroup `block` (of gather_blocks_per_agent) of one agent: thread `tid` copies the floats
@@ -60,7 +53,7 @@ __device__ __forceinline__ void gather_run(const PopDev& d, uint32_t t, int agen
     const int e = base + k * 256 + tid, ec = e <= last ? e : last, b = row_of(ec);
     return src + (size_t)drawn[b - b0] * row + (ec - b * row);
   };
-  if (past_caches(d, count)) {
+  if (d.rows_past) {
     int zero = 0;
     asm volatile("" : "+s"(zero));                   // (two branches of equal addresses become one with ordinary loads)
 #pragma unroll

@@ -140,6 +140,7 @@ struct PopDev {
   // (At the end: the fields before keep their places.  Four bytes on, the layouts' fields come to the kernels in smaller loads, 0.5 us a launch.)
   int spread;                  // kSpread* below
   int stream;                  // the Adam moments are read and written past the caches: a population whose state the Infinity Cache does not hold
+  int rows_past;               // the gather reads replay rows past the caches: filled buffers that the L2s do not hold (pop_api.hip)
   int w2_plain;                // hidden matrices lie row-major (w2_index<true>): critic 1 inside the target workgroups and 16-row actor chains
 };
 

@@ -106,11 +106,14 @@ __global__ __launch_bounds__(G::kThr, PER_CU) void k_actor(PopDev d, uint32_t t)
 // Noise scale sigma[agent] > 0: Gaussian exploration noise, a = clip(pi + sigma[agent] eps, -1, 1) with eps =
 // unit normal number (row_base + r) A + j of the agent's exploration stream at counter `step`
 // (row_base: index of row 0 of this call within the caller's whole request).  Grid: act_grid.
-template <bool PLAIN>
+// NOISE: whether the call has noise scales.  Read behind the head they cost one scalar trip; read with the weights, in one kernel for both, they stood
+// in front of the LDS accesses, which are waited for with them.  us, read early / a kernel for each: with noise, 70 agents 125 rows of 269 inputs
+// 46.96 / 46.34, 13 SAC agents 1409 rows 38.2 / 37.9; without, 3 SAC agents 777 rows 12.75 / 12.74 (read behind the head in one kernel for both: 12.88).
+template <bool PLAIN, bool NOISE>
 __global__ __launch_bounds__(kThreads) void k_act(PopDev d, const float* __restrict__ obs, int n,
                                                   float* __restrict__ act, const float* __restrict__ sigma, uint32_t step,
-                                                  uint32_t row_base, int chunks, int noise, int share_head, SigmaArgs sigma_args) {
-  warm_args<sizeof(PopDev) + 52>();
+                                                  uint32_t row_base, int chunks, int share_head, SigmaArgs sigma_args) {
+  warm_args<sizeof(PopDev) + 48>();
   constexpr int R = 32;
   extern __shared__ float lds[];
   constexpr int kHs = kMaxHead;                      // row stride of the head block
@@ -132,8 +135,6 @@ __global__ __launch_bounds__(kThreads) void k_act(PopDev d, const float* __restr
   LayerPre<1, 2, PLAIN> pre;
   pre.load(an, d.actor, wave, lane);
   const float* rows = obs + ((size_t)agent * n + r0) * d.O;
-  float sg = 0.0f;
-  if (noise) sg = sigma ? sigma[agent] : sigma_args.s[agent < kStaticMaxP ? agent : 0];
   if (d.O <= kMaxIn) {                               // one trip to memory for all of the prologue
     SmallVec ab3;
     InputTile<R> xin;
@@ -145,7 +146,6 @@ __global__ __launch_bounds__(kThreads) void k_act(PopDev d, const float* __restr
     stage_vector(v_ab3, an + d.actor.b3, d.actor.out, tid);
     load_input_wide<R>(Xs, L.xld, rows, d.O, 0, d.O, valid, tid);
   }
-  asm volatile("" ::"v"(sg));                         // in the trip of the weights, not in one of its own behind the head
   __syncthreads();
   first_layer<1, false>(Xs, L.xld, an, d.actor, pre, buf, nullptr, wave, lane);
   __syncthreads();
@@ -155,15 +155,21 @@ __global__ __launch_bounds__(kThreads) void k_act(PopDev d, const float* __restr
   if (share_head) head_mfma_split<R, false>(buf, an + d.actor.w3, d.actor.out, head, kHs, wave, lane, stage);
   else head_mfma<R>(buf, an + d.actor.w3, d.actor.out, head, kHs, wave, lane);
   const bool sac = d.algo == 1;
+  float sg = 0.0f;
+  uint32_t seed_lo = 0u, seed_hi = 0u;
+  if constexpr (NOISE) {
+    sg = sigma ? sigma[agent] : sigma_args.s[agent < kStaticMaxP ? agent : 0];
+    seed_lo = d.hp[agent].seed_lo;
+    seed_hi = d.hp[agent].seed_hi;
+  }
   __syncthreads();
   for (int e = tid; e < valid * d.A; e += kThreads) {
     const int r = e / d.A, j = e - r * d.A;
     const float pre_act = head[r * kHs + j] + v_ab3[j];
     float a = tanhf(pre_act);
-    if (sg > 0.0f) {
-      const HpDev hp = d.hp[agent];
+    if (NOISE && sg > 0.0f) {
       const uint32_t el = (row_base + (uint32_t)(r0 + r)) * (uint32_t)d.A + (uint32_t)j;
-      const U4 blk = philox4x32_10(hp.seed_lo, hp.seed_hi, el >> 2, step, kStreamExplore, 0u);
+      const U4 blk = philox4x32_10(seed_lo, seed_hi, el >> 2, step, kStreamExplore, 0u);
       float n4[4];
       normals4(blk, n4);
       const float nz = (el & 2u) ? ((el & 1u) ? n4[3] : n4[2]) : ((el & 1u) ? n4[1] : n4[0]);
@@ -222,8 +228,10 @@ hipError_t setup_kernels() {
   POP_SET_LDS(k_actor<Rows16, 1, true>);
   POP_SET_LDS(k_target_critic<Rows32<1>, Rows32<1>>);
   POP_SET_LDS(k_target_critic<Rows64, Rows64>);
-  POP_SET_LDS(k_act<false>);
-  POP_SET_LDS(k_act<true>);
+  POP_SET_LDS((k_act<false, false>));
+  POP_SET_LDS((k_act<false, true>));
+  POP_SET_LDS((k_act<true, false>));
+  POP_SET_LDS((k_act<true, true>));
 #undef POP_SET_LDS
   return hipSuccess;
 }
@@ -350,14 +358,14 @@ hipError_t launch_actor(const PopDev& d, uint32_t t, hipStream_t s) {
 }
 hipError_t launch_act_rows(const PopDev& d, const float* obs, int n, float* act, const float* sigma, const SigmaArgs* args, uint32_t step,
                            uint32_t row_base, int whole, hipStream_t s) {
-  auto* kernel = d.w2_plain ? k_act<true> : k_act<false>;
+  auto* kernel = sigma || args ? (d.w2_plain ? k_act<true, true> : k_act<false, true>) : (d.w2_plain ? k_act<true, false> : k_act<false, false>);
   const ActGrid g = act_grid(d.P, n);
   // Up to 16 outputs all four wavefronts share the head, unless rounds of workgroups each read another agent's weights, which then are on their way
   // from memory four times (us, shared / not: 512 agents 33 rows, 3 inputs, 37.0 / 38.2; 768 agents 5 rows 40.3 / 36.5, SAC of 6 actions 45.8 / 41.4; 512
   // agents 27.6 / 27.4).
   const int share_head = d.actor.out <= 16 && (whole > 32 || d.P <= kCUs);
   kernel<<<dim3(xcd_grid(d.P, g.chunks), g.pieces), dim3(kThreads), act_lds_bytes(d), s>>>(d, obs, n, act, sigma, step, row_base,
-                                                                                                        g.chunks, sigma || args, share_head, args ? *args : kNoNoise);
+                                                                                                        g.chunks, share_head, args ? *args : kNoNoise);
   return hipGetLastError();
 }
 
